@@ -15,8 +15,8 @@
 // pointers; nothing is packed per block.  A workgroup owns all tokens of one block
 // (or an M-slice of it) and a range of list positions (gemm1) or of output columns
 // (gemm2).  Workgroup ids are mapped so that the ids one XCD receives (id mod 8) walk
-// the position/column ranges in the same order over that XCD's own group of blocks:
-// blocks that selected the same weight rows then hit them in that XCD's L2.
+// its position/column ranges in the same order over its group of blocks: blocks that
+// selected the same weight rows then hit them in that XCD's L2.
 #include "ff_internal.h"
 
 #include <algorithm>
@@ -38,14 +38,15 @@ __device__ __forceinline__ f32x16_t mfma32(const u32x4_t &a, const u32x4_t &b, f
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// Workgroup id -> (virtual block, n tile).  XCD x = id mod 8 owns virtual blocks
-// x, x+8, ...; its ids enumerate n tiles outermost, its blocks innermost.
+// Workgroup id -> (virtual block, n tile).  The 8 XCDs (id mod 8) form a grid of XV = 2^xs groups of virtual
+// blocks by 8 / XV groups of n tiles: XCD (xv, xn) owns virtual blocks xv, xv + XV, ... and n tiles xn,
+// xn + 8/XV, ...; its ids enumerate its n tiles outermost, its blocks innermost.
 struct TileCoord { int vb, nt; bool valid; };
-__device__ __forceinline__ TileCoord map_tile(int w, int V, int N) {
-  const int cnt = (V + 7) >> 3;
+__device__ __forceinline__ TileCoord map_tile(int w, int V, int N, int xs) {
+  const int cnt = (V + (1 << xs) - 1) >> xs;
   const int xcd = w & 7, l = w >> 3;
-  const int nt = l / cnt, j = l - nt * cnt;
-  const int vb = xcd + 8 * j;
+  const int nl = l / cnt, j = l - nl * cnt;
+  const int vb = (xcd & ((1 << xs) - 1)) + (j << xs), nt = (xcd >> xs) + (nl << (3 - xs));
   TileCoord t = {vb, nt, vb < V && nt < N};
   return t;
 }
@@ -146,7 +147,7 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void *p) {
 // swizzle expects there.  BK = 64 makes every request a whole 128-byte line.
 template <int WM, int WN, int TM, int TN, int BK, int S, int KG = 1>
 __global__ __launch_bounds__(WM * WN * KG * 64) __attribute__((amdgpu_waves_per_eu(TM * TN * 2 <= 8 ? 2 : 1)))
-void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int NX) {
+void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   constexpr int NW = WM * WN * KG;                 // KG groups of WM x WN wavefronts split each stage's k range
   constexpr int BM = WM * TM * 32;
   constexpr int WNn = TN * 32;
@@ -180,7 +181,7 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int NX) {
     tc.nt = N + ((int)blockIdx.x - h * NX);
     tc.valid = true;
   } else {
-    tc = map_tile((int)blockIdx.x - n_first, V, N);
+    tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
   }
   if (!tc.valid) return;
   // wave-uniform by construction; say so, so that everything derived from it stays scalar
@@ -495,7 +496,7 @@ __global__ __launch_bounds__(256) void ff_gemm2_reduce_kernel(Gemm2Params p) {
 // tile, for launches that give every CU one workgroup at most.
 template <int WM, int WN, int TM, int BK, int S, int RM, int KG = 1>
 __global__ __launch_bounds__(WM * WN * KG * 64) __attribute__((amdgpu_waves_per_eu(TM * 4 <= 8 ? 2 : 1)))
-void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N) {
+void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   constexpr int NW = WM * WN * KG;
   constexpr int BM = WM * TM * 32;
   constexpr int BN = WN * 128;
@@ -541,7 +542,7 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N) {
     tc.valid = true;
     if (p.n_pieces > 0) piece = 1 + sp;
   } else {
-    tc = map_tile((int)blockIdx.x - n_first, V, N);
+    tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
     if (tc.valid && p.k.n_heavy > 0) {
       const int hi = heavy_index(p.k, tc.vb / mt);
       if (hi >= 0) {
@@ -944,6 +945,28 @@ hipError_t ff_gemm_init(int lds_limit) {
   return hipSuccess;
 }
 
+constexpr int kNumCU = 256;
+
+// How the 8 XCDs share V virtual blocks x N n-tiles (see map_tile): log2 of the groups of virtual blocks.
+// Eight groups give every XCD its own blocks, whose tokens then stay in one L2, but with V no multiple of 8
+// some XCDs get one block more than others, and below 8 some get none at all.  So: fewest rounds of workgroups
+// on the busiest XCD (32 CUs; below one round its tiles count), but eight groups unless that saves a thirtieth.
+// (Gate/up launch, always eight groups against this rule: 4096/14336, K 7168, 128-token blocks: 1 block 130 -> 69 us,
+// 4 blocks 141 -> 79, 12 blocks 241 -> 192; 65 blocks of 77: 938 -> 894; 64 blocks unchanged; 3584/18944 dense, 300
+// tokens: 459 -> 185, 9001 tokens 2264 -> 2038, and the down launch 1715 -> 1260.)
+static int xcd_groups(long V, long N) {
+  int best = 3;
+  double best_cost = 0.0;
+  for (int xs = 3; xs >= 0; --xs) {
+    const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
+    const long rounds = (tiles + kNumCU / 8 - 1) / (kNumCU / 8);
+    const double cost = rounds > 1 ? (double)rounds : (double)tiles / (kNumCU / 8);
+    if (xs == 3) best_cost = cost * 31.0 / 32.0;
+    else if (cost < best_cost) { best = xs; best_cost = cost; }
+  }
+  return best;
+}
+
 // V virtual blocks (each block cut into M tiles of v.bm tokens) x N tiles, preceded by the
 // heavy blocks' n_first_per_vb tiles each
 static hipError_t launch_variant(const Variant &v, const void *fn, const void *params, int block, int n_blocks,
@@ -951,17 +974,17 @@ static hipError_t launch_variant(const Variant &v, const void *fn, const void *p
   int mt = (block + v.bm - 1) / v.bm;
   int V = n_blocks * mt;
   int NX = n_first_per_vb;
-  int grid = n_heavy * mt * n_first_per_vb + 8 * ((V + 7) / 8) * N;
+  int xs = xcd_groups(V, N);
+  int grid = n_heavy * mt * n_first_per_vb + 8 * ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
   if (grid <= 0) return hipSuccess;
-  void *args1[] = {const_cast<void *>(params), &V, &mt, &N, &NX};
-  void *args2[] = {const_cast<void *>(params), &V, &mt, &N};
+  void *args1[] = {const_cast<void *>(params), &V, &mt, &N, &xs, &NX};
+  void *args2[] = {const_cast<void *>(params), &V, &mt, &N, &xs};
   return hipLaunchKernel(fn, dim3(grid), dim3(v.threads), gemm1 ? args1 : args2, v.lds, s);
 }
 
 constexpr int kRemainderVariant = 7;
 constexpr int kHeavySurplusVariant = 8;
 constexpr int kWide128 = 6;
-constexpr int kNumCU = 256;
 
 hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int heavy_tiles, hipStream_t s) {
   static const int p64[] = {5, 4}, p128[] = {0, 2, 1}, p256[] = {3, 2, 1};

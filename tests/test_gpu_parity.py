@@ -418,6 +418,27 @@ def test_gemm1_remainder_split(ctx, c0):
         ctx.set_option("gemm1_split", -1)
 
 
+@pytest.mark.parametrize("n_blocks", [1, 2, 3, 5, 7, 9, 12, 17])
+def test_block_counts_that_do_not_divide_the_xcds(ctx, n_blocks):
+    """The XCDs share (blocks x tiles) in a way that depends on the block count: every tile of every block must be
+    computed exactly once for counts below, at no multiple of and beyond the 8 XCDs, equal lists and a few longer
+    ones, sparse and dense."""
+    c = Case(W.Shape("xcds", 640, 1064, 32 * n_blocks - 5, 32, 8, 16))
+    for ks in ([600] * n_blocks, [1064] + [601] * (n_blocks - 1)):
+        ref = c.oracle_layer(ks)
+        idx, _ = c.gpu_predict(ctx, ks)
+        _assert_indices(idx, ref.indices, ks)
+        ctx.set_option("merge_blocks", 0)
+        try:
+            _check_y(c.gpu_sparse(ctx, idx, ks, out_f32=True), ref.y, f"{n_blocks} blocks, ks[0]={ks[0]}")
+        finally:
+            ctx.set_option("merge_blocks", -1)
+    ctx.ensure_workspace(c.shape, 1064)
+    y = torch.empty((c.T, 640), dtype=torch.float32, device=DEV)
+    ctx.dense_ffn(c.shape, c.x, c.w, y, B.OUT_F32)
+    _check_y(y, O.dense_ffn(_f32(c.x_bits), c.host("w_gate"), c.host("w_up"), c.host("w_down").T), f"{n_blocks} blocks, dense")
+
+
 def test_static_expert_one_list_for_all_tokens(ctx):
     """Static-expert mode (Sec. 5 ablation "first-block static"): the first block's selection
     serves the whole prompt.  It needs no entry point of its own: ff_sparse_ffn with
