@@ -128,7 +128,9 @@ const char *ff_last_error(const ff_ctx *ctx);
  * tokens the partial sums of the down projection, for blocks shorter than
  * 128 tokens the merged lists of neighbouring blocks, and at most 48 MiB of
  * fp32 partial sums for the rows of a few blocks whose lists are much longer
- * than the others', Sec. 3.4). */
+ * than the others', Sec. 3.4; and for short prompts at most 96 MiB of fp32
+ * partial sums of the down projection, which a call does without where a smaller
+ * workspace has no room for them). */
 ff_status ff_workspace_bytes(const ff_shape *shape, int32_t k_max, size_t *bytes);
 /* Hands the context a caller-owned device buffer (256-byte aligned) to use as
  * scratch until it is replaced or the context is destroyed. */

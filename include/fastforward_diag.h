@@ -39,7 +39,11 @@ extern "C" {
  *       pieces: whether the down GEMM cuts the few lists that are much longer
  *       than the rest (first and last block dense) along the list into a tile
  *       like everybody else's plus short tiles, and adds their fp32 partial
- *       sums in piece order in one more launch. */
+ *       sums in piece order in one more launch.
+ *   "gemm2_nsplit"  -1 = decide by shape, 0 = never, n > 1 = n pieces (fewer
+ *       where the workspace has no room): whether the down GEMM cuts every list
+ *       along the list, for calls with too few tiles for the chip, and adds the
+ *       pieces' fp32 partial sums in order in one more launch. */
 
 /* Per-stage GPU timing with HIP events on the context's stream.
  * ff_profile_enable(ctx, n, mask) makes every later compute call bracket each

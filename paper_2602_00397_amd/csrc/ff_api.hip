@@ -44,7 +44,7 @@ struct ff_ctx {
   void *static_scratch = nullptr;  // this device's copy of `scratch`
   int lds_limit = 65536;
   int validate = 0;
-  int gemm1_variant = -1, gemm2_variant = -1, gemm1_split = -1, gemm2_split = -1, gemm2_row_mode = -1, gemm2_ksplit = -1, gemm1_heavy_tiles = -1;
+  int gemm1_variant = -1, gemm2_variant = -1, gemm1_split = -1, gemm2_split = -1, gemm2_row_mode = -1, gemm2_ksplit = -1, gemm2_nsplit = -1, gemm1_heavy_tiles = -1;
   int small_path = 1;              // few-token calls take the GEMV kernels
   int merge_blocks = -1;           // lists of short blocks merged per 128 tokens: -1 = when it pays, 0 = never, 1 = whenever possible
   std::vector<int32_t> k_sorted;   // host scratch for the K statistics of a call
@@ -369,8 +369,16 @@ ff_status run_ffn(ff_ctx *ctx, const ff_shape &s, const Layout &L, const void *x
     g.part = reinterpret_cast<float *>(wsp(ctx, L.g2part));
     g.part_bytes = L.g2part_bytes;
   }
+  // the room for cutting every list is no part of what a call needs: used where the workspace has it
+  // (a call without a predictor keeps only H, so it starts right behind)
+  const size_t split_at = up(indices == nullptr && comp == nullptr ? (size_t)s.n_tokens * L.hs * 2 : L.total, 256);
+  const size_t split_bytes = ff_gemm2_split_bytes(s.n_tokens, s.d_model);
+  if (split_bytes > 0 && ctx->ws_bytes >= split_at + split_bytes) {
+    g.split_part = reinterpret_cast<float *>(wsp(ctx, split_at));
+    g.split_bytes = split_bytes;
+  }
   prof_begin(&ctx->prof, FF_STAGE_GEMM2, ctx->stream);
-  FF_HIP(ctx, ff_launch_gemm2(g, g2v, ctx->gemm2_split, ctx->gemm2_row_mode, ctx->gemm2_ksplit, ctx->stream));
+  FF_HIP(ctx, ff_launch_gemm2(g, g2v, ctx->gemm2_split, ctx->gemm2_row_mode, ctx->gemm2_ksplit, ctx->gemm2_nsplit, ctx->stream));
   prof_end(&ctx->prof, ctx->stream);
   return FF_OK;
 }
@@ -510,7 +518,8 @@ ff_status ff_workspace_bytes(const ff_shape *shape, int32_t k_max, size_t *bytes
   if (k_max < 1 || k_max > shape->d_ffn) return FF_ERR_INVALID_ARG;
   // (with room for the merged lists of short blocks, whether or not a call will use them)
   *bytes = std::max(make_layout(*shape, k_max).total,
-                    make_layout(*shape, k_max, false, merge_factor(*shape, 160 * 1024)).total);
+                    make_layout(*shape, k_max, false, merge_factor(*shape, 160 * 1024)).total) +
+           ff_gemm2_split_bytes(shape->n_tokens, shape->d_model);
   return FF_OK;
 }
 
@@ -540,6 +549,7 @@ ff_status ff_set_option(ff_ctx *ctx, const char *name, int32_t value) {
     ctx->gemm2_row_mode = value < 0 ? -1 : value;
     return FF_OK;
   }
+  if (!strcmp(name, "gemm2_nsplit")) { ctx->gemm2_nsplit = value < 0 ? -1 : value; return FF_OK; }
   if (!strcmp(name, "gemm2_ksplit")) { ctx->gemm2_ksplit = value < 0 ? -1 : value; return FF_OK; }
   if (!strcmp(name, "gemm2_variant")) {
     if (value >= ff_gemm2_num_variants()) return fail(ctx, FF_ERR_INVALID_ARG, "gemm2_variant %d does not exist", value);

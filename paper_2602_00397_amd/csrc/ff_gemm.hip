@@ -194,7 +194,8 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   const int Kb = __builtin_amdgcn_readfirstlane(block_k(p.k, b, p.d_ffn, p.k_stride, p.idx != nullptr));
   const int ntot = Kb + p.rc;
   const int n0 = __builtin_amdgcn_readfirstlane(p.rem_bn ? min(ntot / p.rem_bn * p.rem_bn, p.rem_cap) : 0) + tc.nt * BNn;
-  if (n0 >= ntot) return;
+  // (H is zero up to the next multiple of 64: a tile narrower than that may hold nothing but zeros)
+  if (n0 >= (BNn < 64 ? (ntot + 63) / 64 * 64 : ntot)) return;
   if (p.full_only && n0 + BNn > ntot) return;   // the remainder launch takes this part-filled tile
   if (p.skip_heavy && is_heavy(p.k, b)) return;  // a launch of their own has covered the heavy blocks' ends
 
@@ -453,23 +454,24 @@ __device__ __forceinline__ void store_out4(const Gemm2Params &p, size_t o, float
 // four columns and has all pieces' loads in flight before the first add.
 constexpr int kMaxPieces = 17;
 __global__ __launch_bounds__(256) void ff_gemm2_reduce_kernel(Gemm2Params p) {
-  const int hslot = (int)blockIdx.x / p.block, r = (int)blockIdx.x - hslot * p.block;
-  const int b = heavy_block(p.k, hslot);
-  const int t = b * p.block + r;
+  const bool all = p.n_split > 1;
+  const int hslot = all ? 0 : (int)blockIdx.x / p.block, r = (int)blockIdx.x - hslot * p.block;
+  const int t = all ? r : heavy_block(p.k, hslot) * p.block + r;
   if (t >= p.T) return;
-  const size_t piece_stride = (size_t)p.block * p.d_model;
+  const int n_pieces = all ? p.n_split : p.n_pieces;
+  const size_t piece_stride = (size_t)(all ? p.T : p.block) * p.d_model;
   const float *src = p.part + ((size_t)hslot * p.n_pieces * p.block + r) * p.d_model;
   const int c = p.col0 + 1024 * (int)blockIdx.y + 4 * (int)threadIdx.x;
   if (c < p.d_model) {
     float4 v[kMaxPieces];
 #pragma unroll
     for (int j = 0; j < kMaxPieces; ++j)
-      if (j < p.n_pieces) v[j] = *reinterpret_cast<const float4 *>(src + j * piece_stride + c);
+      if (j < n_pieces) v[j] = *reinterpret_cast<const float4 *>(src + j * piece_stride + c);
     __builtin_amdgcn_sched_barrier(0);
     float4 s = v[0];
 #pragma unroll
     for (int j = 1; j < kMaxPieces; ++j)
-      if (j < p.n_pieces) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
+      if (j < n_pieces) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
     store_out4(p, (size_t)t * p.d_model + c, s);
   }
 }
@@ -543,6 +545,10 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
     if (p.n_pieces > 0) piece = 1 + sp;
   } else {
     tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
+    if (p.n_split > 1) {   // every list is cut: N counts (piece, column tile) pairs
+      piece = tc.nt / p.n_cols;
+      tc.nt -= piece * p.n_cols;
+    }
     if (tc.valid && p.k.n_heavy > 0) {
       const int hi = heavy_index(p.k, tc.vb / mt);
       if (hi >= 0) {
@@ -566,8 +572,13 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   const int n0 = p.col0 + tc.nt * BN;
   // list positions [kofs, kend) of this tile (kofs a multiple of 64; an empty range gives zeros)
   int kofs = 0, kend = ntot;
-  if (piece == 0) kend = min(ntot, p.cut0);
-  if (piece > 0) {
+  if (p.n_split > 1) {
+    const int len = ((ntot + p.n_split - 1) / p.n_split + 63) / 64 * 64;
+    kofs = min(piece * len, (ntot + 63) / 64 * 64);
+    kend = min(ntot, (piece + 1) * len);
+  } else if (piece == 0) {
+    kend = min(ntot, p.cut0);
+  } else if (piece > 0) {
     kofs = min(p.cut0 + (piece - 1) * p.piece_len, (ntot + 63) / 64 * 64);
     kend = min(ntot, p.cut0 + piece * p.piece_len);
   }
@@ -850,7 +861,8 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
         if (rowl < rows_valid) {
           const float4 v = make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]);
           if (piece >= 0) {
-            const size_t prow = ((size_t)hslot * p.n_pieces + piece) * p.block + (m * BM + rowl);
+            const size_t prow = p.n_split > 1 ? (size_t)piece * p.T + (t0 + rowl)
+                                              : ((size_t)hslot * p.n_pieces + piece) * p.block + (m * BM + rowl);
             *reinterpret_cast<float4 *>(p.part + prow * p.d_model + col) = v;
           } else {
             store_out4(p, (size_t)(t0 + rowl) * p.d_model + col, v);
@@ -895,6 +907,8 @@ const Variant kGemm1[] = {
     g1<2, 4, 2, 2, 64, 2>(),     // 6: 128 x 256, 8 waves, BK 64, 2 stages (160 KB)
     g1<2, 2, 1, 1, 64, 6>(),     // 7: 64 x 64, 4 waves, BK 64, 6 stages (144 KB): remainder tile, latency-bound, deep ring
     g1<2, 2, 2, 1, 64, 4>(),     // 8: 128 x 64, 4 waves, BK 64, 4 stages (128 KB; 2 stages: 67 against 48 us on 224 tiles): the heavy blocks' surplus
+    g1<2, 1, 2, 1, 64, 6, 2>(),  // 9: 128 x 32, 4 waves in 2 k-groups, BK 64, 6 stages (144 KB): a single block over the whole chip
+    g1<1, 1, 2, 1, 64, 8, 2>(),  // 10: 64 x 32, 2 waves in 2 k-groups, BK 64, 8 stages (128 KB): the same for a short block
     // (tiles whose wavefronts need 256 accumulator registers -- 128 x 256 or 256 x 128 on 4 waves -- were measured
     //  10-25% slower: one wavefront per SIMD cannot keep the matrix pipe issuing back to back)
 };
@@ -982,41 +996,86 @@ static hipError_t launch_variant(const Variant &v, const void *fn, const void *p
   return hipLaunchKernel(fn, dim3(grid), dim3(v.threads), gemm1 ? args1 : args2, v.lds, s);
 }
 
+// Rounds of workgroups (one per CU) that V x N tiles take on the busiest XCD under the mapping that
+// launch_variant will use.
+static long xcd_rounds(long V, long N) {
+  const int xs = xcd_groups(V, N);
+  const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
+  return (tiles + kNumCU / 8 - 1) / (kNumCU / 8);
+}
+
+static int up64(int v) { return (v + 63) / 64 * 64; }   // (tiles narrower than 64 positions also zero H up to there)
+
 constexpr int kRemainderVariant = 7;
 constexpr int kHeavySurplusVariant = 8;
 constexpr int kWide128 = 6;
+constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
 
-hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int heavy_tiles, hipStream_t s) {
-  static const int p64[] = {5, 4}, p128[] = {0, 2, 1}, p256[] = {3, 2, 1};
+// Gate/up tiles by the cost of one round of 256 of them, relative to a round of the 128 x 256 tile (117 us at
+// d_model 4096 with the chip full, 4096/14336).  Tiles with fewer positions move more bytes per FLOP, hence cost
+// more than their share (0.52, 0.33 and 0.24 for a half, a quarter and an eighth), but fill the chip where a call has
+// too few big tiles or would start a last round with a few of them.
+struct Gemm1Cost { int variant; double round; };
+constexpr Gemm1Cost kGemm1Short[] = {{5, 0.90}, {kRemainderVariant, 0.27}, {10, 0.22}};                      // blocks up to 64 tokens
+constexpr Gemm1Cost kGemm1Mid[] = {{0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};                      // up to 255
+constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};           // 256 and more, and without a list
+
+hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, hipStream_t s) {
+  Gemm1Params p = p_in;
   const int n_extent = p.k.k_max + p.rc;                  // longest list
   const bool ragged = p.k.per_block != nullptr;           // lists of unequal length
   const int base_extent = (p.k.n_heavy > 0 ? p.k.k_base : p.k.k_max) + p.rc;   // what all but the heavy blocks have
   const bool chosen = variant < 0;
   if (variant < 0) {
-    if (p.block >= 256) variant = choose(kGemm1, p256, 3, p.block, p.n_blocks, base_extent);
-    else if (p.block > 64) {
-      variant = choose(kGemm1, p128, 3, p.block, p.n_blocks, base_extent);
+    // Fewest rounds x cost of a round; a smaller tile has to save a thirtieth.  (Measured, us, the larger tile that
+    // used to be taken against this choice: 4096/14336, K 7168: 100 tokens, 128 x 128 51 -> 128 x 32 29; 30 tokens in
+    // one block, 64 x 256 92 -> 64 x 32 26; K 3584, ten blocks of 64, 64 x 256 114 -> 64 x 64 100; 1100 tokens in blocks
+    // of 256, 256 x 128 216 -> 128 x 128 178; dense 3584/18944, 300 tokens, 256 x 128 190 -> 128 x 128 110.)
+    const Gemm1Cost *tab = p.block > 64 ? (p.block >= 256 ? kGemm1Long : kGemm1Mid) : kGemm1Short;
+    const int n_tab = p.block >= 256 ? 4 : 3;
+    double best = 0.0;
+    for (int i = 0; i < n_tab; ++i) {
+      const Variant &v = kGemm1[tab[i].variant];
+      if (v.lds > g_lds_limit) continue;
+      // without a list the blocks mean nothing: token tiles of this variant's height
+      const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
+      const long first = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * ((up64(n_extent) + v.bn - 1) / v.bn - (up64(base_extent) + v.bn - 1) / v.bn);
+      const long N = (up64(base_extent) + v.bn - 1) / v.bn;
+      const long rounds = first == 0 ? xcd_rounds(V, N) : (V * N + first + kNumCU - 1) / kNumCU;
+      const double cost = rounds * tab[i].round;
+      if (variant < 0 || cost < best * (30.0 / 31.0)) { variant = tab[i].variant; best = cost; }
+    }
+    if (variant < 0) return hipErrorInvalidValue;
+    if (p.block > 64 && p.block < 256) {
       // The 128 x 256 tile moves fewer bytes per FLOP; its part-filled last tile goes to the remainder
-      // launch (with lists of unequal length every block's own).  Against the 128 x 128 two-k-group tile, in
-      // rounds of 256 workgroups of the wide tile's duration: whole rounds of full wide tiles plus 0.22 per
-      // round of remainder tiles, against whole rounds of the smaller tile at 0.52 each.  (Measured, wide
-      // against small: 4096/14336 x 64 blocks K 7168 0.888 / 0.916 ms, K 7300 0.895 / 0.920, K 3584 -- 3.5
-      // rounds of wide tiles -- 0.520 / 0.490; 3584/18944 x 128 blocks K 13126 2.75 / 2.86; 2048/8192 x 32
-      // blocks K 4200 0.155 / 0.172.)
+      // launch (with lists of unequal length every block's own).  In rounds of it: whole rounds of full wide
+      // tiles plus 0.22 per round of remainder tiles, plus the launch of the few much longer lists' ends (half a
+      // round of tiles at most, 0.4; else further wide tiles).  (Measured, wide
+      // against 128 x 128: 4096/14336 x 64 blocks K 7168 0.888 / 0.916 ms, K 7300 0.895 / 0.920, K 3584 -- 3.5
+      // rounds of wide tiles -- 0.520 / 0.490; 16 blocks of 7168 with the first and last dense 0.332 / 0.267;
+      // 3584/18944 x 128 blocks K 13126 2.75 / 2.86; 2048/8192 x 32 blocks K 4200 0.155 / 0.172.)
       const Variant &w = kGemm1[kWide128];
       const int rem_w = base_extent % w.bn;
       const long wide_full = (long)p.n_blocks * (base_extent / w.bn);
       const long rem_wgs = (long)p.n_blocks * 2 * ((rem_w + 63) / 64);
-      const double cost_wide = (double)((wide_full + kNumCU - 1) / kNumCU) + 0.22 * (double)((rem_wgs + kNumCU - 1) / kNumCU);
-      const double cost_small = 0.52 * (double)(((long)p.n_blocks * ((base_extent + 127) / 128) + kNumCU - 1) / kNumCU);
-      if (split != 0 && w.lds <= g_lds_limit && base_extent >= w.bn && (ragged || cost_wide <= cost_small) && wide_full >= 224) {
+      const long surplus = (long)p.k.n_heavy * (n_extent / w.bn - base_extent / w.bn);
+      const bool surplus_own = surplus > 0 && 2 * surplus <= kNumCU;
+      const double cost_wide = (double)((wide_full + (surplus_own ? 0 : surplus) + kNumCU - 1) / kNumCU) + (surplus_own ? 0.4 : 0.0) +
+                               0.22 * (double)((rem_wgs + kNumCU - 1) / kNumCU);
+      // (merged lists: only a bound of their lengths is known here)
+      const bool unknown = ragged && p.k.n_heavy == 0;
+      if (split != 0 && w.lds <= g_lds_limit && base_extent >= w.bn && (unknown || cost_wide <= best) && wide_full >= 224) {
         variant = kWide128;
         if (rem_w > 0 || ragged) split = 1;
       }
-    } else variant = choose(kGemm1, p64, 2, p.block, p.n_blocks, base_extent);
+    }
   }
   if (variant >= kNumGemm1 || kGemm1[variant].lds > g_lds_limit) return hipErrorInvalidValue;
   const Variant &v = kGemm1[variant];
+  if (p.idx == nullptr) {
+    p.block = v.bm;
+    p.n_blocks = (p.T + v.bm - 1) / v.bm;
+  }
   Gemm1Params q = p;
   q.full_only = 0;
   q.rem_bn = 0;
@@ -1026,7 +1085,7 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int hea
   // little work over the whole chip.
   const int rem = n_extent % v.bn;
   bool do_split = false;
-  if ((chosen ? split != 0 : split > 0) && (rem > 0 || ragged) && n_extent >= v.bn && variant != kRemainderVariant) {
+  if ((chosen ? split != 0 : split > 0) && (rem > 0 || ragged) && n_extent >= v.bn && (!chosen || v.bn >= 128) && variant != kRemainderVariant) {
     const int n_full = base_extent / v.bn;
     const int per_cu = g_lds_limit / v.lds > 0 ? (g_lds_limit / v.lds > 2 ? 2 : g_lds_limit / v.lds) : 1;
     const int slots = kNumCU * per_cu;
@@ -1037,7 +1096,7 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int hea
   }
   const int heavy = p.k.n_heavy;
   if (!do_split) {
-    const int N = (base_extent + v.bn - 1) / v.bn, N_all = (n_extent + v.bn - 1) / v.bn;
+    const int N = (up64(base_extent) + v.bn - 1) / v.bn, N_all = (up64(n_extent) + v.bn - 1) / v.bn;
     return launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, heavy, N_all - N, true, s);
   }
   q.full_only = 1;
@@ -1075,10 +1134,58 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int hea
   return launch_variant(r, r.fn, &q, p.block, p.n_blocks, (rem_max + r.bn - 1) / r.bn, 0, 0, true, s);
 }
 
-constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
+
+
+// The tile with its source of gathered row ids: computed for the identity list; else an LDS table of 16-bit ids
+// behind the ring when it fits (ids run up to d_ffn + rc - 1), the streamed list where the tile has it, scalar loads.
+// row_mode > 0 forces one of them where the tile has it and it fits (else fn = nullptr).
+static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_bytes) {
+  if (p.idx == nullptr) return v;
+  const bool table_fits = p.d_ffn + p.rc <= 65536 && v.lds + tab_bytes <= g_lds_limit;
+  const bool ring_fits = v.fn_rm[2] != nullptr && v.lds + kIdRingBytes <= g_lds_limit;
+  const int mode = row_mode > 0 ? row_mode : (table_fits ? 1 : (ring_fits ? 3 : 2));
+  if (mode == 1 && table_fits) {
+    v.lds += tab_bytes;
+    v.fn = v.fn_rm[0];
+  } else if (mode == 3 && ring_fits) {
+    v.lds += kIdRingBytes;
+    v.fn = v.fn_rm[2];
+  } else if (mode == 2) {
+    v.fn = v.fn_rm[1];
+  } else {
+    v.fn = nullptr;
+  }
+  return v;
+}
+
+// every list cut into n pieces (n >= 2, p.split_part has room for them)
+static hipError_t launch_gemm2_cut(Gemm2Params p, int variant, int n, int row_mode, hipStream_t s) {
+  const int len = ((p.k.k_max + p.rc + n - 1) / n + 63) / 64 * 64;
+  const Variant v = with_rows(kGemm2[variant], p, row_mode, 2 * len);
+  if (v.fn == nullptr) return hipErrorInvalidValue;
+  if (p.idx == nullptr) {
+    p.block = v.bm;
+    p.n_blocks = (p.T + v.bm - 1) / v.bm;
+  }
+  p.n_split = n;
+  p.n_cols = (p.d_model + v.bn - 1) / v.bn;
+  p.part = p.split_part;
+  p.k.n_heavy = 0;
+  hipError_t e = launch_variant(v, v.fn, &p, p.block, p.n_blocks, p.n_cols * n, 0, 0, false, s);
+  if (e != hipSuccess) return e;
+  void *args[] = {&p};
+  return hipLaunchKernel(reinterpret_cast<const void *>(&ff_gemm2_reduce_kernel), dim3(p.T, (p.d_model + 1023) / 1024), dim3(256), args, 0, s);
+}
 
 constexpr int kMaxShortPieces = kMaxPieces - 1;
 constexpr size_t kPartCapBytes = (size_t)48 << 20;
+
+constexpr size_t kSplitCapBytes = (size_t)96 << 20;
+size_t ff_gemm2_split_bytes(int n_tokens, int d_model) {
+  const size_t per_piece = (size_t)n_tokens * d_model * sizeof(float);
+  const size_t n = std::min<size_t>(kSplitCapBytes / per_piece, kMaxPieces - 1);
+  return n >= 2 ? n * per_piece : 0;
+}
 
 size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model) {
   if (n_tokens <= block) return 0;   // one block: nothing is longer than the rest
@@ -1086,43 +1193,56 @@ size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model) {
   return want < kPartCapBytes ? want : kPartCapBytes;
 }
 
-hipError_t ff_launch_gemm2(const Gemm2Params &p, int variant, int split, int row_mode, int ksplit, hipStream_t s) {
-  // row ids: computed for the identity list; else from an LDS table of 16-bit ids behind the
-  // ring when it fits (ids run up to d_ffn + rc - 1), else by scalar loads
+hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int row_mode, int ksplit, int nsplit, hipStream_t s) {
+  Gemm2Params p = p_in;
+  const bool chosen = variant < 0;
+  // Few tiles: where the 128 x 256 tiles do not fill the chip, every list is cut into n pieces that run side by
+  // side, write fp32 partial sums and are added in piece order.  In us: a round of tiles costs 5 + 0.75 .. 1.1 per 64
+  // positions (the more CUs are busy, the slower each), the cut 5 for one more launch and its partial sums written and
+  // read once at 4.4 TB/s.  (Measured, whole lists against this choice: 4096/14336, K 7168: 100 tokens 91 -> 28;
+  // 2048/8192, K 4096, 700 tokens 58 -> 32; dense 3584/18944, 300 tokens 275 -> 80.)  Uncut the same tile is
+  // also faster than 64 x 512 ones while it takes one round (ten blocks of 64 tokens, K 3584: 83 -> 60).
+  // (A few much longer lists have a cut of their own, below, that leaves the other blocks' sums alone.)
+  if ((chosen && split < 0 && ksplit < 0 && nsplit < 0 && p.k.n_heavy == 0) || nsplit > 1) {
+    const Variant &v4 = kGemm2[chosen ? kHalf128Wide : std::min(variant, kNumGemm2 - 1)];
+    const long V = p.idx == nullptr ? (p.T + v4.bm - 1) / v4.bm : (long)p.n_blocks * ((p.block + v4.bm - 1) / v4.bm);
+    const long N = (p.d_model + v4.bn - 1) / v4.bn;
+    const size_t per_piece = (size_t)p.T * p.d_model * sizeof(float);
+    const long room = p.split_part != nullptr ? std::min<long>((long)(p.split_bytes / per_piece), kMaxPieces - 1) : 1;
+    const int ntot = p.k.k_max + p.rc;
+    int n = 1;
+    if (nsplit > 1) {
+      n = (int)std::min<long>(nsplit, room);
+    } else if (v4.lds <= g_lds_limit && V * N <= kNumCU) {
+      double best = 0.0;
+      for (int c = 1; c <= room && (c == 1 || ntot >= c * 64); ++c) {
+        const double steps = ((ntot + c - 1) / c + 63) / 64;
+        const double busy = std::min(1.0, (double)(V * N * c) / kNumCU);
+        const double cost = xcd_rounds(V, N * c) * (5.0 + steps * (0.75 + 0.35 * busy)) + (c > 1 ? 5.0 + c * (double)per_piece / 2.2e6 : 0.0);
+        if (c == 1 || cost < best * 0.97) { n = c; best = cost; }
+      }
+    }
+    if (n > 1) return launch_gemm2_cut(p, chosen ? kHalf128Wide : std::min(variant, kNumGemm2 - 1), n, row_mode, s);
+    if (chosen && v4.lds <= g_lds_limit && xcd_rounds(V, N) == 1 && (p.block <= 64 || p.idx == nullptr)) variant = kHalf128Wide;
+  }
   const int n_pad = (p.k.k_max + p.rc + 63) / 64 * 64;   // whole k-steps of the longest BK
   const int tab_bytes = ((2 * n_pad + 15) / 16) * 16;
   // the eight-wavefront 128 x 256 tile leaves 16 KB for that table; a longer list streams through
   // a small LDS ring instead (row-id mode 3)
   const int half128 = kHalf128Wide;
   const int p64[] = {3}, p128[] = {0, half128, 1}, p256[] = {2, 0, half128, 1};
-  const bool chosen = variant < 0;
   if (variant < 0) {
     if (p.block >= 256) variant = choose(kGemm2, p256, 4, p.block, p.n_blocks, p.d_model);
     else if (p.block > 64) variant = choose(kGemm2, p128, 3, p.block, p.n_blocks, p.d_model);
     else variant = choose(kGemm2, p64, 1, p.block, p.n_blocks, p.d_model);
   }
   if (variant >= kNumGemm2) return hipErrorInvalidValue;
+  if (p.idx == nullptr) {   // without a list the blocks mean nothing: token tiles of this variant's height
+    p.block = kGemm2[variant].bm;
+    p.n_blocks = (p.T + p.block - 1) / p.block;
+  }
   Gemm2Params q = p;
-  // row_mode > 0 forces one source of the row ids where the tile has it and it fits (else fn = nullptr)
-  auto with_row_mode = [&](Variant v) {
-    if (p.idx != nullptr) {
-      const bool table_fits = p.d_ffn + p.rc <= 65536 && v.lds + tab_bytes <= g_lds_limit;
-      const bool ring_fits = v.fn_rm[2] != nullptr && v.lds + kIdRingBytes <= g_lds_limit;
-      const int mode = row_mode > 0 ? row_mode : (table_fits ? 1 : (ring_fits ? 3 : 2));
-      if (mode == 1 && table_fits) {
-        v.lds += tab_bytes;
-        v.fn = v.fn_rm[0];
-      } else if (mode == 3 && ring_fits) {
-        v.lds += kIdRingBytes;
-        v.fn = v.fn_rm[2];
-      } else if (mode == 2) {
-        v.fn = v.fn_rm[1];
-      } else {
-        v.fn = nullptr;
-      }
-    }
-    return v;
-  };
+  auto with_row_mode = [&](const Variant &v) { return with_rows(v, p, row_mode, tab_bytes); };
   const Variant v = with_row_mode(kGemm2[variant]);
   if (v.fn == nullptr) return hipErrorInvalidValue;
   const int N = (p.d_model + v.bn - 1) / v.bn;

@@ -135,7 +135,7 @@ static void part2_argument_errors(ff_ctx *ctx) {
   EXPECT(ff_set_option(ctx, "gemm2_row_mode", 0), FF_ERR_INVALID_ARG);
   {
     static const char *const names[] = {"validate", "small_path", "merge_blocks", "gemm1_split", "gemm2_split",
-                                        "gemm1_heavy_tiles", "gemm2_ksplit"};
+                                        "gemm1_heavy_tiles", "gemm2_ksplit", "gemm2_nsplit"};
     size_t n;
     for (n = 0; n < sizeof(names) / sizeof(names[0]); ++n) {   /* every documented name is known; back to the default */
       EXPECT(ff_set_option(ctx, names[n], 1), FF_OK);

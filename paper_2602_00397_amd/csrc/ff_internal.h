@@ -115,6 +115,11 @@ struct Gemm2Params {
   float *part = nullptr;        // [n_heavy][n_pieces][block][d_model]
   size_t part_bytes = 0;
   int32_t n_pieces = 0, cut0 = 0, piece_len = 0;
+  // Every list cut along k into n_split pieces (few tiles; see ff_launch_gemm2): partial sums in
+  // split_part [n_split][T][d_model] (nullptr: never), n_cols column tiles.  n_split <= 1: not cut.
+  float *split_part = nullptr;
+  size_t split_bytes = 0;
+  int32_t n_split = 0, n_cols = 0;
   KSpec k;
 };
 // variant < 0: choose by shape.  Returns hipErrorInvalidValue for an unknown variant.
@@ -135,7 +140,10 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int hea
 // row_mode: where the kernel takes a gathered row's id from: -1 = the launcher decides, 1 = a table of
 // 16-bit ids in LDS, 2 = scalar loads of the list, 3 = the list streamed through a small LDS ring (only
 // the eight-wavefront tile has it).  A forced mode the tile does not have, or that does not fit, is an error.
-hipError_t ff_launch_gemm2(const Gemm2Params &p, int variant, int split, int row_mode, int ksplit, hipStream_t s);
+// nsplit: into how many pieces every list is cut along k: -1 = the launcher decides (few tiles), 0 = never,
+// n > 1 = into n pieces, fewer where split_part has no room for them.
+hipError_t ff_launch_gemm2(const Gemm2Params &p, int variant, int split, int row_mode, int ksplit, int nsplit, hipStream_t s);
+size_t ff_gemm2_split_bytes(int n_tokens, int d_model);   // room for cutting every list (0: too many tokens for that to pay)
 size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model);   // room that lets two heavy blocks be cut as finely as the launcher would
 hipError_t ff_gemm_init(int lds_limit);  // raises the kernels' dynamic-LDS limits; once per process
 int ff_gemm1_num_variants();

@@ -540,6 +540,48 @@ def test_long_lists_cut_along_k(ctx):
         ctx.set_option("gemm2_row_mode", -1)
 
 
+@pytest.mark.parametrize("n_tokens,block,ks", [(9, 9, [33]), (100, 128, [1000]), (150, 64, [700, 40, 1]), (300, 128, [1064, 5, 601]),
+                                               (200, 32, [900] * 7), (600, 300, [513, 512])])
+def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
+    """With few tiles the down GEMM cuts every list into pieces and adds their fp32 partial sums: 2, 5 and 16 pieces,
+    lists shorter than the pieces, merged lists (their length known on the device only), a short last block, both
+    tile widths the gate/up GEMM takes for few tokens (32 and 64 positions; list ends on no multiple of either), and
+    the dense call.  Against the oracle at the stated bars; against the uncut sums only fp32 summation order (1064
+    products of at most a few hundredths: 1e-5 is 30 times their rounding).  A workspace without room for the
+    partial sums gives the uncut result."""
+    c = Case(W.Shape("cut", 640, 1064, n_tokens, block, 8, 24))
+    ref = c.oracle_layer(ks)
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=1064)
+    _assert_indices(idx, ref.indices, ks)
+    ref_d = O.dense_ffn(_f32(c.x_bits), c.host("w_gate"), c.host("w_up"), c.host("w_down").T)
+
+    def dense():
+        y = torch.empty((c.T, 640), dtype=torch.float32, device=DEV)
+        ctx.dense_ffn(c.shape, c.x, c.w, y, B.OUT_F32)
+        return y
+
+    ctx.ensure_workspace(c.shape, 1064)
+    keep = ctx._ws
+    try:
+        ctx.set_option("gemm2_nsplit", 0)
+        y0, d0 = c.gpu_sparse(ctx, idx, ks, out_f32=True), dense()
+        _check_y(y0, ref.y, "whole lists")
+        for n in (2, 5, 16, -1):
+            ctx.set_option("gemm2_nsplit", n)
+            y, d = _check_both(c, ctx, idx, ks, ref.y, f"lists cut into {n}"), dense()
+            _check_y(d, ref_d, f"dense cut into {n}")
+            assert (y - y0).abs().max().item() <= 1e-5 and (d - d0).abs().max().item() <= 1e-5, n
+        ctx.set_option("gemm2_nsplit", 5)
+        part = min((96 << 20) // (4 * n_tokens * 640), 16) * 4 * n_tokens * 640
+        ctx.set_workspace(keep[:B.workspace_bytes(c.shape, 1064) - part])
+        y_small = torch.empty_like(y0)
+        ctx.sparse_ffn(c.shape, c.x, c.w, c.comp, idx, ks, 1064, y_small, B.OUT_F32)
+        _check_y(y_small, ref.y, "no room for the partial sums")
+    finally:
+        ctx.set_option("gemm2_nsplit", -1)
+        ctx.set_workspace(keep)
+
+
 @pytest.mark.parametrize("n_tokens,block", [(256, 64), (6, 4)])
 def test_calls_can_be_captured_in_a_hip_graph(n_tokens, block):
     """predict + sparse_ffn with one K for all blocks enqueue kernels only (no copies, no
