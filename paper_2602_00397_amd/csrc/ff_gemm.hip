@@ -118,6 +118,13 @@ __device__ __forceinline__ void gload_lds16(const void *gptr, uint32_t lds_addr)
                : "v"(gptr), "s"(lds_addr)
                : "memory");
 }
+// the same from a wave-uniform base plus a 32-bit byte offset per lane
+__device__ __forceinline__ void gload_lds16_off(uint64_t base, uint32_t off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(off), "s"(base), "s"(lds_addr)
+               : "memory");
+}
 // the 4-byte form: lane l lands at +4 l (256 bytes per wavefront instruction)
 __device__ __forceinline__ void gload_lds4(const void *gptr, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
@@ -477,6 +484,94 @@ __global__ __launch_bounds__(256) void ff_gemm2_reduce_kernel(Gemm2Params p) {
 }
 
 // ============================ gemm2 =========================================
+// The tile of gemm2 that a workgroup owns: BM tokens from t0, BN output columns from n0, nk steps of BK list positions
+// from kofs (a multiple of 64; no steps gives zeros).  piece: which piece of a cut list (-1: a whole list), hslot:
+// which heavy block.
+struct Gemm2Tile { int b, m, t0, rows_valid, Kb, ntot, n0, kofs, nk, piece, hslot; bool valid; };
+template <int BM, int BN, int BK>
+__device__ __forceinline__ Gemm2Tile gemm2_tile(const Gemm2Params &p, int V, int mt, int N, int xs) {
+  Gemm2Tile t;
+  t.valid = false;
+  // The heavy blocks' tiles (the longest k loops) take the first ids, then everybody else's.  With
+  // n_pieces > 0 a heavy block's list is cut along k instead: its first cut0 positions are a tile like
+  // everybody else's (piece 0, in the common region), the rest goes to n_pieces - 1 short tiles of
+  // piece_len positions with the first ids, and every piece writes fp32 partial sums that
+  // ff_gemm2_reduce_kernel adds up in a fixed order.
+  TileCoord tc;
+  const int n_surplus = p.n_pieces > 0 ? p.n_pieces - 1 : 1;
+  const int n_first = p.k.n_heavy * mt * N * n_surplus;
+  int piece = -1, hslot = 0;   // piece of a cut list (-1: a whole list), and which heavy block
+  if ((int)blockIdx.x < n_first) {
+    // id = ((surplus piece * heavy virtual blocks) + heavy virtual block) * N + column tile
+    const int hv = p.k.n_heavy * mt;
+    const int hn = __builtin_amdgcn_readfirstlane((int)blockIdx.x / N);
+    const int sp = __builtin_amdgcn_readfirstlane(hn / hv);
+    const int h = hn - sp * hv;
+    hslot = __builtin_amdgcn_readfirstlane(h / mt);
+    tc.vb = heavy_block(p.k, hslot) * mt + (h - hslot * mt);
+    tc.nt = (int)blockIdx.x - hn * N;
+    tc.valid = true;
+    if (p.n_pieces > 0) piece = 1 + sp;
+  } else {
+    tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
+    if (p.n_split > 1) {   // every list is cut: N counts (piece, column tile) pairs
+      piece = tc.nt / p.n_cols;
+      tc.nt -= piece * p.n_cols;
+    }
+    if (tc.valid && p.k.n_heavy > 0) {
+      const int hi = heavy_index(p.k, tc.vb / mt);
+      if (hi >= 0) {
+        if (p.n_pieces == 0) return t;
+        piece = 0;
+        hslot = hi;
+      }
+    }
+  }
+  if (!tc.valid) return t;
+  tc.vb = __builtin_amdgcn_readfirstlane(tc.vb);   // wave-uniform by construction
+  tc.nt = __builtin_amdgcn_readfirstlane(tc.nt);
+  piece = __builtin_amdgcn_readfirstlane(piece);
+  hslot = __builtin_amdgcn_readfirstlane(hslot);
+  t.b = tc.vb / mt;
+  t.m = tc.vb - t.b * mt;
+  t.t0 = t.b * p.block + t.m * BM;
+  t.rows_valid = min(p.T, (t.b + 1) * p.block) - t.t0;
+  if (t.rows_valid <= 0) return t;
+  t.Kb = __builtin_amdgcn_readfirstlane(block_k(p.k, t.b, p.d_ffn, p.k_stride, p.idx != nullptr));
+  t.ntot = t.Kb + p.rc;
+  const int ntot = t.ntot;
+  t.n0 = p.col0 + tc.nt * BN;
+  // list positions [kofs, kend) of this tile (kofs a multiple of 64; an empty range gives zeros)
+  int kofs = 0, kend = ntot;
+  if (p.n_split > 1) {
+    const int len = ((ntot + p.n_split - 1) / p.n_split + 63) / 64 * 64;
+    kofs = min(piece * len, (ntot + 63) / 64 * 64);
+    kend = min(ntot, (piece + 1) * len);
+  } else if (piece == 0) {
+    kend = min(ntot, p.cut0);
+  } else if (piece > 0) {
+    kofs = min(p.cut0 + (piece - 1) * p.piece_len, (ntot + 63) / 64 * 64);
+    kend = min(ntot, p.cut0 + piece * p.piece_len);
+  }
+  t.kofs = __builtin_amdgcn_readfirstlane(kofs);
+  t.nk = __builtin_amdgcn_readfirstlane(max(kend - kofs + BK - 1, 0) / BK);
+  t.piece = piece;
+  t.hslot = hslot;
+  t.valid = true;
+  return t;
+}
+// four adjacent columns of row rowl of the tile: a piece's partial sums, or the output
+template <int BM>
+__device__ __forceinline__ void gemm2_store(const Gemm2Params &p, const Gemm2Tile &t, int rowl, int col, float4 v) {
+  if (t.piece >= 0) {
+    const size_t prow = p.n_split > 1 ? (size_t)t.piece * p.T + (t.t0 + rowl)
+                                      : ((size_t)t.hslot * p.n_pieces + t.piece) * p.block + (t.m * BM + rowl);
+    *reinterpret_cast<float4 *>(p.part + prow * p.d_model + col) = v;
+  } else {
+    store_out4(p, (size_t)(t.t0 + rowl) * p.d_model + col, v);
+  }
+}
+
 // WM x WN wavefronts; a wavefront computes 32*TM tokens x 128 output columns.  The B
 // operand tile is [BK list positions][BN columns] as it lies in memory (a gathered row is
 // contiguous along the columns); the k-contiguous MFMA fragments are formed by reading
@@ -523,67 +618,9 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   const int wm = wq / WN, wn = wq % WN;
   const int c = lane & 31, half = lane >> 5;
 
-  // The heavy blocks' tiles (the longest k loops) take the first ids, then everybody else's.  With
-  // n_pieces > 0 a heavy block's list is cut along k instead: its first cut0 positions are a tile like
-  // everybody else's (piece 0, in the common region), the rest goes to n_pieces - 1 short tiles of
-  // piece_len positions with the first ids, and every piece writes fp32 partial sums that
-  // ff_gemm2_reduce_kernel adds up in a fixed order.
-  TileCoord tc;
-  const int n_surplus = p.n_pieces > 0 ? p.n_pieces - 1 : 1;
-  const int n_first = p.k.n_heavy * mt * N * n_surplus;
-  int piece = -1, hslot = 0;   // piece of a cut list (-1: a whole list), and which heavy block
-  if ((int)blockIdx.x < n_first) {
-    // id = ((surplus piece * heavy virtual blocks) + heavy virtual block) * N + column tile
-    const int hv = p.k.n_heavy * mt;
-    const int hn = __builtin_amdgcn_readfirstlane((int)blockIdx.x / N);
-    const int sp = __builtin_amdgcn_readfirstlane(hn / hv);
-    const int h = hn - sp * hv;
-    hslot = __builtin_amdgcn_readfirstlane(h / mt);
-    tc.vb = heavy_block(p.k, hslot) * mt + (h - hslot * mt);
-    tc.nt = (int)blockIdx.x - hn * N;
-    tc.valid = true;
-    if (p.n_pieces > 0) piece = 1 + sp;
-  } else {
-    tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
-    if (p.n_split > 1) {   // every list is cut: N counts (piece, column tile) pairs
-      piece = tc.nt / p.n_cols;
-      tc.nt -= piece * p.n_cols;
-    }
-    if (tc.valid && p.k.n_heavy > 0) {
-      const int hi = heavy_index(p.k, tc.vb / mt);
-      if (hi >= 0) {
-        if (p.n_pieces == 0) return;
-        piece = 0;
-        hslot = hi;
-      }
-    }
-  }
-  if (!tc.valid) return;
-  tc.vb = __builtin_amdgcn_readfirstlane(tc.vb);   // wave-uniform by construction
-  tc.nt = __builtin_amdgcn_readfirstlane(tc.nt);
-  piece = __builtin_amdgcn_readfirstlane(piece);
-  hslot = __builtin_amdgcn_readfirstlane(hslot);
-  const int b = tc.vb / mt, m = tc.vb - b * mt;
-  const int t0 = b * p.block + m * BM;
-  const int rows_valid = min(p.T, (b + 1) * p.block) - t0;
-  if (rows_valid <= 0) return;
-  const int Kb = block_k(p.k, b, p.d_ffn, p.k_stride, p.idx != nullptr);
-  const int ntot = Kb + p.rc;
-  const int n0 = p.col0 + tc.nt * BN;
-  // list positions [kofs, kend) of this tile (kofs a multiple of 64; an empty range gives zeros)
-  int kofs = 0, kend = ntot;
-  if (p.n_split > 1) {
-    const int len = ((ntot + p.n_split - 1) / p.n_split + 63) / 64 * 64;
-    kofs = min(piece * len, (ntot + 63) / 64 * 64);
-    kend = min(ntot, (piece + 1) * len);
-  } else if (piece == 0) {
-    kend = min(ntot, p.cut0);
-  } else if (piece > 0) {
-    kofs = min(p.cut0 + (piece - 1) * p.piece_len, (ntot + 63) / 64 * 64);
-    kend = min(ntot, p.cut0 + piece * p.piece_len);
-  }
-  kofs = __builtin_amdgcn_readfirstlane(kofs);
-  const int nk = __builtin_amdgcn_readfirstlane(max(kend - kofs + BK - 1, 0) / BK);
+  const Gemm2Tile tl = gemm2_tile<BM, BN, BK>(p, V, mt, N, xs);
+  if (!tl.valid) return;
+  const int b = tl.b, t0 = tl.t0, rows_valid = tl.rows_valid, Kb = tl.Kb, ntot = tl.ntot, n0 = tl.n0, kofs = tl.kofs, nk = tl.nk;
 
   const bf16_t *a_src[LA];
 #pragma unroll
@@ -860,16 +897,215 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
         const int rowl = (wm * TM + i) * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
         if (rowl < rows_valid) {
           const float4 v = make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]);
-          if (piece >= 0) {
-            const size_t prow = p.n_split > 1 ? (size_t)piece * p.T + (t0 + rowl)
-                                              : ((size_t)hslot * p.n_pieces + piece) * p.block + (m * BM + rowl);
-            *reinterpret_cast<float4 *>(p.part + prow * p.d_model + col) = v;
-          } else {
-            store_out4(p, (size_t)(t0 + rowl) * p.d_model + col, v);
-          }
+          gemm2_store<BM>(p, tl, rowl, col, v);
         }
       }
   }
+}
+
+// The same product with the gathered rows loaded straight into registers.  A row of W_down is contiguous along the
+// output columns, so 16 lanes of a load instruction ask for 128 contiguous bytes of one row, and the transposition that
+// MFMA wants (eight list positions of one column in a lane) is one byte permute per dword of eight rows' pieces.  Eight
+// (or four) wavefronts side by side, 64 columns each for all 128 tokens: nobody else in the workgroup wants a wavefront's
+// weights, only H passes through LDS.
+// v_mfma_f32_16x16x32_bf16: lane (c, q) holds list positions 8 q .. 8 q + 7 of a step's half of 32; MFMA tile f, column c
+// is output column 4 c + f, so a lane ends with four adjacent columns.
+// RM 0: the identity list; 1: the tile's list in an LDS table of 16-bit ids, as above.
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+__device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+constexpr int kDirectStages = 4, kDirectWaves = 8;
+template <int MT, int RM>
+__global__ __launch_bounds__(kDirectWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
+  constexpr int WN = kDirectWaves, BM = MT * 16, BN = WN * 64, S = kDirectStages, STAGE = BM * 128, D = 4, LA = BM / 8 / WN;
+  constexpr int NB = MT == 8 ? 2 : 4;         // halves of a step whose weights are on their way (as many as registers allow)
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, q = lane >> 4;
+  const Gemm2Tile tl = gemm2_tile<BM, BN, 64>(p, V, mt, N, xs);
+  if (!tl.valid) return;
+  const int Kb = tl.Kb, ntot = tl.ntot, kofs = tl.kofs, nk = tl.nk;
+  const int last = max(nk - 1, 0);
+
+  // H: copy i of a stage covers rows 8 (wave + i WN) .. + 7
+  const uint64_t a_base = (uint64_t)(uintptr_t)(p.h + (size_t)tl.t0 * p.hs + kofs);
+  uint32_t a_off[LA];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int trow = (wave + i * WN) * 8 + lane / 8;
+    a_off[i] = (uint32_t)(min(trow, tl.rows_valid - 1) * p.hs + ((lane & 7) ^ swz<64>(trow)) * 8) * 2u;
+  }
+  const uint32_t lds0 = lds_addr_of(smem);
+  // (no conditions in the loop: past the end the last step is requested again, into a slot nobody reads any more)
+  auto issue_a = [&](int st, int i) __attribute__((always_inline)) {
+    gload_lds16_off(a_base + (uint64_t)(uint32_t)min(st, last) * 128u, a_off[i], lds0 + (uint32_t)(st % S) * STAGE + (uint32_t)(wave + i * WN) * 1024u);
+  };
+  if (nk > 0) {
+#pragma unroll
+    for (int st = 0; st < S - 2; ++st)
+#pragma unroll
+      for (int i = 0; i < LA; ++i) issue_a(st, i);
+  }
+  uint16_t *tab = reinterpret_cast<uint16_t *>(smem + S * STAGE);
+  if (RM == 1) {
+    // eight list entries per thread in flight at a time (left to itself the loop waits for every load)
+    const int32_t *gl = p.idx + (size_t)tl.b * p.k_stride;
+    constexpr int U = 8;
+    for (int i0 = tid; i0 < nk * 64; i0 += U * WN * 64) {
+      int raw[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) raw[u] = gl[min(kofs + i0 + u * WN * 64, Kb - 1)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * WN * 64, pos = kofs + i;
+        if (i < nk * 64) tab[i] = (uint16_t)(pos < Kb ? min(max(raw[u], 0), p.d_ffn - 1) : (pos < ntot ? p.d_ffn + (pos - Kb) : 0));
+      }
+    }
+    __syncthreads();
+  }
+  const int colw = tl.n0 + wave * 64;                              // d_model is a multiple of 64: a wavefront is in or out
+  const int hi = c >> 3;                                           // which of a pair of rows this lane loads
+  const int col4 = 8 * (c & 7) + 4 * hi;                           // this lane's four columns, once the pairs have swapped
+  const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
+  const uint32_t col_bytes = (uint32_t)(min(colw, p.d_model - 64) + 8 * (c & 7)) * 2u;
+  const uint32_t lane_off = (8u * (uint32_t)q + (uint32_t)hi) * row_bytes + col_bytes;
+
+  f32x4_t acc[MT][4];                         // [token tile][f]
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int f = 0; f < 4; ++f) acc[i][f] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+  typedef const __attribute__((address_space(1))) u32x4_t *gptr_t;
+  typedef const __attribute__((address_space(1))) uint8_t *gbyte_t;
+  u32x4_t wb[NB][4];                          // [half of a step mod NB][i]: eight columns of row 8 q + 2 i + hi
+  u32x4_t ids[2];                             // ids of rows 8 q .. 8 q + 7 of the half requested next (by its parity)
+  u32x4_t af[D];                              // ring of token fragments
+  u32x4_t bf[2][4];                           // operands of the half at hand and of the next
+  // (halves are counted through the tile: half hh is half hh % 2 of step hh / 2)
+  auto fetch_ids = [&](int hh, int par) __attribute__((always_inline)) {
+    if (RM == 1) ids[par] = *reinterpret_cast<const u32x4_t *>(tab + min(hh, 2 * last + 1) * 32 + 8 * q);
+  };
+  // load i of half hh.  FAST: all of its positions are W_down rows, whose offsets fit 32 bits (the launcher's check);
+  // else each row's matrix is found lane by lane.
+  auto load_w = [&](int hh_, int par, int buf, int i, auto fast_tag) __attribute__((always_inline)) {
+    const int hh = min(hh_, 2 * last + 1);
+    const uint32_t id = RM == 1 ? (ids[par][i] >> (16 * hi)) & 0xffffu : 0u;
+    if (decltype(fast_tag)::value) {
+      if (RM == 1) {
+        wb[buf][i] = *(gptr_t)((uintptr_t)p.wd + (__umul24(id, row_bytes) + col_bytes));
+      } else {
+        const gbyte_t row0 = (gbyte_t)(uintptr_t)p.wd + (size_t)(uint32_t)(kofs + hh * 32 + 2 * i) * row_bytes;   // scalar
+        wb[buf][i] = *(gptr_t)(row0 + lane_off);
+      }
+    } else {
+      const int pos = kofs + hh * 32 + 8 * q + 2 * i + hi;
+      const uint32_t r = RM == 1 ? id : (uint32_t)(pos < Kb ? min(pos, p.d_ffn - 1) : (pos < ntot ? p.d_ffn + (pos - Kb) : 0));
+      const uintptr_t base = r < (uint32_t)p.d_ffn ? (uintptr_t)p.wd : (uintptr_t)p.wc2 - (size_t)p.d_ffn * row_bytes;
+      wb[buf][i] = *(gptr_t)(base + (size_t)r * row_bytes + col_bytes);
+    }
+  };
+  // Rows 2 i and 2 i + 1 lie in lanes c and c ^ 8, eight columns each.  Those lanes swap halves (DPP rotation by 8 within
+  // 16 lanes, written to eight of them), so that each holds both rows' pieces of its own four columns; one byte permute
+  // per dword then pairs the two rows.
+  auto make_bf = [&](int h, int buf, int i) __attribute__((always_inline)) {
+    constexpr int ROR8 = 0x128;
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const uint32_t lo = wb[buf][i][d], up = wb[buf][i][2 + d];
+      const uint32_t ev = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)up, ROR8, 0xf, 0xc, false);
+      const uint32_t od = (uint32_t)__builtin_amdgcn_update_dpp((int)up, (int)lo, ROR8, 0xf, 0x3, false);
+      bf[h][2 * d][i] = __builtin_amdgcn_perm(od, ev, 0x05040100u);
+      bf[h][2 * d + 1][i] = __builtin_amdgcn_perm(od, ev, 0x07060302u);
+    }
+  };
+  uint32_t aoff[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) aoff[h] = (uint32_t)(c * 128 + (((4 * h + q) ^ swz<64>(c)) << 4));
+  // fragment n of a step: half n / MT, token tile n % MT
+  auto frag = [&](int kt, int n) __attribute__((always_inline)) {
+    af[n % D] = *reinterpret_cast<const u32x4_t *>(smem + (kt % S) * STAGE + aoff[n / MT] + (n % MT) * 2048);
+  };
+  // One step of 64 positions.  During a half the next one's weights are permuted into operands, and those of half
+  // hh + 1 + NB take their registers; H of step kt + S - 2 is requested in the first half; in front of the last D
+  // fragments the workgroup makes sure that H of step kt + 1 has landed (its copies are older than the last 8
+  // requests).  The slot of H requested in a step was last read two steps before, hence by nobody who has passed the
+  // barrier in between.  PH: 2 kt mod NB.
+  // (Spreading the permutes over the half and taking the wait for LDS reads out of the barrier: 412 -> 376 us.)
+  auto step = [&](int kt, auto ph_tag, auto fast_tag) __attribute__((always_inline)) {
+    constexpr int PH = decltype(ph_tag)::value;
+#pragma unroll
+    for (int n = 0; n < 2 * MT; ++n) {
+      const int h = n / MT, r = n % MT;
+      if (n == 2 * MT - D) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+      const u32x4_t a = af[n % D];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) acc[r][f] = mfma16(a, bf[h][f], acc[r][f]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n + D < 2 * MT) frag(kt, n + D); else frag(kt + 1, n + D - 2 * MT);
+      if (n < LA) issue_a(kt + S - 2, n);
+      if (r == 1) fetch_ids(2 * kt + h + 2 + NB, h);
+      if (r >= MT - 4) {
+        const int i = r - (MT - 4), buf = (PH + h + 1) % NB;
+        make_bf(1 - h, buf, i);
+        load_w(2 * kt + h + 1 + NB, 1 - h, buf, i, fast_tag);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (nk > 0) {
+#pragma unroll
+    for (int h = 0; h < NB; ++h) {
+      fetch_ids(h, h & 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_w(h, h & 1, h, i, std::false_type{});
+    }
+    fetch_ids(NB, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) make_bf(0, 0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_w(NB, 0, 0, i, std::false_type{});
+    fetch_ids(NB + 1, 1);
+    asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int n = 0; n < D; ++n) frag(0, n);
+    __builtin_amdgcn_sched_barrier(0);
+    const int nfast = min((Kb - kofs) / 64, nk);
+    constexpr std::integral_constant<int, 0> ph0{};
+    constexpr std::integral_constant<int, 2> ph1{};
+    int kt = 0;
+    if (NB == 2) {
+      for (; kt + 2 < nfast; ++kt) step(kt, ph0, std::true_type{});
+      for (; kt < nk; ++kt) step(kt, ph0, std::false_type{});
+    } else {
+      for (; kt + 4 < nfast; kt += 2) {
+        step(kt, ph0, std::true_type{});
+        step(kt + 1, ph1, std::true_type{});
+      }
+      while (kt < nk) {
+        step(kt, ph0, std::false_type{});
+        if (++kt >= nk) break;
+        step(kt, ph1, std::false_type{});
+        ++kt;
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies requested past the end
+  }
+
+  const int col = colw + col4;
+  if (colw >= p.d_model) return;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int rowl = i * 16 + 4 * q + e;
+      if (rowl < tl.rows_valid)
+        gemm2_store<BM>(p, tl, rowl, col, make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]));
+    }
 }
 
 // ---- variant tables --------------------------------------------------------
@@ -893,6 +1129,11 @@ Variant g2() {
                   reinterpret_cast<const void *>(&ff_gemm2_kernel<WM, WN, TM, BK, S, 2, KG>),
                   // the streamed list only where the table may not fit and scalar loads cost too much
                   KG > 1 ? reinterpret_cast<const void *>(&ff_gemm2_kernel<WM, WN, TM, BK, S, (KG > 1 ? 3 : 2), KG>) : nullptr}};
+}
+template <int MT>
+Variant g2d() {
+  return Variant{reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 0>), MT * 16, kDirectWaves * 64, kDirectWaves * 64,
+                 kDirectStages * MT * 16 * 128, {reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 1>), nullptr, nullptr}};
 }
 constexpr int kIdRingBytes = 8 * 256;   // row-id mode 3: eight stages of 64 raw list entries
 
@@ -919,22 +1160,11 @@ const Variant kGemm2[] = {
     g2<4, 2, 2, 32, 3>(),  // 2: 256 x 256, 8 waves, 3 stages (96 KB)
     g2<1, 4, 2, 32, 3>(),  // 3: 64 x 512, 4 waves, 3 stages (108 KB)
     g2<2, 2, 2, 64, 3, 2>(),  // 4: 128 x 256, 8 waves in 2 k-groups, BK 64, 3 stages (144 KB)
+    g2d<8>(),                 // 5: 128 x 512, 8 waves, weights in registers (64 KB)
+    g2d<4>(),                 // 6: 64 x 512, weights in registers
 };
 constexpr int kNumGemm1 = sizeof(kGemm1) / sizeof(Variant);
 constexpr int kNumGemm2 = sizeof(kGemm2) / sizeof(Variant);
-
-// Tile choice: the largest M tile the block size fills; among those the first in
-// preference order that still gives (nearly) every CU a workgroup.
-int choose(const Variant *tab, const int *pref, int n_pref, int block, int n_blocks, int n_extent) {
-  int best = pref[0], best_tiles = -1;
-  for (int i = 0; i < n_pref; ++i) {
-    const Variant &v = tab[pref[i]];
-    const int tiles = n_blocks * ((block + v.bm - 1) / v.bm) * ((n_extent + v.bn - 1) / v.bn);
-    if (tiles >= 224) return pref[i];
-    if (tiles > best_tiles) { best = pref[i]; best_tiles = tiles; }
-  }
-  return best;
-}
 
 }  // namespace
 
@@ -1009,6 +1239,7 @@ static int up64(int v) { return (v + 63) / 64 * 64; }   // (tiles narrower than 
 constexpr int kRemainderVariant = 7;
 constexpr int kHeavySurplusVariant = 8;
 constexpr int kWide128 = 6;
+constexpr int kDirect128 = 5, kDirect64 = 6;   // the down-GEMM tiles with the weights in registers
 constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
 
 // Gate/up tiles by the cost of one round of 256 of them, relative to a round of the 128 x 256 tile (117 us at
@@ -1144,18 +1375,32 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
   const bool table_fits = p.d_ffn + p.rc <= 65536 && v.lds + tab_bytes <= g_lds_limit;
   const bool ring_fits = v.fn_rm[2] != nullptr && v.lds + kIdRingBytes <= g_lds_limit;
   const int mode = row_mode > 0 ? row_mode : (table_fits ? 1 : (ring_fits ? 3 : 2));
-  if (mode == 1 && table_fits) {
+  if (mode == 1 && table_fits && v.fn_rm[0] != nullptr) {
     v.lds += tab_bytes;
     v.fn = v.fn_rm[0];
   } else if (mode == 3 && ring_fits) {
     v.lds += kIdRingBytes;
     v.fn = v.fn_rm[2];
-  } else if (mode == 2) {
-    v.fn = v.fn_rm[1];
   } else {
-    v.fn = nullptr;
+    v.fn = mode == 2 ? v.fn_rm[1] : nullptr;
   }
   return v;
+}
+
+// What a round of 256 tiles costs, in us, with the weights coming from HBM: fixed + 64-position steps x (idle .. full:
+// a few workgroups on the chip, or all of it busy).  The tiles with the weights in registers run a step of 128 x 512 in 1.6 us
+// with the chip full (1.32 PFLOP/s dense), one of 64 x 512 in 1.1 to 1.24; alone on the chip they wait for their loads.  The 128 x 256 tile with both operands in LDS serves calls with few columns and blocks.
+// The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
+struct Gemm2Cost { int variant; double idle, full, fixed; };
+constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
+                                     {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
+static bool gemm2_direct(int variant) { return variant == kDirect128 || variant == kDirect64; }
+// whether the tile takes these lists of ntot positions: weights in registers need 32-bit offsets into W_down and the row ids in LDS
+static bool gemm2_takes(int variant, const Gemm2Params &p, int row_mode, int ntot) {
+  const Variant &v = kGemm2[variant];
+  if (!gemm2_direct(variant)) return v.lds + kIdRingBytes <= g_lds_limit;
+  if ((uint64_t)p.d_ffn * (uint64_t)p.d_model * 2u >> 32) return false;
+  return p.idx == nullptr ? v.lds <= g_lds_limit : with_rows(v, p, row_mode, 2 * up64(ntot)).fn != nullptr;
 }
 
 // every list cut into n pieces (n >= 2, p.split_part has room for them)
@@ -1196,47 +1441,43 @@ size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model) {
 hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int row_mode, int ksplit, int nsplit, hipStream_t s) {
   Gemm2Params p = p_in;
   const bool chosen = variant < 0;
-  // Few tiles: where the 128 x 256 tiles do not fill the chip, every list is cut into n pieces that run side by
-  // side, write fp32 partial sums and are added in piece order.  In us: a round of tiles costs 5 + 0.75 .. 1.1 per 64
-  // positions (the more CUs are busy, the slower each), the cut 5 for one more launch and its partial sums written and
-  // read once at 4.4 TB/s.  (Measured, whole lists against this choice: 4096/14336, K 7168: 100 tokens 91 -> 28;
-  // 2048/8192, K 4096, 700 tokens 58 -> 32; dense 3584/18944, 300 tokens 275 -> 80.)  Uncut the same tile is
-  // also faster than 64 x 512 ones while it takes one round (ten blocks of 64 tokens, K 3584: 83 -> 60).
-  // (A few much longer lists have a cut of their own, below, that leaves the other blocks' sums alone.)
-  if ((chosen && split < 0 && ksplit < 0 && nsplit < 0 && p.k.n_heavy == 0) || nsplit > 1) {
-    const Variant &v4 = kGemm2[chosen ? kHalf128Wide : std::min(variant, kNumGemm2 - 1)];
-    const long V = p.idx == nullptr ? (p.T + v4.bm - 1) / v4.bm : (long)p.n_blocks * ((p.block + v4.bm - 1) / v4.bm);
-    const long N = (p.d_model + v4.bn - 1) / v4.bn;
-    const size_t per_piece = (size_t)p.T * p.d_model * sizeof(float);
-    const long room = p.split_part != nullptr ? std::min<long>((long)(p.split_bytes / per_piece), kMaxPieces - 1) : 1;
-    const int ntot = p.k.k_max + p.rc;
-    int n = 1;
-    if (nsplit > 1) {
-      n = (int)std::min<long>(nsplit, room);
-    } else if (v4.lds <= g_lds_limit && V * N <= kNumCU) {
-      double best = 0.0;
-      for (int c = 1; c <= room && (c == 1 || ntot >= c * 64); ++c) {
-        const double steps = ((ntot + c - 1) / c + 63) / 64;
-        const double busy = std::min(1.0, (double)(V * N * c) / kNumCU);
-        const double cost = xcd_rounds(V, N * c) * (5.0 + steps * (0.75 + 0.35 * busy)) + (c > 1 ? 5.0 + c * (double)per_piece / 2.2e6 : 0.0);
-        if (c == 1 || cost < best * 0.97) { n = c; best = cost; }
+  const size_t per_piece = (size_t)p.T * p.d_model * sizeof(float);
+  const long room = p.split_part != nullptr ? std::min<long>((long)(p.split_bytes / per_piece), kMaxPieces - 1) : 1;
+  int pieces = nsplit > 1 ? (int)std::min<long>(nsplit, room) : 1;
+  if (chosen) {
+    // The tile, and into how many pieces every list is cut: the cheapest by the measured times above.  A cut adds one
+    // more launch and its partial sums written and read once (5 us + 0.25 per MB).  (A few much longer lists have a cut
+    // of their own, below, that leaves the other blocks' sums alone.)  In us, whole lists on the tiles with both operands in
+    // LDS against this choice: 4096/14336, K 7168: 64 blocks of 128 456 -> 378, one of 100 tokens 91 -> 28; K 3584, 64
+    // blocks of 64 172 -> 145; 2048/8192, K 4096, 700 tokens 58 -> 32; 3584/18944, K 10419, 128 blocks 1220 -> 1005; dense
+    // 4096/14336, 4096 tokens 474 -> 364; dense 3584/18944, 300 tokens 275 -> 75.
+    const bool may_cut = nsplit < 0 && split < 0 && ksplit < 0 && p.k.n_heavy == 0;
+    const int base = (p.k.n_heavy > 0 ? p.k.k_base : p.k.k_max) + p.rc, ntot = p.k.k_max + p.rc;
+    const int n0 = pieces;
+    double best = 0.0;
+    for (const Gemm2Cost &g : kGemm2Cost) {
+      const Variant &v = kGemm2[g.variant];
+      const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
+      const long N = (p.d_model + v.bn - 1) / v.bn;
+      for (int n = n0; n == n0 || (may_cut && n <= room && V * N * n <= 2 * kNumCU && ntot >= n * 64); ++n) {
+        if (!gemm2_takes(g.variant, p, row_mode, (ntot + n - 1) / n)) continue;
+        const int xs = xcd_groups(V, N * n);
+        const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N * n + (8 >> xs) - 1) / (8 >> xs));   // of the busiest XCD
+        const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
+        double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * g.full);
+        if (busy > 0.0) cost += g.fixed + steps * (g.idle + (g.full - g.idle) * busy);
+        if (n > 1) cost += 5.0 + (double)n * (double)per_piece / 4.0e6;
+        if (variant < 0 || cost < best * 0.98) { variant = g.variant; pieces = n; best = cost; }
       }
     }
-    if (n > 1) return launch_gemm2_cut(p, chosen ? kHalf128Wide : std::min(variant, kNumGemm2 - 1), n, row_mode, s);
-    if (chosen && v4.lds <= g_lds_limit && xcd_rounds(V, N) == 1 && (p.block <= 64 || p.idx == nullptr)) variant = kHalf128Wide;
   }
+  if (variant < 0 || variant >= kNumGemm2) return hipErrorInvalidValue;
+  if (pieces > 1) return launch_gemm2_cut(p, variant, pieces, row_mode, s);
   const int n_pad = (p.k.k_max + p.rc + 63) / 64 * 64;   // whole k-steps of the longest BK
   const int tab_bytes = ((2 * n_pad + 15) / 16) * 16;
   // the eight-wavefront 128 x 256 tile leaves 16 KB for that table; a longer list streams through
   // a small LDS ring instead (row-id mode 3)
   const int half128 = kHalf128Wide;
-  const int p64[] = {3}, p128[] = {0, half128, 1}, p256[] = {2, 0, half128, 1};
-  if (variant < 0) {
-    if (p.block >= 256) variant = choose(kGemm2, p256, 4, p.block, p.n_blocks, p.d_model);
-    else if (p.block > 64) variant = choose(kGemm2, p128, 3, p.block, p.n_blocks, p.d_model);
-    else variant = choose(kGemm2, p64, 1, p.block, p.n_blocks, p.d_model);
-  }
-  if (variant >= kNumGemm2) return hipErrorInvalidValue;
   if (p.idx == nullptr) {   // without a list the blocks mean nothing: token tiles of this variant's height
     p.block = kGemm2[variant].bm;
     p.n_blocks = (p.T + p.block - 1) / p.block;
@@ -1280,7 +1521,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
   const bool bigger = v.bm * v.bn > h.bm * h.bn;   // the main tile is larger than the second launch's
   if (split == 1 && N >= 2 && bigger) {
     nq = 1;
-  } else if (split < 0 && chosen && p.k.per_block == nullptr && bigger && v.lds * 2 > g_lds_limit) {
+  } else if (split < 0 && chosen && !gemm2_direct(variant) && p.k.per_block == nullptr && bigger && v.lds * 2 > g_lds_limit) {
     const long tiles = (long)V * N;
     const long full = tiles / kNumCU, rem = tiles % kNumCU;
     if (full >= 2 && rem > 0 && 2 * rem <= kNumCU) {

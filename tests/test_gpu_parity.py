@@ -582,6 +582,34 @@ def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
         ctx.set_workspace(keep)
 
 
+@pytest.mark.parametrize("variant", [5, 6])
+@pytest.mark.parametrize("rc,ks", [(0, [1, 64, 65, 320]), (8, [1064, 56, 127, 440]), (64, [128, 129, 1064, 640]), (24, [1064] * 4)])
+def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
+    """The down-GEMM tiles that load the gathered rows straight into registers (128 x 512 and 64 x 512): lists of
+    one to seventeen steps of 64, ends inside a step, steps that hold neurons and compensator units, the identity list
+    with and without a compensator, a short last block, columns that fill no whole tile.  Against the oracle at the
+    stated bars and against the tile with both operands in LDS (other order of the same fp32 sums: 1e-5)."""
+    c = Case(W.Shape("direct", 640, 1064, 3 * 96 + 33, 96, 8, max(rc, 8)))
+    ref = c.oracle_layer(ks, comp=rc > 0)
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=1064)
+    ref_d = O.dense_ffn(_f32(c.x_bits), c.host("w_gate"), c.host("w_up"), c.host("w_down").T)
+    ctx.ensure_workspace(c.shape, 1064)
+    out = {}
+    try:
+        for v in (1, variant):
+            ctx.set_option("gemm2_variant", v)
+            out[v] = c.gpu_sparse(ctx, idx, ks, comp=rc > 0, out_f32=True)
+            _check_y(out[v], ref.y, f"tile {v}, rc {rc}, ks {ks}")
+            y = torch.empty((c.T, 640), dtype=torch.float32, device=DEV)
+            ctx.dense_ffn(c.shape, c.x, c.w, y, B.OUT_F32)
+            _check_y(y, ref_d, f"tile {v}, dense")
+    finally:
+        ctx.set_option("gemm2_variant", -1)
+    assert (out[variant] - out[1]).abs().max().item() <= 1e-5
+    if min(ks) == 1064:   # the identity list with the compensator behind it, the library's own tiles
+        _check_y(c.gpu_sparse(ctx, idx, ks, comp=True, out_f32=True), ref.y, "identity list")
+
+
 @pytest.mark.parametrize("n_tokens,block", [(256, 64), (6, 4)])
 def test_calls_can_be_captured_in_a_hip_graph(n_tokens, block):
     """predict + sparse_ffn with one K for all blocks enqueue kernels only (no copies, no
