@@ -4,6 +4,8 @@
 // results are bitwise reproducible from run to run.
 #include "ff_internal.h"
 
+#include <algorithm>
+
 namespace {
 
 __device__ __forceinline__ void unpack8(const uint4 &v, double *o) {
@@ -35,7 +37,7 @@ __global__ __launch_bounds__(256) void ff_logits_kernel(const bf16_t *__restrict
 }
 
 // ---- Eq. 12, a_b = sum_t p_t x_t over one block, and its share of Eq. 13's first layer ----
-// grid (ceil(d_model/512), n_blocks), 256 threads: each lane owns 8 channels,
+// grid (ceil(d_model/512), n_blocks, shares of the r outputs), 256 threads: each lane owns 8 channels,
 // the four wavefronts take every fourth token and are summed in wave order.  The workgroup
 // then multiplies its 512 pooled channels into the first predictor layer, hpart[b][slice][j] =
 // sum_{c in slice} a_b[c] W1[c][j]; the next kernel adds the slices in slice order.
@@ -63,15 +65,20 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
       __syncthreads();
     }
     m = red1[0];
-    for (int i = tid; i < n; i += 256) p_s[i] = exp(z[t0 + i] - m);
     __syncthreads();
-    if (tid == 0) {
-      double s = 0.0;
-      for (int i = 0; i < n; ++i) s += p_s[i];
-      red1[1] = s;
+    double part = 0.0;
+    for (int i = tid; i < n; i += 256) {
+      const double e = exp(z[t0 + i] - m);
+      p_s[i] = e;
+      part += e;
     }
+    red1[tid] = part;
     __syncthreads();
-    const double s = red1[1];
+    for (int s = 128; s > 0; s >>= 1) {
+      if (tid < s) red1[tid] += red1[tid + s];
+      __syncthreads();
+    }
+    const double s = red1[0];
     for (int i = tid; i < n; i += 256) p_s[i] = p_s[i] / s;
     __syncthreads();
   }
@@ -133,14 +140,16 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
     // Thread (cl, o) takes the 8 outputs 8 o .. 8 o + 7 (one 16-byte load per channel) over the channels
     // cl, cl + CL, ... in ascending order, eight loads in flight; the CL partial sums of an output are then
     // added in cl order.
-    const int n_oct = r >> 3;                                   // <= 128
+    const int o_per = ((r >> 3) + gridDim.z - 1) / gridDim.z, o0 = blockIdx.z * o_per;
+    const int n_oct = min(o_per, (r >> 3) - o0);                // <= 128
+    if (n_oct <= 0) return;
     int o_ceil = 1;
     while (o_ceil < n_oct) o_ceil <<= 1;
-    const int CL = 256 / o_ceil;                                // >= 2 channel lanes
+    const int CL = 256 / o_ceil;                                // 2 .. 256 channel lanes
     const int o = tid % o_ceil, cl = tid / o_ceil;
     double acc8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (o < n_oct) {
-      const bf16_t *wp = w1 + (size_t)c_base * r + 8 * o;
+      const bf16_t *wp = w1 + (size_t)c_base * r + 8 * (o0 + o);
       int cq = cl;
       for (; cq + 7 * CL < n_ch; cq += 8 * CL) {
         uint4 wv[8];
@@ -168,14 +177,15 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
 #pragma unroll
     for (int q = 0; q < 8; ++q) ps[(cl * o_ceil + o) * 8 + q] = acc8[q];
     __syncthreads();
-    for (int j = tid; j < r; j += 256) {
+    for (int j = tid; j < 8 * n_oct; j += 256) {
       double tot = 0.0;
+#pragma unroll 8
       for (int q = 0; q < CL; ++q) tot += ps[q * o_ceil * 8 + j];
-      dst[j] = tot;
+      dst[8 * o0 + j] = tot;
     }
   } else {
     // any r: a thread per output, channels in ascending order
-    for (int j = tid; j < r; j += 256) {
+    for (int j = tid + 256 * blockIdx.z; j < r; j += 256 * gridDim.z) {
       const bf16_t *col = w1 + (size_t)c_base * r + j;
       double acc = 0.0;
       for (int cq = 0; cq < n_ch; ++cq) acc = fma(a_s[cq], (double)bf16_to_f32(col[(size_t)cq * r]), acc);
@@ -266,6 +276,96 @@ __global__ __launch_bounds__(256) void ff_scores_kernel(const double *__restrict
         *reinterpret_cast<double2 *>(dst) = make_double2(acc[0][i], acc[1][i]);
         *reinterpret_cast<double2 *>(dst + 2) = make_double2(acc[2][i], acc[3][i]);
       }
+  }
+}
+
+// The same layer for calls with too few blocks to fill the chip above (a workgroup there walks all r rows of its
+// 1024 columns: one block is 14 workgroups at d_ffn 14336).  Here a workgroup has 4 * QUADS columns and its THREADS / QUADS row
+// groups take every so-many-th row of W2, so that few rounds of loads are all a thread waits for; the groups' sums are
+// added through LDS in group order.  Bound by the latency of its two dependent rounds of loads.
+template <int BB, int QUADS, int THREADS>
+__global__ __launch_bounds__(THREADS) void ff_scores_split_kernel(const double *__restrict__ hpart,
+                                                                  const bf16_t *__restrict__ w2,
+                                                                  double *__restrict__ scores, int n_blocks, int r,
+                                                                  int n_slices, int d_ffn) {
+  constexpr int JG = THREADS / QUADS, LD = 8;
+  extern __shared__ double hid[];          // [BB][r]
+  __shared__ __align__(16) double red[JG][4 * QUADS];
+  const int tid = threadIdx.x, g = tid / QUADS;
+  const int b0 = blockIdx.y * BB;
+  const int nb = min(BB, n_blocks - b0);
+  const int n_quads = d_ffn >> 2;
+  const int quad = (int)(blockIdx.x * QUADS) + tid % QUADS;
+  const bf16_t *wp = w2 + 4 * min(quad, n_quads - 1);       // past the end: the last group again, not stored
+  // the first rows are on their way while the hidden units are formed
+  uint2 wv[LD];
+#pragma unroll
+  for (int u = 0; u < LD; ++u) wv[u] = *reinterpret_cast<const uint2 *>(wp + (size_t)min(g + u * JG, r - 1) * d_ffn);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int e = tid; e < BB * r; e += THREADS) {
+    const int i = e / r, j = e - i * r;
+    double acc = 0.0;
+    if (i < nb) {
+      const double *src = hpart + (size_t)(b0 + i) * n_slices * r + j;
+      int s = 0;
+      for (; s + 8 <= n_slices; s += 8) {      // eight loads in flight, added in slice order
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(s + u) * r];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+      }
+      for (; s < n_slices; ++s) acc += src[(size_t)s * r];
+    }
+    hid[e] = fmax(acc, 0.0);
+  }
+  __syncthreads();
+  double acc[BB][4];
+#pragma unroll
+  for (int i = 0; i < BB; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[i][q] = 0.0;
+  for (int j = g; j < r; j += LD * JG) {
+    uint2 nx[LD];
+    const int jn = j + LD * JG;
+    if (jn < r) {
+#pragma unroll
+      for (int u = 0; u < LD; ++u) nx[u] = *reinterpret_cast<const uint2 *>(wp + (size_t)min(jn + u * JG, r - 1) * d_ffn);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < LD; ++u)
+      if (j + u * JG < r) {
+        const double wd[4] = {(double)__uint_as_float(wv[u].x << 16), (double)__uint_as_float(wv[u].x & 0xffff0000u),
+                              (double)__uint_as_float(wv[u].y << 16), (double)__uint_as_float(wv[u].y & 0xffff0000u)};
+#pragma unroll
+        for (int i = 0; i < BB; ++i) {
+          const double hv = hid[i * r + j + u * JG];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[i][q] = fma(hv, wd[q], acc[i][q]);
+        }
+      }
+    if (jn < r) {
+#pragma unroll
+      for (int u = 0; u < LD; ++u) wv[u] = nx[u];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < BB; ++i) {
+    if (i >= nb) break;
+    double *mine = &red[g][4 * (tid % QUADS)];
+    *reinterpret_cast<double2 *>(mine) = make_double2(acc[i][0], acc[i][1]);
+    *reinterpret_cast<double2 *>(mine + 2) = make_double2(acc[i][2], acc[i][3]);
+    __syncthreads();
+    const int col = (int)(blockIdx.x * QUADS) * 4 + tid;
+    if (tid < 4 * QUADS && col < d_ffn) {
+      double tot = 0.0;
+#pragma unroll 8
+      for (int q = 0; q < JG; ++q) tot += red[q][tid];
+      scores[(size_t)(b0 + i) * d_ffn + col] = tot;
+    }
+    __syncthreads();
   }
 }
 
@@ -685,23 +785,40 @@ static int g_topk_lds_raised = 0;
 
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
   const int n_slices = (p.d_model + 511) / 512;
+  // Few blocks: the first layer's outputs are shared out over up to 8 workgroups per slice (each pools the slice again),
+  // at least 32 outputs each, until there is one for every CU (d_model 4096, r 256: one token 7.5 -> 5.3 us, a block of
+  // 100 9.0 -> 7.5, 16 blocks 12.8 -> 11.6).
+  int oz = 256 / (n_slices * p.n_blocks);
+  oz = std::max(1, std::min({oz, 8, p.r / 32}));
   prof_begin(prof, FF_STAGE_POOL, s);
   if (p.q_pred) {
     hipLaunchKernelGGL(ff_logits_kernel, dim3((p.T + 3) / 4), dim3(256), 0, s, p.x, p.q_pred, p.z,
                        p.T, p.d_model);
-    hipLaunchKernelGGL(ff_pool_kernel<true>, dim3(n_slices, p.n_blocks), dim3(256),
+    hipLaunchKernelGGL(ff_pool_kernel<true>, dim3(n_slices, p.n_blocks, oz), dim3(256),
                        (size_t)p.block * sizeof(double), s, p.x, p.z, p.w1, p.hpart, p.T, p.d_model,
                        p.block, p.r);
   } else {
-    hipLaunchKernelGGL(ff_pool_kernel<false>, dim3(n_slices, p.n_blocks), dim3(256),
+    hipLaunchKernelGGL(ff_pool_kernel<false>, dim3(n_slices, p.n_blocks, oz), dim3(256),
                        0, s, p.x, (const double *)nullptr, p.w1, p.hpart, p.T, p.d_model, p.block, p.r);
   }
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_MLP, s);
   const int n_groups = (p.n_blocks + MLP_BB - 1) / MLP_BB;
-  hipLaunchKernelGGL(ff_scores_kernel, dim3((p.d_ffn + 1023) / 1024, n_groups), dim3(256),
-                     (size_t)MLP_BB * p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r,
-                     n_slices, p.d_ffn);
+  // One or two blocks: 128 columns per workgroup and 32 row groups, else 256 columns and 8 row groups with every weight
+  // shared by four blocks, as long as 1024 columns per workgroup would leave half of the CUs without one.  (d_ffn 14336,
+  // r 256: one block 14.1 -> 4.5 us, 16 blocks 18.2 -> 8.2; d_ffn 8192, r 128: 6 blocks 9.1 -> 5.4, 32 blocks 9.2 -> 5.6.
+  // Beyond that the hidden units, which every workgroup forms again, cost the narrow ones what they gain.)
+  if (p.n_blocks <= 2) {
+    hipLaunchKernelGGL((ff_scores_split_kernel<1, 32, 1024>), dim3((p.d_ffn + 127) / 128, p.n_blocks), dim3(1024),
+                       (size_t)p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);
+  } else if (n_groups * ((p.d_ffn + 1023) / 1024) <= 128) {
+    hipLaunchKernelGGL((ff_scores_split_kernel<MLP_BB, 64, 512>), dim3((p.d_ffn + 255) / 256, n_groups), dim3(512),
+                       (size_t)MLP_BB * p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);
+  } else {
+    hipLaunchKernelGGL(ff_scores_kernel, dim3((p.d_ffn + 1023) / 1024, n_groups), dim3(256),
+                       (size_t)MLP_BB * p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r,
+                       n_slices, p.d_ffn);
+  }
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_TOPK, s);
   if (p.d_ffn <= 16 * 1024) {

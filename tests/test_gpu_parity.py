@@ -865,6 +865,23 @@ def test_predictor_ranks_and_widths(ctx, r):
             _assert_indices(idx, ref.indices, ks)
 
 
+@pytest.mark.parametrize("n_blocks", [1, 2, 3, 9, 33])
+@pytest.mark.parametrize("df,r", [(8, 3), (264, 32), (1016, 72), (4104, 264)])
+def test_predictor_few_blocks(ctx, n_blocks, df, r):
+    """The kernels that share one or a few blocks out over the chip, at column counts around their tiles (128 and 256), ranks
+    around their batches of rows (256 and 64) and outputs cut into uneven shares; scores and lists as above."""
+    shp = W.Shape(f"few{n_blocks}_{df}_{r}", 640, df, n_blocks * 20 - 7, 20, r, 8)
+    c = Case(shp, with_q=n_blocks % 2 == 1, seed=5 + df + n_blocks)
+    ks = [max(1, df // 3)] * n_blocks
+    ref = c.oracle_layer(ks, compute_ffn=False)
+    idx, sc = c.gpu_predict(ctx, ks, k_stride=max(ks), scores=True)
+    q = _f32(c.lt.q_pred) if n_blocks % 2 == 1 else None
+    x = _f32(c.x_bits)
+    ref_s = np.stack([O.predictor_scores(x[b * 20:(b + 1) * 20], q, c.host("w1"), c.host("w2")) for b in range(n_blocks)])
+    np.testing.assert_allclose(sc.cpu().numpy(), ref_s, rtol=1e-12, atol=1e-13 * np.abs(ref_s).max())
+    _assert_indices(idx, ref.indices, ks)
+
+
 def test_diagnostic_calls(ctx):
     a = torch.arange(1 << 20, dtype=torch.int32, device=DEV)
     b = torch.zeros_like(a)
