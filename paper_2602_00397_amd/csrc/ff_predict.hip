@@ -388,24 +388,31 @@ __device__ __forceinline__ double key_score(unsigned long long k) {
   return __longlong_as_double((long long)u);
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(v, d);
-    if (lane >= d) v += t;
-  }
-  return v;
+// inclusive prefix sum over the wavefront by data-parallel-primitive lane exchanges (six lane exchanges through LDS, each
+// waiting for the one before, take several times as long): shifts inside the rows of 16 lanes, then each row's last lane
+// into the rows above
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add_step(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v = dpp_add_step<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
+  v = dpp_add_step<0x112, 0xf>(v);
+  v = dpp_add_step<0x114, 0xf>(v);
+  v = dpp_add_step<0x118, 0xf>(v);
+  v = dpp_add_step<0x142, 0xa>(v);   // lane 15 into row 1, lane 47 into row 3
+  return dpp_add_step<0x143, 0xc>(v);   // lane 31 into rows 2 and 3
 }
 
 // exclusive prefix over the 1024 threads of the block; total returned too
 __device__ __forceinline__ int block_excl_scan(int v, int *wsum, int &total) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int inc = wave_incl_scan(v, lane);
+  const int inc = wave_incl_scan(v);
   if (lane == 63) wsum[wave] = inc;
   __syncthreads();
   if (wave == 0) {
     const int w = lane < 16 ? wsum[lane] : 0;
-    const int ws = wave_incl_scan(w, lane);
+    const int ws = wave_incl_scan(w);
     if (lane < 16) wsum[lane] = ws - w;
     if (lane == 15) wsum[16] = ws;
   }
@@ -432,20 +439,27 @@ struct TopkShared {
 
 // The key theta of the K-th largest score and the number of keys equal to theta that are kept, found
 // exactly by the 1024 threads of a workgroup.  each(fn) calls fn(key) once for every key the calling thread
-// owns.  [lo_v, hi_v] encloses the scores (it only shapes the bucket map); need_radix skips the buckets.
+// owns, as fn(key, score rounded to fp32).  [lo_v, hi_v] encloses the scores (it only shapes the bucket map); need_radix
+// skips the buckets.  The map works on fp32 roundings of the scores (fp64 arithmetic on every key, twice, took longer than
+// the histogram itself; with the scans below by lane exchanges one block of 14336 scores 13.8 -> 11.9 us, 16 blocks
+// 19.1 -> 15.7): rounding is monotone too, and scores that fp32 cannot tell apart share a bucket or, where it has
+// no ordered range for them at all, go to the radix path.
 // On entry sh.hist is zero, sh.n_cand is 0 and a barrier has been passed.
 template <class Each>
 __device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_v, double hi_v, bool need_radix,
                                                Each each, unsigned long long &theta, int &ties_taken) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const double scale = need_radix ? 0.0 : (double)TOPK_BUCKETS / (hi_v - lo_v);
+  const float lo_f = (float)lo_v, range_f = (float)hi_v - lo_f;
+  // (1e-30 and 1e30 keep the scale, and every product with it, a finite number)
+  need_radix = need_radix || !(range_f > 1e-30f && fabsf(lo_f) < 1e30f && range_f < 1e30f);
+  const float scale = need_radix ? 0.0f : (float)TOPK_BUCKETS / range_f;
   // monotone: s1 <= s2 implies bucket(s1) <= bucket(s2), so a key in a higher bucket is a larger key
-  auto bucket_of = [&](unsigned long long k) -> int {
-    const double t = (key_score(k) - lo_v) * scale;
+  auto bucket_of = [&](float s) -> int {
+    const float t = (s - lo_f) * scale;
     return min(TOPK_BUCKETS - 1, max(0, (int)t));
   };
   if (!need_radix) {
-    each([&](unsigned long long k) { atomicAdd(&sh.hist[bucket_of(k)], 1u); });
+    each([&](unsigned long long, float s) { atomicAdd(&sh.hist[bucket_of(s)], 1u); });
     __syncthreads();
     // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = keys in higher buckets
     int local = 0;
@@ -469,17 +483,22 @@ __device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_
     if (c > TOPK_CAND) {
       need_radix = true;                          // uniform: every thread reads the same hist[tb]
     } else {
-      each([&](unsigned long long k) {
-        if (bucket_of(k) == tb) sh.cand[atomicAdd(&sh.n_cand, 1u)] = k;
+      each([&](unsigned long long k, float s) {
+        if (bucket_of(s) == tb) sh.cand[atomicAdd(&sh.n_cand, 1u)] = k;
       });
       __syncthreads();
       if (tid < c) {
         const unsigned long long mine = sh.cand[tid];
         int n_gt = 0, n_eq = 0;
-        for (int j = 0; j < c; ++j) {
-          const unsigned long long o = sh.cand[j];
-          n_gt += o > mine;
-          n_eq += o == mine;
+        for (int j0 = 0; j0 < c; j0 += 8) {          // eight reads in flight
+          unsigned long long o[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) o[u] = sh.cand[min(j0 + u, c - 1)];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            n_gt += j0 + u < c && o[u] > mine;
+            n_eq += j0 + u < c && o[u] == mine;
+          }
         }
         // the need-th largest of the bucket: n_gt < need <= n_gt + n_eq (all holders of that key agree)
         if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; }
@@ -496,7 +515,7 @@ __device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_
       __syncthreads();
       if (tid < 256) sh.hist[tid] = 0;
       __syncthreads();
-      each([&](unsigned long long k) {
+      each([&](unsigned long long k, float) {
         const bool match = (pass == 7) || ((k >> (shift + 8)) == prefix);
         if (match) atomicAdd(&sh.hist[(unsigned int)(k >> shift) & 255u], 1u);
       });
@@ -587,7 +606,7 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
   unsigned long long theta;
   int ties_taken;
   topk_threshold(sh, K, lo_v, hi_v, need_radix,
-                 [&](auto fn) __attribute__((always_inline)) { for (int i = tid; i < d_ffn; i += 1024) fn(key_at(i)); },
+                 [&](auto fn) __attribute__((always_inline)) { for (int i = tid; i < d_ffn; i += 1024) fn(key_at(i), (float)sc[i]); },
                  theta, ties_taken);
 
   if (LDS_MODE == 1) {
@@ -620,10 +639,10 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
   __syncthreads();
   // every wavefront scans the 16 pairs itself: lane l < 16 holds wavefront l's totals
   const int e_l = lane < 16 ? wcnt_eq[lane] : 0;
-  const int e_incl = wave_incl_scan(e_l, lane);
+  const int e_incl = wave_incl_scan(e_l);
   const int quota_l = max(0, min(e_l, ties_taken - (e_incl - e_l)));
   const int kept_l = (lane < 16 ? wsum[lane] : 0) + quota_l;
-  const int kept_incl = wave_incl_scan(kept_l, lane);
+  const int kept_incl = wave_incl_scan(kept_l);
   int eq_seen = __shfl(e_incl - e_l, wave);          // ties at lower indices than this wavefront's range
   int pos = __shfl(kept_incl - kept_l, wave);        // kept indices below this wavefront's range
   const unsigned long long lower = (1ull << lane) - 1ull;
@@ -683,6 +702,7 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
   // shapes the bucket map, so bounds that enclose it are as good as the exact ends: the high words of
   // the smallest and largest key, which cost 32-bit wavefront reductions.
   unsigned long long key[ROWS];
+  float score[ROWS];
   unsigned int lo_w = 0xffffffffu, hi_w = 0u;
 #pragma unroll
   for (int u0 = 0; u0 < ROWS; u0 += 16) {
@@ -694,6 +714,7 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
     for (int u = 0; u < 16; ++u)
       if (u0 + u < ROWS) {
         key[u0 + u] = score_key(v[u]);
+        score[u0 + u] = (float)v[u];
         lo_w = min(lo_w, (unsigned int)(key[u0 + u] >> 32));
         hi_w = max(hi_w, (unsigned int)(key[u0 + u] >> 32));
       }
@@ -717,7 +738,7 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
                  [&](auto fn) __attribute__((always_inline)) {
 #pragma unroll
                    for (int u = 0; u < ROWS; ++u)
-                     if (valid(u)) fn(key[u]);
+                     if (valid(u)) fn(key[u], score[u]);
                  },
                  theta, ties_taken);
 
@@ -743,7 +764,7 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
     int e[PER], g[PER], es = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) { e[q] = cnt_eq[lane * PER + q]; g[q] = cnt_gt[lane * PER + q]; es += e[q]; }
-    int eq_before = wave_incl_scan(es, lane) - es;   // ties at lower indices than this lane's entries
+    int eq_before = wave_incl_scan(es) - es;   // ties at lower indices than this lane's entries
     int ks_ = 0, kept[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -754,7 +775,7 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
       eq_before += eq_q;
       ks_ += kept[q];
     }
-    int pos = wave_incl_scan(ks_, lane) - ks_;
+    int pos = wave_incl_scan(ks_) - ks_;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       cnt_eq[lane * PER + q] = e[q];
@@ -807,7 +828,7 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   // One or two blocks: 128 columns per workgroup and 32 row groups, else 256 columns and 8 row groups with every weight
   // shared by four blocks, as long as 1024 columns per workgroup would leave half of the CUs without one.  (d_ffn 14336,
   // r 256: one block 14.1 -> 4.5 us, 16 blocks 18.2 -> 8.2; d_ffn 8192, r 128: 6 blocks 9.1 -> 5.4, 32 blocks 9.2 -> 5.6.
-  // Beyond that the hidden units, which every workgroup forms again, cost the narrow ones what they gain.)
+  // 64 blocks at d_ffn 14336 take 21.4 us as they are, 23.0 this way: every workgroup forms the hidden units again.)
   if (p.n_blocks <= 2) {
     hipLaunchKernelGGL((ff_scores_split_kernel<1, 32, 1024>), dim3((p.d_ffn + 127) / 128, p.n_blocks), dim3(1024),
                        (size_t)p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);

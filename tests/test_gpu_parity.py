@@ -953,6 +953,29 @@ def test_heavy_ties_at_the_threshold(ctx, df):
     _assert_indices(idx, [O.select_topk(s2[b], ks[b]) for b in range(2)], ks)
 
 
+@pytest.mark.parametrize("df", [2048, 20480, 28672, 40960])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -110, 2.0 ** 80])
+def test_scores_that_fp32_cannot_tell_apart(ctx, df, scale):
+    """The bucket map of the top-K kernels works on fp32 roundings: scores 2^26 + 0 .. 255 (fp32 steps of 8 there), and the
+    same so small or so large that the map has no use for them, are selected by their fp64 values all the same."""
+    def bits(a):
+        return (np.asarray(a, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    dm, T, r = 128, 64, 8
+    w1, w2 = np.zeros((dm, r)), np.zeros((r, df))
+    w1[0, 0], w1[0, 1] = 2.0 ** 20, 1.0
+    w2[0], w2[1] = 64.0 * scale, np.random.default_rng(df).integers(0, 256, df) * scale
+    s = 2.0 ** 20 * w2[0] + w2[1]
+    xd, w1d, w2d = (B.to_device_bf16(bits(a), DEV) for a in (np.ones((T, dm)), w1, w2))
+    shape = B.Shape(dm, df, T, 64, r, 0)
+    pred = B.Predictor(None, w1d.data_ptr(), w2d.data_ptr())
+    ctx.ensure_workspace(shape, df)
+    for k in (1, df // 3, df // 2 + 1, df):
+        idx = torch.empty((1, k), dtype=torch.int32, device=DEV)
+        ctx.predict(shape, xd, pred, [k], k, idx, None)
+        np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
+
+
 @pytest.mark.parametrize("df", [2048, 40960])
 def test_scores_that_are_not_finite_still_give_a_valid_list(ctx, df):
     """Scores are expected to be finite.  If they are not (an infinity among the hidden states makes
