@@ -1423,6 +1423,7 @@ static hipError_t launch_gemm2_cut(Gemm2Params p, int variant, int n, int row_mo
 }
 
 constexpr int kMaxShortPieces = kMaxPieces - 1;
+constexpr int kMaxFreePieces = 4;   // what the launcher takes by itself: more partial sums cost more than shorter pieces gain
 constexpr size_t kPartCapBytes = (size_t)48 << 20;
 
 constexpr size_t kSplitCapBytes = (size_t)96 << 20;
@@ -1455,7 +1456,13 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     const int base = (p.k.n_heavy > 0 ? p.k.k_base : p.k.k_max) + p.rc, ntot = p.k.k_max + p.rc;
     const int n0 = pieces;
     double best = 0.0;
+    // A few much longer lists that will be cut (below): their pieces start first, on CUs that the common tiles leave idle
+    // where there are such, else ahead of everybody.  That favours the large tiles with the weights in registers, which
+    // leave the most; the others only where those do not apply.
+    const int surplus = up64(ntot) - up64(base);
+    const bool heavy_cut = split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= up64(base);
     for (const Gemm2Cost &g : kGemm2Cost) {
+      if (heavy_cut && variant >= 0 && gemm2_direct(variant) && !gemm2_direct(g.variant)) break;
       const Variant &v = kGemm2[g.variant];
       const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
       const long N = (p.d_model + v.bn - 1) / v.bn;
@@ -1467,7 +1474,16 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
         double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * g.full);
         if (busy > 0.0) cost += g.fixed + steps * (g.idle + (g.full - g.idle) * busy);
         if (n > 1) cost += 5.0 + (double)n * (double)per_piece / 4.0e6;
-        if (variant < 0 || cost < best * 0.98) { variant = g.variant; pieces = n; best = cost; }
+        if (heavy_cut) {
+          const long heavy = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;
+          const long free_pieces = std::max<long>(1, std::min<long>(kNumCU / heavy, kMaxFreePieces));
+          const double piece_steps = (double)((surplus + free_pieces - 1) / free_pieces) / 64;
+          if (V * N + heavy * free_pieces <= kNumCU)
+            cost = g.fixed + steps * (g.idle + (g.full - g.idle) * (double)(V * N + heavy * free_pieces) / kNumCU);
+          else
+            cost += (double)((heavy * free_pieces + kNumCU - 1) / kNumCU) * (g.fixed + piece_steps * g.full);
+        }
+        if (variant < 0 || cost < best * (heavy_cut ? 0.9 : 0.98)) { variant = g.variant; pieces = n; best = cost; }
       }
     }
   }
@@ -1498,8 +1514,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
   if (ksplit != 0 && split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= cut0) {
     const long heavy_tiles = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;
     const size_t per_piece = (size_t)p.k.n_heavy * p.block * p.d_model * sizeof(float);
-    long want = ksplit > 0 ? ksplit : kNumCU / heavy_tiles;
-    want = std::min<long>(want, kMaxShortPieces);
+    long want = std::min<long>(ksplit > 0 ? ksplit : kNumCU / heavy_tiles, ksplit > 0 ? kMaxShortPieces : kMaxFreePieces);
     want = std::min<long>(want, (long)(p.part_bytes / per_piece) - 1);
     if (want >= (ksplit > 0 ? 1 : 2)) {
       const int len = std::max(256, (int)((surplus + want - 1) / want + 63) / 64 * 64);
