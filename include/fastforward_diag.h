@@ -22,7 +22,8 @@ extern "C" {
  *   "gemm1_split"  -1 = decide by shape, 0 = never, 1 = always: whether the
  *       list positions beyond the last full tile of the gate/up GEMM (the
  *       compensator's units, typically) run as a second launch of small tiles
- *       (-1 never splits under a forced gemm1_variant).
+ *       (-1 never splits under a forced gemm1_variant; tiles of less than 64
+ *       positions take a list whole, whatever this says).
  *   "gemm1_heavy_tiles"  -1 / 0 / 1 likewise: whether, in a split launch, the
  *       positions of a few much longer lists (first and last block dense)
  *       beyond the common length run as a launch of their own with small tiles

@@ -86,5 +86,16 @@ def build_host_checks() -> str:
     return exe
 
 
+def build_launch_checks() -> str:
+    """csrc/ff_launch_checks.hip with the GEMM launchers' object file (as build() left it): the program records their
+    launches instead of making them, so it needs no GPU."""
+    exe = os.path.join(OBJ, "ff_launch_checks")
+    obj = os.path.join(OBJ, "ff_launch_checks.o")
+    _run([HIPCC, *FLAGS, "-c", os.path.join(CSRC, "ff_launch_checks.hip"), "-o", obj])
+    _run([HIPCC, "--offload-arch=gfx950", obj, os.path.join(OBJ, "ff_gemm.o"), "-o", exe,
+          "-Wl,-rpath," + os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "lib")])
+    return exe
+
+
 if __name__ == "__main__":
     print(build(verbose=True, extra_flags=sys.argv[1:]))

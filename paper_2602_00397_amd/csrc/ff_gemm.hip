@@ -1316,7 +1316,9 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
   // little work over the whole chip.
   const int rem = n_extent % v.bn;
   bool do_split = false;
-  if ((chosen ? split != 0 : split > 0) && (rem > 0 || ragged) && n_extent >= v.bn && (!chosen || v.bn >= 128) && variant != kRemainderVariant) {
+  // (Never with a tile of less than 64 positions, forced or not: H is zero up to the next multiple of 64 behind a list, and
+  // a remainder that may start on any multiple of 32 would leave that to nobody where a list ends on one.)
+  if ((chosen ? split != 0 : split > 0) && (rem > 0 || ragged) && n_extent >= v.bn && v.bn >= (chosen ? 128 : 64) && variant != kRemainderVariant) {
     const int n_full = base_extent / v.bn;
     const int per_cu = g_lds_limit / v.lds > 0 ? (g_lds_limit / v.lds > 2 ? 2 : g_lds_limit / v.lds) : 1;
     const int slots = kNumCU * per_cu;

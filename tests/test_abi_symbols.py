@@ -109,6 +109,17 @@ def test_host_code_under_sanitizers_without_a_gpu():
     assert "0 wrong" in out
 
 
+def test_launchers_give_the_kernels_what_they_assume():
+    """csrc/ff_launch_checks.hip: the GEMM launchers over shapes, list lengths and options with every launch recorded
+    instead of made; each must fit what its kernel assumes."""
+    import subprocess
+    exe = os.path.join(ROOT, "paper_2602_00397_amd", "_build", "ff_launch_checks")
+    if not os.path.exists(exe):
+        pytest.skip("ff_launch_checks not built (python -c 'import __graft_entry__ as g; g.build()')")
+    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0 and ", 0 wrong" in r.stdout, r.stdout
+
+
 @pytest.mark.gpu
 def test_host_code_under_sanitizers_with_a_gpu():
     """The same program on a machine with a GPU: every argument error of every compute call (nothing

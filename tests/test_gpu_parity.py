@@ -418,6 +418,41 @@ def test_gemm1_remainder_split(ctx, c0):
         ctx.set_option("gemm1_split", -1)
 
 
+def _variants(ctx, option):
+    """Every tile number the option takes, each set in turn."""
+    v = 0
+    while True:
+        try:
+            ctx.set_option(option, v)
+        except B.FFError:
+            return
+        yield v
+        v += 1
+
+
+def test_list_ends_of_every_gate_up_tile_and_split(ctx):
+    """The gate/up GEMM leaves H zero from a block's last position up to the next multiple of 64, where the down GEMM
+    reads on.  Every gate/up tile with and without the remainder launch, lists of unequal length that end on an odd
+    multiple of 32, off every multiple and on a whole tile, in a workspace full of NaN: one position left out gives NaN."""
+    try:
+        ctx.set_option("merge_blocks", 0)
+        for block, rc, ks in ((128, 8, [96, 96, 100]), (128, 8, [88, 280, 100]), (64, 8, [96, 224, 160, 96, 37]), (300, 32, [64, 600])):
+            c = Case(W.Shape("ends", 256, 640, block * (len(ks) - 1) + 17, block, 8, rc))
+            for comp in (False, True):
+                ref = c.oracle_layer(ks, comp=comp)
+                idx, _ = c.gpu_predict(ctx, ks, k_stride=640)
+                for v in _variants(ctx, "gemm1_variant"):
+                    for split in (0, 1):
+                        ctx.set_option("gemm1_split", split)
+                        ctx._ws.fill_(0xFF)
+                        _check_y(c.gpu_sparse(ctx, idx, ks, comp=comp, out_f32=True), ref.y, f"tile {v} split {split} ks {ks} comp {comp}")
+                ctx.set_option("gemm1_variant", -1)
+    finally:
+        ctx.set_option("gemm1_variant", -1)
+        ctx.set_option("gemm1_split", -1)
+        ctx.set_option("merge_blocks", -1)
+
+
 @pytest.mark.parametrize("n_blocks", [1, 2, 3, 5, 7, 9, 12, 17])
 def test_block_counts_that_do_not_divide_the_xcds(ctx, n_blocks):
     """The XCDs share (blocks x tiles) in a way that depends on the block count: every tile of every block must be
