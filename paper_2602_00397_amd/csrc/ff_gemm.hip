@@ -1397,11 +1397,19 @@ struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
 static bool gemm2_direct(int variant) { return variant == kDirect128 || variant == kDirect64; }
-// whether the tile takes these lists of ntot positions: weights in registers need 32-bit offsets into W_down and the row ids in LDS
+// Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
+// product of two 24-bit numbers in 32 bits, a token's offset into a tile of H has 32 bits too.
+static bool gemm2_direct_addresses(const Gemm2Params &p) {
+  const uint64_t row_bytes = (uint64_t)p.d_model * 2u;
+  if (row_bytes >> 24 || (uint64_t)kGemm2[kDirect128].bm * (uint64_t)p.hs * 2u >> 32) return false;
+  return p.idx == nullptr || (uint64_t)p.d_ffn * row_bytes >> 32 == 0;
+}
+// whether the launcher takes the tile for these lists of ntot positions: weights in registers need W_down below 4 GiB and the
+// row ids in LDS
 static bool gemm2_takes(int variant, const Gemm2Params &p, int row_mode, int ntot) {
   const Variant &v = kGemm2[variant];
   if (!gemm2_direct(variant)) return v.lds + kIdRingBytes <= g_lds_limit;
-  if ((uint64_t)p.d_ffn * (uint64_t)p.d_model * 2u >> 32) return false;
+  if (!gemm2_direct_addresses(p) || (uint64_t)p.d_ffn * (uint64_t)p.d_model * 2u >> 32) return false;
   return p.idx == nullptr ? v.lds <= g_lds_limit : with_rows(v, p, row_mode, 2 * up64(ntot)).fn != nullptr;
 }
 
@@ -1492,6 +1500,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     }
   }
   if (variant < 0 || variant >= kNumGemm2) return hipErrorInvalidValue;
+  if (gemm2_direct(variant) && !gemm2_direct_addresses(p)) return hipErrorInvalidValue;   // forced
   if (pieces > 1) return launch_gemm2_cut(p, variant, pieces, row_mode, s);
   const int n_pad = (p.k.k_max + p.rc + 63) / 64 * 64;   // whole k-steps of the longest BK
   const int tab_bytes = ((2 * n_pad + 15) / 16) * 16;

@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <set>
 #include <vector>
 
 #include "ff_internal.h"
@@ -13,13 +14,16 @@ struct Launch {
   unsigned grid, threads;
   size_t lds;
   Gemm1Params g1;
+  Gemm2Params g2;
 };
 static std::vector<Launch> g_log;
 static int g_fail = 0, g_calls = 0;
+static bool g_down = false;   // which GEMM's launches are being recorded
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
-  Launch l = {fn, grid.x, block.x, lds, {}};
-  memcpy(&l.g1, args[0], sizeof(l.g1));
+  Launch l = {fn, grid.x, block.x, lds, {}, {}};
+  if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
+  else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
   g_log.push_back(l);
   return hipSuccess;
 }
@@ -58,8 +62,28 @@ static hipError_t gemm1(const Shape &s, bool list, int variant, int split, int h
   p.k = lists(s, p.n_blocks);
   p.hs = (p.k.k_max + s.rc + 63) / 64 * 64;
   g_log.clear();
+  g_down = false;
   ++g_calls;
   return ff_launch_gemm1(p, variant, split, heavy_tiles, nullptr);
+}
+struct DownOptions { int variant = -1, split = -1, row_mode = -1, ksplit = -1, nsplit = -1; };
+static float g_room[1];       // stands for the workspace's room for partial sums: never touched
+static hipError_t gemm2(const Shape &s, bool list, const DownOptions &o, bool room) {
+  Gemm2Params p = {};
+  p.T = s.T; p.d_model = s.d_model; p.d_ffn = s.d_ffn; p.block = s.block; p.n_blocks = (s.T + s.block - 1) / s.block;
+  p.rc = s.rc; p.idx = list ? g_idx : nullptr; p.k_stride = s.d_ffn;
+  p.k = lists(s, p.n_blocks);
+  p.hs = (p.k.k_max + s.rc + 63) / 64 * 64;
+  if (room) {
+    p.part_bytes = ff_gemm2_part_bytes(s.T, s.block, s.d_model);
+    p.split_bytes = ff_gemm2_split_bytes(s.T, s.d_model);
+    if (p.part_bytes) p.part = g_room;
+    if (p.split_bytes) p.split_part = g_room;
+  }
+  g_log.clear();
+  g_down = true;
+  ++g_calls;
+  return ff_launch_gemm2(p, o.variant, o.split, o.row_mode, o.ksplit, o.nsplit, nullptr);
 }
 
 // Gate/up: the kernel leaves H zero up to the next multiple of 64 behind a block's list.  Where the list's end goes to a
@@ -77,6 +101,42 @@ static void check_gemm1(const Shape &s) {
       }
 }
 
+// Down: the tiles with the weights in registers (5 and 6) form 32-bit offsets into W_down and H.  Where those do not
+// reach, the library takes another tile and a forced one is an error, cut along the list or not.
+static void check_gemm2_addresses() {
+  std::set<const void *> in_registers;
+  for (int variant : {5, 6})
+    for (bool list : {false, true}) {
+      DownOptions o;
+      o.variant = variant;
+      CHECK(gemm2({700, 128, 256, 1024, 32, 512, 0, 0}, list, o, true) == hipSuccess && g_log.size() == 1, "tile %d", variant);
+      for (const Launch &l : g_log) in_registers.insert(l.fn);
+    }
+  CHECK(in_registers.size() == 4, "%zu kernels", in_registers.size());
+  // rows of 16 MiB; a matrix of 4 GiB, and just below; H of 2^24 positions
+  struct { Shape s; bool ok, ok_list; } sizes[] = {{{20, 10, 8388608, 8, 0, 8, 0, 0}, false, false},
+                                                  {{20, 10, 8388608 - 128, 8, 0, 8, 0, 0}, true, true},
+                                                  {{20, 10, 65536, 32768, 0, 700, 0, 0}, true, false},
+                                                  {{300, 128, 65536, 32768, 32, 700, 0, 0}, true, false},
+                                                  {{300, 128, 65536, 32760, 0, 700, 0, 0}, true, true},
+                                                  {{300, 128, 128, 1 << 24, 0, 1 << 24, 0, 0}, false, false}};
+  for (const auto &z : sizes)
+    for (bool list : {false, true})
+      for (int nsplit : {-1, 0, 3}) {
+        DownOptions o;
+        o.nsplit = nsplit;
+        CHECK(gemm2(z.s, list, o, true) == hipSuccess, "d_model %d d_ffn %d", z.s.d_model, z.s.d_ffn);
+        const bool may = list ? z.ok_list : z.ok;
+        for (const Launch &l : g_log)
+          CHECK(may || !in_registers.count(l.fn), "d_model %d d_ffn %d list %d", z.s.d_model, z.s.d_ffn, list);
+        for (int variant : {5, 6}) {
+          o.variant = variant;
+          const hipError_t e = gemm2(z.s, list, o, true);
+          CHECK((e == hipSuccess) == may && g_log.empty() == !may, "d_model %d d_ffn %d list %d tile %d nsplit %d", z.s.d_model, z.s.d_ffn, list, variant, nsplit);
+        }
+      }
+}
+
 int main() {
   if (ff_gemm_init(kLds) != hipSuccess) return 1;
   for (int T : {9, 70, 300, 700, 2000, 8192})
@@ -85,6 +145,7 @@ int main() {
         for (int k : {33, 96, 160, 1000, 3584, 7168})
           for (int rc : {0, 32, 64})
             check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
+  check_gemm2_addresses();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);
   return g_fail != 0;
 }
