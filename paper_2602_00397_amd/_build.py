@@ -37,7 +37,12 @@ def build(verbose: bool = False, extra_flags=()) -> str:
 
     def one(pair):
         src, obj = pair
-        return _run([HIPCC, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj])
+        out = _run([HIPCC, *FLAGS, *extra_flags, "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, src), "-o", obj])
+        # the compiler's remarks on every kernel's registers and scratch memory stay beside the object file
+        lines = out.splitlines()
+        with open(obj[:-2] + ".resources.txt", "w") as f:
+            f.writelines(l + "\n" for l in lines if "[-Rpass-analysis" in l)
+        return "\n".join(l for l in lines if "[-Rpass-analysis" not in l)
 
     with ThreadPoolExecutor(max_workers=min(5, len(SOURCES))) as ex:
         outs = list(ex.map(one, zip(SOURCES, objs)))

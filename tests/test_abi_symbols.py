@@ -120,6 +120,26 @@ def test_launchers_give_the_kernels_what_they_assume():
     assert r.returncode == 0 and ", 0 wrong" in r.stdout, r.stdout
 
 
+def test_no_kernel_spills_to_scratch_memory():
+    """Every kernel of the library keeps its state in registers: no scratch memory per lane, by the compiler's own remarks
+    (written beside the object files when they were built)."""
+    from paper_2602_00397_amd import _build
+    seen = 0
+    for src in _build.SOURCES:
+        path = os.path.join(_build.OBJ, src.replace(".hip", ".resources.txt"))
+        if not os.path.exists(path):
+            pytest.skip("resource remarks not written (python -c 'import __graft_entry__ as g; g.build()')")
+        text = open(path).read()
+        names = re.findall(r"Function Name: (\S+)", text)
+        scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", text)]
+        spilled = [int(v) for v in re.findall(r"VGPRs Spill: (\d+)", text)]
+        assert len(names) == len(scratch) == len(spilled), path
+        for name, s, v in zip(names, scratch, spilled):
+            assert s == 0 and v == 0, f"{name}: {s} bytes of scratch per lane, {v} spilled registers"
+        seen += len(names)
+    assert seen >= 40
+
+
 @pytest.mark.gpu
 def test_host_code_under_sanitizers_with_a_gpu():
     """The same program on a machine with a GPU: every argument error of every compute call (nothing
