@@ -78,6 +78,37 @@ struct PredictParams {
 };
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof);
 
+// Top-K's map of scores to buckets: monotone (s1 <= s2 gives bucket(s1) <= bucket(s2)), so a key in a higher bucket is a
+// larger key.  It works on fp32 roundings of the scores, which are monotone too (fp64 arithmetic on every key, twice, takes
+// longer than the histogram itself), as long as their steps are finer than the buckets: a range of 2^-9 of the scores' size
+// has 2^14 steps for its 4096 buckets.  A narrower range, or one that fp32 cannot hold, is cut in fp64; without an ordered,
+// finite range there are no buckets.
+constexpr int TOPK_BUCKETS = 4096;
+constexpr int TOPK_CAND = 1024;   // most keys the threshold bucket may hold for the ranking step
+struct TopkMap {
+  bool none, fine;       // no buckets; buckets of the fp64 scores
+  float lo, scale;
+  double lo64, scale64;
+  __host__ __device__ __forceinline__ int bucket(float s) const { return clamp((int)((s - lo) * scale)); }
+  __host__ __device__ __forceinline__ int bucket64(double s) const { return clamp((int)((s - lo64) * scale64)); }
+  static __host__ __device__ __forceinline__ int clamp(int b) { return b < 0 ? 0 : (b < TOPK_BUCKETS ? b : TOPK_BUCKETS - 1); }
+};
+// [lo, hi] encloses the scores
+__host__ __device__ __forceinline__ TopkMap topk_map(double lo, double hi) {
+  TopkMap m = {};
+  m.lo = (float)lo;
+  m.lo64 = lo;
+  const float hi_f = (float)hi, range = hi_f - m.lo;
+  const double range64 = hi - lo;
+  // (the limits keep every scale, and every product with it, a finite number)
+  m.none = !(range64 > 1e-300 && range64 < 1e300);
+  m.fine = !(range > 1e-30f && fabsf(m.lo) < 1e30f && range < 1e30f && range >= fmaxf(fabsf(m.lo), fabsf(hi_f)) * 0x1p-9f);
+  if (m.none) return m;
+  if (m.fine) m.scale64 = (double)TOPK_BUCKETS / range64;
+  else m.scale = (float)TOPK_BUCKETS / range;
+  return m;
+}
+
 // ---- gathered GEMMs (Eq. 15-18, 20-21; Eq. 10 with idx == nullptr) ---------
 struct Gemm1Params {
   const bf16_t *x;     // [T][d_model]

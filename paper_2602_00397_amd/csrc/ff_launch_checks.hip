@@ -1,6 +1,7 @@
-// Checks of the GEMM launchers' choices, without a GPU: this program is linked with the launchers' object file and defines
+// Checks of the GEMM launchers' choices (and of top-K's bucket map), without a GPU: this program is linked with the launchers' object file and defines
 // hipLaunchKernel itself, so every launch is recorded instead of made.  Swept over shapes, list lengths and options, every
 // launch must fit what its kernel assumes.  Exit code 0 = all hold.
+#include <math.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -137,6 +138,31 @@ static void check_gemm2_addresses() {
       }
 }
 
+// Top-K's bucket map: monotone over the scores, and scores spread evenly over their range fill the buckets evenly, however
+// narrow the range is against the scores' size and however small or large they are.  (A bucket of more than TOPK_CAND keys
+// sends the whole block to eight passes over its scores.)
+static void check_topk_map() {
+  constexpr int n = 16384;
+  for (int centre = -1; centre <= 1; ++centre)
+    for (int e = 0; e <= 36; ++e)
+      for (double size : {1.0, 0x1p-140, 0x1p-40, 0x1p40, 0x1p140}) {
+        ++g_calls;
+        double s[n];
+        std::vector<int> hist(TOPK_BUCKETS, 0);
+        for (int i = 0; i < n; ++i) s[i] = size * (centre + ldexp((double)i / n, -e));
+        const TopkMap m = topk_map(s[0], s[n - 1]);
+        int last = 0, most = 0;
+        for (int i = 0; i < n && !m.none; ++i) {
+          const int b = m.fine ? m.bucket64(s[i]) : m.bucket((float)s[i]);
+          CHECK(b >= last && b < TOPK_BUCKETS, "size %g centre %d range 2^-%d: score %d", size, centre, e, i);
+          last = b;
+          if (++hist[b] > most) most = hist[b];
+        }
+        CHECK(!m.none && most <= 8, "size %g centre %d range 2^-%d: %d in one bucket", size, centre, e, most);
+      }
+  CHECK(topk_map(1.0, 1.0).none && topk_map(0.0, INFINITY).none && topk_map(-INFINITY, 0.0).none && topk_map(0.0, NAN).none && topk_map(NAN, 0.0).none, "no range");
+}
+
 int main() {
   if (ff_gemm_init(kLds) != hipSuccess) return 1;
   for (int T : {9, 70, 300, 700, 2000, 8192})
@@ -146,6 +172,7 @@ int main() {
           for (int rc : {0, 32, 64})
             check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
   check_gemm2_addresses();
+  check_topk_map();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);
   return g_fail != 0;
 }

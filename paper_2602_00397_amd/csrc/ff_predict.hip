@@ -423,9 +423,6 @@ __device__ __forceinline__ int block_excl_scan(int v, int *wsum, int &total) {
   return res;
 }
 
-constexpr int TOPK_BUCKETS = 4096;
-constexpr int TOPK_CAND = 1024;   // most keys the threshold bucket may hold for the ranking step
-
 // LDS of the threshold search, shared by both top-K kernels
 struct TopkShared {
   unsigned int hist[TOPK_BUCKETS];           // also the 256-bin histogram of the radix path
@@ -440,26 +437,20 @@ struct TopkShared {
 // The key theta of the K-th largest score and the number of keys equal to theta that are kept, found
 // exactly by the 1024 threads of a workgroup.  each(fn) calls fn(key) once for every key the calling thread
 // owns, as fn(key, score rounded to fp32).  [lo_v, hi_v] encloses the scores (it only shapes the bucket map); need_radix
-// skips the buckets.  The map works on fp32 roundings of the scores (fp64 arithmetic on every key, twice, took longer than
-// the histogram itself; with the scans below by lane exchanges one block of 14336 scores 13.8 -> 11.9 us, 16 blocks
-// 19.1 -> 15.7): rounding is monotone too, and scores that fp32 cannot tell apart share a bucket or, where it has
-// no ordered range for them at all, go to the radix path.
+// skips the buckets.  (Buckets of the fp32 roundings, against fp64 arithmetic on every key with the scans' lane exchanges
+// through LDS: one block of 14336 scores 13.3 -> 11.5 us, 64 blocks 14.0 -> 12.3; scores whose range is 2^-14 of their size,
+// which fp32 has no steps for: 12.6 and 13.9 in fp64 buckets, 30.2 and 56.2 on the radix path.)
 // On entry sh.hist is zero, sh.n_cand is 0 and a barrier has been passed.
 template <class Each>
 __device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_v, double hi_v, bool need_radix,
                                                Each each, unsigned long long &theta, int &ties_taken) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float lo_f = (float)lo_v, range_f = (float)hi_v - lo_f;
-  // (1e-30 and 1e30 keep the scale, and every product with it, a finite number)
-  need_radix = need_radix || !(range_f > 1e-30f && fabsf(lo_f) < 1e30f && range_f < 1e30f);
-  const float scale = need_radix ? 0.0f : (float)TOPK_BUCKETS / range_f;
-  // monotone: s1 <= s2 implies bucket(s1) <= bucket(s2), so a key in a higher bucket is a larger key
-  auto bucket_of = [&](float s) -> int {
-    const float t = (s - lo_f) * scale;
-    return min(TOPK_BUCKETS - 1, max(0, (int)t));
-  };
-  if (!need_radix) {
-    each([&](unsigned long long, float s) { atomicAdd(&sh.hist[bucket_of(s)], 1u); });
+  const TopkMap map = topk_map(lo_v, hi_v);
+  const bool fine = __builtin_amdgcn_readfirstlane(map.fine);   // the same for all threads, as everything about the range
+  need_radix = need_radix || map.none;
+  // bucket_of(key, rounding): the bucket map.  False: the threshold's bucket holds too many keys.
+  auto by_buckets = [&](auto bucket_of) __attribute__((always_inline)) -> bool {
+    each([&](unsigned long long k, float s) { atomicAdd(&sh.hist[bucket_of(k, s)], 1u); });
     __syncthreads();
     // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = keys in higher buckets
     int local = 0;
@@ -480,33 +471,36 @@ __device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_
     const int tb = (int)sh.sel_bin;
     const int need = (int)sh.sel_rem;             // rank of theta inside bucket tb (1 = largest)
     const int c = (int)sh.hist[tb];
-    if (c > TOPK_CAND) {
-      need_radix = true;                          // uniform: every thread reads the same hist[tb]
-    } else {
-      each([&](unsigned long long k, float s) {
-        if (bucket_of(s) == tb) sh.cand[atomicAdd(&sh.n_cand, 1u)] = k;
-      });
-      __syncthreads();
-      if (tid < c) {
-        const unsigned long long mine = sh.cand[tid];
-        int n_gt = 0, n_eq = 0;
-        for (int j0 = 0; j0 < c; j0 += 8) {          // eight reads in flight
-          unsigned long long o[8];
+    if (c > TOPK_CAND) return false;              // uniform: every thread reads the same hist[tb]
+    each([&](unsigned long long k, float s) {
+      if (bucket_of(k, s) == tb) sh.cand[atomicAdd(&sh.n_cand, 1u)] = k;
+    });
+    __syncthreads();
+    if (tid < c) {
+      const unsigned long long mine = sh.cand[tid];
+      int n_gt = 0, n_eq = 0;
+      for (int j0 = 0; j0 < c; j0 += 8) {          // eight reads in flight
+        unsigned long long o[8];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) o[u] = sh.cand[min(j0 + u, c - 1)];
+        for (int u = 0; u < 8; ++u) o[u] = sh.cand[min(j0 + u, c - 1)];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            n_gt += j0 + u < c && o[u] > mine;
-            n_eq += j0 + u < c && o[u] == mine;
-          }
+        for (int u = 0; u < 8; ++u) {
+          n_gt += j0 + u < c && o[u] > mine;
+          n_eq += j0 + u < c && o[u] == mine;
         }
-        // the need-th largest of the bucket: n_gt < need <= n_gt + n_eq (all holders of that key agree)
-        if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; }
       }
-      __syncthreads();
+      // the need-th largest of the bucket: n_gt < need <= n_gt + n_eq (all holders of that key agree)
+      if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; }
     }
+    __syncthreads();
+    return true;
+  };
+  // (the rare map's code out of the way: between the other's passes it made every call 0.5 to 1.4 us longer)
+  if (!need_radix) {
+    if (__builtin_expect(fine, 0)) need_radix = !by_buckets([&](unsigned long long k, float) { return map.bucket64(key_score(k)); });
+    else need_radix = !by_buckets([&](unsigned long long, float s) { return map.bucket(s); });
   }
-  if (need_radix) {
+  if (__builtin_expect(need_radix, 0)) {
     // 8-pass MSB-first radix select on the keys themselves (heavy ties, or no ordered range)
     unsigned long long prefix = 0;  // digits decided so far (high part of theta)
     unsigned int rem = (unsigned int)K;

@@ -1011,6 +1011,26 @@ def test_scores_that_fp32_cannot_tell_apart(ctx, df, scale):
         np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
 
 
+@pytest.mark.parametrize("df", [2048, 20480, 28672, 40960])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -130, 2.0 ** 80])
+def test_scores_in_a_narrow_range(ctx, df, scale):
+    """Scores 2^26 + 0 .. 65535, few of them equal: a range of 2^-10 of their size, which top-K cuts into buckets in fp64."""
+    dm, T, r = 128, 64, 8
+    w1, w2 = np.zeros((dm, r)), np.zeros((r, df))
+    w1[0, :3] = 2.0 ** 20, 1.0, 256.0
+    rng = np.random.default_rng(df)
+    w2[0], w2[1], w2[2] = 64.0 * scale, rng.integers(0, 256, df) * scale, rng.integers(0, 256, df) * scale
+    s = 2.0 ** 20 * w2[0] + w2[1] + 256.0 * w2[2]
+    xd, w1d, w2d = (B.to_device_bf16(W.f32_to_bf16_bits(np.asarray(a, dtype=np.float32)), DEV) for a in (np.ones((T, dm)), w1, w2))
+    shape = B.Shape(dm, df, T, 64, r, 0)
+    pred = B.Predictor(None, w1d.data_ptr(), w2d.data_ptr())
+    ctx.ensure_workspace(shape, df)
+    for k in (1, df // 3, df // 2 + 1, df - 1):
+        idx = torch.empty((1, k), dtype=torch.int32, device=DEV)
+        ctx.predict(shape, xd, pred, [k], k, idx, None)
+        np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
+
+
 @pytest.mark.parametrize("df", [2048, 40960])
 def test_scores_that_are_not_finite_still_give_a_valid_list(ctx, df):
     """Scores are expected to be finite.  If they are not (an infinity among the hidden states makes
