@@ -1439,7 +1439,13 @@ constexpr size_t kPartCapBytes = (size_t)48 << 20;
 constexpr size_t kSplitCapBytes = (size_t)96 << 20;
 size_t ff_gemm2_split_bytes(int n_tokens, int d_model) {
   const size_t per_piece = (size_t)n_tokens * d_model * sizeof(float);
-  const size_t n = std::min<size_t>(kSplitCapBytes / per_piece, kMaxPieces - 1);
+  // (cuts are tried up to two rounds of tiles; blocks only make the tiles more)
+  long tiles = 2 * kNumCU;
+  for (const Gemm2Cost &g : kGemm2Cost) {
+    const Variant &v = kGemm2[g.variant];
+    tiles = std::min<long>(tiles, (long)((n_tokens + v.bm - 1) / v.bm) * ((d_model + v.bn - 1) / v.bn));
+  }
+  const size_t n = std::min<size_t>({kSplitCapBytes / per_piece, (size_t)(kMaxPieces - 1), (size_t)(2 * kNumCU / tiles)});
   return n >= 2 ? n * per_piece : 0;
 }
 

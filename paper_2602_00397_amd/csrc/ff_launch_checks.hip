@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <set>
 #include <vector>
 
@@ -138,6 +139,25 @@ static void check_gemm2_addresses() {
       }
 }
 
+// The room that ff_workspace_bytes asks for to cut every list: no more pieces than the launcher would take by itself on the
+// tile with the fewest tiles (two rounds of the chip), and room for every cut that it makes.
+static void check_gemm2_room() {
+  const int tiles[][2] = {{128, 512}, {64, 512}, {128, 256}, {256, 256}};
+  for (int T : {9, 100, 700, 2000, 3000, 4500, 16000, 60000, 400000})
+    for (int dm : {128, 256, 640, 1024, 4096, 8320}) {
+      long fewest = 1 << 30;
+      for (const auto &t : tiles) fewest = std::min(fewest, (long)((T + t[0] - 1) / t[0]) * ((dm + t[1] - 1) / t[1]));
+      const size_t piece = (size_t)T * dm * 4, room = ff_gemm2_split_bytes(T, dm);
+      CHECK(room % piece == 0 && room <= ((size_t)96 << 20) && room / piece != 1 && room / piece <= 16, "T %d d_model %d: %zu bytes", T, dm, room);
+      CHECK((long)(room / piece) * fewest <= 512, "T %d d_model %d: room for %zu pieces of %ld tiles", T, dm, room / piece, fewest);
+      for (int k : {500, 4000, 14336})
+        for (bool list : {false, true}) {
+          CHECK(gemm2({T, 128, dm, 14336, 0, list ? k : 14336, 0, 0}, list, DownOptions(), true) == hipSuccess, "T %d d_model %d", T, dm);
+          for (const Launch &l : g_log) CHECK(l.g2.n_split <= 1 || (size_t)l.g2.n_split * piece <= room, "T %d d_model %d: %d pieces", T, dm, l.g2.n_split);
+        }
+    }
+}
+
 // Down, a few much longer lists: their surplus is cut into short pieces where the option allows it and the workspace has room.
 // With the option off the tile is priced as for a call that has no room for them.
 static void check_gemm2_heavy(const Shape &s) {
@@ -189,6 +209,7 @@ int main() {
             if (s.n_heavy > 0) check_gemm2_heavy(s);
           }
   check_gemm2_addresses();
+  check_gemm2_room();
   check_topk_map();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);
   return g_fail != 0;
