@@ -1478,7 +1478,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     // priced without the pieces against this: 2000 tokens 502 / 471, 500 327 / 303, 2000 in blocks of 256 565 / 537, 1500 in
     // blocks of 64, K 3584 361 / 336; 64 x 512 tiles must save a tenth, since they take twice the pieces.)
     const int surplus = up64(ntot) - up64(base);
-    const bool heavy_cut = ksplit != 0 && split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= up64(base);
+    const bool heavy_cut = split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= up64(base);
     for (const Gemm2Cost &g : kGemm2Cost) {
       if (heavy_cut && variant >= 0 && gemm2_direct(variant) && !gemm2_direct(g.variant)) break;
       const Variant &v = kGemm2[g.variant];

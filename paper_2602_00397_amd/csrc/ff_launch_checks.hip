@@ -158,20 +158,6 @@ static void check_gemm2_room() {
     }
 }
 
-// Down, a few much longer lists: their surplus is cut into short pieces where the option allows it and the workspace has room.
-// With the option off the tile is priced as for a call that has no room for them.
-static void check_gemm2_heavy(const Shape &s) {
-  DownOptions o;
-  o.ksplit = 0;
-  const hipError_t e = gemm2(s, true, o, true);
-  CHECK(e == hipSuccess && g_log.size() >= 1, "T %d block %d K %d", s.T, s.block, s.k);
-  const std::vector<Launch> off = g_log;
-  o.ksplit = -1;
-  CHECK(gemm2(s, true, o, false) == hipSuccess && g_log.size() == off.size(), "T %d block %d d_model %d K %d: %zu launches, %zu without room", s.T, s.block, s.d_model, s.k, off.size(), g_log.size());
-  for (size_t i = 0; i < off.size() && i < g_log.size(); ++i)
-    CHECK(off[i].fn == g_log[i].fn && off[i].grid == g_log[i].grid && off[i].g2.n_pieces == 0, "T %d block %d d_model %d K %d", s.T, s.block, s.d_model, s.k);
-}
-
 // Top-K's bucket map: monotone over the scores, and scores spread evenly over their range fill the buckets evenly, however
 // narrow the range is against the scores' size and however small or large they are.  (A bucket of more than TOPK_CAND keys
 // sends the whole block to eight passes over its scores.)
@@ -203,11 +189,8 @@ int main() {
     for (int block : {16, 64, 96, 128, 300})
       for (int dm : {256, 2048, 4096})
         for (int k : {33, 96, 160, 1000, 3584, 7168})
-          for (int rc : {0, 32, 64}) {
-            const Shape s = {T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0};
-            check_gemm1(s);
-            if (s.n_heavy > 0) check_gemm2_heavy(s);
-          }
+          for (int rc : {0, 32, 64})
+            check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
   check_gemm2_addresses();
   check_gemm2_room();
   check_topk_map();
