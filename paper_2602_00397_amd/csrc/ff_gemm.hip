@@ -1476,7 +1476,8 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     // where there are such, else ahead of everybody.  That favours the large tiles with the weights in registers, which
     // leave the most; the others only where those do not apply.  (First and last block dense, us per call at 4096/14336,
     // priced without the pieces against this: 2000 tokens 502 / 471, 500 327 / 303, 2000 in blocks of 256 565 / 537, 1500 in
-    // blocks of 64, K 3584 361 / 336; 64 x 512 tiles must save a tenth, since they take twice the pieces.)
+    // blocks of 64, K 3584 361 / 336; 64 x 512 tiles must save a tenth, since they take twice the pieces.)  Not asked: ksplit,
+    // which is to change the long lists' sums and no others, hence no tile.
     const int surplus = up64(ntot) - up64(base);
     const bool heavy_cut = split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= up64(base);
     for (const Gemm2Cost &g : kGemm2Cost) {

@@ -139,6 +139,22 @@ static void check_gemm2_addresses() {
       }
 }
 
+// Calls that the GPU tests take for a route of their own: the library's choice has to be that kernel.
+static void check_gemm2_routes() {
+  struct { Shape s; bool list; int variant, row_mode; bool cut; } routes[] = {
+      {{9000, 256, 1024, 1064, 24, 1064, 0, 0}, false, 5, -1, false},   // the identity list with compensator rows behind it
+      {{300, 256, 2048, 4096, 24, 4096, 0, 0}, false, 6, -1, true},
+      {{3000, 64, 512, 65536, 16, 3000, 0, 0}, true, 3, 2, true}};     // ids of more than 16 bits: scalar loads
+  for (const auto &r : routes) {
+    CHECK(gemm2(r.s, r.list, DownOptions(), true) == hipSuccess && !g_log.empty(), "T %d", r.s.T);
+    const std::vector<Launch> chosen = g_log;
+    DownOptions o;
+    o.variant = r.variant;
+    o.row_mode = r.row_mode;
+    CHECK(gemm2(r.s, r.list, o, true) == hipSuccess && g_log[0].fn == chosen[0].fn && (chosen[0].g2.n_split > 1) == r.cut, "T %d d_model %d d_ffn %d", r.s.T, r.s.d_model, r.s.d_ffn);
+  }
+}
+
 // The room that ff_workspace_bytes asks for to cut every list: no more pieces than the launcher would take by itself on the
 // tile with the fewest tiles (two rounds of the chip), and room for every cut that it makes.
 static void check_gemm2_room() {
@@ -192,6 +208,7 @@ int main() {
           for (int rc : {0, 32, 64})
             check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
   check_gemm2_addresses();
+  check_gemm2_routes();
   check_gemm2_room();
   check_topk_map();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);

@@ -260,7 +260,8 @@ def test_gemm2_scalar_loads_of_the_list(ctx):
     """The down GEMM's fallback source of row ids: scalar loads of the list in the k-loop, taken when
     the ids do not fit 16 bits (d_ffn + r_comp > 65536) or no LDS is left for a table.  Forced on lists
     the table takes as well (must agree with it and with the oracle, on the two main tile shapes), and
-    reached the natural way on a layer of 65536 neurons plus compensator units."""
+    reached the natural way on layers of 65536 neurons plus compensator units: two blocks, which take the tile with the
+    streamed list, and 47 short ones, which take one that has neither (csrc/ff_launch_checks.hip holds the choice)."""
     shp = W.Shape("g2scalar", 256, 4096, 300, 128, 8, 16)
     c = Case(shp)
     try:
@@ -289,6 +290,11 @@ def test_gemm2_scalar_loads_of_the_list(ctx):
     idx, _ = wide.gpu_predict(ctx, ks, k_stride=65536)
     _assert_indices(idx, ref.indices, ks)
     _check_both(wide, ctx, idx, ks, ref.y, "d_ffn 65536 + 16 compensator units (ids beyond 16 bits)")
+    wide = Case(W.Shape("g2wide64", 512, 65536, 3000, 64, 8, 16))
+    ks = [3000] * wide.n_blocks
+    ref = wide.oracle_layer(ks, blocks=[0, 23, 46])
+    idx, _ = wide.gpu_predict(ctx, ks)
+    _check_both(wide, ctx, idx, ks, ref.y, "the same, 47 blocks of 64: scalar loads of the list")
 
 
 def test_nothing_is_written_outside_the_buffers(ctx):
@@ -582,8 +588,9 @@ def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
     lists shorter than the pieces, merged lists (their length known on the device only), a short last block, both
     tile widths the gate/up GEMM takes for few tokens (32 and 64 positions; list ends on no multiple of either), and
     the dense call.  Against the oracle at the stated bars; against the uncut sums only fp32 summation order (1064
-    products of at most a few hundredths: 1e-5 is 30 times their rounding).  A workspace without room for the
-    partial sums gives the uncut result."""
+    products of at most a few hundredths: 1e-5 is 30 times their rounding).  The cut is really made: it writes so many
+    more words of a workspace full of ones, each piece of every row once.  A workspace without room for the partial
+    sums gives the uncut result, bit for bit."""
     c = Case(W.Shape("cut", 640, 1064, n_tokens, block, 8, 24))
     ref = c.oracle_layer(ks)
     idx, _ = c.gpu_predict(ctx, ks, k_stride=1064)
@@ -597,7 +604,20 @@ def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
 
     ctx.ensure_workspace(c.shape, 1064)
     keep = ctx._ws
+
+    def words_written(n, call):
+        ctx.set_option("gemm2_nsplit", n)
+        keep.fill_(0xFF)
+        call()
+        return int((keep.view(torch.int32) != -1).sum().item())
+
     try:
+        ctx.set_option("gemm2_ksplit", 0)           # (the partial sums of a few longer lists are not what is counted)
+        for call in (lambda: c.gpu_sparse(ctx, idx, ks, out_f32=True), dense):
+            whole = words_written(0, call)
+            for n in (2, 5, 16):
+                assert words_written(n, call) - whole == n * n_tokens * 640, n
+        ctx.set_option("gemm2_ksplit", -1)
         ctx.set_option("gemm2_nsplit", 0)
         y0, d0 = c.gpu_sparse(ctx, idx, ks, out_f32=True), dense()
         _check_y(y0, ref.y, "whole lists")
@@ -611,9 +631,10 @@ def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
         ctx.set_workspace(keep[:B.workspace_bytes(c.shape, 1064) - part])
         y_small = torch.empty_like(y0)
         ctx.sparse_ffn(c.shape, c.x, c.w, c.comp, idx, ks, 1064, y_small, B.OUT_F32)
-        _check_y(y_small, ref.y, "no room for the partial sums")
+        assert torch.equal(y_small, y0), "no room for the partial sums"
     finally:
         ctx.set_option("gemm2_nsplit", -1)
+        ctx.set_option("gemm2_ksplit", -1)
         ctx.set_workspace(keep)
 
 
@@ -622,8 +643,9 @@ def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
 def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
     """The down-GEMM tiles that load the gathered rows straight into registers (128 x 512 and 64 x 512): lists of
     one to seventeen steps of 64, ends inside a step, steps that hold neurons and compensator units, the identity list
-    with and without a compensator, a short last block, columns that fill no whole tile.  Against the oracle at the
-    stated bars and against the tile with both operands in LDS (other order of the same fp32 sums: 1e-5)."""
+    of the dense call, a short last block, columns that fill no whole tile; whole lists, and all of them cut into 2, 5
+    and 16 pieces, some of which hold nothing.  Against the oracle at the stated bars and against the tile with both
+    operands in LDS (other order of the same fp32 sums: 1e-5)."""
     c = Case(W.Shape("direct", 640, 1064, 3 * 96 + 33, 96, 8, max(rc, 8)))
     ref = c.oracle_layer(ks, comp=rc > 0)
     idx, _ = c.gpu_predict(ctx, ks, k_stride=1064)
@@ -631,18 +653,58 @@ def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
     ctx.ensure_workspace(c.shape, 1064)
     out = {}
     try:
-        for v in (1, variant):
+        for v, nsplit in ((1, 0), (variant, 0), (variant, 2), (variant, 5), (variant, 16)):
             ctx.set_option("gemm2_variant", v)
-            out[v] = c.gpu_sparse(ctx, idx, ks, comp=rc > 0, out_f32=True)
-            _check_y(out[v], ref.y, f"tile {v}, rc {rc}, ks {ks}")
+            ctx.set_option("gemm2_nsplit", nsplit)
             y = torch.empty((c.T, 640), dtype=torch.float32, device=DEV)
             ctx.dense_ffn(c.shape, c.x, c.w, y, B.OUT_F32)
-            _check_y(y, ref_d, f"tile {v}, dense")
+            out[v, nsplit] = c.gpu_sparse(ctx, idx, ks, comp=rc > 0, out_f32=True), y
+            _check_y(out[v, nsplit][0], ref.y, f"tile {v}, rc {rc}, ks {ks}, {nsplit} pieces")
+            _check_y(y, ref_d, f"tile {v}, dense, {nsplit} pieces")
     finally:
         ctx.set_option("gemm2_variant", -1)
-    assert (out[variant] - out[1]).abs().max().item() <= 1e-5
-    if min(ks) == 1064:   # the identity list with the compensator behind it, the library's own tiles
-        _check_y(c.gpu_sparse(ctx, idx, ks, comp=True, out_f32=True), ref.y, "identity list")
+        ctx.set_option("gemm2_nsplit", -1)
+    for got in out.values():
+        assert all((g - o).abs().max().item() <= 1e-5 for g, o in zip(got, out[1, 0]))
+
+
+@pytest.mark.parametrize("d_model,d_ffn,n_tokens", [(1024, 1064, 9000), (2048, 4096, 300)])
+def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
+    """Lists that hold every neuron are the identity list, with the compensator's rows behind it: two calls for which the
+    down GEMM takes the 128 x 512 and, cut into pieces, the 64 x 512 tile with the weights in registers
+    (csrc/ff_launch_checks.hip holds that choice)."""
+    c = Case(W.Shape("keepall", d_model, d_ffn, n_tokens, 256, 8, 24))
+    ks = [d_ffn] * c.n_blocks
+    ref = c.oracle_layer(ks, blocks=sorted({0, c.n_blocks // 2, c.n_blocks - 1}))
+    idx, _ = c.gpu_predict(ctx, ks)
+    _check_both(c, ctx, idx, ks, ref.y, f"all of {d_ffn} neurons and 24 units, {n_tokens} tokens")
+
+
+@pytest.mark.parametrize("variant", [5, 6])
+def test_largest_row_ids_and_longest_lists_in_registers(ctx, variant):
+    """The row-id table of the tiles with the weights in registers: ids up to 65535 (the last compensator unit behind 65528
+    neurons), and the longest list whose table fits beside the 128 x 512 tile (49152 positions); one unit more, or one
+    neuron more on the list, and a forced tile is an error while the library takes another."""
+    def layer(d_ffn, ks):
+        c = Case(W.Shape("regid", 128, d_ffn, 60, 24, 8, 8))
+        ref = c.oracle_layer(ks)
+        idx, _ = c.gpu_predict(ctx, ks, k_stride=max(ks))
+        _check_y(c.gpu_sparse(ctx, idx, ks, out_f32=True), ref.y, f"library's tile, d_ffn {d_ffn}, ks {ks}")
+        ctx.set_option("gemm2_variant", variant)
+        ctx.set_option("gemm2_nsplit", 0)
+        ctx.set_option("gemm2_ksplit", 0)
+        try:
+            _check_y(c.gpu_sparse(ctx, idx, ks, out_f32=True), ref.y, f"tile {variant}, d_ffn {d_ffn}, ks {ks}")
+        finally:
+            for option in ("gemm2_variant", "gemm2_nsplit", "gemm2_ksplit"):
+                ctx.set_option(option, -1)
+
+    layer(65528, [40000, 49144, 17])
+    with pytest.raises(B.FFError):
+        layer(65536, [40000, 100, 17])
+    if variant == 5:
+        with pytest.raises(B.FFError):
+            layer(65528, [40000, 49145, 17])
 
 
 @pytest.mark.parametrize("n_tokens,block", [(256, 64), (6, 4)])
