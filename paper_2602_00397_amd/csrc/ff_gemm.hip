@@ -1404,13 +1404,13 @@ static bool gemm2_direct_addresses(const Gemm2Params &p) {
   if (row_bytes >> 24 || (uint64_t)kGemm2[kDirect128].bm * (uint64_t)p.hs * 2u >> 32) return false;
   return p.idx == nullptr || (uint64_t)p.d_ffn * row_bytes >> 32 == 0;
 }
-// whether the launcher takes the tile for these lists of ntot positions: weights in registers need W_down below 4 GiB and the
-// row ids in LDS
+// whether the launcher takes the tile for these lists of ntot positions: it has the source of row ids that was asked for, if
+// any; weights in registers need W_down below 4 GiB and the row ids in LDS
 static bool gemm2_takes(int variant, const Gemm2Params &p, int row_mode, int ntot) {
   const Variant &v = kGemm2[variant];
-  if (!gemm2_direct(variant)) return v.lds + kIdRingBytes <= g_lds_limit;
-  if (!gemm2_direct_addresses(p) || (uint64_t)p.d_ffn * (uint64_t)p.d_model * 2u >> 32) return false;
-  return p.idx == nullptr ? v.lds <= g_lds_limit : with_rows(v, p, row_mode, 2 * up64(ntot)).fn != nullptr;
+  if (gemm2_direct(variant) && (!gemm2_direct_addresses(p) || (uint64_t)p.d_ffn * (uint64_t)p.d_model * 2u >> 32)) return false;
+  if (v.lds + (gemm2_direct(variant) ? 0 : kIdRingBytes) > g_lds_limit) return false;
+  return with_rows(v, p, row_mode, 2 * up64(ntot)).fn != nullptr;
 }
 
 // every list cut into n pieces (n >= 2, p.split_part has room for them)

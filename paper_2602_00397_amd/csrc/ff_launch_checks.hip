@@ -155,6 +155,27 @@ static void check_gemm2_routes() {
   }
 }
 
+// A forced source of the row ids: the library chooses among the tiles that have it, and refuses only where none does.
+static void check_gemm2_row_sources() {
+  for (int T : {9, 300, 2000, 8192, 20000})
+    for (int block : {16, 64, 128, 300})
+      for (int dm : {256, 2048, 4096})
+        for (int df : {14336, 65536})
+          for (int k : {100, 7168, 14336})
+            for (int heavy : {0, 2})
+              for (int row_mode = 1; row_mode <= 3; ++row_mode)
+                for (int nsplit : {-1, 0, 3}) {
+                  const Shape s = {T, block, dm, df, 32, k, df, heavy};
+                  DownOptions o;
+                  o.row_mode = row_mode;
+                  o.nsplit = nsplit;
+                  const hipError_t e = gemm2(s, true, o, true);
+                  bool any = false;
+                  for (o.variant = 0; o.variant < ff_gemm2_num_variants() && !any; ++o.variant) any = gemm2(s, true, o, true) == hipSuccess;
+                  CHECK(e == hipSuccess || !any, "T %d block %d d_model %d d_ffn %d K %d, %d dense, source %d, nsplit %d", T, block, dm, df, k, heavy, row_mode, nsplit);
+                }
+}
+
 // The room that ff_workspace_bytes asks for to cut every list: no more pieces than the launcher would take by itself on the
 // tile with the fewest tiles (two rounds of the chip), and room for every cut that it makes.
 static void check_gemm2_room() {
@@ -209,6 +230,7 @@ int main() {
             check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
   check_gemm2_addresses();
   check_gemm2_routes();
+  check_gemm2_row_sources();
   check_gemm2_room();
   check_topk_map();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);
