@@ -173,6 +173,9 @@ ff_status ff_layer_budgets(const double *importance, int32_t n_layers,
  *   scores_opt   dev f64 [n_blocks][d_ffn] out, or NULL
  * Scores are computed in float64 without intermediate rounding; the K highest
  * are kept and equal scores go to the lower index (-0 and +0 are equal).
+ * A call repeated on the same inputs gives the same bits.  The order of the
+ * sums depends on the number of blocks in the call: a prompt given in parts
+ * may differ from the whole prompt in the last bits of its scores.
  * Scores are expected to be finite; if one is not, exactly K in-range indices
  * are still written, with NaN ranked by its bit pattern. */
 ff_status ff_predict(ff_ctx *ctx, const ff_shape *shape, const void *x,
@@ -201,7 +204,10 @@ ff_status ff_predict_static(ff_ctx *ctx, const ff_shape *shape, const void *x,
  * neurons (Eq. 15-18), plus the compensation term if `comp` is not NULL
  * (Eq. 20-21).  Any valid ascending index list may be given, not only
  * predict's.  bf16 operands, fp32 accumulation; the activations H and the
- * compensator's hidden units are rounded to bf16 once.
+ * compensator's hidden units are rounded to bf16 once.  A call repeated with
+ * the same shape, lists, options and room in the workspace gives the same bits;
+ * which tiles run, and so the order of the fp32 sums, depends on all of those
+ * (as it does for ff_dense_ffn and ff_ffn_stack).
  *   indices      dev int32 [n_blocks][k_stride]
  *   y            dev [n_tokens][d_model], bf16 or f32 by out_dtype */
 ff_status ff_sparse_ffn(ff_ctx *ctx, const ff_shape *shape, const void *x,

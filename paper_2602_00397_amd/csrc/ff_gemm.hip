@@ -906,10 +906,10 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
 // The same product with the gathered rows loaded straight into registers.  A row of W_down is contiguous along the
 // output columns, so 16 lanes of a load instruction ask for 128 contiguous bytes of one row, and the transposition that
 // MFMA wants (eight list positions of one column in a lane) is one byte permute per dword of eight rows' pieces.  Eight
-// (or four) wavefronts side by side, 64 columns each for all 128 tokens: nobody else in the workgroup wants a wavefront's
+// wavefronts side by side, 64 columns each for all tokens of the tile: nobody else in the workgroup wants a wavefront's
 // weights, only H passes through LDS.
 // v_mfma_f32_16x16x32_bf16: lane (c, q) holds list positions 8 q .. 8 q + 7 of a step's half of 32; MFMA tile f, column c
-// is output column 4 c + f, so a lane ends with four adjacent columns.
+// is output column 8 (c mod 8) + 4 (c / 8) + f of the wavefront's 64, so a lane ends with four adjacent columns.
 // RM 0: the identity list; 1: the tile's list in an LDS table of 16-bit ids, as above.
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f32x4_t c) {
@@ -1137,7 +1137,9 @@ Variant g2d() {
 }
 constexpr int kIdRingBytes = 8 * 256;   // row-id mode 3: eight stages of 64 raw list entries
 
-// tokens x list positions of the tile, wavefronts, BK, ring stages (LDS)
+// tokens x list positions of the tile, wavefronts, BK, ring stages (LDS).  1, 2 and 4 run only where an option names them: at
+// none of twelve shapes from 60 to 8192 tokens were they faster than the choice below (222 us against 225, 264 and 342 at the
+// closest, 700 tokens of 4096/14336).  They keep their numbers, and add the same sums in another order for comparisons.
 const Variant kGemm1[] = {
     g1<2, 2, 2, 2, 64, 3, 2>(),  // 0: 128 x 128, 8 waves in 2 k-groups, BK 64, 3 stages (144 KB)
     g1<2, 4, 2, 2, 32, 3>(),     // 1: 128 x 256, 8 waves, BK 32, 3 stages (120 KB)
@@ -1153,7 +1155,7 @@ const Variant kGemm1[] = {
     // (tiles whose wavefronts need 256 accumulator registers -- 128 x 256 or 256 x 128 on 4 waves -- were measured
     //  10-25% slower: one wavefront per SIMD cannot keep the matrix pipe issuing back to back)
 };
-// tokens x output columns of the tile
+// tokens x output columns of the tile (1 likewise only where an option names it)
 const Variant kGemm2[] = {
     g2<2, 4, 2, 32, 3>(),  // 0: 128 x 512, 8 waves, 3 stages (120 KB)
     g2<2, 2, 2, 32, 3>(),  // 1: 128 x 256, 4 waves, 3 stages (72 KB)
@@ -1548,7 +1550,8 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
   // round that is at most half full wastes the rest of the chip (3584 columns, 128 blocks: 896 tiles,
   // 3.5 rounds).  Then the last nq column tiles of every block leave the main launch, which
   // becomes whole rounds, and run as tiles of half the size in a second launch of one round that
-  // takes little more than half a tile time.
+  // takes little more than half a tile time.  (Tiles with both operands in LDS only; those with the weights in registers
+  // are priced with their part-filled last round.)
   Variant h = with_row_mode(kGemm2[half128]);
   if (h.fn == nullptr) { row_mode = -1; h = with_row_mode(kGemm2[half128]); }   // the second launch's tile picks its own
   const int V = p.n_blocks * ((p.block + v.bm - 1) / v.bm);

@@ -804,8 +804,9 @@ static int g_topk_lds_raised = 0;
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
   const int n_slices = (p.d_model + 511) / 512;
   // Few blocks: the first layer's outputs are shared out over up to 8 workgroups per slice (each pools the slice again),
-  // at least 32 outputs each, until there is one for every CU (d_model 4096, r 256: one token 7.5 -> 5.3 us, a block of
-  // 100 9.0 -> 7.5, 16 blocks 12.8 -> 11.6).
+  // at least 32 outputs each, until there is one for every CU (d_model 4096, r 128: one token 7.5 -> 5.3 us, a block of
+  // 100 9.0 -> 7.5, 16 blocks 12.8 -> 11.6).  How many share them decides which channels are summed together first, so the
+  // last bits of fp64 scores depend on the number of blocks, here and below.
   int oz = 256 / (n_slices * p.n_blocks);
   oz = std::max(1, std::min({oz, 8, p.r / 32}));
   prof_begin(prof, FF_STAGE_POOL, s);
@@ -824,7 +825,7 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   const int n_groups = (p.n_blocks + MLP_BB - 1) / MLP_BB;
   // One or two blocks: 128 columns per workgroup and 32 row groups, else 256 columns and 8 row groups with every weight
   // shared by four blocks, as long as 1024 columns per workgroup would leave half of the CUs without one.  (d_ffn 14336,
-  // r 256: one block 14.1 -> 4.5 us, 16 blocks 18.2 -> 8.2; d_ffn 8192, r 128: 6 blocks 9.1 -> 5.4, 32 blocks 9.2 -> 5.6.
+  // r 128: one block 14.1 -> 4.5 us, 16 blocks 18.2 -> 8.2; d_ffn 8192, r 64: 6 blocks 9.1 -> 5.4, 32 blocks 9.2 -> 5.6.
   // 64 blocks at d_ffn 14336 take 21.4 us as they are, 23.0 this way: every workgroup forms the hidden units again.)
   if (p.n_blocks <= 2) {
     hipLaunchKernelGGL((ff_scores_split_kernel<1, 32, 1024>), dim3((p.d_ffn + 127) / 128, p.n_blocks), dim3(1024),
