@@ -36,8 +36,10 @@ extern "C" {
  *   "gemm2_row_mode"  -1 = decide by shape, 1 = the down GEMM reads the ids of
  *       its gathered rows from a table of 16-bit ids in LDS, 2 = by scalar
  *       loads of the list, 3 = from a small LDS ring the list streams through
- *       (only the eight-wavefront tile has it).  A mode the chosen tile lacks,
- *       or that does not fit, makes the compute call fail with FF_ERR_DEVICE.
+ *       (only the 128 x 256 tile with eight wavefronts has it).  The library
+ *       chooses among the tiles that have the mode; a mode that a forced tile
+ *       lacks, or that fits nowhere, makes the compute call fail with
+ *       FF_ERR_DEVICE.
  *   "gemm2_ksplit"  -1 = decide by shape, 0 = never, n > 0 = at most n short
  *       pieces: whether the down GEMM cuts the few lists that are much longer
  *       than the rest (first and last block dense) along the list into a tile
