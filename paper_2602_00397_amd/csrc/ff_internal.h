@@ -170,7 +170,8 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int hea
 // and p.part has room for at least two short pieces, 0 = never, n > 0 = into at most n short pieces.
 // row_mode: where the kernel takes a gathered row's id from: -1 = the launcher decides, 1 = a table of
 // 16-bit ids in LDS, 2 = scalar loads of the list, 3 = the list streamed through a small LDS ring (only
-// the eight-wavefront tile has it).  A forced mode the tile does not have, or that does not fit, is an error.
+// the eight-wavefront tile has it).  The launcher chooses among the tiles that have a forced mode; one that
+// a forced tile does not have, or that fits nowhere, is an error.
 // nsplit: into how many pieces every list is cut along k: -1 = the launcher decides (few tiles), 0 = never,
 // n > 1 = into n pieces, fewer where split_part has no room for them.
 hipError_t ff_launch_gemm2(const Gemm2Params &p, int variant, int split, int row_mode, int ksplit, int nsplit, hipStream_t s);
