@@ -18,7 +18,10 @@ extern "C" {
  * kernels that compute the same sums (fp32 rounding order may differ):
  *   "gemm1_variant", "gemm2_variant"  -1 = choose by shape (default), else one
  *       tile shape of the gate/up or the down GEMM; an unknown number is an
- *       error.  The down tiles 5 and 6 (weights in registers) address a listed
+ *       error.  The gate/up tiles 11 and 12 (weights in registers) address a
+ *       listed row by a 32-bit offset: W_gate, W_up and Wc1 below 4 GiB, else
+ *       the call fails with FF_ERR_DEVICE.
+ *       The down tiles 5 and 6 (weights in registers) address a listed
  *       row by a 32-bit offset: W_down below 4 GiB, d_model below 2^23, and H
  *       below 2^24 neurons wide; a call beyond that fails with FF_ERR_DEVICE.
  *   "gemm1_split"  -1 = decide by shape, 0 = never, 1 = always: whether the

@@ -142,6 +142,45 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void *p) {
 }
 
 // ============================ gemm1 =========================================
+// The tile of gemm1 that a workgroup owns: BM tokens from t0 (rows_valid of them there), BN list positions from n0.
+struct Gemm1Tile { int b, m, t0, rows_valid, Kb, ntot, n0; bool valid; };
+template <int BM, int BN>
+__device__ __forceinline__ Gemm1Tile gemm1_tile(const Gemm1Params &p, int V, int mt, int N, int xs, int NX) {
+  Gemm1Tile t;
+  t.valid = false;
+  // ids [0, heavy virtual blocks x NX): the NX tiles beyond the common N of the heavy blocks;
+  // then the common region, N tiles for every block
+  TileCoord tc;
+  const int n_first = p.k.n_heavy * mt * NX;
+  if ((int)blockIdx.x < n_first) {
+    const int h = __builtin_amdgcn_readfirstlane((int)blockIdx.x / NX);
+    const int hb = __builtin_amdgcn_readfirstlane(h / mt);
+    tc.vb = heavy_block(p.k, hb) * mt + (h - hb * mt);
+    tc.nt = N + ((int)blockIdx.x - h * NX);
+    tc.valid = true;
+  } else {
+    tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
+  }
+  if (!tc.valid) return t;
+  // wave-uniform by construction; say so, so that everything derived from it stays scalar
+  tc.vb = __builtin_amdgcn_readfirstlane(tc.vb);
+  tc.nt = __builtin_amdgcn_readfirstlane(tc.nt);
+  t.b = tc.vb / mt;
+  t.m = tc.vb - t.b * mt;
+  t.t0 = t.b * p.block + t.m * BM;
+  t.rows_valid = min(p.T, (t.b + 1) * p.block) - t.t0;
+  if (t.rows_valid <= 0) return t;
+  t.Kb = __builtin_amdgcn_readfirstlane(block_k(p.k, t.b, p.d_ffn, p.k_stride, p.idx != nullptr));
+  const int ntot = t.ntot = t.Kb + p.rc;
+  const int n0 = t.n0 = __builtin_amdgcn_readfirstlane(p.rem_bn ? min(ntot / p.rem_bn * p.rem_bn, p.rem_cap) : 0) + tc.nt * BN;
+  // (H is zero up to the next multiple of 64: a tile narrower than that may hold nothing but zeros)
+  if (n0 >= (BN < 64 ? (ntot + 63) / 64 * 64 : ntot)) return t;
+  if (p.full_only && n0 + BN > ntot) return t;   // the remainder launch takes this part-filled tile
+  if (p.skip_heavy && is_heavy(p.k, t.b)) return t;  // a launch of their own has covered the heavy blocks' ends
+  t.valid = true;
+  return t;
+}
+
 // KG groups of WM x WN wavefronts; a wavefront computes 32*TM tokens x 32*TN list positions
 // for the gate and the up projection at once (the SiLU(g)*u epilogue is lane-local); with
 // KG = 2 the two groups split each stage's k range and exchange halves of their
@@ -177,34 +216,9 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   const int wm = wq / WN, wn = wq % WN;
   const int c = lane & 31, half = lane >> 5;
 
-  // ids [0, heavy virtual blocks x NX): the NX tiles beyond the common N of the heavy blocks;
-  // then the common region, N tiles for every block
-  TileCoord tc;
-  const int n_first = p.k.n_heavy * mt * NX;
-  if ((int)blockIdx.x < n_first) {
-    const int h = __builtin_amdgcn_readfirstlane((int)blockIdx.x / NX);
-    const int hb = __builtin_amdgcn_readfirstlane(h / mt);
-    tc.vb = heavy_block(p.k, hb) * mt + (h - hb * mt);
-    tc.nt = N + ((int)blockIdx.x - h * NX);
-    tc.valid = true;
-  } else {
-    tc = map_tile((int)blockIdx.x - n_first, V, N, xs);
-  }
-  if (!tc.valid) return;
-  // wave-uniform by construction; say so, so that everything derived from it stays scalar
-  tc.vb = __builtin_amdgcn_readfirstlane(tc.vb);
-  tc.nt = __builtin_amdgcn_readfirstlane(tc.nt);
-  const int b = tc.vb / mt, m = tc.vb - b * mt;
-  const int t0 = b * p.block + m * BM;
-  const int rows_valid = min(p.T, (b + 1) * p.block) - t0;
-  if (rows_valid <= 0) return;
-  const int Kb = __builtin_amdgcn_readfirstlane(block_k(p.k, b, p.d_ffn, p.k_stride, p.idx != nullptr));
-  const int ntot = Kb + p.rc;
-  const int n0 = __builtin_amdgcn_readfirstlane(p.rem_bn ? min(ntot / p.rem_bn * p.rem_bn, p.rem_cap) : 0) + tc.nt * BNn;
-  // (H is zero up to the next multiple of 64: a tile narrower than that may hold nothing but zeros)
-  if (n0 >= (BNn < 64 ? (ntot + 63) / 64 * 64 : ntot)) return;
-  if (p.full_only && n0 + BNn > ntot) return;   // the remainder launch takes this part-filled tile
-  if (p.skip_heavy && is_heavy(p.k, b)) return;  // a launch of their own has covered the heavy blocks' ends
+  const Gemm1Tile tl = gemm1_tile<BM, BNn>(p, V, mt, N, xs, NX);
+  if (!tl.valid) return;
+  const int b = tl.b, m = tl.m, t0 = tl.t0, rows_valid = tl.rows_valid, Kb = tl.Kb, ntot = tl.ntot, n0 = tl.n0;
 
   // wave-load j = wave + i * NW of a stage covers stage bytes [1024 j, 1024 j + 1024)
   const bf16_t *src[L];
@@ -435,6 +449,236 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
         }
       }
   }
+}
+
+// The same product with the gathered rows loaded straight into registers.  With both operands in LDS a step's LDS traffic
+// (272 KB per 64 k of a 128 x 256 tile) took three quarters of the time of its MFMAs and did not overlap with them to the full
+// (the chip is at its power limit); here only X passes through LDS (144 KB).  Eight wavefronts side by side, 32 positions of
+// both projections each for all 128 tokens: nobody else in the workgroup wants a wavefront's weights.
+// The k-loop walks along the gathered rows, so an MFMA operand (32x32x16: lane (c, half) holds eight k of row c) loaded as it
+// is has every lane at a row of its own, and the address unit takes one lane per cycle then; four lanes that ask for 64
+// contiguous bytes go together (L2-resident rows, 256 workgroups: 30 TB/s by fours, 18 by twos, 9 one by one).  So load j of a
+// step (64 k) takes rows j + 4 ((lane / 4) mod 8), lanes 0 .. 3 and 32 .. 35 the eight 16-byte chunks of one, and two rounds
+// of exchanges inside the fours (transpose4) turn the four loads of 32 rows into the operands of four MFMA groups: group g
+// has chunk g in the lower half of the wavefront and chunk g + 4 in the upper.  The order of k inside a step is free as long
+// as X is read in the same one.
+// Measured, both operands in LDS against this (one MI355X, 4096/14336): 64 blocks of 128, K 7168, both launches 843 -> 830 us;
+// K 10035 1216 -> 1178; 64 blocks of 64, K 3584 398 -> 343, K 7168 698 -> 645.  With 128 tokens it is the chip's power that
+// binds: without the weights' loads 756 us, without X's copies 775, without the exchanges 803, MFMAs alone 640.  With 64 the
+// loads from beyond L2 do: each row serves 64 tokens.
+// Tiles whose 32 rows of a wavefront are all list rows take 32-bit offsets from the two matrices; compensator units and
+// padding find their matrix lane by lane.
+__device__ __forceinline__ void transpose4(u32x4_t (&r)[4], int d) {
+  // lanes a = 0 .. 3 of every four hold r[j] = (row j, chunk a); afterwards r[g] = (row a, chunk g), dword d
+  uint32_t a = r[0][d], b = r[1][d], c = r[2][d], e = r[3][d], t, s, u;
+  // (a DPP source written by the two instructions before would be read too early: s_nop, and the order below)
+  asm volatile(
+      "s_nop 1\n\t"
+      "s_mov_b64 vcc, %7\n\t"
+      "v_cndmask_b32_dpp %4, %1, %0, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %5, %3, %2, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_not_b64 vcc, vcc\n\t"
+      "v_cndmask_b32_dpp %6, %0, %1, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %3, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_mov_b64 vcc, %8\n\t"
+      "v_cndmask_b32_dpp %0, %5, %4, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %1, %3, %6, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_not_b64 vcc, vcc\n\t"
+      "v_cndmask_b32_dpp %2, %4, %5, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %3, %6, %3, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+v"(a), "+v"(b), "+v"(c), "+v"(e), "=&v"(t), "=&v"(s), "=&v"(u)
+      : "s"(0x5555555555555555ull), "s"(0x3333333333333333ull)
+      : "vcc", "scc");
+  r[0][d] = a; r[1][d] = b; r[2][d] = c; r[3][d] = e;
+}
+constexpr int kDirectStages = 4, kDirectWaves = 8;
+template <int MT, int WN, int NBUF>
+__global__ __launch_bounds__(WN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
+  constexpr int BM = MT * 32, BN = WN * 32, S = kDirectStages, STAGE = BM * 128, D = 4, LA = BM / 8 / WN;
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, half = lane >> 5;
+  const Gemm1Tile tl = gemm1_tile<BM, BN>(p, V, mt, N, xs, NX);
+  if (!tl.valid) return;
+  const int Kb = tl.Kb, ntot = tl.ntot, rows_valid = tl.rows_valid;
+  const int nk = p.d_model / 64, last = nk - 1;
+  const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
+
+  // X: copy i of a stage covers rows 8 (wave + i WN) .. + 7
+  const uint64_t a_base = (uint64_t)(uintptr_t)(p.x + (size_t)tl.t0 * p.d_model);
+  uint32_t a_off[LA];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int trow = (wave + i * WN) * 8 + lane / 8;
+    a_off[i] = (uint32_t)min(trow, rows_valid - 1) * row_bytes + (uint32_t)((lane & 7) ^ swz<64>(trow)) * 16u;
+  }
+  const uint32_t lds0 = lds_addr_of(smem);
+  // (no conditions in the loop: past the end the last step is requested again, into a slot nobody reads any more)
+  auto issue_a = [&](int st, int i) __attribute__((always_inline)) {
+    gload_lds16_off(a_base + (uint64_t)(uint32_t)min(st, last) * 128u, a_off[i], lds0 + (uint32_t)(st % S) * STAGE + (uint32_t)(wave + i * WN) * 1024u);
+  };
+#pragma unroll
+  for (int st = 0; st < NBUF; ++st)
+#pragma unroll
+    for (int i = 0; i < LA; ++i) issue_a(st, i);
+
+  // this lane's rows: position nw + j + 4 lr in load j
+  const int nw = tl.n0 + wave * 32;
+  const int lr = (lane >> 2) & 7, chunk = (lane & 3) + 4 * half;
+  const bool fast = nw + 32 <= Kb;
+  uint32_t w_off[4];            // fast, or a list row: offset into both matrices; else into wc1 (or, past the lists' end, of row 0)
+  uint32_t is_comp = 0;         // bit j: row j is a compensator unit's
+  {
+    int entry[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int pos = nw + j + 4 * lr;
+      entry[j] = p.idx != nullptr ? p.idx[(size_t)tl.b * p.k_stride + min(pos, Kb - 1)] : pos;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int pos = nw + j + 4 * lr;
+      int row = 0;
+      if (pos < Kb) {
+        row = min(max(entry[j], 0), p.d_ffn - 1);
+      } else if (pos < ntot) {
+        row = pos - Kb;
+        is_comp |= 1u << j;
+      }
+      w_off[j] = (uint32_t)row * row_bytes + (uint32_t)chunk * 16u;
+    }
+  }
+
+  f32x16_t acc[MT][2];                        // [token tile][gate, up]
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][f][e] = 0.0f;
+
+  typedef const __attribute__((address_space(1))) u32x4_t *gptr_t;
+  u32x4_t wb[NBUF][2][4];                     // [step mod NBUF][gate, up]: loads j, then (transposed) the operands of group g
+  u32x4_t af[D];                              // ring of token fragments
+  auto load_w = [&](int kt, int buf, int f, int j, auto fast_tag) __attribute__((always_inline)) {
+    const uint32_t ko = (uint32_t)min(kt, last) * 128u;
+    uintptr_t base = (uintptr_t)(f ? p.wu : p.wg) + ko;
+    if (decltype(fast_tag)::value) {
+      asm("" : "+s"(base));                   // a scalar base and the lane's 32-bit offset: no address arithmetic in the loop
+      wb[buf][f][j] = *(gptr_t)(base + w_off[j]);
+    } else {
+      if ((is_comp >> j) & 1u) base = (uintptr_t)p.wc1 + ko;
+      wb[buf][f][j] = *(gptr_t)(base + w_off[j]);
+    }
+  };
+  uint32_t aoff[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) aoff[g] = (uint32_t)(c * 128 + (((g + 4 * half) ^ swz<64>(c)) << 4));
+  // fragment n of a step: group n / MT, token tile n % MT
+  auto frag = [&](int kt, int n) __attribute__((always_inline)) {
+    af[n % D] = *reinterpret_cast<const u32x4_t *>(smem + (kt % S) * STAGE + aoff[n / MT] + (n % MT) * 4096);
+  };
+  // One step of 64 k from buffer kt mod NBUF.  As a group's MFMAs are out, loads of step kt + NBUF take its registers; in the
+  // second half the next buffer's loads (step kt + 1) are transposed; in front of the last D fragments the workgroup makes
+  // sure that X of step kt + 1 has landed, and behind that X of step kt + NBUF is requested, in front of the step's last two
+  // loads.  Requests complete in order, so the wait for X names how many younger ones may still be on their way: all of them.
+  // The slot of X requested in a step was last read in step kt + NBUF - S, hence by nobody who has passed this step's barrier.
+  constexpr int NF = 4 * MT, TR0 = NF / 2;
+  constexpr int NEWER = 2 + 2 * ((NF - D) / MT) + (NBUF - 2) * (8 + LA);
+  static_assert(NBUF < S && (NF - D) % MT == 0, "ring of X");
+  // END: the steps behind the unrolled loop.  Their loads would be for steps that do not exist, so there are none, and the wait
+  // for X cannot count on them.
+  auto step = [&](int kt, auto buf_tag, auto fast_tag, auto end_tag) __attribute__((always_inline)) {
+    constexpr int buf = decltype(buf_tag)::value;
+    constexpr bool END = decltype(end_tag)::value;
+#pragma unroll
+    for (int n = 0; n < NF; ++n) {
+      const int g = n / MT, i = n % MT;
+      if (n == NF - D) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(END ? 0 : NEWER) : "memory");
+      const u32x4_t a = af[n % D];
+#pragma unroll
+      for (int f = 0; f < 2; ++f) acc[i][f] = mfma32(a, wb[buf][f][g], acc[i][f]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n + D < NF) frag(kt, n + D); else frag(kt + 1, n + D - NF);
+      if (n >= NF - 1 - LA && n < NF - 1) issue_a(kt + NBUF, n - (NF - 1 - LA));
+      if (n >= TR0) {
+        constexpr int PER = 8 / (NF - TR0);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+          const int x = (n - TR0) * PER + q;
+          transpose4(wb[(buf + 1) % NBUF][x / 4], x % 4);
+        }
+      }
+      if (!END && i == MT - 1) {
+        load_w(kt + NBUF, buf, 0, g, fast_tag);
+        load_w(kt + NBUF, buf, 1, g, fast_tag);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto run = [&](auto fast_tag) __attribute__((always_inline)) {
+#pragma unroll
+    for (int st = 0; st < NBUF; ++st)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        load_w(st, st, 0, j, fast_tag);
+        load_w(st, st, 1, j, fast_tag);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) transpose4(wb[0][x / 4], x % 4);
+    asm volatile("s_barrier" ::: "memory");            // (the copies of the first two steps are older than those loads)
+#pragma unroll
+    for (int n = 0; n < D; ++n) frag(0, n);
+    __builtin_amdgcn_sched_barrier(0);
+    int kt = 0;
+    constexpr std::integral_constant<int, 0> b0{};
+    constexpr std::integral_constant<int, 1> b1{};
+    constexpr std::integral_constant<int, NBUF - 1> b2{};
+    for (; kt + NBUF <= nk; kt += NBUF) {
+      step(kt, b0, fast_tag, std::false_type{});
+      step(kt + 1, b1, fast_tag, std::false_type{});
+      if (NBUF == 3) step(kt + 2, b2, fast_tag, std::false_type{});
+    }
+    if (kt < nk) step(kt, b0, fast_tag, std::true_type{});
+    if (NBUF == 3 && kt + 1 < nk) step(kt + 1, b1, fast_tag, std::true_type{});
+  };
+  if (fast) run(std::true_type{}); else run(std::false_type{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies requested past the end
+
+  // Lane (c, half) holds position nw + c of rows 8 (e / 4) + 4 half + e mod 4.  Neighbouring lanes exchange one of two
+  // rows, so that each stores two adjacent positions of one row.
+  const int pos = nw + c, odd = c & 1;
+  if (nw >= p.hs) return;                     // (hs is a multiple of 64)
+  const bool plain = p.mask == nullptr && fast;
+  const uint32_t member = (p.mask != nullptr && pos < Kb) ? (uint32_t)p.mask[(size_t)tl.b * p.k_stride + pos] : 0xffffffffu;
+  const uint32_t pick = odd ? 0x03020706u : 0x05040100u;
+  bf16_t *dst0 = p.h + (size_t)tl.t0 * p.hs + (pos - odd);
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+      const int row0 = i * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+      float hv[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const float gt = acc[i][0][e + r], up = acc[i][1][e + r];
+        if (plain) {
+          hv[r] = act_apply(FF_ACT_SILU, gt) * up;
+        } else {
+          hv[r] = pos < Kb ? act_apply(FF_ACT_SILU, gt) * up : (pos < ntot ? act_apply(p.comp_act, gt) : 0.0f);
+          if (p.mask != nullptr && !((member >> ((tl.m * BM + row0 + r) >> p.sub_shift)) & 1u)) hv[r] = 0.0f;
+        }
+      }
+      const uint32_t mine = pack_bf16x2(hv[0], hv[1]);
+      const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, true);   // lane c ^ 1
+      if (row0 + odd < rows_valid)
+        *reinterpret_cast<uint32_t *>(dst0 + (size_t)(row0 + odd) * p.hs) = __builtin_amdgcn_perm(other, mine, pick);
+    }
 }
 
 // Four adjacent outputs of one token row on their way out of the down projection: Y in fp32, Y in
@@ -915,7 +1159,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-constexpr int kDirectStages = 4, kDirectWaves = 8;
 template <int MT, int RM>
 __global__ __launch_bounds__(kDirectWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
@@ -1130,6 +1373,11 @@ Variant g2() {
                   // the streamed list only where the table may not fit and scalar loads cost too much
                   KG > 1 ? reinterpret_cast<const void *>(&ff_gemm2_kernel<WM, WN, TM, BK, S, (KG > 1 ? 3 : 2), KG>) : nullptr}};
 }
+template <int MT, int WN, int NBUF>
+Variant g1d() {
+  return Variant{reinterpret_cast<const void *>(&ff_gemm1_direct_kernel<MT, WN, NBUF>), MT * 32, WN * 32, WN * 64,
+                 kDirectStages * MT * 32 * 128, {nullptr, nullptr, nullptr}};
+}
 template <int MT>
 Variant g2d() {
   return Variant{reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 0>), MT * 16, kDirectWaves * 64, kDirectWaves * 64,
@@ -1152,6 +1400,9 @@ const Variant kGemm1[] = {
     g1<2, 2, 2, 1, 64, 4>(),     // 8: 128 x 64, 4 waves, BK 64, 4 stages (128 KB; 2 stages: 67 against 48 us on 224 tiles): the heavy blocks' surplus
     g1<2, 1, 2, 1, 64, 6, 2>(),  // 9: 128 x 32, 4 waves in 2 k-groups, BK 64, 6 stages (144 KB): a single block over the whole chip
     g1<1, 1, 2, 1, 64, 8, 2>(),  // 10: 64 x 32, 2 waves in 2 k-groups, BK 64, 8 stages (128 KB): the same for a short block
+    g1d<4, 8, 2>(),                 // 11: 128 x 256, 8 waves, weights in registers (64 KB)
+    g1d<2, 8, 3>(),              // 12: 64 x 256, the same, weights of three steps on their way (32 KB)
+    // (5 and 6 serve matrices of 4 GiB and more, whose rows' offsets have more than 32 bits)
     // (tiles whose wavefronts need 256 accumulator registers -- 128 x 256 or 256 x 128 on 4 waves -- were measured
     //  10-25% slower: one wavefront per SIMD cannot keep the matrix pipe issuing back to back)
 };
@@ -1241,15 +1492,24 @@ static int up64(int v) { return (v + 63) / 64 * 64; }   // (tiles narrower than 
 constexpr int kRemainderVariant = 7;
 constexpr int kHeavySurplusVariant = 8;
 constexpr int kWide128 = 6;
-constexpr int kDirect128 = 5, kDirect64 = 6;   // the down-GEMM tiles with the weights in registers
+constexpr int kGemm1Direct128 = 11, kGemm1Direct64 = 12;   // the gate/up tiles with the weights in registers
+constexpr int kDirect128 = 5, kDirect64 = 6;   // the down-GEMM tiles
 constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
+
+static bool gemm1_direct(int variant) { return variant >= kGemm1Direct128; }
+// whether the tile with the weights in registers can address these matrices: the offsets of a row and of a token of its tile
+// have 32 bits
+static bool gemm1_direct_addresses(const Gemm1Params &p) {
+  const uint64_t row_bytes = (uint64_t)p.d_model * 2u;
+  return (uint64_t)std::max(p.d_ffn, p.rc) * row_bytes >> 32 == 0 && (uint64_t)kGemm1[kGemm1Direct128].bm * row_bytes >> 32 == 0;
+}
 
 // Gate/up tiles by the cost of one round of 256 of them, relative to a round of the 128 x 256 tile (117 us at
 // d_model 4096 with the chip full, 4096/14336).  Tiles with fewer positions move more bytes per FLOP, hence cost
 // more than their share (0.52, 0.33 and 0.24 for a half, a quarter and an eighth), but fill the chip where a call has
 // too few big tiles or would start a last round with a few of them.
 struct Gemm1Cost { int variant; double round; };
-constexpr Gemm1Cost kGemm1Short[] = {{5, 0.90}, {kRemainderVariant, 0.27}, {10, 0.22}};                      // blocks up to 64 tokens
+constexpr Gemm1Cost kGemm1Short[] = {{kGemm1Direct64, 0.74}, {5, 0.90}, {kRemainderVariant, 0.27}, {10, 0.22}};   // blocks up to 64 tokens
 constexpr Gemm1Cost kGemm1Mid[] = {{0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};                      // up to 255
 constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};           // 256 and more, and without a list
 
@@ -1265,11 +1525,11 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     // one block, 64 x 256 92 -> 64 x 32 26; K 3584, ten blocks of 64, 64 x 256 114 -> 64 x 64 100; 1100 tokens in blocks
     // of 256, 256 x 128 216 -> 128 x 128 178; dense 3584/18944, 300 tokens, 256 x 128 190 -> 128 x 128 110.)
     const Gemm1Cost *tab = p.block > 64 ? (p.block >= 256 ? kGemm1Long : kGemm1Mid) : kGemm1Short;
-    const int n_tab = p.block >= 256 ? 4 : 3;
+    const int n_tab = p.block >= 256 || p.block <= 64 ? 4 : 3;
     double best = 0.0;
     for (int i = 0; i < n_tab; ++i) {
       const Variant &v = kGemm1[tab[i].variant];
-      if (v.lds > g_lds_limit) continue;
+      if (v.lds > g_lds_limit || (gemm1_direct(tab[i].variant) && !gemm1_direct_addresses(p))) continue;
       // without a list the blocks mean nothing: token tiles of this variant's height
       const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
       const long first = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * ((up64(n_extent) + v.bn - 1) / v.bn - (up64(base_extent) + v.bn - 1) / v.bn);
@@ -1280,14 +1540,15 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     }
     if (variant < 0) return hipErrorInvalidValue;
     if (p.block > 64 && p.block < 256) {
-      // The 128 x 256 tile moves fewer bytes per FLOP; its part-filled last tile goes to the remainder
+      // The 128 x 256 tile (with the weights in registers where it can address them) moves fewer bytes per FLOP; its part-filled last tile goes to the remainder
       // launch (with lists of unequal length every block's own).  In rounds of it: whole rounds of full wide
       // tiles plus 0.22 per round of remainder tiles, plus the launch of the few much longer lists' ends (half a
       // round of tiles at most, 0.4; else further wide tiles).  (Measured, wide
       // against 128 x 128: 4096/14336 x 64 blocks K 7168 0.888 / 0.916 ms, K 7300 0.895 / 0.920, K 3584 -- 3.5
       // rounds of wide tiles -- 0.520 / 0.490; 16 blocks of 7168 with the first and last dense 0.332 / 0.267;
       // 3584/18944 x 128 blocks K 13126 2.75 / 2.86; 2048/8192 x 32 blocks K 4200 0.155 / 0.172.)
-      const Variant &w = kGemm1[kWide128];
+      const int wide = gemm1_direct_addresses(p) ? kGemm1Direct128 : kWide128;
+      const Variant &w = kGemm1[wide];
       const int rem_w = base_extent % w.bn;
       const long wide_full = (long)p.n_blocks * (base_extent / w.bn);
       const long rem_wgs = (long)p.n_blocks * 2 * ((rem_w + 63) / 64);
@@ -1298,12 +1559,13 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
       // (merged lists: only a bound of their lengths is known here)
       const bool unknown = ragged && p.k.n_heavy == 0;
       if (split != 0 && w.lds <= g_lds_limit && base_extent >= w.bn && (unknown || cost_wide <= best) && wide_full >= 224) {
-        variant = kWide128;
+        variant = wide;
         if (rem_w > 0 || ragged) split = 1;
       }
     }
   }
   if (variant >= kNumGemm1 || kGemm1[variant].lds > g_lds_limit) return hipErrorInvalidValue;
+  if (gemm1_direct(variant) && !gemm1_direct_addresses(p)) return hipErrorInvalidValue;   // forced
   const Variant &v = kGemm1[variant];
   if (p.idx == nullptr) {
     p.block = v.bm;

@@ -103,6 +103,27 @@ static void check_gemm1(const Shape &s) {
       }
 }
 
+// Gate/up: the tiles with the weights in registers (11 and 12) form 32-bit offsets into a matrix.  Where those do not reach,
+// the library takes another tile and a forced one is an error.
+static void check_gemm1_addresses() {
+  std::set<const void *> in_registers;
+  for (int variant : {11, 12}) {
+    CHECK(gemm1({700, 128, 256, 1024, 32, 512, 0, 0}, true, variant, 0, -1) == hipSuccess && g_log.size() == 1, "tile %d", variant);
+    for (const Launch &l : g_log) in_registers.insert(l.fn);
+  }
+  struct { Shape s; bool ok; } sizes[] = {{{9000, 128, 65536, 32768, 32, 7168, 0, 0}, false}, {{9000, 64, 65536, 32768, 32, 7168, 0, 0}, false},
+                                         {{9000, 128, 65536, 32760, 32, 7168, 0, 0}, true},   {{9000, 64, 65536, 32760, 32, 7168, 0, 0}, true},
+                                         {{20, 10, 16777216, 8, 0, 8, 0, 0}, false},          {{20, 10, 4194304, 8, 0, 8, 0, 0}, true}};
+  for (const auto &z : sizes) {
+    CHECK(gemm1(z.s, true, -1, -1, -1) == hipSuccess, "d_model %d d_ffn %d", z.s.d_model, z.s.d_ffn);
+    int used = 0;
+    for (const Launch &l : g_log) used += in_registers.count(l.fn);
+    CHECK(z.s.T < 9000 ? z.ok || !used : (used > 0) == z.ok, "d_model %d d_ffn %d block %d", z.s.d_model, z.s.d_ffn, z.s.block);
+    for (int variant : {11, 12})
+      CHECK((gemm1(z.s, true, variant, 0, -1) == hipSuccess) == z.ok && g_log.empty() == !z.ok, "d_model %d d_ffn %d tile %d", z.s.d_model, z.s.d_ffn, variant);
+  }
+}
+
 // Down: the tiles with the weights in registers (5 and 6) form 32-bit offsets into W_down and H.  Where those do not
 // reach, the library takes another tile and a forced one is an error, cut along the list or not.
 static void check_gemm2_addresses() {
@@ -228,6 +249,7 @@ int main() {
         for (int k : {33, 96, 160, 1000, 3584, 7168})
           for (int rc : {0, 32, 64})
             check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
+  check_gemm1_addresses();
   check_gemm2_addresses();
   check_gemm2_routes();
   check_gemm2_row_sources();

@@ -638,6 +638,41 @@ def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
         ctx.set_workspace(keep)
 
 
+@pytest.mark.parametrize("d_model", [128, 256, 384, 640])
+@pytest.mark.parametrize("variant,block", [(11, 96), (11, 200), (12, 33), (12, 96)])
+def test_gate_up_gemm_with_weights_in_registers(ctx, variant, block, d_model):
+    """The gate/up tiles that load the gathered rows straight into registers (128 x 256 and 64 x 256): 2 to 10 steps of 64
+    channels (the shortest loops, and every remainder of the unrolled ones), lists that end inside a wavefront's 32 rows, on
+    one and on a whole tile, rows that are compensator units next to list rows, blocks that fill no tile and take two, the
+    identity list.  In a workspace full of NaN, against the oracle at the stated bars and against the tile with both operands
+    in LDS: H differs where other fp32 sums of the same products round to the other bf16 neighbour, at most one step of
+    2^-8 of a value in a few positions, which a sum over up to 700 positions of |w| = 0.02 keeps far below 1e-3 of max |y|."""
+    ks = [31, 256, 257, 600]
+    c = Case(W.Shape("g1direct", d_model, 704, 3 * block + 17, block, 8, 40))
+    ref = c.oracle_layer(ks)
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=704)
+    ref_d = O.dense_ffn(_f32(c.x_bits), c.host("w_gate"), c.host("w_up"), c.host("w_down").T)
+    ctx.ensure_workspace(c.shape, 704)
+    out = {}
+    try:
+        ctx.set_option("merge_blocks", 0)
+        for v, split in ((2, 0), (variant, 0), (variant, 1)):
+            ctx.set_option("gemm1_variant", v)
+            ctx.set_option("gemm1_split", split)
+            ctx._ws.fill_(0xFF)
+            y = torch.empty((c.T, d_model), dtype=torch.float32, device=DEV)
+            ctx.dense_ffn(c.shape, c.x, c.w, y, B.OUT_F32)
+            ctx._ws.fill_(0xFF)
+            out[v, split] = c.gpu_sparse(ctx, idx, ks, out_f32=True), y
+            _check_y(out[v, split][0], ref.y, f"tile {v} split {split}, block {block}, d_model {d_model}")
+            _check_y(y, ref_d, f"tile {v} split {split}, dense, d_model {d_model}")
+    finally:
+        for option in ("gemm1_variant", "gemm1_split", "merge_blocks"):
+            ctx.set_option(option, -1)
+    for got in out.values():
+        assert all((g - o).abs().max().item() <= 1e-3 * o.abs().max().item() for g, o in zip(got, out[2, 0]))
+
+
 @pytest.mark.parametrize("variant", [5, 6])
 @pytest.mark.parametrize("rc,ks", [(0, [1, 64, 65, 320]), (8, [1064, 56, 127, 440]), (64, [128, 129, 1064, 640]), (24, [1064] * 4)])
 def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
