@@ -1451,27 +1451,56 @@ constexpr int kNumCU = 256;
 // (Gate/up launch, always eight groups against this rule: 4096/14336, K 7168, 128-token blocks: 1 block 130 -> 69 us,
 // 4 blocks 141 -> 79, 12 blocks 241 -> 192; 65 blocks of 77: 938 -> 894; 64 blocks unchanged; 3584/18944 dense, 300
 // tokens: 459 -> 185, 9001 tokens 2264 -> 2038, and the down launch 1715 -> 1260.)
-static int xcd_groups(long V, long N) {
+// Among grids of no more rounds, the one that fetches less from beyond an XCD's L2: an XCD holds 32 tiles at a time, as many
+// of its blocks as it has and the rest tiles of the same block.  A weight line is fetched once for those of its resident
+// blocks that keep the neuron, a line of X once for the resident tiles of its block, so more blocks and fewer tiles pay where
+// blocks are short and lists sparse.  Fewer groups of blocks have to save a sixth of it.  (4096/14336, eight groups against
+// this: 64 blocks of 64, K 3584: gate/up 343 -> 333 us, down 147 -> 138; 64 blocks of 128, K 7168: down 397 -> 389; 2048/8192,
+// 32 blocks of 128, K 4096: both 1% less.)
+struct Share {
+  int w_rows, x_rows;   // a tile's rows (or their pieces) of weights and of X or H, in proportion to the bytes
+  double keep;          // share of the neurons on a list; 0: tiles that share nothing to speak of
+  int mt;               // token tiles of a block, which share its list
+};
+static int xcd_groups(long V, long N, const Share &sh) {
   int best = 3;
-  double best_cost = 0.0;
+  double best_cost = 0.0, cost[4];
   for (int xs = 3; xs >= 0; --xs) {
     const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
     const long rounds = (tiles + kNumCU / 8 - 1) / (kNumCU / 8);
-    const double cost = rounds > 1 ? (double)rounds : (double)tiles / (kNumCU / 8);
-    if (xs == 3) best_cost = cost * 31.0 / 32.0;
-    else if (cost < best_cost) { best = xs; best_cost = cost; }
+    cost[xs] = rounds > 1 ? (double)rounds : (double)tiles / (kNumCU / 8);
+    if (xs == 3) best_cost = cost[xs] * 31.0 / 32.0;
+    else if (cost[xs] < best_cost) { best = xs; best_cost = cost[xs]; }
   }
+  if (sh.keep <= 0.0 || cost[best] <= 1.0) return best;
+  auto fetch = [&](int xs) {
+    const long blocks = std::min<long>((V + (1 << xs) - 1) >> xs, kNumCU / 8);
+    const long tiles = std::min<long>((N + (8 >> xs) - 1) / (8 >> xs), std::max<long>(1, kNumCU / 8 / blocks));
+    double none = 1.0;
+    for (long l = 0; l < std::max<long>(1, blocks / sh.mt); ++l) none *= 1.0 - sh.keep;
+    return sh.w_rows * (1.0 - none) / ((double)blocks * sh.keep) + (double)sh.x_rows / (double)tiles;
+  };
+  const int rounds_best = best;
+  for (int xs = best - 1; xs >= 0; --xs)
+    if (cost[xs] <= cost[rounds_best] && fetch(xs) < fetch(best) * 5.0 / 6.0) best = xs;
   return best;
+}
+// what the tiles of variant v share in a launch of these parameters
+template <class Params>
+static Share share_of(const Variant &v, const Params &p, bool gemm1) {
+  // (a few much longer lists: their tiles are everywhere; 16 blocks, two of them dense, lose 20 us of 260 in four groups)
+  const double keep = p.k.n_heavy > 0 ? 0.0 : (p.idx == nullptr ? 1.0 : std::min(1.0, (double)p.k.k_max / p.d_ffn));
+  return Share{gemm1 ? 2 * v.bn : v.bn, v.bm, keep, p.idx == nullptr ? 1 : (p.block + v.bm - 1) / v.bm};
 }
 
 // V virtual blocks (each block cut into M tiles of v.bm tokens) x N tiles, preceded by the
 // heavy blocks' n_first_per_vb tiles each
 static hipError_t launch_variant(const Variant &v, const void *fn, const void *params, int block, int n_blocks,
-                                 int N, int n_heavy, int n_first_per_vb, bool gemm1, hipStream_t s) {
+                                 int N, int n_heavy, int n_first_per_vb, bool gemm1, const Share &share, hipStream_t s) {
   int mt = (block + v.bm - 1) / v.bm;
   int V = n_blocks * mt;
   int NX = n_first_per_vb;
-  int xs = xcd_groups(V, N);
+  int xs = xcd_groups(V, N, share);
   int grid = n_heavy * mt * n_first_per_vb + 8 * ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
   if (grid <= 0) return hipSuccess;
   void *args1[] = {const_cast<void *>(params), &V, &mt, &N, &xs, &NX};
@@ -1482,7 +1511,7 @@ static hipError_t launch_variant(const Variant &v, const void *fn, const void *p
 // Rounds of workgroups (one per CU) that V x N tiles take on the busiest XCD under the mapping that
 // launch_variant will use.
 static long xcd_rounds(long V, long N) {
-  const int xs = xcd_groups(V, N);
+  const int xs = xcd_groups(V, N, Share{});   // (what is shared takes no grid of more rounds)
   const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
   return (tiles + kNumCU / 8 - 1) / (kNumCU / 8);
 }
@@ -1594,7 +1623,7 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
   const int heavy = p.k.n_heavy;
   if (!do_split) {
     const int N = (up64(base_extent) + v.bn - 1) / v.bn, N_all = (up64(n_extent) + v.bn - 1) / v.bn;
-    return launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, heavy, N_all - N, true, s);
+    return launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, heavy, N_all - N, true, share_of(v, p, true), s);
   }
   q.full_only = 1;
   const int N = base_extent / v.bn, N_all = n_extent / v.bn;
@@ -1613,7 +1642,7 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
   const bool heavy_small = heavy > 0 && surplus_tiles > 0 && hv.bm <= v.bm && variant != kHeavySurplusVariant &&
                            (heavy_tiles > 0 || (heavy_tiles < 0 && 2 * surplus_tiles <= kNumCU));
   {
-    hipError_t e = launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, heavy, heavy_small ? 0 : N_all - N, true, s);
+    hipError_t e = launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, heavy, heavy_small ? 0 : N_all - N, true, share_of(v, p, true), s);
     if (e != hipSuccess) return e;
   }
   q.full_only = 0;
@@ -1622,13 +1651,13 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     // everything of a heavy block from where the main launch stopped, its part-filled last tile included
     Gemm1Params qh = q;
     qh.rem_cap = N * v.bn;
-    hipError_t e = launch_variant(hv, hv.fn, &qh, p.block, p.n_blocks, 0, heavy, (n_extent - qh.rem_cap + hv.bn - 1) / hv.bn, true, s);
+    hipError_t e = launch_variant(hv, hv.fn, &qh, p.block, p.n_blocks, 0, heavy, (n_extent - qh.rem_cap + hv.bn - 1) / hv.bn, true, Share{}, s);
     if (e != hipSuccess) return e;
     q.skip_heavy = 1;
   }
   q.k.n_heavy = heavy_small ? q.k.n_heavy : 0;   // every block has at most one part-filled tile: no heavy region
   const int rem_max = ragged ? v.bn - 1 : rem;
-  return launch_variant(r, r.fn, &q, p.block, p.n_blocks, (rem_max + r.bn - 1) / r.bn, 0, 0, true, s);
+  return launch_variant(r, r.fn, &q, p.block, p.n_blocks, (rem_max + r.bn - 1) / r.bn, 0, 0, true, Share{}, s);
 }
 
 
@@ -1690,7 +1719,7 @@ static hipError_t launch_gemm2_cut(Gemm2Params p, int variant, int n, int row_mo
   p.n_cols = (p.d_model + v.bn - 1) / v.bn;
   p.part = p.split_part;
   p.k.n_heavy = 0;
-  hipError_t e = launch_variant(v, v.fn, &p, p.block, p.n_blocks, p.n_cols * n, 0, 0, false, s);
+  hipError_t e = launch_variant(v, v.fn, &p, p.block, p.n_blocks, p.n_cols * n, 0, 0, false, Share{}, s);
   if (e != hipSuccess) return e;
   void *args[] = {&p};
   return hipLaunchKernel(reinterpret_cast<const void *>(&ff_gemm2_reduce_kernel), dim3(p.T, (p.d_model + 1023) / 1024), dim3(256), args, 0, s);
@@ -1751,7 +1780,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
       const long N = (p.d_model + v.bn - 1) / v.bn;
       for (int n = n0; n == n0 || (may_cut && n <= room && V * N * n <= 2 * kNumCU && ntot >= n * 64); ++n) {
         if (!gemm2_takes(g.variant, p, row_mode, (ntot + n - 1) / n)) continue;
-        const int xs = xcd_groups(V, N * n);
+        const int xs = xcd_groups(V, N * n, n > 1 ? Share{} : share_of(v, p, false));
         const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N * n + (8 >> xs) - 1) / (8 >> xs));   // of the busiest XCD
         const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
         double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * g.full);
@@ -1832,16 +1861,16 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     }
   }
   if (q.n_pieces > 0) {   // (then nq == 0: the column split is for lists of equal length, or forced)
-    hipError_t e = launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, q.k.n_heavy, N * (q.n_pieces - 1), false, s);
+    hipError_t e = launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, q.k.n_heavy, N * (q.n_pieces - 1), false, share_of(v, p, false), s);
     if (e != hipSuccess) return e;
     void *args[] = {&q};
     return hipLaunchKernel(reinterpret_cast<const void *>(&ff_gemm2_reduce_kernel), dim3(q.k.n_heavy * p.block, (p.d_model + 1023) / 1024), dim3(256),
                            args, 0, s);
   }
-  if (nq == 0) return launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, q.k.n_heavy, N, false, s);
-  hipError_t e = launch_variant(v, v.fn, &q, p.block, p.n_blocks, N - nq, q.k.n_heavy, N - nq, false, s);
+  if (nq == 0) return launch_variant(v, v.fn, &q, p.block, p.n_blocks, N, q.k.n_heavy, N, false, share_of(v, p, false), s);
+  hipError_t e = launch_variant(v, v.fn, &q, p.block, p.n_blocks, N - nq, q.k.n_heavy, N - nq, false, share_of(v, p, false), s);
   if (e != hipSuccess) return e;
   q.col0 = (N - nq) * v.bn;
   const int N2 = (p.d_model - q.col0 + h.bn - 1) / h.bn;
-  return launch_variant(h, h.fn, &q, p.block, p.n_blocks, N2, q.k.n_heavy, N2, false, s);
+  return launch_variant(h, h.fn, &q, p.block, p.n_blocks, N2, q.k.n_heavy, N2, false, share_of(h, p, false), s);
 }
