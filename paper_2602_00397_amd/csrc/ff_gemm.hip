@@ -30,7 +30,6 @@ constexpr int kSpreadGroupsTwoStage = 2;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
 __device__ __forceinline__ f32x16_t mfma32(const u32x4_t &a, const u32x4_t &b, f32x16_t c) {
@@ -468,30 +467,6 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
 // loads from beyond L2 do: each row serves 64 tokens.
 // Tiles whose 32 rows of a wavefront are all list rows take 32-bit offsets from the two matrices; compensator units and
 // padding find their matrix lane by lane.
-__device__ __forceinline__ void transpose4(u32x4_t (&r)[4], int d) {
-  // lanes a = 0 .. 3 of every four hold r[j] = (row j, chunk a); afterwards r[g] = (row a, chunk g), dword d
-  uint32_t a = r[0][d], b = r[1][d], c = r[2][d], e = r[3][d], t, s, u;
-  // (a DPP source written by the two instructions before would be read too early: s_nop, and the order below)
-  asm volatile(
-      "s_nop 1\n\t"
-      "s_mov_b64 vcc, %7\n\t"
-      "v_cndmask_b32_dpp %4, %1, %0, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %5, %3, %2, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "s_not_b64 vcc, vcc\n\t"
-      "v_cndmask_b32_dpp %6, %0, %1, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %3, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "s_mov_b64 vcc, %8\n\t"
-      "v_cndmask_b32_dpp %0, %5, %4, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %1, %3, %6, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "s_not_b64 vcc, vcc\n\t"
-      "v_cndmask_b32_dpp %2, %4, %5, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %3, %6, %3, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1"
-      : "+v"(a), "+v"(b), "+v"(c), "+v"(e), "=&v"(t), "=&v"(s), "=&v"(u)
-      : "s"(0x5555555555555555ull), "s"(0x3333333333333333ull)
-      : "vcc", "scc");
-  r[0][d] = a; r[1][d] = b; r[2][d] = c; r[3][d] = e;
-}
 constexpr int kDirectStages = 4, kDirectWaves = 8;
 template <int MT, int WN, int NBUF>
 __global__ __launch_bounds__(WN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))

@@ -1,278 +1,308 @@
 // Few-token path of the sparse FFN (Eq. 15-18, 20-21 for prompts of at most kGemvMaxTokens
 // tokens: the generation-time regime, where a block is a handful of tokens or a single one).
 // With so few rows the work is a gather of 3 K weight rows per block read exactly once, i.e.
-// bound by HBM, and the MFMA tiles of the prefill kernels would leave most of the chip idle
-// (one block gives the down GEMM only d_model / 512 workgroups).  Three plain-ALU kernels:
+// bound by HBM, and the tiles of the prefill kernels would leave most of the chip idle
+// (one block gives the down GEMM only d_model / 512 workgroups).  Two kernels:
 //   gemv1: H[t][p] = bf16( SiLU(x_t . Wgate[r]) * (x_t . Wup[r]) ), r = idx_b[p]   (p <  K_b)
 //          H[t][p] = bf16( act(x_t . Wc1[p - K_b]) )                                (compensator units)
-//          one wavefront per list position, the lanes split d_model, fixed-order lane reduction;
-//   gemv2: partial Y over a chunk of list positions for 256 output columns per wavefront
-//          (split along the list so that one block still fills the chip), fp32;
-//   gemv3: Y[t] = sum of the chunk partials in a fixed order, rounded once (or added to the
-//          residual stream).
+//          H[t][p] = 0                                                      up to the next multiple of 32
+//   gemv2: Y[t] = sum_p H[t][p] * R_b[p][:], the list in chunks whose fp32 partial sums the last workgroup of a column
+//          group adds in chunk order; rounded once (or added to the residual stream).
 // Same rounding points as the prefill kernels (H in bf16, fp32 accumulation); every reduction has
 // a fixed order, so results are reproducible.
+// The products are MFMAs with weight rows on one side and the tokens, repeated to fill an operand, on the
+// other: with multiply-adds the arithmetic of several tokens and its lane reductions took longer than the loads.
 #include "ff_internal.h"
 
 namespace {
 
-constexpr int kMaxPosPerWg = 32;   // gemv1: most list positions per workgroup (8 per wavefront)
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
+constexpr int kGemv1Waves = 4, kGemvWaves = 8;   // wavefronts per workgroup of gemv1 and gemv2
+constexpr int kGemv1Pos = 16;      // list positions per workgroup of gemv1
+constexpr int kGemv2Cols = 128;    // output columns per workgroup of gemv2
+constexpr int kGemv1Red = kGemv1Waves * 16 * 16 * 4;  // bytes of gemv1's reduction
+
+__device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t mfma32(const u32x4_t &a, const u32x4_t &b, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
 // list length of block b; without a list (dense: position p is row p) the pitch does not bound it
 __device__ __forceinline__ int gv_block_k(const GemvParams &p, int b) {
   int K = p.k.per_block ? p.k.per_block[b] : p.k.uniform;
   K = max(1, min(K, p.d_ffn));
   return p.idx ? min(K, p.k_stride) : K;
 }
-__device__ __forceinline__ int gv_row(const int32_t *list, int pos, int d_ffn) {
-  return min(max(list ? list[pos] : pos, 0), d_ffn - 1);
-}
 __device__ __forceinline__ float gv_act(int act, float g) {
   if (act == FF_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
   if (act == FF_ACT_RELU) return fmaxf(g, 0.0f);
   return g;
 }
-__device__ __forceinline__ void unpack8(const uint4 &v, float (&f)[8]) {
-  f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
-  f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
-  f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xffff0000u);
-  f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
-}
-// sum over the 64 lanes in a fixed butterfly order; every lane ends with the total
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
 
-// grid (ceil(max list length / pos_per_wg), n_blocks), 256 or 1024 threads, LDS = nt * d_model bf16
-__global__ __launch_bounds__(1024) void ff_gemv1_kernel(GemvParams p) {
+// One workgroup per 16 list positions; its wavefronts split the channels (steps steps of 64 each), every wavefront with a ring
+// of 2 steps on their way, and their sums are added in wavefront order.  The 32 rows of an MFMA (32x32x16) are the 16 gate rows
+// and the 16 up rows; they are loaded by fours of lanes and exchanged as in the gate/up GEMM (lane by lane, as the operand wants
+// them, the address unit made it 54.9 us for a dense token of 4096/14336).  The block's tokens go through LDS, each
+// wavefront its own channels, 16-byte chunks swizzled by the token; the tokens repeat past the last one.
+// Bound by HBM.  Few wavefronts, few steps of each on their way and small workgroups: what counts is that workgroups start and
+// end next to each other (a dense token: 8 wavefronts with 4 steps 54.5 us, with 2 steps 52.6, 4 wavefronts with 2 steps 47.8).
+// With multiply-adds, a wavefront per position, it took 44 us, 23.4 on a list of 7168 as now, but 19.0 for five tokens on
+// 4096 positions of 2048/8192 (now 15.2) and 24.5 for eight (17.1).
+// grid (groups of 16 positions, n_blocks), LDS = gemv1_lds.
+__global__ __launch_bounds__(kGemv1Waves * 64) __attribute__((amdgpu_waves_per_eu(6)))
+void ff_gemv1_kernel(GemvParams p, int steps) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, half = lane >> 5;
   const int b = blockIdx.y;
   const int t0 = b * p.block;
   const int nt = min(p.T, t0 + p.block) - t0;          // <= kGemvMaxTokens by the launcher's check
   const int Kb = gv_block_k(p, b);
   const int ntot = Kb + p.rc;
-  const int pos0 = blockIdx.x * p.pos_per_wg;
-  if (pos0 >= ntot) return;
-  // the block's tokens, as they are
-  const uint4 *xg = reinterpret_cast<const uint4 *>(p.x + (size_t)t0 * p.d_model);
-  uint4 *xs = reinterpret_cast<uint4 *>(smem);
-  const int n16 = nt * (p.d_model / 8);
-  for (int i = tid; i < n16; i += blockDim.x) xs[i] = xg[i];
-  __syncthreads();
-  const int32_t *list = p.idx ? p.idx + (size_t)b * p.k_stride : nullptr;
-  for (int pp = wave; pp < p.pos_per_wg; pp += nw) {
-    const int pos = pos0 + pp;
-    if (pos >= ntot) break;
-    const bool gated = pos < Kb;
-    const uint32_t member = (p.mask != nullptr && gated) ? (uint32_t)p.mask[(size_t)b * p.k_stride + pos] : 0xffffffffu;
-    const bf16_t *grow, *urow;
-    if (gated) {
-      const int r = gv_row(list, pos, p.d_ffn);
-      grow = p.wg + (size_t)r * p.d_model;
-      urow = p.wu + (size_t)r * p.d_model;
-    } else {
-      grow = urow = p.wc1 + (size_t)(pos - Kb) * p.d_model;
-    }
-    float ag[kGemvMaxTokens], au[kGemvMaxTokens];
+  const int pos0 = blockIdx.x * kGemv1Pos;
+  // (the counters of the next kernel's column groups start at zero)
+  if (blockIdx.x == 0)
+    for (int i = tid; i < p.d_model / kGemv2Cols; i += kGemv1Waves * 64) p.counter[b * (p.d_model / kGemv2Cols) + i] = 0;
+  if (pos0 >= (ntot + 31) / 32 * 32) return;
+  // load j of a step: chunk (lane mod 4) + 4 (lane / 32) of row j + 4 (lane / 4 mod 8), gate rows in front of the up rows
+  // (positions past the list's end: the last one's rows again; H is written as zero there)
+  const bool up = (lane >> 4) & 1;
+  int entry[4];
 #pragma unroll
-    for (int t = 0; t < kGemvMaxTokens; ++t) { ag[t] = 0.0f; au[t] = 0.0f; }
-    // lanes take 8-element chunks l, l + 64, ...; four chunks of each matrix in flight
-    for (int c0 = lane * 8; c0 < p.d_model; c0 += 4 * 512) {
-      uint4 gv[4], uv[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = c0 + j * 512;
-        const bool in = c < p.d_model;
-        gv[j] = in ? *reinterpret_cast<const uint4 *>(grow + c) : make_uint4(0, 0, 0, 0);
-        uv[j] = (in && gated) ? *reinterpret_cast<const uint4 *>(urow + c) : make_uint4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = c0 + j * 512;
-        if (c < p.d_model) {
-          float gf[8], uf[8];
-          unpack8(gv[j], gf);
-          unpack8(uv[j], uf);
-#pragma unroll
-          for (int t = 0; t < kGemvMaxTokens; ++t)
-            if (t < nt) {
-              float xf[8];
-              unpack8(xs[t * (p.d_model / 8) + c / 8], xf);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                ag[t] = fmaf(gf[e], xf[e], ag[t]);
-                au[t] = fmaf(uf[e], xf[e], au[t]);
-              }
-            }
-        }
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < kGemvMaxTokens; ++t)
-      if (t < nt) {
-        const float g = wave_sum(ag[t]);
-        const float u = wave_sum(au[t]);
-        if (lane == 0) {
-          float hv = gated ? gv_act(FF_ACT_SILU, g) * u : gv_act(p.comp_act, g);
-          if (p.mask != nullptr && !((member >> (t / p.sub_block)) & 1u)) hv = 0.0f;   // not selected for this token
-          p.h[(size_t)(t0 + t) * p.hs + pos] = f32_to_bf16(hv);
-        }
-      }
+  for (int j = 0; j < 4; ++j) {
+    const int pos = min(pos0 + j + 4 * ((lane >> 2) & 3), ntot - 1);
+    entry[j] = p.idx ? p.idx[(size_t)b * p.k_stride + min(pos, Kb - 1)] : pos;
   }
+  const int ch0 = wave * steps * 64;                             // this wavefront's first channel
+  const int n = max(0, min(p.d_model - ch0, steps * 64)) / 64;   // its steps
+  const int pitch = steps * 128;                                 // bytes per token in LDS
+  uint8_t *xs = smem + (size_t)wave * nt * pitch;
+  uint4 xv[kGemvMaxTokens];
+  const int nc = n * 8;                                          // 16-byte chunks per token
+#pragma unroll
+  for (int t = 0; t < kGemvMaxTokens; ++t)
+    if (t < nt && lane < nc) xv[t] = *reinterpret_cast<const uint4 *>(p.x + (size_t)(t0 + t) * p.d_model + ch0 + lane * 8);
+  __builtin_amdgcn_sched_barrier(0);
+  const bf16_t *rows[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int pos = min(pos0 + j + 4 * ((lane >> 2) & 3), ntot - 1);
+    const bf16_t *row = pos < Kb ? (up ? p.wu : p.wg) + (size_t)min(max(entry[j], 0), p.d_ffn - 1) * p.d_model
+                                 : p.wc1 + (size_t)(pos - Kb) * p.d_model;
+    rows[j] = row + ch0 + ((lane & 3) + 4 * half) * 8;
+  }
+  constexpr int U = 2;
+  u32x4_t w[U][4];
+  if (n > 0) {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[i][j] = *reinterpret_cast<const u32x4_t *>(rows[j] + min(i, n - 1) * 64);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < kGemvMaxTokens; ++t)
+    if (t < nt && lane < nc) *reinterpret_cast<uint4 *>(xs + t * pitch + ((lane ^ t) << 4)) = xv[t];
+  for (int t = 0; t < nt; ++t)
+    for (int ch = lane + 64; ch < nc; ch += 64)
+      *reinterpret_cast<uint4 *>(xs + t * pitch + ((ch ^ t) << 4)) = *reinterpret_cast<const uint4 *>(p.x + (size_t)(t0 + t) * p.d_model + ch0 + ch * 8);
+  // (a wavefront reads what it wrote itself: no barrier)
+  f32x16_t acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+  const int tok = min(c & 7, nt - 1);
+  for (int s0 = 0; s0 < n; s0 += U) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int s = s0 + i;
+      if (s < n) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) transpose4(w[i], d);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          acc = mfma32(w[i][g], *reinterpret_cast<const u32x4_t *>(xs + tok * pitch + (((8 * s + g + 4 * half) ^ tok) << 4)), acc);
+      }
+      if (s + U < n) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[i][j] = *reinterpret_cast<const u32x4_t *>(rows[j] + (s + U) * 64);
+      }
+    }
+  }
+  // lane (c, half) holds rows 8 (e / 4) + 4 half + e mod 4 of token c
+  __syncthreads();                                               // the tokens' LDS is free
+  float *red = reinterpret_cast<float *>(smem);
+  if (c < 8) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[(wave * 16 + e) * 16 + 8 * half + c] = acc[e];
+  }
+  __syncthreads();
+  const int pp = tid & 15, t = tid >> 4;                         // position and token of this thread
+  static_assert(kGemv1Waves * 64 >= 16 * kGemvMaxTokens, "a thread for every output");
+  if (t >= nt) return;
+  const int at = ((pp & 3) + 4 * (pp >> 3)) * 16 + 8 * ((pp >> 2) & 1) + t;
+  float g = 0.0f, u = 0.0f;
+#pragma unroll
+  for (int v = 0; v < kGemv1Waves; ++v) {
+    g += red[v * 256 + at];
+    u += red[v * 256 + 128 + at];
+  }
+  const int pos = pos0 + pp;
+  float hv = pos < Kb ? gv_act(FF_ACT_SILU, g) * u : (pos < ntot ? gv_act(p.comp_act, g) : 0.0f);
+  if (p.mask != nullptr && pos < Kb && !(((uint32_t)p.mask[(size_t)b * p.k_stride + pos] >> (t / p.sub_block)) & 1u)) hv = 0.0f;   // not selected for this token
+  p.h[(size_t)(t0 + t) * p.hs + pos] = f32_to_bf16(hv);
 }
 
-// grid (ceil(column groups / 4), n_chunks, n_blocks), 256 threads: a wavefront owns a group of
-// NV * 512 output columns (NV units of 512, a lane holding 8 adjacent columns of each) for at most
-// NT tokens and walks its chunk of the list, two groups of U weight rows in flight; nothing is shared
-// between the wavefronts, so there is no barrier.  Wider groups read longer contiguous pieces of a
-// gathered row; they cost NT * NV * 8 accumulators, hence fewer tokens.
-template <int NV, int NT, int U>
-__global__ __launch_bounds__(256) void ff_gemv2_kernel(GemvParams p) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// One workgroup per 128 output columns and chunk of the list; a wavefront takes every eighth group of 32 positions of the
+// chunk, two groups on their way.  Lane (c, q) loads columns 8 c .. 8 c + 7 of rows 8 q .. 8 q + 7, which one byte permute per
+// dword turns into the operands of eight MFMAs (tile f: column 8 c + f).  The wavefronts' sums are added in order through
+// LDS, the chunks' through memory by the workgroup of the column group that is last to finish.  They are stored and loaded as
+// relaxed atomics of device scope, hence past the L2 that this XCD does not share with the others, and counted when they have
+// arrived (vmcnt); a release fence would write back the whole L2 instead (13.7 us become 28.4, a dense token's 27 become 140).
+// Bound by HBM.  (Multiply-adds and a third launch for the sum: five tokens on 4096 positions of 2048/8192 20.0 us, now 13.7; one
+// token on 7168 of 4096/14336 19.0 and 15.9, dense 31.2 and 27.0; eight tokens of a list each 39.2 and 23.7.)
+// grid (d_model / 128, n_chunks, n_blocks)
+__global__ __launch_bounds__(kGemvWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
+void ff_gemv2_kernel(GemvParams p) {
+  constexpr int PITCH = kGemv2Cols + 4;
+  __shared__ __align__(16) float red[kGemvWaves][kGemvMaxTokens][PITCH];
+  __shared__ int last_s;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, q = lane >> 4;
   const int b = blockIdx.z, ch = blockIdx.y;
   const int t0 = b * p.block;
-  const int nt = min(min(p.T, t0 + p.block) - t0, NT);
+  const int nt = min(p.T, t0 + p.block) - t0;
   const int Kb = gv_block_k(p, b);
   const int ntot = Kb + p.rc;
-  const int cl = ((ntot + p.n_chunks - 1) / p.n_chunks + 7) / 8 * 8;   // chunk length
-  const int pb = ch * cl, pe = min(ntot, pb + cl);
-  const int col0 = (blockIdx.x * 4 + wave) * (NV * 512) + lane * 8;
-  if (col0 - lane * 8 >= p.d_model) return;
-  // d_model is a multiple of 8, so a lane's 8 columns of a unit are in or out together; a unit that is
-  // out reads the last 8 columns instead and stores nothing
-  int colj[NV];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) colj[j] = min(col0 + j * 512, p.d_model - 8);
+  const int n_groups = (ntot + 31) / 32;
+  const int per = (n_groups + p.n_chunks - 1) / p.n_chunks;
+  const int g_end = min(n_groups, (ch + 1) * per);
+  const int col0 = blockIdx.x * kGemv2Cols;
   const int32_t *list = p.idx ? p.idx + (size_t)b * p.k_stride : nullptr;
-  // lane t < nt reads token t's H values; the other lanes' values are never used
-  const bf16_t *hrow = p.h + (size_t)(t0 + min(lane, nt - 1)) * p.hs;
-  float acc[NT][NV][8];
+  const bf16_t *hrow = p.h + (size_t)(t0 + min(c & 7, nt - 1)) * p.hs + 8 * q;
+  const size_t lane_col = (size_t)(col0 + 8 * c);
+  f32x4_t acc[8];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+  for (int f = 0; f < 8; ++f) acc[f] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  // rows of this lane in group g (positions past the list's end: the last one again, next to zeros of H)
+  auto ids = [&](int g, int (&id)[8]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[t][j][e] = 0.0f;
-  // Loads never branch: a position past the chunk's end re-reads the last row and its H value
-  // counts as zero.  Two groups of U rows alternate, so that the next group's rows are on their
-  // way while this one is multiplied.
-  const int last = pe - 1;
-  auto load = [&](int q0, uint4 (&wv)[U][NV], bf16_t (&hv)[U]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int pos = min(q0 + u, last);
-      const bf16_t *row = pos < Kb ? p.wd + (size_t)gv_row(list, pos, p.d_ffn) * p.d_model
-                                   : p.wc2 + (size_t)(pos - Kb) * p.d_model;
-#pragma unroll
-      for (int j = 0; j < NV; ++j) wv[u][j] = *reinterpret_cast<const uint4 *>(row + colj[j]);
-      hv[u] = hrow[pos];
+    for (int i = 0; i < 8; ++i) {
+      const int pos = min(g * 32 + 8 * q + i, ntot - 1);
+      id[i] = list ? list[min(pos, Kb - 1)] : pos;
     }
   };
-  auto fma_rows = [&](int q0, const uint4 (&wv)[U][NV], const bf16_t (&hv)[U]) {
+  auto load = [&](int g, const int (&id)[8], u32x4_t (&w)[8], u32x4_t &hf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float hm = q0 + u < pe ? bf16_to_f32(hv[u]) : 0.0f;
-      float hs[NT];
+    for (int i = 0; i < 8; ++i) {
+      const int pos = min(g * 32 + 8 * q + i, ntot - 1);
+      const bf16_t *row = pos < Kb ? p.wd + (size_t)min(max(id[i], 0), p.d_ffn - 1) * p.d_model : p.wc2 + (size_t)(pos - Kb) * p.d_model;
+      w[i] = *reinterpret_cast<const u32x4_t *>(row + lane_col);
+    }
+    hf = *reinterpret_cast<const u32x4_t *>(hrow + g * 32);
+  };
+  auto fma_group = [&](const u32x4_t (&w)[8], const u32x4_t &hf) __attribute__((always_inline)) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) hs[t] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(hm), t));
+    for (int d = 0; d < 4; ++d) {
+      u32x4_t ev, od;
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        float wf[8];
-        unpack8(wv[u][j], wf);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          if (t < nt) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[t][j][e] = fmaf(hs[t], wf[e], acc[t][j][e]);
-          }
+      for (int i = 0; i < 4; ++i) {
+        ev[i] = __builtin_amdgcn_perm(w[2 * i + 1][d], w[2 * i][d], 0x05040100u);
+        od[i] = __builtin_amdgcn_perm(w[2 * i + 1][d], w[2 * i][d], 0x07060302u);
       }
+      acc[2 * d] = mfma16(ev, hf, acc[2 * d]);
+      acc[2 * d + 1] = mfma16(od, hf, acc[2 * d + 1]);
     }
   };
-  if (pb < pe) {
-    uint4 wa[U][NV], wb[U][NV];
-    bf16_t ha[U], hb[U];
-    load(pb, wa, ha);
-    for (int q0 = pb; q0 < pe; q0 += 2 * U) {
-      load(q0 + U, wb, hb);
-      fma_rows(q0, wa, ha);
-      load(q0 + 2 * U, wa, ha);
-      fma_rows(q0 + U, wb, hb);
+  for (int g = ch * per + wave; g < g_end; g += 2 * kGemvWaves) {
+    const int g2 = g + kGemvWaves;
+    int ida[8], idb[8];
+    u32x4_t wa[8], wb[8], ha, hb;
+    ids(g, ida);
+    ids(min(g2, g_end - 1), idb);
+    __builtin_amdgcn_sched_barrier(0);
+    load(g, ida, wa, ha);
+    if (g2 < g_end) load(g2, idb, wb, hb);
+    __builtin_amdgcn_sched_barrier(0);
+    fma_group(wa, ha);
+    if (g2 < g_end) fma_group(wb, hb);
+  }
+  // lane (c, q): columns 8 (4 q + e) + f of token c
+  if (c < nt) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float *o = &red[wave][c][8 * (4 * q + e)];
+      *reinterpret_cast<float4 *>(o) = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
+      *reinterpret_cast<float4 *>(o + 4) = make_float4(acc[4][e], acc[5][e], acc[6][e], acc[7][e]);
     }
   }
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-    if (t < nt) {
-#pragma unroll
-      for (int j = 0; j < NV; ++j)
-        if (col0 + j * 512 < p.d_model) {
-          float *o = p.part + ((size_t)ch * p.T + (t0 + t)) * p.d_model + col0 + j * 512;
-          *reinterpret_cast<float4 *>(o) = make_float4(acc[t][j][0], acc[t][j][1], acc[t][j][2], acc[t][j][3]);
-          *reinterpret_cast<float4 *>(o + 4) = make_float4(acc[t][j][4], acc[t][j][5], acc[t][j][6], acc[t][j][7]);
-        }
-    }
-}
-
-struct Gemv2Variant {
-  void (*fn)(GemvParams);
-  int nv, nt;
-};
-const Gemv2Variant kGemv2[] = {
-    {ff_gemv2_kernel<1, 2, 8>, 1, 2},   // one or two tokens per block
-    {ff_gemv2_kernel<2, 2, 8>, 2, 2},   // the same with four or more blocks: enough wavefronts for longer row pieces
-    {ff_gemv2_kernel<1, 4, 4>, 1, 4},
-    {ff_gemv2_kernel<1, 8, 4>, 1, 8},
-};
-
-// grid (ceil(d_model / 256), T), 1024 threads: wavefront w adds the chunks w, w + 16, ... for 256
-// columns (4 per lane), then thread c < 256 adds the 16 wavefronts' sums for column c in order.
-__global__ __launch_bounds__(1024) void ff_gemv3_kernel(GemvParams p) {
-  __shared__ __align__(16) float red[16][256];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, t = blockIdx.y;
-  const int col = blockIdx.x * 256 + lane * 4;
-  float4 s4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  if (col < p.d_model) {
-    constexpr int R = kGemvChunks / 16;
-    float4 v[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int ch = wave + 16 * j;
-      v[j] = ch < p.n_chunks ? *reinterpret_cast<const float4 *>(p.part + ((size_t)ch * p.T + t) * p.d_model + col)
-                             : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-#pragma unroll
-    for (int j = 0; j < R; ++j) { s4.x += v[j].x; s4.y += v[j].y; s4.z += v[j].z; s4.w += v[j].w; }
-  }
-  *reinterpret_cast<float4 *>(&red[wave][lane * 4]) = s4;
   __syncthreads();
-  const int c = blockIdx.x * 256 + tid;
-  if (tid >= 256 || c >= p.d_model) return;
-  float s = 0.0f;
+  auto store = [&](int t, int col, float s) __attribute__((always_inline)) {
+    const size_t o = (size_t)(t0 + t) * p.d_model + col;
+    if (p.res) {
+      p.res[o] = f32_to_bf16(bf16_to_f32(p.res[o]) + bf16_to_f32(f32_to_bf16(s)));
+    } else if (p.out_f32) {
+      reinterpret_cast<float *>(p.y)[o] = s;
+    } else {
+      reinterpret_cast<bf16_t *>(p.y)[o] = f32_to_bf16(s);
+    }
+  };
+  for (int v = tid; v < nt * kGemv2Cols; v += kGemvWaves * 64) {
+    const int t = v / kGemv2Cols, col = v % kGemv2Cols;
+    float s = 0.0f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) s += red[w][tid];
-  const size_t o = (size_t)t * p.d_model + c;
-  if (p.res) {
-    p.res[o] = f32_to_bf16(bf16_to_f32(p.res[o]) + bf16_to_f32(f32_to_bf16(s)));
-  } else if (p.out_f32) {
-    reinterpret_cast<float *>(p.y)[o] = s;
-  } else {
-    reinterpret_cast<bf16_t *>(p.y)[o] = f32_to_bf16(s);
+    for (int w = 0; w < kGemvWaves; ++w) s += red[w][t][col];
+    if (p.n_chunks == 1) store(t, col0 + col, s);
+    else __hip_atomic_store(p.part + ((size_t)ch * p.T + t0 + t) * p.d_model + col0 + col, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (p.n_chunks == 1) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // this wavefront's sums have arrived
+  __syncthreads();
+  if (tid == 0)
+    last_s = __hip_atomic_fetch_add(p.counter + b * gridDim.x + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.n_chunks - 1;
+  __syncthreads();
+  if (!last_s) return;
+  for (int v = tid; v < nt * kGemv2Cols; v += kGemvWaves * 64) {
+    const int t = v / kGemv2Cols, col = v % kGemv2Cols;
+    float *src = p.part + (size_t)(t0 + t) * p.d_model + col0 + col;
+    float s = 0.0f;
+    for (int j0 = 0; j0 < p.n_chunks; j0 += 8) {                 // eight loads in flight, added in chunk order
+      float x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        x[j] = __hip_atomic_load(src + (size_t)min(j0 + j, p.n_chunks - 1) * p.T * p.d_model, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (j0 + j < p.n_chunks) s += x[j];
+    }
+    store(t, col0 + col, s);
   }
 }
 
 int g_gemv_lds_raised = 0;
 
+// gemv1: steps of 64 channels per wavefront, and LDS for nt tokens
+int gemv1_steps(int d_model) { return (d_model / 64 + kGemv1Waves - 1) / kGemv1Waves; }
+size_t gemv1_lds(int nt, int d_model) {
+  const size_t x = (size_t)kGemv1Waves * nt * gemv1_steps(d_model) * 128;
+  return x > kGemv1Red ? x : kGemv1Red;
+}
+
 }  // namespace
 
+// (the chunks' sums, and behind them a counter for every column group of every block)
 size_t ff_gemv_part_bytes(int n_tokens, int d_model) {
-  return n_tokens <= kGemvMaxTokens ? (size_t)kGemvChunks * n_tokens * d_model * sizeof(float) : 0;
+  return n_tokens <= kGemvMaxTokens ? (size_t)(kGemvChunks + 1) * n_tokens * d_model * sizeof(float) : 0;
 }
 
 bool ff_gemv_eligible(int n_tokens, int block, int d_model, int lds_limit) {
   const int nt = block < n_tokens ? block : n_tokens;
-  return n_tokens <= kGemvMaxTokens && (size_t)nt * d_model * 2 <= (size_t)lds_limit;
+  return n_tokens <= kGemvMaxTokens && gemv1_lds(nt, d_model) <= (size_t)lds_limit;
 }
 
 hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, Profiler *prof) {
@@ -286,29 +316,18 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   }
   const int nt = p.block < p.T ? p.block : p.T;
   const int n_extent = p.k.k_max + p.rc;
-  // Both grids aim at about 2048 units of work (workgroups of gemv1, wavefronts of gemv2): eight
-  // or more per compute unit, each with 4 to 16 KB of weight rows in flight, which is what it takes
-  // to keep HBM busy from so few tokens.
-  constexpr int kTarget = 2048;
-  // gemv1 copies the block's tokens into LDS once per workgroup: with more than two tokens a
-  // workgroup of 16 wavefronts shares that copy
-  const int threads1 = nt > 2 ? 1024 : 256, nw1 = threads1 / 64;
-  int ppw = (int)(((long)n_extent * p.n_blocks / kTarget) / nw1 * nw1);
-  p.pos_per_wg = ppw < nw1 ? nw1 : (ppw > kMaxPosPerWg ? kMaxPosPerWg : ppw);
-  // gemv2: chunks of at least 32 rows, so that a wavefront's row reads outweigh the fp32 partials
-  // it writes (nt * 32 bytes per lane against 32 * 16)
-  const int gv = nt <= 2 ? (p.n_blocks >= 4 ? 1 : 0) : nt <= 4 ? 2 : 3;
-  const int col_groups = (p.d_model + kGemv2[gv].nv * 512 - 1) / (kGemv2[gv].nv * 512);
-  int nc = kTarget / (col_groups * p.n_blocks);
-  if (nc > n_extent / 32) nc = n_extent / 32;
+  p.counter = reinterpret_cast<int32_t *>(p.part + (size_t)kGemvChunks * p.T * p.d_model);
+  // gemv2: two workgroups per CU, as far as each of their wavefronts has a group of 32 positions
+  const int cols = p.d_model / kGemv2Cols, groups = (n_extent + 31) / 32;
+  int nc = 512 / (cols * p.n_blocks);
+  if (nc > (groups + kGemvWaves - 1) / kGemvWaves) nc = (groups + kGemvWaves - 1) / kGemvWaves;
   p.n_chunks = nc < 1 ? 1 : (nc > kGemvChunks ? kGemvChunks : nc);
   prof_begin(prof, FF_STAGE_GEMM1, s);
-  hipLaunchKernelGGL(ff_gemv1_kernel, dim3((n_extent + p.pos_per_wg - 1) / p.pos_per_wg, p.n_blocks), dim3(threads1),
-                     (size_t)nt * p.d_model * 2, s, p);
+  hipLaunchKernelGGL(ff_gemv1_kernel, dim3((n_extent + 31) / 32 * (32 / kGemv1Pos), p.n_blocks), dim3(kGemv1Waves * 64),
+                     gemv1_lds(nt, p.d_model), s, p, gemv1_steps(p.d_model));
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_GEMM2, s);
-  hipLaunchKernelGGL(kGemv2[gv].fn, dim3((col_groups + 3) / 4, p.n_chunks, p.n_blocks), dim3(256), 0, s, p);
-  hipLaunchKernelGGL(ff_gemv3_kernel, dim3((p.d_model + 255) / 256, p.T), dim3(1024), 0, s, p);
+  hipLaunchKernelGGL(ff_gemv2_kernel, dim3(cols, p.n_chunks, p.n_blocks), dim3(kGemvWaves * 64), 0, s, p);
   prof_end(prof, s);
   return hipGetLastError();
 }

@@ -25,6 +25,33 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   return (bf16_t)(pack_bf16x2(f, 0.0f) & 0xffffu);
 }
 
+// Four loads of 16 bytes per lane in which lanes a = 0 .. 3 of every four ask for 64 contiguous bytes: r[j] = (row j, chunk a).
+// Afterwards r[g] = (row a, chunk g): MFMA operands.  Dword d of each; all four dwords are to be done.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+__device__ __forceinline__ void transpose4(u32x4_t (&r)[4], int d) {
+  uint32_t a = r[0][d], b = r[1][d], c = r[2][d], e = r[3][d], t, s, u;
+  // (a DPP source written by the two instructions before would be read too early: s_nop, and the order below)
+  asm volatile(
+      "s_nop 1\n\t"
+      "s_mov_b64 vcc, %7\n\t"
+      "v_cndmask_b32_dpp %4, %1, %0, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %5, %3, %2, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_not_b64 vcc, vcc\n\t"
+      "v_cndmask_b32_dpp %6, %0, %1, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %3, %2, %3, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_mov_b64 vcc, %8\n\t"
+      "v_cndmask_b32_dpp %0, %5, %4, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %1, %3, %6, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_not_b64 vcc, vcc\n\t"
+      "v_cndmask_b32_dpp %2, %4, %5, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_cndmask_b32_dpp %3, %6, %3, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1"
+      : "+v"(a), "+v"(b), "+v"(c), "+v"(e), "=&v"(t), "=&v"(s), "=&v"(u)
+      : "s"(0x5555555555555555ull), "s"(0x3333333333333333ull)
+      : "vcc", "scc");
+  r[0][d] = a; r[1][d] = b; r[2][d] = c; r[3][d] = e;
+}
+
 // Per-block neuron count: either one value for all blocks or a device array.
 constexpr int kMaxHeavy = 8;
 struct KSpec {
@@ -183,16 +210,17 @@ int ff_gemm2_num_variants();
 
 // ---- few-token path (at most kGemvMaxTokens tokens in the whole call) ---------
 constexpr int kGemvMaxTokens = 8;
-constexpr int kGemvChunks = 256;   // most pieces the list is cut into for the down projection
+constexpr int kGemvChunks = 64;    // most pieces the list is cut into for the down projection
 struct GemvParams {
   const bf16_t *x, *wg, *wu, *wd, *wc1, *wc2;
   const int32_t *idx;  // [n_blocks][k_stride], or nullptr: list position p is row p (dense)
   bf16_t *h;           // [T][hs]
-  float *part;         // [n_chunks][T][d_model]
+  float *part;         // [n_chunks][T][d_model], ff_gemv_part_bytes
   void *y;             // [T][d_model] bf16 or f32
   bf16_t *res;         // or nullptr: residual mode as in Gemm2Params
   int32_t T, d_model, d_ffn, block, n_blocks, rc, comp_act, k_stride, hs, out_f32;
-  int32_t n_chunks, pos_per_wg;   // chosen by ff_launch_gemv
+  int32_t n_chunks = 1;           // chosen by ff_launch_gemv, and
+  int32_t *counter = nullptr;     // [n_blocks][column groups], how many chunks are done
   // merged lists (as in Gemm1Params): position p belongs to token t iff bit (t - block start) / sub_block of
   // mask[b * k_stride + p] is set; nullptr = every position belongs to every token
   const uint8_t *mask = nullptr;

@@ -937,6 +937,38 @@ def test_few_token_calls_take_the_gemv_path(ctx):
         ctx.set_option("merge_blocks", -1)
 
 
+@pytest.mark.parametrize("d_model,d_ffn,T,block,rc,ks", [
+    (128, 640, 1, 1, 0, [1]), (128, 640, 8, 8, 8, [31]), (640, 4096, 7, 3, 24, [33, 4000, 15]), (640, 4096, 8, 2, 0, [512, 513, 2048, 16]),
+    (1152, 1064, 5, 5, 40, [1064]), (4224, 4096, 3, 1, 64, [2049, 4096, 256]), (8192, 520, 8, 8, 8, [96])])
+def test_few_token_kernels_at_their_edges(ctx, d_model, d_ffn, T, block, rc, ks):
+    """The few-token kernels where their splits end: channels that some wavefronts have none or fewer of, lists of one position,
+    ends inside and on groups of 16 and 32 and chunks that hold nothing for the shorter lists, compensator units in a group
+    with list rows, one to eight tokens in LDS up to its limit.  In a workspace full of NaN, lists read as they are
+    and merged, and the dense call.  Which workgroup adds up a column group's chunks changes from run to run, the order
+    of the sum does not: repeated calls are bit-equal."""
+    c = Case(W.Shape("fewedge", d_model, d_ffn, T, block, 8, max(rc, 8)))
+    ref = c.oracle_layer(ks, comp=rc > 0)
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=d_ffn)
+    ref_d = O.dense_ffn(_f32(c.x_bits), c.host("w_gate"), c.host("w_up"), c.host("w_down").T)
+    ctx.ensure_workspace(c.shape, d_ffn)
+    try:
+        for merge in (0, 1):
+            ctx.set_option("merge_blocks", merge)
+            ys = []
+            for _ in range(5):
+                ctx._ws.fill_(0xFF)
+                ys.append(c.gpu_sparse(ctx, idx, ks, comp=rc > 0, out_f32=True))
+            _check_y(ys[0], ref.y, f"{T} tokens of {d_model}, blocks of {block}, ks {ks}, merged {merge}")
+            assert all(torch.equal(y, ys[0]) for y in ys)
+            _check_bf16_storage(c.gpu_sparse(ctx, idx, ks, comp=rc > 0), ys[0])
+    finally:
+        ctx.set_option("merge_blocks", -1)
+    ctx._ws.fill_(0xFF)
+    y = torch.empty((T, d_model), dtype=torch.float32, device=DEV)
+    ctx.dense_ffn(c.shape, c.x, c.w, y, B.OUT_F32)
+    _check_y(y, ref_d, f"dense, {T} tokens of {d_model}")
+
+
 def test_c0_ragged_tail_and_per_block_k(ctx):
     # 230 tokens in blocks of 64 -> 64, 64, 64, 38; first and last block dense, odd K elsewhere
     c = Case(W.CONFIGS["c0"], n_tokens=230)
