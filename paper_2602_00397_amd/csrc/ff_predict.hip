@@ -404,83 +404,68 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return dpp_add_step<0x143, 0xc>(v);   // lane 31 into rows 2 and 3
 }
 
-// exclusive prefix over the 1024 threads of the block; total returned too
-__device__ __forceinline__ int block_excl_scan(int v, int *wsum, int &total) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int inc = wave_incl_scan(v);
-  if (lane == 63) wsum[wave] = inc;
-  __syncthreads();
-  if (wave == 0) {
-    const int w = lane < 16 ? wsum[lane] : 0;
-    const int ws = wave_incl_scan(w);
-    if (lane < 16) wsum[lane] = ws - w;
-    if (lane == 15) wsum[16] = ws;
-  }
-  __syncthreads();
-  total = wsum[16];
-  const int res = wsum[wave] + inc - v;
-  __syncthreads();
-  return res;
-}
-
 // LDS of the threshold search, shared by both top-K kernels
 struct TopkShared {
-  unsigned int hist[TOPK_BUCKETS];           // also the 256-bin histogram of the radix path
-  unsigned long long cand[TOPK_CAND];
-  int wsum[17];
+  __align__(16) unsigned int hist[TOPK_BUCKETS];   // also the 256-bin histogram of the radix path
+  double cand[TOPK_CAND];
+  int wsum[16];
   unsigned int wtot[4];
   unsigned int sel_bin, sel_rem, n_cand;
-  unsigned long long theta;
+  double theta;
   int ties;
 };
 
-// The key theta of the K-th largest score and the number of keys equal to theta that are kept, found
-// exactly by the 1024 threads of a workgroup.  each(fn) calls fn(key) once for every key the calling thread
-// owns, as fn(key, score rounded to fp32).  [lo_v, hi_v] encloses the scores (it only shapes the bucket map); need_radix
-// skips the buckets.  (Buckets of the fp32 roundings, against fp64 arithmetic on every key with the scans' lane exchanges
-// through LDS: one block of 14336 scores 13.3 -> 11.5 us, 64 blocks 14.0 -> 12.3; scores whose range is 2^-14 of their size,
-// which fp32 has no steps for: 12.6 and 13.9 in fp64 buckets, 30.2 and 56.2 on the radix path.)
+// The K-th largest score theta and the number of scores equal to theta that are kept, found exactly by the 1024 threads of a
+// workgroup.  each(fn) calls fn(score, score rounded to fp32) once for every score the calling thread owns; gather(bucket_of,
+// tb, append) calls append(score) for those of bucket tb.  [lo_v, hi_v]
+// encloses the scores (it only shapes the bucket map); need_radix skips the buckets.  Scores are compared as numbers (-0 ==
+// +0), except where the radix path had to order them: it returns true, and theta as a key.  A chain of latencies, so: a
+// prefix sum whose 16 totals every wavefront scans itself, candidates that every wavefront ranks itself, no 64-bit keys.
+// (Against three barriers in the prefix sum, a ranking for all by one wavefront's threads, compaction in two rounds and rows
+// of keys for 16384 scores whatever their number, us between events: one block of 14336 scores 14.1 -> 12.8, blocks of 8192
+// 14.0 -> 10.2, of 688 13.3 -> 7.9, of 18944 19.4 -> 18.3, of 28672 25.5 -> 23.3.)
+// (Buckets of the fp32 roundings, against fp64 arithmetic on every score: one block of 14336 1.8 us less; scores whose range is
+// 2^-14 of their size, which fp32 has no steps for: 12.6 us in fp64 buckets, 30.2 on the radix path.)
 // On entry sh.hist is zero, sh.n_cand is 0 and a barrier has been passed.
-template <class Each>
-__device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_v, double hi_v, bool need_radix,
-                                               Each each, unsigned long long &theta, int &ties_taken) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <class Each, class Gather>
+__device__ __forceinline__ bool topk_threshold(TopkShared &sh, int K, double lo_v, double hi_v, bool need_radix,
+                                               Each each, Gather gather, double &theta, unsigned long long &theta_key, int &ties_taken) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const TopkMap map = topk_map(lo_v, hi_v);
   const bool fine = __builtin_amdgcn_readfirstlane(map.fine);   // the same for all threads, as everything about the range
   need_radix = need_radix || map.none;
-  // bucket_of(key, rounding): the bucket map.  False: the threshold's bucket holds too many keys.
+  // bucket_of(score, rounding): the bucket map.  False: the threshold's bucket holds too many scores.
   auto by_buckets = [&](auto bucket_of) __attribute__((always_inline)) -> bool {
-    each([&](unsigned long long k, float s) { atomicAdd(&sh.hist[bucket_of(k, s)], 1u); });
+    each([&](double v, float s) { atomicAdd(&sh.hist[bucket_of(v, s)], 1u); });
     __syncthreads();
-    // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = keys in higher buckets
-    int local = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) local += (int)sh.hist[TOPK_BUCKETS - 1 - (4 * tid + q)];
-    int total;
-    int above = block_excl_scan(local, sh.wsum, total);
+    // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = scores in higher buckets
+    const uint4 h4 = *reinterpret_cast<const uint4 *>(&sh.hist[TOPK_BUCKETS - 4 - 4 * tid]);
+    const int h[4] = {(int)h4.w, (int)h4.z, (int)h4.y, (int)h4.x};
+    const int local = (h[0] + h[1]) + (h[2] + h[3]);
+    const int inc = wave_incl_scan(local);
+    if (lane == 63) sh.wsum[wave] = inc;
+    __syncthreads();
+    const int w = lane < 16 ? sh.wsum[lane] : 0;                // every wavefront scans the 16 totals itself
+    int above = __builtin_amdgcn_readlane(wave_incl_scan(w) - w, wave) + inc - local;
     if (above < K && K <= above + local) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int bk = TOPK_BUCKETS - 1 - (4 * tid + q);
-        const int h = (int)sh.hist[bk];
-        if (above < K && K <= above + h) { sh.sel_bin = (unsigned int)bk; sh.sel_rem = (unsigned int)(K - above); }
-        above += h;
+        if (above < K && K <= above + h[q]) { sh.sel_bin = (unsigned int)(TOPK_BUCKETS - 1 - (4 * tid + q)); sh.sel_rem = (unsigned int)(K - above); }
+        above += h[q];
       }
     }
     __syncthreads();
-    const int tb = (int)sh.sel_bin;
-    const int need = (int)sh.sel_rem;             // rank of theta inside bucket tb (1 = largest)
-    const int c = (int)sh.hist[tb];
+    const int tb = __builtin_amdgcn_readfirstlane((int)sh.sel_bin);
+    const int need = __builtin_amdgcn_readfirstlane((int)sh.sel_rem);   // rank of theta inside bucket tb (1 = largest)
+    const int c = __builtin_amdgcn_readfirstlane((int)sh.hist[tb]);
     if (c > TOPK_CAND) return false;              // uniform: every thread reads the same hist[tb]
-    each([&](unsigned long long k, float s) {
-      if (bucket_of(k, s) == tb) sh.cand[atomicAdd(&sh.n_cand, 1u)] = k;
-    });
+    gather(bucket_of, tb, [&](double v) { sh.cand[atomicAdd(&sh.n_cand, 1u)] = v; });
     __syncthreads();
-    if (tid < c) {
-      const unsigned long long mine = sh.cand[tid];
-      int n_gt = 0, n_eq = 0;
+    // rank of candidate i among the c; the need-th largest has n_gt < need <= n_gt + n_eq (all holders of its value agree)
+    auto rank = [&](double mine, int &n_gt, int &n_eq) __attribute__((always_inline)) {
+      n_gt = n_eq = 0;
       for (int j0 = 0; j0 < c; j0 += 8) {          // eight reads in flight
-        unsigned long long o[8];
+        double o[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) o[u] = sh.cand[min(j0 + u, c - 1)];
 #pragma unroll
@@ -489,61 +474,76 @@ __device__ __forceinline__ void topk_threshold(TopkShared &sh, int K, double lo_
           n_eq += j0 + u < c && o[u] == mine;
         }
       }
-      // the need-th largest of the bucket: n_gt < need <= n_gt + n_eq (all holders of that key agree)
-      if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; }
+    };
+    int n_gt, n_eq;
+    if (c <= 64) {                                 // every wavefront finds it itself
+      const double mine = sh.cand[min(lane, c - 1)];
+      rank(mine, n_gt, n_eq);
+      const int src = __ffsll((unsigned long long)__ballot(lane < c && n_gt < need && need <= n_gt + n_eq)) - 1;
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(mine);
+      const unsigned int b0 = __builtin_amdgcn_readlane((unsigned int)bits, src), b1 = __builtin_amdgcn_readlane((unsigned int)(bits >> 32), src);
+      theta = __longlong_as_double((long long)(((unsigned long long)b1 << 32) | b0));
+      ties_taken = need - __builtin_amdgcn_readlane(n_gt, src);
+    } else {
+      if (tid < c) {
+        const double mine = sh.cand[tid];
+        rank(mine, n_gt, n_eq);
+        if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; }
+      }
+      __syncthreads();
+      theta = sh.theta;
+      ties_taken = sh.ties;
     }
-    __syncthreads();
     return true;
   };
   // (the rare map's code out of the way: between the other's passes it made every call 0.5 to 1.4 us longer)
   if (!need_radix) {
-    if (__builtin_expect(fine, 0)) need_radix = !by_buckets([&](unsigned long long k, float) { return map.bucket64(key_score(k)); });
-    else need_radix = !by_buckets([&](unsigned long long, float s) { return map.bucket(s); });
+    if (__builtin_expect(fine, 0)) need_radix = !by_buckets([&](double v, float) { return map.bucket64(v); });
+    else need_radix = !by_buckets([&](double, float s) { return map.bucket(s); });
   }
-  if (__builtin_expect(need_radix, 0)) {
-    // 8-pass MSB-first radix select on the keys themselves (heavy ties, or no ordered range)
-    unsigned long long prefix = 0;  // digits decided so far (high part of theta)
-    unsigned int rem = (unsigned int)K;
-    for (int pass = 7; pass >= 0; --pass) {
-      const int shift = pass * 8;
-      __syncthreads();
-      if (tid < 256) sh.hist[tid] = 0;
-      __syncthreads();
-      each([&](unsigned long long k, float) {
-        const bool match = (pass == 7) || ((k >> (shift + 8)) == prefix);
-        if (match) atomicAdd(&sh.hist[(unsigned int)(k >> shift) & 255u], 1u);
-      });
-      __syncthreads();
-      // suffix sums S[d] = sum_{d' >= d} hist[d'] over the 256 digits
-      unsigned int hv = 0, suf = 0;
-      if (tid < 256) {
-        hv = sh.hist[tid];
-        suf = hv;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const unsigned int t = __shfl_down(suf, off);
-          if (lane + off < 64) suf += t;
-        }
-        if (lane == 0) sh.wtot[wave] = suf;
-      }
-      __syncthreads();
-      if (tid < 256) {
-        for (int w = wave + 1; w < 4; ++w) suf += sh.wtot[w];
-        // the digit of the K-th largest: S[d] >= rem > S[d+1]
-        if (suf >= rem && suf - hv < rem) {
-          sh.sel_bin = (unsigned int)tid;
-          sh.sel_rem = rem - (suf - hv);
-        }
-      }
-      __syncthreads();
-      prefix = (prefix << 8) | (unsigned long long)sh.sel_bin;
-      rem = sh.sel_rem;
-    }
-    if (tid == 0) { sh.theta = prefix; sh.ties = (int)rem; }
+  if (__builtin_expect(!need_radix, 1)) return false;
+  // 8-pass MSB-first radix select on the keys (heavy ties, or no ordered range)
+  unsigned long long prefix = 0;  // digits decided so far (high part of theta)
+  unsigned int rem = (unsigned int)K;
+  for (int pass = 7; pass >= 0; --pass) {
+    const int shift = pass * 8;
     __syncthreads();
+    if (tid < 256) sh.hist[tid] = 0;
+    __syncthreads();
+    each([&](double v, float) {
+      const unsigned long long k = score_key(v);
+      const bool match = (pass == 7) || ((k >> (shift + 8)) == prefix);
+      if (match) atomicAdd(&sh.hist[(unsigned int)(k >> shift) & 255u], 1u);
+    });
+    __syncthreads();
+    // suffix sums S[d] = sum_{d' >= d} hist[d'] over the 256 digits
+    unsigned int hv = 0, suf = 0;
+    if (tid < 256) {
+      hv = sh.hist[tid];
+      suf = hv;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const unsigned int t = __shfl_down(suf, off);
+        if (lane + off < 64) suf += t;
+      }
+      if (lane == 0) sh.wtot[wave] = suf;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      for (int w = wave + 1; w < 4; ++w) suf += sh.wtot[w];
+      // the digit of the K-th largest: S[d] >= rem > S[d+1]
+      if (suf >= rem && suf - hv < rem) {
+        sh.sel_bin = (unsigned int)tid;
+        sh.sel_rem = rem - (suf - hv);
+      }
+    }
+    __syncthreads();
+    prefix = (prefix << 8) | (unsigned long long)sh.sel_bin;
+    rem = sh.sel_rem;
   }
-  theta = sh.theta;        // key of the K-th largest score
-  ties_taken = sh.ties;    // keys equal to theta that are kept
+  theta_key = prefix;      // key of the K-th largest score
+  ties_taken = (int)rem;   // keys equal to it that are kept
+  return true;
 }
 
 // The general kernel, for d_ffn beyond what ff_topk_reg_kernel keeps in registers: every pass
@@ -566,7 +566,6 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
   K = max(1, min(K, min(d_ffn, k_stride)));
 
   unsigned char *cls = reinterpret_cast<unsigned char *>(dyn);
-  auto key_at = [&](int i) -> unsigned long long { return score_key(sc[i]); };
 
   // keys, and the score range
   double lo_v = INFINITY, hi_v = -INFINITY;
@@ -597,11 +596,17 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
 #pragma unroll
   for (int w = 1; w < 16; ++w) { lo_v = fmin(lo_v, red_lo[w]); hi_v = fmax(hi_v, red_hi[w]); }
   const bool need_radix = not_finite || !(hi_v > lo_v);   // all scores equal (or not ordered): no range to cut into buckets
-  unsigned long long theta;
+  double theta_v = 0.0;
+  unsigned long long theta = 0;
   int ties_taken;
-  topk_threshold(sh, K, lo_v, hi_v, need_radix,
-                 [&](auto fn) __attribute__((always_inline)) { for (int i = tid; i < d_ffn; i += 1024) fn(key_at(i), (float)sc[i]); },
-                 theta, ties_taken);
+  if (!topk_threshold(sh, K, lo_v, hi_v, need_radix,
+                      [&](auto fn) __attribute__((always_inline)) { for (int i = tid; i < d_ffn; i += 1024) fn(sc[i], (float)sc[i]); },
+                      [&](auto bucket_of, int tb, auto append) __attribute__((always_inline)) {
+                        for (int i = tid; i < d_ffn; i += 1024)
+                          if (bucket_of(sc[i], (float)sc[i]) == tb) append(sc[i]);
+                      },
+                      theta_v, theta, ties_taken))
+    theta = score_key(theta_v);
 
   if (LDS_MODE == 1) {
     for (int i = tid; i < d_ffn; i += 1024) {
@@ -613,7 +618,7 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
   // 2 = above theta, 1 = equal, 0 = below
   auto class_at = [&](int i) -> int {
     if (LDS_MODE == 1) return cls[i];
-    const unsigned long long key = key_at(i);
+    const unsigned long long key = score_key(sc[i]);
     return key > theta ? 2 : (key == theta ? 1 : 0);
   };
   // Ordered compaction.  Wavefront w owns the index range [w * span, (w + 1) * span) and walks it 64
@@ -672,127 +677,139 @@ __device__ __forceinline__ unsigned int wave_minmax_u32(unsigned int v) {
   return MAX ? max(max(a, b), max(c, d)) : min(min(a, b), min(c, d));
 }
 
-// The same selection for d_ffn <= 1024 * ROWS with every key in a register: thread t owns the
-// indices t, t + 1024, ... (row u = index / 1024), so the scores are read with all loads in flight
-// and no pass reads keys back from LDS.  Index order is row-major over (row, wavefront, lane): the rank
-// of a kept index among the kept ones is a scan over the ROWS x 16 per-(row, wavefront) ballot counts
-// (one wavefront does it) plus the count over lower lanes of its own ballot.
+// The same selection for d_ffn <= 1024 * ROWS with every score in a register.  Wavefront w owns the consecutive indices
+// [64 w R, 64 (w + 1) R), R = ceil(d_ffn / 1024) rows of 64, so the scores are read with all loads in flight, no pass reads them
+// back from LDS, and the rank of a kept index among the kept ones is a scan over 16 per-wavefront totals plus counts over
+// earlier rows and lower lanes (ballots).
 template <int ROWS>
 __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restrict__ scores,
                                                            int32_t *__restrict__ indices, int d_ffn,
                                                            int k_stride, KSpec ks) {
   __shared__ TopkShared sh;
   __shared__ unsigned int red_lo[16], red_hi[16];
-  __shared__ int cnt_gt[ROWS * 16], cnt_eq[ROWS * 16];  // per (row, wavefront); then their exclusive scans
+  __shared__ int2 cnt[16];              // scores above theta and equal to it, per wavefront
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = blockIdx.x;
   const double *sc = scores + (size_t)b * d_ffn;
   int32_t *out = indices + (size_t)b * k_stride;
   int K = ks.per_block ? ks.per_block[b] : ks.uniform;
   K = max(1, min(K, min(d_ffn, k_stride)));
+  const int R = (d_ffn + 1023) / 1024;
+  const int i0 = wave * R * 64 + lane;   // this thread's index in row 0
 
-  // keys; a row past the end repeats the last score and is masked by `valid`.  The score range only
+  // An index past the end repeats the last score and is masked by `valid`.  The score range only
   // shapes the bucket map, so bounds that enclose it are as good as the exact ends: the high words of
   // the smallest and largest key, which cost 32-bit wavefront reductions.
-  unsigned long long key[ROWS];
-  // Their fp32 roundings are kept beside them as far as the 128 registers of 1024 threads reach; 32 rows make them of the
-  // key each time (28672 scores, one block: 27.2 us with 29 registers in scratch memory, 22.6 this way).
-  constexpr bool KEEP = ROWS <= 24;
+  double v[ROWS];
+  // The fp32 roundings are kept beside them as far as the 128 registers of 1024 threads reach; 24 and 32 rows round each time
+  // (of a copy that the compiler cannot follow: it would keep the roundings, and the buckets, in scratch memory).
+  constexpr bool KEEP = ROWS <= 16;
   float score[ROWS];
   unsigned int lo_w = 0xffffffffu, hi_w = 0u;
 #pragma unroll
-  for (int u0 = 0; u0 < ROWS; u0 += 16) {
-    double v[16];
+  for (int u = 0; u < ROWS; ++u) v[u] = sc[min(i0 + u * 64, d_ffn - 1)];
+  *reinterpret_cast<uint4 *>(&sh.hist[4 * tid]) = make_uint4(0, 0, 0, 0);
+  if (tid == 0) sh.n_cand = 0;
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (u0 + u < ROWS) v[u] = sc[min((u0 + u) * 1024 + tid, d_ffn - 1)];
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (u0 + u < ROWS) {
-        key[u0 + u] = score_key(v[u]);
-        if (KEEP) score[u0 + u] = (float)v[u];
-        lo_w = min(lo_w, (unsigned int)(key[u0 + u] >> 32));
-        hi_w = max(hi_w, (unsigned int)(key[u0 + u] >> 32));
-      }
+  for (int u = 0; u < ROWS; ++u) {
+    if (KEEP) score[u] = (float)v[u];
+    const unsigned int hw = (unsigned int)((unsigned long long)__double_as_longlong(v[u]) >> 32);
+    const unsigned int key = hw ^ ((unsigned int)((int)hw >> 31) | 0x80000000u);   // unsigned order = score order
+    lo_w = min(lo_w, key);
+    hi_w = max(hi_w, key);
   }
-  auto valid = [&](int u) -> bool { return u * 1024 + tid < d_ffn; };
+  auto valid = [&](int u) -> bool { return u < R && i0 + u * 64 < d_ffn; };
   lo_w = wave_minmax_u32<false>(lo_w);
   hi_w = wave_minmax_u32<true>(hi_w);
   if (lane == 0) { red_lo[wave] = lo_w; red_hi[wave] = hi_w; }
-  for (int i = tid; i < TOPK_BUCKETS; i += 1024) sh.hist[i] = 0;
-  if (tid == 0) sh.n_cand = 0;
   __syncthreads();
-  lo_w = red_lo[0]; hi_w = red_hi[0];
-#pragma unroll
-  for (int w = 1; w < 16; ++w) { lo_w = min(lo_w, red_lo[w]); hi_w = max(hi_w, red_hi[w]); }
+  lo_w = wave_minmax_u32<false>(red_lo[lane & 15]);
+  hi_w = wave_minmax_u32<true>(red_hi[lane & 15]);
   const double lo_v = key_score((unsigned long long)lo_w << 32);
   const double hi_v = key_score(((unsigned long long)hi_w << 32) | 0xffffffffull);
   const bool need_radix = !(hi_v > lo_v);   // no ordered range to cut into buckets (not finite)
-  unsigned long long theta;
+  double theta = 0.0;
+  unsigned long long theta_key = 0;
   int ties_taken;
-  topk_threshold(sh, K, lo_v, hi_v, need_radix,
-                 [&](auto fn) __attribute__((always_inline)) {
+  static_assert(TOPK_BUCKETS == 4 * 1024, "a thread clears and scans four buckets");
+  // A row's scores in higher buckets than the threshold's are above it, those in lower ones below; only rows that hold a
+  // candidate have to be compared with theta afterwards.  (One block of 14336 scores: 1.3 us less than comparing every score
+  // twice, of 8192 0.5 us; with few rows there is nothing to save, and more rows than 16 do not leave the registers.)
+  constexpr bool MASKS = ROWS == 8 || ROWS == 16;
+  unsigned long long m_gt[ROWS];
+  unsigned int open_rows = 0;
+  const bool by_key = topk_threshold(sh, K, lo_v, hi_v, need_radix,
+                                     [&](auto fn) __attribute__((always_inline)) {
 #pragma unroll
-                   for (int u = 0; u < ROWS; ++u)
-                     if (valid(u)) fn(key[u], KEEP ? score[u] : (float)key_score(key[u]));
-                 },
-                 theta, ties_taken);
-
+                                       for (int u = 0; u < ROWS; ++u)
+                                         if (valid(u)) {
+                                           double x = v[u];
+                                           if (!KEEP) asm volatile("" : "+v"(x));
+                                           fn(x, KEEP ? score[u] : (float)x);
+                                         }
+                                     },
+                                     [&](auto bucket_of, int tb, auto append) __attribute__((always_inline)) {
+#pragma unroll
+                                       for (int u = 0; u < ROWS; ++u) {
+                                         double x = v[u];
+                                         if (!KEEP) asm volatile("" : "+v"(x));
+                                         const int bk = bucket_of(x, KEEP ? score[u] : (float)x);
+                                         const bool is_cand = valid(u) && bk == tb;
+                                         if (MASKS) {
+                                           m_gt[u] = __ballot(valid(u) && bk > tb);
+                                           if (__ballot(is_cand)) open_rows |= 1u << u;
+                                         }
+                                         if (is_cand) append(x);
+                                       }
+                                     },
+                                     theta, theta_key, ties_taken);
   // ordered compaction
-  unsigned long long m_gt[ROWS], m_eq[ROWS];
-#pragma unroll
-  for (int u = 0; u < ROWS; ++u) {
-    m_gt[u] = __ballot(valid(u) && key[u] > theta);
-    m_eq[u] = __ballot(valid(u) && key[u] == theta);
-  }
-  // lane u < ROWS publishes row u of this wavefront
-  {
-    int g = 0, e = 0;
+  auto below = [&](unsigned long long m) -> int {                             // set bits in lower lanes
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+  };
+  auto compact = [&](auto above, auto equal) __attribute__((always_inline)) {
+    int n_gt = 0, n_eq = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
-      if (lane == u) { g = __popcll(m_gt[u]); e = __popcll(m_eq[u]); }
-    if (lane < ROWS) { cnt_gt[lane * 16 + wave] = g; cnt_eq[lane * 16 + wave] = e; }
-  }
-  __syncthreads();
-  if (wave == 0) {
-    // lane l scans entries [l * PER, (l + 1) * PER) of the (row, wavefront) order
-    constexpr int PER = ROWS * 16 / 64;
-    int e[PER], g[PER], es = 0;
+      if (MASKS ? (open_rows >> u) & 1u : u < R) {
+        const unsigned long long m = __ballot(valid(u) && above(v[u]));
+        if (MASKS) m_gt[u] = m;
+        else n_gt += __popcll(m);
+        n_eq += __popcll(__ballot(valid(u) && equal(v[u])));
+      }
+    if (MASKS) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) { e[q] = cnt_eq[lane * PER + q]; g[q] = cnt_gt[lane * PER + q]; es += e[q]; }
-    int eq_before = wave_incl_scan(es) - es;   // ties at lower indices than this lane's entries
-    int ks_ = 0, kept[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int eq_q = e[q];
-      const int quota = max(0, min(eq_q, ties_taken - eq_before));
-      kept[q] = g[q] + quota;
-      e[q] = eq_before;                               // ties at lower indices than the entry
-      eq_before += eq_q;
-      ks_ += kept[q];
+      for (int u = 0; u < ROWS; ++u) n_gt += __popcll(m_gt[u]);
     }
-    int pos = wave_incl_scan(ks_) - ks_;
+    if (lane == 0) cnt[wave] = make_int2(n_gt, n_eq);
+    __syncthreads();
+    // every wavefront scans the 16 pairs itself: lane l < 16 holds wavefront l's totals
+    const int2 mine = lane < 16 ? cnt[lane] : make_int2(0, 0);
+    const int e_before = wave_incl_scan(mine.y) - mine.y;
+    const int kept = mine.x + max(0, min(mine.y, ties_taken - e_before));
+    int eq_seen = __builtin_amdgcn_readlane(e_before, wave);                    // ties at lower indices
+    int pos = __builtin_amdgcn_readlane(wave_incl_scan(kept) - kept, wave);     // kept at lower indices
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      cnt_eq[lane * PER + q] = e[q];
-      cnt_gt[lane * PER + q] = pos;                   // kept indices below the entry
-      pos += kept[q];
+    for (int u = 0; u < ROWS; ++u) {
+      if (!MASKS && u >= R) continue;
+      unsigned long long m_take = MASKS ? m_gt[u] : __ballot(valid(u) && above(v[u]));
+      if (!MASKS || ((open_rows >> u) & 1u)) {
+        const bool eq = valid(u) && equal(v[u]);
+        const unsigned long long m_eq = __ballot(eq);
+        m_take |= __ballot(eq && eq_seen + below(m_eq) < ties_taken);
+        eq_seen += __popcll(m_eq);
+      }
+      const int at = pos + below(m_take);
+      if (((m_take >> lane) & 1ull) && at < K) out[at] = i0 + u * 64;           // never past the list, whatever the scores were
+      pos += __popcll(m_take);
     }
-  }
-  __syncthreads();
-  int eq_row = 0, pos_row = 0;
-  if (lane < ROWS) { eq_row = cnt_eq[lane * 16 + wave]; pos_row = cnt_gt[lane * 16 + wave]; }
-  const unsigned long long lower = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int u = 0; u < ROWS; ++u) {
-    const int eq_seen = __builtin_amdgcn_readlane(eq_row, u);
-    const int pos = __builtin_amdgcn_readlane(pos_row, u);
-    const bool is_gt = (m_gt[u] >> lane) & 1ull, is_eq = (m_eq[u] >> lane) & 1ull;
-    const bool take = is_gt || (is_eq && eq_seen + (int)__popcll(m_eq[u] & lower) < ties_taken);
-    const unsigned long long m_take = __ballot(take);
-    const int at = pos + __popcll(m_take & lower);
-    if (take && at < K) out[at] = u * 1024 + tid;   // never past the list, whatever the scores were
+  };
+  if (__builtin_expect(by_key, 0)) {
+    open_rows = 0xffffffffu;
+    compact([&](double s) { return score_key(s) > theta_key; }, [&](double s) { return score_key(s) == theta_key; });
+  } else {
+    compact([&](double s) { return s > theta; }, [&](double s) { return s == theta; });
   }
   for (int i = K + tid; i < k_stride; i += 1024) out[i] = -1;
 }
@@ -840,15 +857,14 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   }
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_TOPK, s);
-  if (p.d_ffn <= 16 * 1024) {
-    hipLaunchKernelGGL(ff_topk_reg_kernel<16>, dim3(p.n_blocks), dim3(1024), 0, s, p.scores, p.indices,
-                       p.d_ffn, p.k_stride, p.k);
-  } else if (p.d_ffn <= 24 * 1024) {
-    hipLaunchKernelGGL(ff_topk_reg_kernel<24>, dim3(p.n_blocks), dim3(1024), 0, s, p.scores, p.indices,
-                       p.d_ffn, p.k_stride, p.k);
-  } else if (p.d_ffn <= 32 * 1024) {
-    hipLaunchKernelGGL(ff_topk_reg_kernel<32>, dim3(p.n_blocks), dim3(1024), 0, s, p.scores, p.indices,
-                       p.d_ffn, p.k_stride, p.k);
+  // (as few rows as hold the block: a row that none of its indices is in still costs its share of the loads)
+  const auto topk_reg = p.d_ffn <= 4 * 1024    ? ff_topk_reg_kernel<4>
+                        : p.d_ffn <= 8 * 1024  ? ff_topk_reg_kernel<8>
+                        : p.d_ffn <= 16 * 1024 ? ff_topk_reg_kernel<16>
+                        : p.d_ffn <= 24 * 1024 ? ff_topk_reg_kernel<24>
+                                               : ff_topk_reg_kernel<32>;
+  if (p.d_ffn <= 32 * 1024) {
+    hipLaunchKernelGGL(topk_reg, dim3(p.n_blocks), dim3(1024), 0, s, p.scores, p.indices, p.d_ffn, p.k_stride, p.k);
   } else {
     // the kernel's own static arrays (bucket histogram, candidates, scan scratch) take under 26 KiB
     const size_t dyn_limit = (size_t)lds_limit - 26 * 1024;
