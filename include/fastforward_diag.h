@@ -21,7 +21,7 @@ extern "C" {
  *       error.  The gate/up tiles 11 and 12 (weights in registers) address a
  *       listed row by a 32-bit offset: W_gate, W_up and Wc1 below 4 GiB, else
  *       the call fails with FF_ERR_DEVICE.
- *       The down tiles 5 and 6 (weights in registers) address a listed
+ *       The down tiles 5 to 8 (weights in registers) address a listed
  *       row by a 32-bit offset: W_down below 4 GiB, d_model below 2^23, and H
  *       below 2^24 neurons wide; a call beyond that fails with FF_ERR_DEVICE.
  *   "gemm1_split"  -1 = decide by shape, 0 = never, 1 = always: whether the

@@ -1126,18 +1126,21 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
 // output columns, so 16 lanes of a load instruction ask for 128 contiguous bytes of one row, and the transposition that
 // MFMA wants (eight list positions of one column in a lane) is one byte permute per dword of eight rows' pieces.  Eight
 // wavefronts side by side, 64 columns each for all tokens of the tile: nobody else in the workgroup wants a wavefront's
-// weights, only H passes through LDS.
+// weights, only H passes through LDS.  KG = 2: two groups of four wavefronts take the steps in turn and exchange halves of
+// their accumulators at the end (fixed order), for calls with few columns and blocks.
 // v_mfma_f32_16x16x32_bf16: lane (c, q) holds list positions 8 q .. 8 q + 7 of a step's half of 32; MFMA tile f, column c
+  const int kgrp = KG == 1 ? 0 : wave / WN, wn = KG == 1 ? wave : wave % WN;
 // is output column 8 (c mod 8) + 4 (c / 8) + f of the wavefront's 64, so a lane ends with four adjacent columns.
 // RM 0: the identity list; 1: the tile's list in an LDS table of 16-bit ids, as above.
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-template <int MT, int RM>
+template <int MT, int RM, int KG>
 __global__ __launch_bounds__(kDirectWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
-  constexpr int WN = kDirectWaves, BM = MT * 16, BN = WN * 64, S = kDirectStages, STAGE = BM * 128, D = 4, LA = BM / 8 / WN;
+  constexpr int NW = kDirectWaves, WN = NW / KG, BM = MT * 16, BN = WN * 64, S = kDirectStages, D = 4;
+  constexpr int STAGE = BM * 128, LA = BM * KG / 8 / NW;   // a stage: H of 64 positions; a round of the loop takes KG of them
   constexpr int NB = MT == 8 ? 2 : 4;         // halves of a step whose weights are on their way (as many as registers allow)
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1146,20 +1149,22 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   const Gemm2Tile tl = gemm2_tile<BM, BN, 64>(p, V, mt, N, xs);
   if (!tl.valid) return;
   const int Kb = tl.Kb, ntot = tl.ntot, kofs = tl.kofs, nk = tl.nk;
-  const int last = max(nk - 1, 0);
+  const int last = max(nk - 1, 0), rounds = (nk + KG - 1) / KG;
 
-  // H: copy i of a stage covers rows 8 (wave + i WN) .. + 7
+  // H: copy i of a round covers rows 8 (wave + i NW) .. + 7 of its KG stages
   const uint64_t a_base = (uint64_t)(uintptr_t)(p.h + (size_t)tl.t0 * p.hs + kofs);
   uint32_t a_off[LA];
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
-    const int trow = (wave + i * WN) * 8 + lane / 8;
+    const int trow = ((wave + i * NW) * 8 + lane / 8) % (KG == 1 ? 1 << 30 : BM);
     a_off[i] = (uint32_t)(min(trow, tl.rows_valid - 1) * p.hs + ((lane & 7) ^ swz<64>(trow)) * 8) * 2u;
   }
   const uint32_t lds0 = lds_addr_of(smem);
-  // (no conditions in the loop: past the end the last step is requested again, into a slot nobody reads any more)
-  auto issue_a = [&](int st, int i) __attribute__((always_inline)) {
-    gload_lds16_off(a_base + (uint64_t)(uint32_t)min(st, last) * 128u, a_off[i], lds0 + (uint32_t)(st % S) * STAGE + (uint32_t)(wave + i * WN) * 1024u);
+  // (no conditions in the loop: past the end the last step is requested again, into a slot nobody reads any more, or next to
+  // weights that are not multiplied)
+  auto issue_a = [&](int rd, int i) __attribute__((always_inline)) {
+    const int st = KG == 1 ? rd : rd * KG + (wave + i * NW) * 8 / BM;
+    gload_lds16_off(a_base + (uint64_t)(uint32_t)min(st, last) * 128u, a_off[i], lds0 + (uint32_t)(rd % S) * (KG * STAGE) + (uint32_t)(wave + i * NW) * 1024u);
   };
   if (nk > 0) {
 #pragma unroll
@@ -1167,25 +1172,25 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
 #pragma unroll
       for (int i = 0; i < LA; ++i) issue_a(st, i);
   }
-  uint16_t *tab = reinterpret_cast<uint16_t *>(smem + S * STAGE);
+  uint16_t *tab = reinterpret_cast<uint16_t *>(smem + S * KG * STAGE);
   if (RM == 1) {
     // eight list entries per thread in flight at a time (left to itself the loop waits for every load)
     const int32_t *gl = p.idx + (size_t)tl.b * p.k_stride;
     constexpr int U = 8;
-    for (int i0 = tid; i0 < nk * 64; i0 += U * WN * 64) {
+    for (int i0 = tid; i0 < nk * 64; i0 += U * NW * 64) {
       int raw[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) raw[u] = gl[min(kofs + i0 + u * WN * 64, Kb - 1)];
+      for (int u = 0; u < U; ++u) raw[u] = gl[min(kofs + i0 + u * NW * 64, Kb - 1)];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int i = i0 + u * WN * 64, pos = kofs + i;
+        const int i = i0 + u * NW * 64, pos = kofs + i;
         if (i < nk * 64) tab[i] = (uint16_t)(pos < Kb ? min(max(raw[u], 0), p.d_ffn - 1) : (pos < ntot ? p.d_ffn + (pos - Kb) : 0));
       }
     }
     __syncthreads();
   }
-  const int colw = tl.n0 + wave * 64;                              // d_model is a multiple of 64: a wavefront is in or out
+  const int colw = tl.n0 + wn * 64;                              // d_model is a multiple of 64: a wavefront is in or out
   const int hi = c >> 3;                                           // which of a pair of rows this lane loads
   const int col4 = 8 * (c & 7) + 4 * hi;                           // this lane's four columns, once the pairs have swapped
   const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
@@ -1204,14 +1209,15 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   u32x4_t ids[2];                             // ids of rows 8 q .. 8 q + 7 of the half requested next (by its parity)
   u32x4_t af[D];                              // ring of token fragments
   u32x4_t bf[2][4];                           // operands of the half at hand and of the next
-  // (halves are counted through the tile: half hh is half hh % 2 of step hh / 2)
+  // (halves are counted through the wavefront's own steps: half hh is half hh % 2 of its step hh / 2)
+  auto half_at = [&](int hh) __attribute__((always_inline)) -> int { return KG == 1 ? min(hh, 2 * last + 1) : 2 * min((hh >> 1) * KG + kgrp, last) + (hh & 1); };
   auto fetch_ids = [&](int hh, int par) __attribute__((always_inline)) {
-    if (RM == 1) ids[par] = *reinterpret_cast<const u32x4_t *>(tab + min(hh, 2 * last + 1) * 32 + 8 * q);
+    if (RM == 1) ids[par] = *reinterpret_cast<const u32x4_t *>(tab + half_at(hh) * 32 + 8 * q);
   };
   // load i of half hh.  FAST: all of its positions are W_down rows, whose offsets fit 32 bits (the launcher's check);
   // else each row's matrix is found lane by lane.
   auto load_w = [&](int hh_, int par, int buf, int i, auto fast_tag) __attribute__((always_inline)) {
-    const int hh = min(hh_, 2 * last + 1);
+    const int hh = half_at(hh_);
     const uint32_t id = RM == 1 ? (ids[par][i] >> (16 * hi)) & 0xffffu : 0u;
     if (decltype(fast_tag)::value) {
       if (RM == 1) {
@@ -1246,9 +1252,10 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   for (int h = 0; h < 2; ++h) aoff[h] = (uint32_t)(c * 128 + (((4 * h + q) ^ swz<64>(c)) << 4));
   // fragment n of a step: half n / MT, token tile n % MT
   auto frag = [&](int kt, int n) __attribute__((always_inline)) {
-    af[n % D] = *reinterpret_cast<const u32x4_t *>(smem + (kt % S) * STAGE + aoff[n / MT] + (n % MT) * 2048);
+      if (KG == 1 || decltype(fast_tag)::value || kt * KG + kgrp < nk) {      // (an odd number of steps: one group has one less)
+    af[n % D] = *reinterpret_cast<const u32x4_t *>(smem + ((kt % S) * KG + kgrp) * STAGE + aoff[n / MT] + (n % MT) * 2048);
   };
-  // One step of 64 positions.  During a half the next one's weights are permuted into operands, and those of half
+  // One step of 64 positions in each k-group.  During a half the next one's weights are permuted into operands, and those of half
   // hh + 1 + NB take their registers; H of step kt + S - 2 is requested in the first half; in front of the last D
   // fragments the workgroup makes sure that H of step kt + 1 has landed (its copies are older than the last 8
   // requests).  The slot of H requested in a step was last read two steps before, hence by nobody who has passed the
@@ -1262,7 +1269,8 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
       if (n == 2 * MT - D) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
       const u32x4_t a = af[n % D];
 #pragma unroll
-      for (int f = 0; f < 4; ++f) acc[r][f] = mfma16(a, bf[h][f], acc[r][f]);
+        for (int f = 0; f < 4; ++f) acc[r][f] = mfma16(a, bf[h][f], acc[r][f]);
+      }
       __builtin_amdgcn_sched_barrier(0);
       if (n + D < 2 * MT) frag(kt, n + D); else frag(kt + 1, n + D - 2 * MT);
       if (n < LA) issue_a(kt + S - 2, n);
@@ -1292,21 +1300,42 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
 #pragma unroll
     for (int n = 0; n < D; ++n) frag(0, n);
     __builtin_amdgcn_sched_barrier(0);
-    const int nfast = min((Kb - kofs) / 64, nk);
+    const int nfast = min((Kb - kofs) / (64 * KG), nk / KG);
     constexpr std::integral_constant<int, 0> ph0{};
     constexpr std::integral_constant<int, 2> ph1{};
     int kt = 0;
     if (NB == 2) {
       for (; kt + 2 < nfast; ++kt) step(kt, ph0, std::true_type{});
-      for (; kt < nk; ++kt) step(kt, ph0, std::false_type{});
+      for (; kt < rounds; ++kt) step(kt, ph0, std::false_type{});
+  if (KG > 1) {
+    // group g keeps token tiles i with i % 2 == g and hands the others over through LDS
+    static_assert(KG == 1 || (KG == 2 && MT % 2 == 0 && S * KG * STAGE >= NW * MT / 2 * 4 * 1024), "ring too small for the hand-over");
+    __syncthreads();                                       // everyone is done with the ring
+    f32x4_t *red = reinterpret_cast<f32x4_t *>(smem);
+    const int mine = wave * (MT / 2 * 4) * 64 + lane, other = (wave + (kgrp ? -WN : WN)) * (MT / 2 * 4) * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      if ((i & 1) != kgrp) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) red[mine + (i / 2 * 4 + f) * 64] = acc[i][f];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      if ((i & 1) == kgrp) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) acc[i][f] += red[other + (i / 2 * 4 + f) * 64];
+      }
+  }
     } else {
       for (; kt + 4 < nfast; kt += 2) {
         step(kt, ph0, std::true_type{});
         step(kt + 1, ph1, std::true_type{});
+    if (KG == 1 || (i & 1) == kgrp)
       }
-      while (kt < nk) {
+      while (kt < rounds) {
         step(kt, ph0, std::false_type{});
-        if (++kt >= nk) break;
+        if (++kt >= rounds) break;
         step(kt, ph1, std::false_type{});
         ++kt;
       }
@@ -1353,10 +1382,10 @@ Variant g1d() {
   return Variant{reinterpret_cast<const void *>(&ff_gemm1_direct_kernel<MT, WN, NBUF>), MT * 32, WN * 32, WN * 64,
                  kDirectStages * MT * 32 * 128, {nullptr, nullptr, nullptr}};
 }
-template <int MT>
+template <int MT, int KG = 1>
 Variant g2d() {
-  return Variant{reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 0>), MT * 16, kDirectWaves * 64, kDirectWaves * 64,
-                 kDirectStages * MT * 16 * 128, {reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 1>), nullptr, nullptr}};
+  return Variant{reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 0, KG>), MT * 16, kDirectWaves / KG * 64, kDirectWaves * 64,
+                 kDirectStages * KG * MT * 16 * 128, {reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 1, KG>), nullptr, nullptr}};
 }
 constexpr int kIdRingBytes = 8 * 256;   // row-id mode 3: eight stages of 64 raw list entries
 
@@ -1375,6 +1404,8 @@ const Variant kGemm1[] = {
     g1<2, 2, 2, 1, 64, 4>(),     // 8: 128 x 64, 4 waves, BK 64, 4 stages (128 KB; 2 stages: 67 against 48 us on 224 tiles): the heavy blocks' surplus
     g1<2, 1, 2, 1, 64, 6, 2>(),  // 9: 128 x 32, 4 waves in 2 k-groups, BK 64, 6 stages (144 KB): a single block over the whole chip
     g1<1, 1, 2, 1, 64, 8, 2>(),  // 10: 64 x 32, 2 waves in 2 k-groups, BK 64, 8 stages (128 KB): the same for a short block
+    g2d<8, 2>(),              // 7: 128 x 256, weights in registers, 2 k-groups (128 KB)
+    g2d<4, 2>(),              // 8: 64 x 256, the same (64 KB)
     g1d<4, 8, 2>(),                 // 11: 128 x 256, 8 waves, weights in registers (64 KB)
     g1d<2, 8, 3>(),              // 12: 64 x 256, the same, weights of three steps on their way (32 KB)
     // (5 and 6 serve matrices of 4 GiB and more, whose rows' offsets have more than 32 bits)
@@ -1497,13 +1528,14 @@ constexpr int kRemainderVariant = 7;
 constexpr int kHeavySurplusVariant = 8;
 constexpr int kWide128 = 6;
 constexpr int kGemm1Direct128 = 11, kGemm1Direct64 = 12;   // the gate/up tiles with the weights in registers
-constexpr int kDirect128 = 5, kDirect64 = 6;   // the down-GEMM tiles
+constexpr int kDirect128 = 5, kDirect64 = 6, kDirect128Narrow = 7, kDirect64Narrow = 8;   // the down-GEMM tiles
 constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
 
 static bool gemm1_direct(int variant) { return variant >= kGemm1Direct128; }
 // whether the tile with the weights in registers can address these matrices: the offsets of a row and of a token of its tile
 // have 32 bits
 static bool gemm1_direct_addresses(const Gemm1Params &p) {
+  p.block = std::min(p.block, p.T);                       // (one short block: tiles for the tokens that there are)
   const uint64_t row_bytes = (uint64_t)p.d_model * 2u;
   return (uint64_t)std::max(p.d_ffn, p.rc) * row_bytes >> 32 == 0 && (uint64_t)kGemm1[kGemm1Direct128].bm * row_bytes >> 32 == 0;
 }
@@ -1650,6 +1682,7 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
     v.fn = v.fn_rm[0];
   } else if (mode == 3 && ring_fits) {
     v.lds += kIdRingBytes;
+                                     {kDirect128Narrow, 0.72, 0.92, 9.0}, {kDirect64Narrow, 0.45, 0.9, 6.0},
     v.fn = v.fn_rm[2];
   } else {
     v.fn = mode == 2 ? v.fn_rm[1] : nullptr;
@@ -1659,12 +1692,14 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 
 // What a round of 256 tiles costs, in us, with the weights coming from HBM: fixed + 64-position steps x (idle .. full:
 // a few workgroups on the chip, or all of it busy).  The tiles with the weights in registers run a step of 128 x 512 in 1.6 us
-// with the chip full (1.32 PFLOP/s dense), one of 64 x 512 in 1.1 to 1.24; alone on the chip they wait for their loads.  The 128 x 256 tile with both operands in LDS serves calls with few columns and blocks.
+// with the chip full (1.32 PFLOP/s dense), one of 64 x 512 in 1.1 to 1.24; alone on the chip they wait for their loads.  The
+// tiles of 256 columns serve calls with few columns and blocks (2048/8192, K 4096, 32 blocks of 128, one round: 75.9 us with both
+// operands in LDS, 66.5 with the weights in registers; 256 tokens of the smallest configuration 13.7 cut in pieces, 11.7 as 64 x 256).
 // The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
 struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
-static bool gemm2_direct(int variant) { return variant == kDirect128 || variant == kDirect64; }
+static bool gemm2_direct(int variant) { return variant >= kDirect128 && variant <= kDirect64Narrow; }
 // Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
 // product of two 24-bit numbers in 32 bits, a token's offset into a tile of H has 32 bits too.
 static bool gemm2_direct_addresses(const Gemm2Params &p) {
@@ -1710,6 +1745,7 @@ size_t ff_gemm2_split_bytes(int n_tokens, int d_model) {
   // (cuts are tried up to two rounds of tiles; blocks only make the tiles more)
   long tiles = 2 * kNumCU;
   for (const Gemm2Cost &g : kGemm2Cost) {
+  p.block = std::min(p.block, p.T);
     const Variant &v = kGemm2[g.variant];
     tiles = std::min<long>(tiles, (long)((n_tokens + v.bm - 1) / v.bm) * ((d_model + v.bn - 1) / v.bn));
   }
@@ -1749,7 +1785,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     const int surplus = up64(ntot) - up64(base);
     const bool heavy_cut = split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= up64(base);
     for (const Gemm2Cost &g : kGemm2Cost) {
-      if (heavy_cut && variant >= 0 && gemm2_direct(variant) && !gemm2_direct(g.variant)) break;
+      if (heavy_cut && variant >= 0 && gemm2_direct(variant) && !gemm2_direct(g.variant)) continue;
       const Variant &v = kGemm2[g.variant];
       const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
       const long N = (p.d_model + v.bn - 1) / v.bn;

@@ -673,11 +673,11 @@ def test_gate_up_gemm_with_weights_in_registers(ctx, variant, block, d_model):
         assert all((g - o).abs().max().item() <= 1e-3 * o.abs().max().item() for g, o in zip(got, out[2, 0]))
 
 
-@pytest.mark.parametrize("variant", [5, 6])
+@pytest.mark.parametrize("variant", [5, 6, 7, 8])
 @pytest.mark.parametrize("rc,ks", [(0, [1, 64, 65, 320]), (8, [1064, 56, 127, 440]), (64, [128, 129, 1064, 640]), (24, [1064] * 4)])
 def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
-    """The down-GEMM tiles that load the gathered rows straight into registers (128 x 512 and 64 x 512): lists of
-    one to seventeen steps of 64, ends inside a step, steps that hold neurons and compensator units, the identity list
+    """The down-GEMM tiles that load the gathered rows straight into registers (128 x 512, 64 x 512, and 256 columns in two
+    k-groups, of which one has a step less where their number is odd): lists of one to seventeen steps of 64, ends inside a step, steps that hold neurons and compensator units, the identity list
     of the dense call, a short last block, columns that fill no whole tile; whole lists, and all of them cut into 2, 5
     and 16 pieces, some of which hold nothing.  Against the oracle at the stated bars and against the tile with both
     operands in LDS (other order of the same fp32 sums: 1e-5)."""
@@ -703,10 +703,10 @@ def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
         assert all((g - o).abs().max().item() <= 1e-5 for g, o in zip(got, out[1, 0]))
 
 
-@pytest.mark.parametrize("d_model,d_ffn,n_tokens", [(1024, 1064, 9000), (2048, 4096, 300)])
+@pytest.mark.parametrize("d_model,d_ffn,n_tokens", [(1024, 1064, 9000), (2048, 4096, 300), (4096, 4096, 150), (256, 688, 256)])
 def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
-    """Lists that hold every neuron are the identity list, with the compensator's rows behind it: two calls for which the
-    down GEMM takes the 128 x 512 and, cut into pieces, the 64 x 512 tile with the weights in registers
+    """Lists that hold every neuron are the identity list, with the compensator's rows behind it: calls for which the
+    down GEMM takes the 128 x 512 tile, the 64 x 256 and 64 x 512 tiles cut into pieces and the 64 x 256 tile, all with the weights in registers
     (csrc/ff_launch_checks.hip holds that choice)."""
     c = Case(W.Shape("keepall", d_model, d_ffn, n_tokens, 256, 8, 24))
     ks = [d_ffn] * c.n_blocks
