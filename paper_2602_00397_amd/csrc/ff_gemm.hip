@@ -103,21 +103,8 @@ __device__ __forceinline__ u32x4_t mk4(uint32_t a, uint32_t b, uint32_t c, uint3
   return v;
 }
 
-// ---- asynchronous global -> LDS staging --------------------------------------
-// One wavefront instruction moves 64 x 16 bytes from per-lane global addresses to
-// 1 KiB of LDS starting at a wave-uniform address (lane l lands at +16 l).  The copy
-// bypasses the registers and is tracked by vmcnt only, so loads for later k-steps stay
-// in flight across barriers; they are waited for with explicit counts.
-// m0 (the LDS base of the copy) is written without being listed as clobbered: it is a reserved register
-// that the compiler never allocates and never keeps a value in across statements (it rewrites m0 in front
-// of each of its own uses); naming it in the clobber list only draws a "reserved register" warning.
-__device__ __forceinline__ void gload_lds16(const void *gptr, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(gptr), "s"(lds_addr)
-               : "memory");
-}
-// the same from a wave-uniform base plus a 32-bit byte offset per lane
+// ---- asynchronous global -> LDS staging (gload_lds16, in the internal header) ----
+// from a wave-uniform base plus a 32-bit byte offset per lane
 __device__ __forceinline__ void gload_lds16_off(uint64_t base, uint32_t off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
@@ -135,9 +122,6 @@ template <int N>
 __device__ __forceinline__ void wait_vm_barrier() {
   // lgkmcnt(0): this wavefront's own LDS reads of the slot about to be refilled have completed
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
-}
-__device__ __forceinline__ uint32_t lds_addr_of(const void *p) {
-  return (uint32_t)(size_t)(__attribute__((address_space(3))) const uint8_t *)p;
 }
 
 // ============================ gemm1 =========================================
@@ -461,10 +445,11 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
 // of exchanges inside the fours (transpose4) turn the four loads of 32 rows into the operands of four MFMA groups: group g
 // has chunk g in the lower half of the wavefront and chunk g + 4 in the upper.  The order of k inside a step is free as long
 // as X is read in the same one.
-// Measured, both operands in LDS against this (one MI355X, 4096/14336): 64 blocks of 128, K 7168, both launches 843 -> 830 us;
-// K 10035 1216 -> 1178; 64 blocks of 64, K 3584 398 -> 343, K 7168 698 -> 645.  With 128 tokens it is the chip's power that
-// binds: without the weights' loads 756 us, without X's copies 775, without the exchanges 803, MFMAs alone 640.  With 64 the
-// loads from beyond L2 do: each row serves 64 tokens.
+// Measured, both operands in LDS against this (one MI355X, 4096/14336): 64 blocks of 128, K 7168, both launches 839 -> 809 us;
+// 64 blocks of 64, K 3584 398 -> 325, K 7168 698 -> 645; 16384 tokens of 3584/18944, four layers 7640 -> 7410.  With 128 tokens
+// the chip's power and the issue of instructions bind: without the weights' loads 8% less, without X's copies 6%, without the
+// exchanges 3%, MFMAs alone three quarters; 64-bit additions for the loads' addresses cost 3%, two idle cycles around every
+// exchange 0.7%.  With 64 tokens the loads from beyond L2 do: each row serves 64 tokens.
 // Tiles whose 32 rows of a wavefront are all list rows take 32-bit offsets from the two matrices; compensator units and
 // padding find their matrix lane by lane.
 constexpr int kDirectStages = 4, kDirectWaves = 8;
@@ -543,8 +528,9 @@ void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX)
     const uint32_t ko = (uint32_t)min(kt, last) * 128u;
     uintptr_t base = (uintptr_t)(f ? p.wu : p.wg) + ko;
     if (decltype(fast_tag)::value) {
-      asm("" : "+s"(base));                   // a scalar base and the lane's 32-bit offset: no address arithmetic in the loop
-      wb[buf][f][j] = *(gptr_t)(base + w_off[j]);
+      uint32_t off = w_off[j];
+      asm("" : "+v"(off));                    // a scalar base and the lane's 32-bit offset: no address arithmetic in the loop
+      wb[buf][f][j] = *(gptr_t)(base + off);
     } else {
       if ((is_comp >> j) & 1u) base = (uintptr_t)p.wc1 + ko;
       wb[buf][f][j] = *(gptr_t)(base + w_off[j]);
@@ -585,7 +571,7 @@ void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX)
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
           const int x = (n - TR0) * PER + q;
-          transpose4(wb[(buf + 1) % NBUF][x / 4], x % 4);
+          if (x < 7) transpose4<false>(wb[(buf + 1) % NBUF][x / 4], x % 4); else transpose4<true>(wb[(buf + 1) % NBUF][x / 4], x % 4);
         }
       }
       if (!END && i == MT - 1) {
@@ -605,7 +591,7 @@ void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX)
       }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int x = 0; x < 8; ++x) transpose4(wb[0][x / 4], x % 4);
+    for (int x = 0; x < 8; ++x) transpose4<true>(wb[0][x / 4], x % 4);
     asm volatile("s_barrier" ::: "memory");            // (the copies of the first two steps are older than those loads)
 #pragma unroll
     for (int n = 0; n < D; ++n) frag(0, n);
@@ -1129,7 +1115,6 @@ void ff_gemm2_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
 // weights, only H passes through LDS.  KG = 2: two groups of four wavefronts take the steps in turn and exchange halves of
 // their accumulators at the end (fixed order), for calls with few columns and blocks.
 // v_mfma_f32_16x16x32_bf16: lane (c, q) holds list positions 8 q .. 8 q + 7 of a step's half of 32; MFMA tile f, column c
-  const int kgrp = KG == 1 ? 0 : wave / WN, wn = KG == 1 ? wave : wave % WN;
 // is output column 8 (c mod 8) + 4 (c / 8) + f of the wavefront's 64, so a lane ends with four adjacent columns.
 // RM 0: the identity list; 1: the tile's list in an LDS table of 16-bit ids, as above.
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
@@ -1145,6 +1130,7 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kgrp = KG == 1 ? 0 : wave / WN, wn = KG == 1 ? wave : wave % WN;
   const int c = lane & 15, q = lane >> 4;
   const Gemm2Tile tl = gemm2_tile<BM, BN, 64>(p, V, mt, N, xs);
   if (!tl.valid) return;
@@ -1252,7 +1238,6 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
   for (int h = 0; h < 2; ++h) aoff[h] = (uint32_t)(c * 128 + (((4 * h + q) ^ swz<64>(c)) << 4));
   // fragment n of a step: half n / MT, token tile n % MT
   auto frag = [&](int kt, int n) __attribute__((always_inline)) {
-      if (KG == 1 || decltype(fast_tag)::value || kt * KG + kgrp < nk) {      // (an odd number of steps: one group has one less)
     af[n % D] = *reinterpret_cast<const u32x4_t *>(smem + ((kt % S) * KG + kgrp) * STAGE + aoff[n / MT] + (n % MT) * 2048);
   };
   // One step of 64 positions in each k-group.  During a half the next one's weights are permuted into operands, and those of half
@@ -1268,6 +1253,7 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
       const int h = n / MT, r = n % MT;
       if (n == 2 * MT - D) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
       const u32x4_t a = af[n % D];
+      if (KG == 1 || decltype(fast_tag)::value || kt * KG + kgrp < nk) {      // (an odd number of steps: one group has one less)
 #pragma unroll
         for (int f = 0; f < 4; ++f) acc[r][f] = mfma16(a, bf[h][f], acc[r][f]);
       }
@@ -1307,6 +1293,21 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
     if (NB == 2) {
       for (; kt + 2 < nfast; ++kt) step(kt, ph0, std::true_type{});
       for (; kt < rounds; ++kt) step(kt, ph0, std::false_type{});
+    } else {
+      for (; kt + 4 < nfast; kt += 2) {
+        step(kt, ph0, std::true_type{});
+        step(kt + 1, ph1, std::true_type{});
+      }
+      while (kt < rounds) {
+        step(kt, ph0, std::false_type{});
+        if (++kt >= rounds) break;
+        step(kt, ph1, std::false_type{});
+        ++kt;
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies requested past the end
+  }
+
   if (KG > 1) {
     // group g keeps token tiles i with i % 2 == g and hands the others over through LDS
     static_assert(KG == 1 || (KG == 2 && MT % 2 == 0 && S * KG * STAGE >= NW * MT / 2 * 4 * 1024), "ring too small for the hand-over");
@@ -1327,26 +1328,11 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
         for (int f = 0; f < 4; ++f) acc[i][f] += red[other + (i / 2 * 4 + f) * 64];
       }
   }
-    } else {
-      for (; kt + 4 < nfast; kt += 2) {
-        step(kt, ph0, std::true_type{});
-        step(kt + 1, ph1, std::true_type{});
-    if (KG == 1 || (i & 1) == kgrp)
-      }
-      while (kt < rounds) {
-        step(kt, ph0, std::false_type{});
-        if (++kt >= rounds) break;
-        step(kt, ph1, std::false_type{});
-        ++kt;
-      }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies requested past the end
-  }
-
   const int col = colw + col4;
   if (colw >= p.d_model) return;
 #pragma unroll
   for (int i = 0; i < MT; ++i)
+    if (KG == 1 || (i & 1) == kgrp)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int rowl = i * 16 + 4 * q + e;
@@ -1404,8 +1390,6 @@ const Variant kGemm1[] = {
     g1<2, 2, 2, 1, 64, 4>(),     // 8: 128 x 64, 4 waves, BK 64, 4 stages (128 KB; 2 stages: 67 against 48 us on 224 tiles): the heavy blocks' surplus
     g1<2, 1, 2, 1, 64, 6, 2>(),  // 9: 128 x 32, 4 waves in 2 k-groups, BK 64, 6 stages (144 KB): a single block over the whole chip
     g1<1, 1, 2, 1, 64, 8, 2>(),  // 10: 64 x 32, 2 waves in 2 k-groups, BK 64, 8 stages (128 KB): the same for a short block
-    g2d<8, 2>(),              // 7: 128 x 256, weights in registers, 2 k-groups (128 KB)
-    g2d<4, 2>(),              // 8: 64 x 256, the same (64 KB)
     g1d<4, 8, 2>(),                 // 11: 128 x 256, 8 waves, weights in registers (64 KB)
     g1d<2, 8, 3>(),              // 12: 64 x 256, the same, weights of three steps on their way (32 KB)
     // (5 and 6 serve matrices of 4 GiB and more, whose rows' offsets have more than 32 bits)
@@ -1421,6 +1405,8 @@ const Variant kGemm2[] = {
     g2<2, 2, 2, 64, 3, 2>(),  // 4: 128 x 256, 8 waves in 2 k-groups, BK 64, 3 stages (144 KB)
     g2d<8>(),                 // 5: 128 x 512, 8 waves, weights in registers (64 KB)
     g2d<4>(),                 // 6: 64 x 512, weights in registers
+    g2d<8, 2>(),              // 7: 128 x 256, weights in registers, 2 k-groups (128 KB)
+    g2d<4, 2>(),              // 8: 64 x 256, the same (64 KB)
 };
 constexpr int kNumGemm1 = sizeof(kGemm1) / sizeof(Variant);
 constexpr int kNumGemm2 = sizeof(kGemm2) / sizeof(Variant);
@@ -1535,7 +1521,6 @@ static bool gemm1_direct(int variant) { return variant >= kGemm1Direct128; }
 // whether the tile with the weights in registers can address these matrices: the offsets of a row and of a token of its tile
 // have 32 bits
 static bool gemm1_direct_addresses(const Gemm1Params &p) {
-  p.block = std::min(p.block, p.T);                       // (one short block: tiles for the tokens that there are)
   const uint64_t row_bytes = (uint64_t)p.d_model * 2u;
   return (uint64_t)std::max(p.d_ffn, p.rc) * row_bytes >> 32 == 0 && (uint64_t)kGemm1[kGemm1Direct128].bm * row_bytes >> 32 == 0;
 }
@@ -1551,6 +1536,7 @@ constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 
 
 hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, hipStream_t s) {
   Gemm1Params p = p_in;
+  p.block = std::min(p.block, p.T);                       // (one short block: tiles for the tokens that there are)
   const int n_extent = p.k.k_max + p.rc;                  // longest list
   const bool ragged = p.k.per_block != nullptr;           // lists of unequal length
   const int base_extent = (p.k.n_heavy > 0 ? p.k.k_base : p.k.k_max) + p.rc;   // what all but the heavy blocks have
@@ -1682,7 +1668,6 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
     v.fn = v.fn_rm[0];
   } else if (mode == 3 && ring_fits) {
     v.lds += kIdRingBytes;
-                                     {kDirect128Narrow, 0.72, 0.92, 9.0}, {kDirect64Narrow, 0.45, 0.9, 6.0},
     v.fn = v.fn_rm[2];
   } else {
     v.fn = mode == 2 ? v.fn_rm[1] : nullptr;
@@ -1698,6 +1683,7 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 // The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
 struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
+                                     {kDirect128Narrow, 0.72, 0.92, 9.0}, {kDirect64Narrow, 0.45, 0.9, 6.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
 static bool gemm2_direct(int variant) { return variant >= kDirect128 && variant <= kDirect64Narrow; }
 // Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
@@ -1745,7 +1731,6 @@ size_t ff_gemm2_split_bytes(int n_tokens, int d_model) {
   // (cuts are tried up to two rounds of tiles; blocks only make the tiles more)
   long tiles = 2 * kNumCU;
   for (const Gemm2Cost &g : kGemm2Cost) {
-  p.block = std::min(p.block, p.T);
     const Variant &v = kGemm2[g.variant];
     tiles = std::min<long>(tiles, (long)((n_tokens + v.bm - 1) / v.bm) * ((d_model + v.bn - 1) / v.bn));
   }
@@ -1761,6 +1746,7 @@ size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model) {
 
 hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int row_mode, int ksplit, int nsplit, hipStream_t s) {
   Gemm2Params p = p_in;
+  p.block = std::min(p.block, p.T);
   const bool chosen = variant < 0;
   const size_t per_piece = (size_t)p.T * p.d_model * sizeof(float);
   const long room = p.split_part != nullptr ? std::min<long>((long)(p.split_bytes / per_piece), kMaxPieces - 1) : 1;

@@ -49,9 +49,9 @@ __device__ __forceinline__ float gv_act(int act, float g) {
 // them, the address unit made it 54.9 us for a dense token of 4096/14336).  The block's tokens go through LDS, each
 // wavefront its own channels, 16-byte chunks swizzled by the token; the tokens repeat past the last one.
 // Bound by HBM.  Few wavefronts, few steps of each on their way and small workgroups: what counts is that workgroups start and
-// end next to each other (a dense token: 8 wavefronts with 4 steps 54.5 us, with 2 steps 52.6, 4 wavefronts with 2 steps 47.8).
-// With multiply-adds, a wavefront per position, it took 44 us, 23.4 on a list of 7168 as now, but 19.0 for five tokens on
-// 4096 positions of 2048/8192 (now 15.2) and 24.5 for eight (17.1).
+// end next to each other (a dense token: 8 wavefronts with 4 steps 54.5 us, with 2 steps 52.6, 4 wavefronts with 2 steps 46.7).
+// With multiply-adds, a wavefront per position, it took 44 us and 23.5 on a list of 7168 (now 22.8), 19.5 for five tokens on
+// 4096 positions of 2048/8192 (now 12.3), 24.3 for eight (12.7) and 73.6 for eight with a list each (60.5).
 // grid (groups of 16 positions, n_blocks), LDS = gemv1_lds.
 __global__ __launch_bounds__(kGemv1Waves * 64) __attribute__((amdgpu_waves_per_eu(6)))
 void ff_gemv1_kernel(GemvParams p, int steps) {
@@ -82,11 +82,11 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
   const int n = max(0, min(p.d_model - ch0, steps * 64)) / 64;   // its steps
   const int pitch = steps * 128;                                 // bytes per token in LDS
   uint8_t *xs = smem + (size_t)wave * nt * pitch;
-  uint4 xv[kGemvMaxTokens];
   const int nc = n * 8;                                          // 16-byte chunks per token
-#pragma unroll
-  for (int t = 0; t < kGemvMaxTokens; ++t)
-    if (t < nt && lane < nc) xv[t] = *reinterpret_cast<const uint4 *>(p.x + (size_t)(t0 + t) * p.d_model + ch0 + lane * 8);
+  for (int t = 0; t < nt; ++t)
+    for (int c0 = 0; c0 < nc; c0 += 64)
+      if (c0 + lane < nc)
+        gload_lds16(p.x + (size_t)(t0 + t) * p.d_model + ch0 + ((c0 + lane) ^ t) * 8, lds_addr_of(xs) + (uint32_t)(t * pitch + c0 * 16));
   __builtin_amdgcn_sched_barrier(0);
   const bf16_t *rows[4];
 #pragma unroll
@@ -105,13 +105,9 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
       for (int j = 0; j < 4; ++j) w[i][j] = *reinterpret_cast<const u32x4_t *>(rows[j] + min(i, n - 1) * 64);
   }
   __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int t = 0; t < kGemvMaxTokens; ++t)
-    if (t < nt && lane < nc) *reinterpret_cast<uint4 *>(xs + t * pitch + ((lane ^ t) << 4)) = xv[t];
-  for (int t = 0; t < nt; ++t)
-    for (int ch = lane + 64; ch < nc; ch += 64)
-      *reinterpret_cast<uint4 *>(xs + t * pitch + ((ch ^ t) << 4)) = *reinterpret_cast<const uint4 *>(p.x + (size_t)(t0 + t) * p.d_model + ch0 + ch * 8);
-  // (a wavefront reads what it wrote itself: no barrier)
+  // the tokens are older than the weights: they have landed by the time that one step of those is all that is on its way
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"((U - 1) * 4) : "memory");
+  // (a wavefront reads what it copied itself: no barrier)
   f32x16_t acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
@@ -122,7 +118,7 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
       const int s = s0 + i;
       if (s < n) {
 #pragma unroll
-        for (int d = 0; d < 4; ++d) transpose4(w[i], d);
+        for (int d = 0; d < 4; ++d) transpose4<true>(w[i], d);
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           acc = mfma32(w[i][g], *reinterpret_cast<const u32x4_t *>(xs + tok * pitch + (((8 * s + g + 4 * half) ^ tok) << 4)), acc);

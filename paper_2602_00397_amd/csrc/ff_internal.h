@@ -28,11 +28,14 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
 // Four loads of 16 bytes per lane in which lanes a = 0 .. 3 of every four ask for 64 contiguous bytes: r[j] = (row j, chunk a).
 // Afterwards r[g] = (row a, chunk g): MFMA operands.  Dword d of each; all four dwords are to be done.
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+// NEXT: the next instruction may be an MFMA that reads them (two wait states after a VALU write, which the compiler does not
+// count behind inline asm).
+template <bool NEXT>
 __device__ __forceinline__ void transpose4(u32x4_t (&r)[4], int d) {
   uint32_t a = r[0][d], b = r[1][d], c = r[2][d], e = r[3][d], t, s, u;
-  // (a DPP source written by the two instructions before would be read too early: s_nop, and the order below)
+  // (a DPP source written by the two instructions before would be read too early: s_nop and s_mov, and the order below)
   asm volatile(
-      "s_nop 1\n\t"
+      "s_nop 0\n\t"
       "s_mov_b64 vcc, %7\n\t"
       "v_cndmask_b32_dpp %4, %1, %0, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
       "v_cndmask_b32_dpp %5, %3, %2, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
@@ -44,12 +47,30 @@ __device__ __forceinline__ void transpose4(u32x4_t (&r)[4], int d) {
       "v_cndmask_b32_dpp %1, %3, %6, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
       "s_not_b64 vcc, vcc\n\t"
       "v_cndmask_b32_dpp %2, %4, %5, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_cndmask_b32_dpp %3, %6, %3, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1"
+      "v_cndmask_b32_dpp %3, %6, %3, vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
       : "+v"(a), "+v"(b), "+v"(c), "+v"(e), "=&v"(t), "=&v"(s), "=&v"(u)
       : "s"(0x5555555555555555ull), "s"(0x3333333333333333ull)
       : "vcc", "scc");
+  if (NEXT) asm volatile("s_nop 1");
   r[0][d] = a; r[1][d] = b; r[2][d] = c; r[3][d] = e;
+}
+
+// ---- asynchronous global -> LDS staging --------------------------------------
+// One wavefront instruction moves 64 x 16 bytes from per-lane global addresses to
+// 1 KiB of LDS starting at a wave-uniform address (lane l lands at +16 l).  The copy
+// bypasses the registers and is tracked by vmcnt only, so loads for later k-steps stay
+// in flight across barriers; they are waited for with explicit counts.
+// m0 (the LDS base of the copy) is written without being listed as clobbered: it is a reserved register
+// that the compiler never allocates and never keeps a value in across statements (it rewrites m0 in front
+// of each of its own uses); naming it in the clobber list only draws a "reserved register" warning.
+__device__ __forceinline__ void gload_lds16(const void *gptr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(gptr), "s"(lds_addr)
+               : "memory");
+}
+__device__ __forceinline__ uint32_t lds_addr_of(const void *p) {
+  return (uint32_t)(size_t)(__attribute__((address_space(3))) const uint8_t *)p;
 }
 
 // Per-block neuron count: either one value for all blocks or a device array.
