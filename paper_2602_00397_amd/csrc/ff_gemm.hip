@@ -190,7 +190,7 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   constexpr int NL = STAGE / 1024;                 // wave-loads per stage
   constexpr int L = NL / NW;                       // wave-loads per wavefront per stage
   static_assert(NL % NW == 0, "stage must split evenly over the wavefronts");
-  static_assert(A_BYTES % 1024 == 0, "A tile must be whole wave-loads");
+  static_assert(A_BYTES % 1024 == 0 && BNn % RPL == 0, "A and B tiles must be whole wave-loads");
   extern __shared__ __align__(16) uint8_t smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -204,7 +204,6 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   const int b = tl.b, m = tl.m, t0 = tl.t0, rows_valid = tl.rows_valid, Kb = tl.Kb, ntot = tl.ntot, n0 = tl.n0;
 
   // wave-load j = wave + i * NW of a stage covers stage bytes [1024 j, 1024 j + 1024)
-  const bf16_t *src[L];
   // list position of the B row that copy i of a stage fills (-1: an A row)
   auto b_pos = [&](int i) __attribute__((always_inline)) -> int {
     const int trow = (wave + i * NW) * RPL + lane / CPR;
@@ -221,41 +220,33 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
     entry[i] = (p.idx != nullptr && pos >= 0) ? p.idx[(size_t)b * p.k_stride + min(pos, Kb - 1)] : pos;
   }
   __builtin_amdgcn_sched_barrier(0);
+  // A wave-load is of X or of one matrix (RPL divides both tiles): where its rows start, and which row and chunk this lane takes
+  uint64_t from[L];
+  int row[L];
+  uint32_t is_comp = 0;                              // bit i: a compensator unit's row instead
+  auto chunk_of = [&](int i) __attribute__((always_inline)) -> int {
+    const int trow = (wave + i * NW) * RPL + lane / CPR;
+    return (lane % CPR) ^ swz<BK>(trow);             // BM is a multiple of 32: the B rows keep the swizzle phase
+  };
 #pragma unroll
   for (int i = 0; i < L; ++i) {
-    const int j = wave + i * NW;
-    const int trow = j * RPL + lane / CPR;          // row within the stage (A rows, then B rows)
-    const int ch = (lane % CPR) ^ swz<BK>(trow);  // BM is a multiple of 32: the B rows keep the swizzle phase
-    if (trow < BM) {
-      const int tok = t0 + min(trow, rows_valid - 1);
-      src[i] = p.x + (size_t)tok * p.d_model + ch * 8;
+    const int trow0 = (wave + i * NW) * RPL;         // row within the stage (A rows, then B rows) of lane 0
+    if (trow0 < BM) {
+      from[i] = (uint64_t)(uintptr_t)(p.x + (size_t)t0 * p.d_model);
+      row[i] = min(trow0 + lane / CPR, rows_valid - 1);
     } else {
-      const int mat = (trow - BM) / BNn;
+      from[i] = (uint64_t)(uintptr_t)((trow0 - BM) / BNn ? p.wu : p.wg);
       const int pos = b_pos(i);
-      const bf16_t *base = p.wg;
-      int row = 0;
+      row[i] = 0;
       if (pos < Kb) {
-        row = min(max(entry[i], 0), p.d_ffn - 1);
-        base = mat ? p.wu : p.wg;
+        row[i] = min(max(entry[i], 0), p.d_ffn - 1);
       } else if (pos < ntot) {
-        row = pos - Kb;
-        base = p.wc1;
+        row[i] = pos - Kb;
+        is_comp |= 1u << i;
       }
-      src[i] = base + (size_t)row * p.d_model + ch * 8;
     }
   }
   const uint32_t lds0 = lds_addr_of(smem);
-  auto issue = [&](int kt) __attribute__((always_inline)) {
-    const uint32_t st = lds0 + (uint32_t)(kt % S) * STAGE + (uint32_t)wave * 1024u;
-#pragma unroll
-    for (int i = 0; i < L; ++i) gload_lds16(src[i] + kt * BK, st + (uint32_t)i * (NW * 1024u));
-  };
-
-  auto issue_one = [&](int kt, int i) __attribute__((always_inline)) {
-    const uint32_t st = lds0 + (uint32_t)(kt % S) * STAGE + (uint32_t)wave * 1024u;
-    gload_lds16(src[i] + kt * BK, st + (uint32_t)i * (NW * 1024u));
-  };
-
   f32x16_t accg[TM][TN], accu[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -270,6 +261,30 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   // stage kt, so its ring slot takes the copies of stage kt+S: they are issued one at a time
   // between the MFMAs of the next KQ groups (a burst would park the wavefront on a full
   // memory-issue queue with its matrix pipe idle).
+  // FAST: all rows are list rows, and their offsets have 32 bits (p.off32): a scalar address and the lane's offset per copy.
+  // (Added up in 64 bits in the loop: a dense gate/up launch of 4096 tokens 785 us, this way 755.)
+  auto run = [&](auto fast_tag) __attribute__((always_inline)) {
+  constexpr bool FAST = decltype(fast_tag)::value;
+  uint32_t off[L];
+  uint64_t base[L];
+  const bf16_t *src[L];
+#pragma unroll
+  for (int i = 0; i < L; ++i) {
+    if (FAST) {
+      off[i] = (uint32_t)row[i] * ((uint32_t)p.d_model * 2u) + (uint32_t)chunk_of(i) * 16u;
+      base[i] = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)from[i]) |
+                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(from[i] >> 32)) << 32;   // wave-uniform by construction
+    } else src[i] = reinterpret_cast<const bf16_t *>((is_comp >> i) & 1u ? (uint64_t)(uintptr_t)p.wc1 : from[i]) + (size_t)row[i] * p.d_model + chunk_of(i) * 8;
+  }
+  auto issue_one = [&](int kt, int i) __attribute__((always_inline)) {
+    const uint32_t st = lds0 + (uint32_t)(kt % S) * STAGE + (uint32_t)(wave + i * NW) * 1024u;
+    if (FAST) gload_lds16_off(base[i], off[i] + (uint32_t)(kt * BK * 2), st);
+    else gload_lds16(src[i] + kt * BK, st);
+  };
+  auto issue = [&](int kt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) issue_one(kt, i);
+  };
   constexpr int KQ = BK / 16 / KG;                     // MFMA groups (16 k each) per stage and k-group
   static_assert(KQ % 2 == 0, "fragment double buffer needs an even number of groups per stage");
   constexpr int NMF = TM * TN;                         // gate/up MFMA pairs per group
@@ -352,6 +367,8 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   const int n_main = max(nk - S, 0);
   for (int kt = 0; kt < n_main; ++kt) step(kt, std::true_type{});
   for (int kt = n_main; kt < nk; ++kt) step(kt, std::false_type{});
+  };
+  if (p.off32 && n0 + BNn <= Kb) run(std::true_type{}); else run(std::false_type{});
 
   // k-groups: group g keeps token tiles i with i % KG == g and hands the others over through LDS
   if (KG > 1) {
@@ -1518,11 +1535,10 @@ constexpr int kDirect128 = 5, kDirect64 = 6, kDirect128Narrow = 7, kDirect64Narr
 constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
 
 static bool gemm1_direct(int variant) { return variant >= kGemm1Direct128; }
-// whether the tile with the weights in registers can address these matrices: the offsets of a row and of a token of its tile
-// have 32 bits
+// whether the offsets of a row and of a token of a tile have 32 bits, which the tiles with the weights in registers need
 static bool gemm1_direct_addresses(const Gemm1Params &p) {
   const uint64_t row_bytes = (uint64_t)p.d_model * 2u;
-  return (uint64_t)std::max(p.d_ffn, p.rc) * row_bytes >> 32 == 0 && (uint64_t)kGemm1[kGemm1Direct128].bm * row_bytes >> 32 == 0;
+  return (uint64_t)std::max({p.d_ffn, p.rc, 256}) * row_bytes >> 32 == 0;   // (256: the highest tile)
 }
 
 // Gate/up tiles by the cost of one round of 256 of them, relative to a round of the 128 x 256 tile (117 us at
@@ -1537,6 +1553,7 @@ constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 
 hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, hipStream_t s) {
   Gemm1Params p = p_in;
   p.block = std::min(p.block, p.T);                       // (one short block: tiles for the tokens that there are)
+  p.off32 = gemm1_direct_addresses(p);
   const int n_extent = p.k.k_max + p.rc;                  // longest list
   const bool ragged = p.k.per_block != nullptr;           // lists of unequal length
   const int base_extent = (p.k.n_heavy > 0 ? p.k.k_base : p.k.k_max) + p.rc;   // what all but the heavy blocks have
