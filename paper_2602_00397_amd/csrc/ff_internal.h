@@ -177,6 +177,7 @@ struct Gemm1Params {
   int32_t full_only, rem_bn;
   int32_t rem_cap = 0x7fffffff;   // with rem_bn: the launch starts no later than this position (where the main launch stopped)
   int32_t skip_heavy = 0;         // this launch leaves out the blocks of k.heavy
+  int32_t spread = 0;             // the tiles start their sums at different channels
   int32_t off32 = 0;              // rows' offsets into a matrix and into a tile of X have 32 bits
   KSpec k;
 };

@@ -49,73 +49,81 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
                                                       int d_model, int Nb, int r) {
   extern __shared__ double p_s[];          // SOFTMAX: Nb weights
   __shared__ double red[4][512];
-  __shared__ double red1[256];
+  __shared__ double red1[8];
   __shared__ double a_s[512];              // this workgroup's pooled channels
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int b = blockIdx.y;
   const int t0 = b * Nb;
   const int n = min(T, t0 + Nb) - t0;
+  const int c = blockIdx.x * 512 + lane * 8;
+  const bf16_t *xc = x + (size_t)t0 * d_model + min(c, d_model - 8);   // (channels past d_model: not used)
+  uint4 v[8];
+  auto load_rows = [&](int i) __attribute__((always_inline)) {     // past the end: the last row again, not added
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4 *>(xc + (size_t)min(i + 4 * u, n - 1) * d_model);
+  };
   if (SOFTMAX) {
+    // the first rows are on their way while the weights are formed
+    const double z0 = z[t0 + min(tid, n - 1)];
+    if (wave < n) load_rows(wave);
+    __builtin_amdgcn_sched_barrier(0);
+    // every wavefront reduces by lane exchanges, the four results go through LDS once (a tree over the workgroup had sixteen
+    // barriers: 700 tokens in blocks of 128, logits and pooling 18.2 us,
+    // this way, with the first rows requested above, 16.7)
     double m = -INFINITY;
-    for (int i = tid; i < n; i += 256) m = fmax(m, z[t0 + i]);
-    red1[tid] = m;
+    for (int i = tid; i < n; i += 256) m = fmax(m, i == tid ? z0 : z[t0 + i]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+    if (lane == 0) red1[wave] = m;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) red1[tid] = fmax(red1[tid], red1[tid + s]);
-      __syncthreads();
-    }
-    m = red1[0];
-    __syncthreads();
+    m = fmax(fmax(red1[0], red1[1]), fmax(red1[2], red1[3]));
     double part = 0.0;
     for (int i = tid; i < n; i += 256) {
-      const double e = exp(z[t0 + i] - m);
+      const double e = exp((i == tid ? z0 : z[t0 + i]) - m);
       p_s[i] = e;
       part += e;
     }
-    red1[tid] = part;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+    if (lane == 0) red1[4 + wave] = part;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) red1[tid] += red1[tid + s];
-      __syncthreads();
-    }
-    const double s = red1[0];
+    const double s = (red1[4] + red1[5]) + (red1[6] + red1[7]);
     for (int i = tid; i < n; i += 256) p_s[i] = p_s[i] / s;
     __syncthreads();
   }
-  const int c = blockIdx.x * 512 + lane * 8;
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (c < d_model) {
-    const bf16_t *xc = x + (size_t)t0 * d_model + c;
+  if (SOFTMAX) {
+    for (int i = wave; i < n; i += 32) {     // 8 token rows in flight, added in token order
+      if (i > wave) load_rows(i);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (i + 4 * u < n) {
+          double xv[8];
+          unpack8(v[u], xv);
+          const double w = p_s[i + 4 * u];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) acc[j] = fma(w, xv[j], acc[j]);
+        }
+    }
+  } else if (c < d_model) {
+    // (the mean: with the loop above, its conditions cost 1.2 us of 13.3 for 32 blocks)
     int i = wave;
-    for (; i + 28 < n; i += 32) {          // 8 token rows in flight, added in token order
-      uint4 v[8];
+    for (; i + 28 < n; i += 32) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4 *>(xc + (size_t)(i + 4 * u) * d_model);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         double xv[8];
         unpack8(v[u], xv);
-        if (SOFTMAX) {
-          const double w = p_s[i + 4 * u];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) acc[j] = fma(w, xv[j], acc[j]);
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[j] += xv[j];
-        }
+        for (int j = 0; j < 8; ++j) acc[j] += xv[j];
       }
     }
     for (; i < n; i += 4) {
       double xv[8];
       unpack8(*reinterpret_cast<const uint4 *>(xc + (size_t)i * d_model), xv);
-      if (SOFTMAX) {
-        const double w = p_s[i];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = fma(w, xv[j], acc[j]);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += xv[j];
-      }
+      for (int j = 0; j < 8; ++j) acc[j] += xv[j];
     }
   }
 #pragma unroll
