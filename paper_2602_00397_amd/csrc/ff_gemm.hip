@@ -278,15 +278,18 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   }
   // (p.spread: the workgroups walk the channels from different places)
   const int first = p.spread ? __builtin_amdgcn_readfirstlane((int)(blockIdx.x >> 3) * 5 % (p.d_model / BK)) : 0;
-  auto issue_one = [&](int kt, int i) __attribute__((always_inline)) {
-    const uint32_t st = lds0 + (uint32_t)(kt % S) * STAGE + (uint32_t)(wave + i * NW) * 1024u;
-    const int at = kt + first, k = at >= p.d_model / BK ? at - p.d_model / BK : at;
+  // slot: which stage of the ring (kt mod S)
+  auto issue_one = [&](int kt, int slot, int i) __attribute__((always_inline)) {
+    const uint32_t st = lds0 + (uint32_t)slot * STAGE + (uint32_t)(wave + i * NW) * 1024u;
+    const int at = kt + first;
+    int k = at >= p.d_model / BK ? at - p.d_model / BK : at;
+    asm("" : "+s"(k));                                 // (a scalar: the choice is not made lane by lane, offset by offset)
     if (FAST) gload_lds16_off(base[i], off[i] + (uint32_t)(k * BK * 2), st);
     else gload_lds16(src[i] + k * BK, st);
   };
   auto issue = [&](int kt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < L; ++i) issue_one(kt, i);
+    for (int i = 0; i < L; ++i) issue_one(kt, kt % S, i);
   };
   constexpr int KQ = BK / 16 / KG;                     // MFMA groups (16 k each) per stage and k-group
   static_assert(KQ % 2 == 0, "fragment double buffer needs an even number of groups per stage");
@@ -298,8 +301,8 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   constexpr int SLOTS = (NMF + EVERY - 1) / EVERY * PER;  // copy slots between the MFMAs of a group
   const int nk = p.d_model / BK;
   u32x4_t af[2][TM], bg[2][TN], bu[2][TN];
-  auto frags = [&](int kt, int kq, int buf) __attribute__((always_inline)) {
-    const uint8_t *cur = smem + (kt % S) * STAGE;
+  auto frags = [&](int slot, int kq, int buf) __attribute__((always_inline)) {
+    const uint8_t *cur = smem + slot * STAGE;
     const int q = 2 * (kgrp * KQ + kq) + half;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -316,7 +319,7 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   };
   // MFMA group kq of the current stage from fragment buffer kq & 1, with part `part` (of KQ) of
   // stage `st`'s copies issued in between when `load` is set
-  auto group = [&](int kq, int st, int part, bool load) __attribute__((always_inline)) {
+  auto group = [&](int kq, int st, int slot, int part, bool load) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -328,7 +331,7 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
           for (int r = 0; r < PER; ++r) {
             const int n = (i * TN + j) / EVERY * PER + r;
             if (n < LQ && part * LQ + n < L) {
-              if (load) issue_one(st, part * LQ + n);
+              if (load) issue_one(st, slot, part * LQ + n);
               __builtin_amdgcn_sched_barrier(0);
             }
           }
@@ -336,27 +339,30 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
       }
 #pragma unroll
     for (int n = SLOTS; n < LQ; ++n)
-      if (load && part * LQ + n < L) issue_one(st, part * LQ + n);
+      if (load && part * LQ + n < L) issue_one(st, slot, part * LQ + n);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // MAIN: stages kt+S-1 and kt+S both exist (no conditions in the loop body)
-  auto step = [&](int kt, auto main_tag) __attribute__((always_inline)) {
+  // MAIN: stages kt+S-1 and kt+S both exist (no conditions in the loop body).  slot = kt mod S, a constant in the main loop of
+  // rings of three, which is unrolled (1000 tokens of 4096/14336 in blocks of 128, K 7168: 127.7 -> 125.5 us; a ring of two
+  // has stages of 64 KB, beyond what an LDS address adds at once: 760 -> 765 for 4096 dense tokens).
+  auto step = [&](int kt, auto main_tag, auto slot_) __attribute__((always_inline)) {
     constexpr bool MAIN = decltype(main_tag)::value;
+    const int slot = slot_, next = (slot + 1) % S, prev = (slot + S - 1) % S;
     const bool la = MAIN || kt + S - 1 < nk;
     const bool lb = MAIN || kt + S < nk;
 #pragma unroll
     for (int kq = 0; kq < KQ - 1; ++kq) {
-      frags(kt, kq + 1, (kq + 1) & 1);
+      frags(slot, kq + 1, (kq + 1) & 1);
       __builtin_amdgcn_sched_barrier(0);
-      group(kq, kt + S - 1, kq + 1, la);
+      group(kq, kt + S - 1, prev, kq + 1, la);
     }
     if (MAIN || kt + 1 < nk) {
       // stage kt+1 must have landed; stages kt+2 .. kt+S-1 may still be in flight
       if (MAIN || kt + S - 1 < nk) wait_vm_barrier<(S - 2) * L>(); else wait_vm_barrier<0>();
-      frags(kt + 1, 0, 0);
+      frags(next, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    group(KQ - 1, kt + S, 0, lb);
+    group(KQ - 1, kt + S, slot, 0, lb);
   };
 #pragma unroll
   for (int s = 0; s < S - 1; ++s)
@@ -364,12 +370,21 @@ void ff_gemm1_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX) {
   if (S - 1 <= nk) wait_vm_barrier<(S - 2) * L>(); else wait_vm_barrier<0>();
   if (S - 1 < nk) {
 #pragma unroll
-    for (int i = 0; i < (LQ < L ? LQ : L); ++i) issue_one(S - 1, i);
+    for (int i = 0; i < (LQ < L ? LQ : L); ++i) issue_one(S - 1, S - 1, i);
   }
   frags(0, 0, 0);
   const int n_main = max(nk - S, 0);
-  for (int kt = 0; kt < n_main; ++kt) step(kt, std::true_type{});
-  for (int kt = n_main; kt < nk; ++kt) step(kt, std::false_type{});
+  int kt = 0;
+  if (S == 3) {
+    for (; kt + S <= n_main; kt += S) {
+      step(kt, std::true_type{}, std::integral_constant<int, 0>{});
+      step(kt + 1, std::true_type{}, std::integral_constant<int, 1>{});
+      step(kt + 2, std::true_type{}, std::integral_constant<int, 2>{});
+    }
+  } else {
+    for (; kt < n_main; ++kt) step(kt, std::true_type{}, kt % S);
+  }
+  for (; kt < nk; ++kt) step(kt, std::false_type{}, kt % S);
   };
   if (p.off32 && n0 + BNn <= Kb) run(std::true_type{}); else run(std::false_type{});
 
