@@ -1570,7 +1570,7 @@ constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 
 
 hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, hipStream_t s) {
   Gemm1Params p = p_in;
-  p.block = std::min(p.block, p.T);                       // (one short block: tiles for the tokens that there are)
+  if (p.idx != nullptr) p.block = std::min(p.block, p.T);   // (one short block: tiles for the tokens that there are)
   p.off32 = gemm1_direct_addresses(p);
   const int n_extent = p.k.k_max + p.rc;                  // longest list
   const bool ragged = p.k.per_block != nullptr;           // lists of unequal length
@@ -1722,7 +1722,7 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 // The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
 struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
-                                     {kDirect128Narrow, 0.72, 0.92, 9.0}, {kDirect64Narrow, 0.45, 0.9, 6.0},
+                                     {kDirect128Narrow, 0.8, 0.95, 9.0}, {kDirect64Narrow, 0.45, 1.1, 6.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
 static bool gemm2_direct(int variant) { return variant >= kDirect128 && variant <= kDirect64Narrow; }
 // Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
@@ -1792,7 +1792,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
   int pieces = nsplit > 1 ? (int)std::min<long>(nsplit, room) : 1;
   if (chosen) {
     // The tile, and into how many pieces every list is cut: the cheapest by the measured times above.  A cut adds one
-    // more launch and its partial sums written and read once (5 us + 0.25 per MB).  (A few much longer lists have a cut
+    // more launch and its partial sums written and read once (3 us + 0.3 per MB).  (A few much longer lists have a cut
     // of their own, below, that leaves the other blocks' sums alone.)  In us, whole lists on the tiles with both operands in
     // LDS against this choice: 4096/14336, K 7168: 64 blocks of 128 456 -> 378, one of 100 tokens 91 -> 28; K 3584, 64
     // blocks of 64 172 -> 145; 2048/8192, K 4096, 700 tokens 58 -> 32; 3584/18944, K 10419, 128 blocks 1220 -> 1005; dense
@@ -1821,7 +1821,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
         const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
         double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * g.full);
         if (busy > 0.0) cost += g.fixed + steps * (g.idle + (g.full - g.idle) * busy);
-        if (n > 1) cost += 5.0 + (double)n * (double)per_piece / 4.0e6;
+        if (n > 1) cost += 3.0 + (double)n * (double)per_piece / 3.3e6;
         if (heavy_cut) {
           const long heavy = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;
           const long free_pieces = std::max<long>(1, std::min<long>(kNumCU / heavy, kMaxFreePieces));

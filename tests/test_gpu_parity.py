@@ -703,10 +703,12 @@ def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
         assert all((g - o).abs().max().item() <= 1e-5 for g, o in zip(got, out[1, 0]))
 
 
-@pytest.mark.parametrize("d_model,d_ffn,n_tokens", [(1024, 1064, 9000), (2048, 4096, 300), (4096, 4096, 150), (256, 688, 256)])
+@pytest.mark.parametrize("d_model,d_ffn,n_tokens", [(1024, 1064, 9000), (2048, 4096, 300), (4096, 4096, 150), (2048, 4096, 60),
+                                                    (256, 344, 256)])
 def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
-    """Lists that hold every neuron are the identity list, with the compensator's rows behind it: calls for which the
-    down GEMM takes the 128 x 512 tile, the 64 x 256 and 64 x 512 tiles cut into pieces and the 64 x 256 tile, all with the weights in registers
+    """Lists that hold every neuron are the identity list, with the compensator's rows behind it: calls for which the down
+    GEMM takes the 128 x 512 tile, (the second: a tile with both operands in LDS), the 64 x 512 and the 64 x 256 tile cut into
+    pieces and the 64 x 256 tile whole, with the weights in registers
     (csrc/ff_launch_checks.hip holds that choice)."""
     c = Case(W.Shape("keepall", d_model, d_ffn, n_tokens, 256, 8, 24))
     ks = [d_ffn] * c.n_blocks
