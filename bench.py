@@ -543,7 +543,7 @@ def main():
             "mlp": (shp.r_pred * shp.d_ffn * 2.0 + nB * (((dm + 511) // 512) * shp.r_pred + shp.d_ffn) * 8.0)
                    / (stages["mlp"] * 1e-3) / 1e9,
         },
-        "roofline": {"bound": "mfma", "kernel": "ff_gemm1_kernel (gathered gate/up GEMM + SiLU*up)",
+        "roofline": {"bound": "mfma", "kernel": "ff_gemm1_direct_kernel (gathered gate/up GEMM + SiLU*up)",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS, "traffic": measured_traffic(args.config),
                      "launch_ms": g1_ms, "flops_per_launch": g1_flops},
