@@ -76,9 +76,9 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void *p) {
 // Per-block neuron count: either one value for all blocks or a device array.
 constexpr int kMaxHeavy = 8;
 struct KSpec {
-  const int32_t *per_block;  // device, [n_blocks], or nullptr
-  int32_t uniform;           // used when per_block == nullptr
-  int32_t k_max;             // host-known maximum over blocks
+  const int32_t *per_block = nullptr;  // device, [n_blocks], or nullptr
+  int32_t uniform = 0;                 // used when per_block == nullptr
+  int32_t k_max = 0;                   // host-known maximum over blocks
   // Scheduling hints for lists of unequal length (host-known; never needed for correctness):
   // k_base = the most common K; heavy[0 .. n_heavy) = the blocks with K > k_base when there
   // are at most kMaxHeavy of them (the "first and last block dense" pattern), else n_heavy = 0

@@ -44,11 +44,14 @@ extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) {
 constexpr int kLds = 160 * 1024;
 static int32_t g_idx[1];      // stands for a list: the launchers only ask whether there is one
 
+// n_heavy: how many blocks have k_heavy positions instead of k; -1: lengths that only the device knows, k bounds them (merged
+// lists)
 struct Shape { int T, block, d_model, d_ffn, rc, k, k_heavy, n_heavy; };
 
 static KSpec lists(const Shape &s, int n_blocks) {
   KSpec k;
   k.uniform = k.k_max = k.k_base = s.k;
+  if (s.n_heavy < 0) k.per_block = g_idx;
   if (s.n_heavy > 0 && s.k_heavy > s.k && n_blocks > s.n_heavy) {
     k.per_block = g_idx;
     k.k_max = s.k_heavy;
@@ -93,7 +96,7 @@ static hipError_t gemm2(const Shape &s, bool list, const DownOptions &o, bool ro
 static void check_gemm1(const Shape &s) {
   for (int variant = -1; variant < ff_gemm1_num_variants(); ++variant)
     for (int split = -1; split <= 1; ++split)
-      for (int list = s.n_heavy > 0; list < 2; ++list) {
+      for (int list = s.n_heavy != 0; list < 2; ++list) {
         const hipError_t e = gemm1(s, list, variant, split, -1);
         CHECK(e == hipSuccess && !g_log.empty(), "T %d block %d K %d tile %d split %d", s.T, s.block, s.k, variant, split);
         for (const Launch &l : g_log) {
@@ -185,7 +188,7 @@ static void check_gemm2_row_sources() {
       for (int dm : {256, 2048, 4096})
         for (int df : {14336, 65536})
           for (int k : {100, 7168, 14336})
-            for (int heavy : {0, 2})
+            for (int heavy : {-1, 0, 2})
               for (int row_mode = 1; row_mode <= 3; ++row_mode)
                 for (int nsplit : {-1, 0, 3}) {
                   const Shape s = {T, block, dm, df, 32, k, df, heavy};
@@ -250,7 +253,7 @@ int main() {
       for (int dm : {256, 2048, 4096})
         for (int k : {33, 96, 160, 1000, 3584, 7168})
           for (int rc : {0, 32, 64})
-            check_gemm1({T, block, dm, 14336, rc, k, 14336, (T + block - 1) / block > 2 ? 2 : 0});
+            for (int heavy : {-1, 0, 2}) check_gemm1({T, block, dm, 14336, rc, k, 14336, heavy});
   check_gemm1_addresses();
   check_gemm2_addresses();
   check_gemm2_routes();
