@@ -1645,11 +1645,13 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
   // a remainder that may start on any multiple of 32 would leave that to nobody where a list ends on one.)
   if ((chosen ? split != 0 : split > 0) && (rem > 0 || ragged) && n_extent >= v.bn && v.bn >= (chosen ? 128 : 64) && variant != kRemainderVariant) {
     const int n_full = base_extent / v.bn;
-    const int per_cu = g_lds_limit / v.lds > 0 ? (g_lds_limit / v.lds > 2 ? 2 : g_lds_limit / v.lds) : 1;
-    const int slots = kNumCU * per_cu;
+    // One workgroup per CU, whatever its LDS would allow: every tile chosen here has eight wavefronts of more than 128
+    // registers.  Rounds are those of the busiest XCD.  (With two workgroups per CU where LDS has room for two, which the tiles
+    // with the weights in registers leave, and rounds over the whole chip, gate/up us -> this: 64-token blocks of 4096/14336, 4096
+    // tokens, K 7168 626 -> 595, K 5120 478 -> 452, 2103 tokens, K 3584 238 -> 208; 2048/8192, 2785 tokens, K 4096 160 -> 139;
+    // 128-token blocks of 4096/14336, 2795 tokens, K 7168 339 -> 324.  Of 90 calls that it changes the least favoured: 423 -> 430.)
     const long vb = (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
-    const long rounds_all = (vb * (n_full + 1) + slots - 1) / slots;
-    const long rounds_full = (vb * n_full + slots - 1) / slots;
+    const long rounds_all = xcd_rounds(vb, n_full + 1), rounds_full = xcd_rounds(vb, n_full);
     do_split = split > 0 || (rounds_full < rounds_all && 2 * (base_extent % v.bn) <= v.bn);
   }
   const int heavy = p.k.n_heavy;

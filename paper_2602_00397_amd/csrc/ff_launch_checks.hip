@@ -127,6 +127,20 @@ static void check_gemm1_addresses() {
   }
 }
 
+// Gate/up: positions beyond the last full tile get a launch of their own where the tile that they would need starts a further
+// round of workgroups, one per CU; not where it fits into the last one.
+static void check_gemm1_splits() {
+  struct { Shape s; size_t launches; unsigned rem_grid; } calls[] = {
+      {{4096, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 64}, {{4096, 64, 4096, 14336, 64, 5120, 0, 0}, 2, 64},   // 7 and 5 whole rounds
+      {{2126, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 40}, {{3000, 64, 2048, 8192, 64, 4096, 0, 0}, 2, 48},    // by the busiest XCD's count
+      {{4096, 64, 4096, 14336, 64, 3584, 0, 0}, 1, 0},  {{3000, 64, 4096, 14336, 64, 7168, 0, 0}, 1, 0},    // 3.5 and 5.1 rounds
+      {{8192, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 128}};
+  for (const auto &c : calls) {
+    CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && g_log.size() == c.launches, "T %d block %d K %d: %zu launches", c.s.T, c.s.block, c.s.k, g_log.size());
+    if (c.launches > 1 && g_log.size() > 1) CHECK(g_log[1].g1.rem_bn == 256 && g_log[1].grid == c.rem_grid, "T %d K %d: grid %u", c.s.T, c.s.k, g_log[1].grid);
+  }
+}
+
 // Down: the tiles with the weights in registers (5 to 8) form 32-bit offsets into W_down and H.  Where those do not
 // reach, the library takes another tile and a forced one is an error, cut along the list or not.
 static void check_gemm2_addresses() {
@@ -255,6 +269,7 @@ int main() {
           for (int rc : {0, 32, 64})
             for (int heavy : {-1, 0, 2}) check_gemm1({T, block, dm, 14336, rc, k, 14336, heavy});
   check_gemm1_addresses();
+  check_gemm1_splits();
   check_gemm2_addresses();
   check_gemm2_routes();
   check_gemm2_row_sources();
