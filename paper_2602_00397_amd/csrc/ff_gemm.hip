@@ -1629,8 +1629,12 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     p.n_blocks = (p.T + v.bm - 1) / v.bm;
   }
   // One or two blocks: tiles in step ask for the same channels of all their rows at once, which lie a power of two apart as a
-  // rule.  From different places on (one block of 4096/14336, K 7168: 30 tokens 33.8 -> 31.6 us, 100 40.7 -> 39.7; 2 blocks of 128
-  // 57.2 -> 54.7; six blocks of 2048/8192 37.3 -> 39.8, 300 dense tokens of 3584/18944 113.6 -> 143.1: they share rows).
+  // rule, and how much that costs depends on where the matrices lie in memory.  From different places on, 4096/14336, list of
+  // 14193, 30 tokens: 57.6 -> 47.4 us in one process, 45.5 -> 46.0 in another; 256 tokens in two blocks, K 10752, 80.0 -> 74.8 and
+  // 74.8 -> 74.6 (at worst: two merged lists of 3584/18944, 141 -> 147).  More blocks share rows, and lose: three blocks of
+  // 3584/18944, K 9472, 66.9 -> 84.9, four of 4096/14336, K 10752, 124 -> 155, five 121 -> 169.  (A start by the tile's position,
+  // the same for all blocks, is as good with one block, gains nothing with two and still loses from three on.  The tiles with the
+  // weights in registers do not have it.)
   p.spread = p.idx != nullptr && p.block <= v.bm && p.n_blocks <= 2;
   Gemm1Params q = p;
   q.full_only = 0;
