@@ -80,8 +80,8 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
   }
   const int ch0 = wave * steps * 64;                             // this wavefront's first channel
   const int n = max(0, min(p.d_model - ch0, steps * 64)) / 64;   // its steps
-  const int pitch = steps * 128;                                 // bytes per token in LDS
-  uint8_t *xs = smem + (size_t)wave * nt * pitch;
+  const int pitch = n * 128;                                     // bytes per token in LDS
+  uint8_t *xs = smem + (size_t)nt * min(ch0, p.d_model) * 2;
   const int nc = n * 8;                                          // 16-byte chunks per token
   for (int t = 0; t < nt; ++t)
     for (int c0 = 0; c0 < nc; c0 += 64)
@@ -282,10 +282,10 @@ void ff_gemv2_kernel(GemvParams p) {
 
 int g_gemv_lds_raised = 0;
 
-// gemv1: steps of 64 channels per wavefront, and LDS for nt tokens
+// gemv1: steps of 64 channels per wavefront (the last ones may have fewer), and LDS for nt tokens
 int gemv1_steps(int d_model) { return (d_model / 64 + kGemv1Waves - 1) / kGemv1Waves; }
 size_t gemv1_lds(int nt, int d_model) {
-  const size_t x = (size_t)kGemv1Waves * nt * gemv1_steps(d_model) * 128;
+  const size_t x = (size_t)nt * d_model * 2;
   return x > kGemv1Red ? x : kGemv1Red;
 }
 

@@ -1,5 +1,5 @@
-// Checks of the GEMM launchers' choices (and of top-K's bucket map), without a GPU: this program is linked with the launchers' object file and defines
-// hipLaunchKernel itself, so every launch is recorded instead of made.  Swept over shapes, list lengths and options, every
+// Checks of the GEMM launchers' choices, of the few-token path's limits and of top-K's bucket map, without a GPU: this program
+// is linked with the launchers' object files and defines hipLaunchKernel itself, so every launch is recorded instead of made.  Swept over shapes, list lengths and options, every
 // launch must fit what its kernel assumes.  Exit code 0 = all hold.
 #include <math.h>
 #include <stdio.h>
@@ -17,19 +17,32 @@ struct Launch {
   size_t lds;
   Gemm1Params g1;
   Gemm2Params g2;
+  GemvParams gv;
 };
 static std::vector<Launch> g_log;
 static int g_fail = 0, g_calls = 0;
-static bool g_down = false;   // which GEMM's launches are being recorded
+static bool g_down = false, g_few = false;   // whose launches are being recorded
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
-  Launch l = {fn, grid.x, block.x, lds, {}, {}};
-  if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
+  Launch l = {fn, grid.x, block.x, lds, {}, {}, {}};
+  if (g_few) memcpy(static_cast<void *>(&l.gv), args[0], sizeof(l.gv));
+  else if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
   else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
   g_log.push_back(l);
   return hipSuccess;
 }
 extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+// (what a launch with <<< >>> hands to hipLaunchKernel)
+static struct { dim3 grid, block; size_t lds; hipStream_t stream; } g_config;
+extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  g_config = {grid, block, lds, stream};
+  return hipSuccess;
+}
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *stream) {
+  *grid = g_config.grid; *block = g_config.block; *lds = g_config.lds; *stream = g_config.stream;
+  return hipSuccess;
+}
 
 #define CHECK(cond, ...)                                  \
   do {                                                    \
@@ -235,6 +248,24 @@ static void check_gemm2_room() {
     }
 }
 
+// Few tokens: the path takes a call wherever its tokens, as they are, fit into LDS.
+static void check_few_tokens() {
+  g_few = true;
+  for (int nt = 1; nt <= kGemvMaxTokens + 1; ++nt)
+    for (int dm = 128; dm <= 90112; dm += 128) {
+      const bool fits = nt <= kGemvMaxTokens && (size_t)nt * dm * 2 <= kLds;
+      CHECK(ff_gemv_eligible(nt, nt, dm, kLds) == fits, "%d tokens of %d", nt, dm);
+      GemvParams p = {};
+      p.T = p.block = nt; p.n_blocks = 1; p.d_model = dm; p.d_ffn = p.k_stride = 4096; p.idx = g_idx; p.part = g_room;
+      p.k.uniform = p.k.k_max = p.k.k_base = 2048;
+      g_log.clear();
+      ++g_calls;
+      CHECK((ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess) == fits && g_log.size() == (fits ? 2 : 0), "%d tokens of %d: %zu launches", nt, dm, g_log.size());
+      for (const Launch &l : g_log) CHECK(l.lds <= kLds && l.grid > 0, "%d tokens of %d", nt, dm);
+    }
+  g_few = false;
+}
+
 // Top-K's bucket map: monotone over the scores, and scores spread evenly over their range fill the buckets evenly, however
 // narrow the range is against the scores' size and however small or large they are.  (A bucket of more than TOPK_CAND keys
 // sends the whole block to eight passes over its scores.)
@@ -274,6 +305,7 @@ int main() {
   check_gemm2_routes();
   check_gemm2_row_sources();
   check_gemm2_room();
+  check_few_tokens();
   check_topk_map();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);
   return g_fail != 0;
