@@ -20,10 +20,10 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
-constexpr int kGemv1Waves = 4, kGemvWaves = 8;   // wavefronts per workgroup of gemv1 and gemv2
+constexpr int kGemvWaves = 8;      // wavefronts per workgroup of gemv2
 constexpr int kGemv1Pos = 16;      // list positions per workgroup of gemv1
 constexpr int kGemv2Cols = 128;    // output columns per workgroup of gemv2
-constexpr int kGemv1Red = kGemv1Waves * 16 * 16 * 4;  // bytes of gemv1's reduction
+constexpr int kGemv1Red = 16 * 16 * 4;  // bytes of gemv1's reduction, per wavefront
 
 __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
@@ -48,12 +48,13 @@ __device__ __forceinline__ float gv_act(int act, float g) {
 // and the 16 up rows; they are loaded by fours of lanes and exchanged as in the gate/up GEMM (lane by lane, as the operand wants
 // them, the address unit made it 54.9 us for a dense token of 4096/14336).  The block's tokens go through LDS, each
 // wavefront its own channels, 16-byte chunks swizzled by the token; the tokens repeat past the last one.
-// Bound by HBM.  Few wavefronts, few steps of each on their way and small workgroups: what counts is that workgroups start and
-// end next to each other (a dense token: 8 wavefronts with 4 steps 54.5 us, with 2 steps 52.6, 4 wavefronts with 2 steps 46.7).
-// With multiply-adds, a wavefront per position, it took 44 us and 23.5 on a list of 7168 (now 22.8), 19.5 for five tokens on
-// 4096 positions of 2048/8192 (now 12.3), 24.3 for eight (12.7) and 73.6 for eight with a list each (60.5).
+// Bound by HBM.  Few steps of each wavefront on their way and small workgroups: what counts is that workgroups start and
+// end next to each other (a dense token, 8 wavefronts: with 4 steps 54.5 us, with 2 52.6).  How many wavefronts: gemv1_waves.
+// With multiply-adds, a wavefront per position, a dense token of 4096/14336 took 44.5 us (now 45.5), one on a list of 7168 23.2
+// (22.6), one on 4096 positions of 8192/28672 86.1 (87.5), five tokens on 4096 positions of 2048/8192 19.5 (12.3).
 // grid (groups of 16 positions, n_blocks), LDS = gemv1_lds.
-__global__ __launch_bounds__(kGemv1Waves * 64) __attribute__((amdgpu_waves_per_eu(6)))
+template <int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : 6)))
 void ff_gemv1_kernel(GemvParams p, int steps) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -67,7 +68,7 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
   const int pos0 = blockIdx.x * kGemv1Pos;
   // (the counters of the next kernel's column groups start at zero)
   if (blockIdx.x == 0)
-    for (int i = tid; i < p.d_model / kGemv2Cols; i += kGemv1Waves * 64) p.counter[b * (p.d_model / kGemv2Cols) + i] = 0;
+    for (int i = tid; i < p.d_model / kGemv2Cols; i += NW * 64) p.counter[b * (p.d_model / kGemv2Cols) + i] = 0;
   if (pos0 >= (ntot + 31) / 32 * 32) return;
   // load j of a step: chunk (lane mod 4) + 4 (lane / 32) of row j + 4 (lane / 4 mod 8), gate rows in front of the up rows
   // (positions past the list's end: the last one's rows again; H is written as zero there)
@@ -138,12 +139,12 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
   }
   __syncthreads();
   const int pp = tid & 15, t = tid >> 4;                         // position and token of this thread
-  static_assert(kGemv1Waves * 64 >= 16 * kGemvMaxTokens, "a thread for every output");
+  static_assert(NW * 64 >= 16 * kGemvMaxTokens, "a thread for every output");
   if (t >= nt) return;
   const int at = ((pp & 3) + 4 * (pp >> 3)) * 16 + 8 * ((pp >> 2) & 1) + t;
   float g = 0.0f, u = 0.0f;
 #pragma unroll
-  for (int v = 0; v < kGemv1Waves; ++v) {
+  for (int v = 0; v < NW; ++v) {
     g += red[v * 256 + at];
     u += red[v * 256 + 128 + at];
   }
@@ -282,11 +283,27 @@ void ff_gemv2_kernel(GemvParams p) {
 
 int g_gemv_lds_raised = 0;
 
+// gemv1: its wavefronts per workgroup.  One workgroup's channels are a chain of loads, steps / wavefronts long, and a CU wants
+// some sixteen wavefronts with loads on their way.  Four where the groups of 16 positions give it those; eight where there is
+// about one workgroup per CU or LDS holds no more of them, sixteen where there are half as many or LDS holds one; eight again
+// for long rows in so many workgroups that these follow each other, sixteen for the longest.  One token, us with 4 / 8 / 16:
+// 4096/14336, K 1434 15.1 / 11.5 / 10.4, K 3584 15.7 / 14.4 / 15.2, K 7168 22.6 / 23.9 / 24.1, dense 46.4 / 45.5 / 49.2;
+// 2048/8192, K 2048 9.9 / 8.3 / 8.2, K 4096 11.9 / 11.7 / 13.5; 3584/18944, K 4736 17.2 / 18.1 / 20.2, dense 54.0 / 51.2 / 57.4;
+// 8192/4096, K 2048 25.2 / 18.5 / 16.6; 16384/16384, dense 276 / 266 / 211; 1024/4096, K 1024 7.1 / 6.7 / 7.3.  Eight tokens:
+// 3584/18944, K 9472 34.7 / 29.9 / 32.8; 8192/28672, K 14336 135 / 99 / 101.
+int gemv1_waves(long groups, int nt, int d_model, int lds_limit) {
+  constexpr int kCU = 256;
+  const int steps = d_model / 64, per_cu = lds_limit / (nt * d_model * 2);
+  if (groups <= kCU * 9 / 16) return steps >= 48 ? 16 : 8;
+  if (groups <= kCU * 9 / 8) return per_cu <= 1 ? 16 : 8;
+  if (groups > (long)per_cu * kCU || (groups > 3 * kCU && steps >= 48)) return per_cu <= 1 || steps >= 192 ? 16 : 8;
+  return 4;
+}
 // gemv1: steps of 64 channels per wavefront (the last ones may have fewer), and LDS for nt tokens
-int gemv1_steps(int d_model) { return (d_model / 64 + kGemv1Waves - 1) / kGemv1Waves; }
-size_t gemv1_lds(int nt, int d_model) {
-  const size_t x = (size_t)nt * d_model * 2;
-  return x > kGemv1Red ? x : kGemv1Red;
+int gemv1_steps(int nw, int d_model) { return (d_model / 64 + nw - 1) / nw; }
+size_t gemv1_lds(int nw, int nt, int d_model) {
+  const size_t x = (size_t)nt * d_model * 2, red = (size_t)nw * kGemv1Red;
+  return x > red ? x : red;
 }
 
 }  // namespace
@@ -298,16 +315,17 @@ size_t ff_gemv_part_bytes(int n_tokens, int d_model) {
 
 bool ff_gemv_eligible(int n_tokens, int block, int d_model, int lds_limit) {
   const int nt = block < n_tokens ? block : n_tokens;
-  return n_tokens <= kGemvMaxTokens && gemv1_lds(nt, d_model) <= (size_t)lds_limit;
+  return n_tokens <= kGemvMaxTokens && gemv1_lds(16, nt, d_model) <= (size_t)lds_limit;
 }
 
 hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, Profiler *prof) {
   GemvParams p = p_in;
   if (!ff_gemv_eligible(p.T, p.block, p.d_model, lds_limit)) return hipErrorInvalidValue;
   if (!g_gemv_lds_raised) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(ff_gemv1_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-    if (e != hipSuccess) return e;
+    for (const auto k : {ff_gemv1_kernel<4>, ff_gemv1_kernel<8>, ff_gemv1_kernel<16>}) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
+      if (e != hipSuccess) return e;
+    }
     g_gemv_lds_raised = 1;
   }
   const int nt = p.block < p.T ? p.block : p.T;
@@ -318,9 +336,12 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   int nc = 512 / (cols * p.n_blocks);
   if (nc > (groups + kGemvWaves - 1) / kGemvWaves) nc = (groups + kGemvWaves - 1) / kGemvWaves;
   p.n_chunks = nc < 1 ? 1 : (nc > kGemvChunks ? kGemvChunks : nc);
+  const int groups1 = (n_extent + 31) / 32 * (32 / kGemv1Pos);
+  const int nw = gemv1_waves((long)groups1 * p.n_blocks, nt, p.d_model, lds_limit);
+  const auto fn = nw == 4 ? ff_gemv1_kernel<4> : nw == 8 ? ff_gemv1_kernel<8> : ff_gemv1_kernel<16>;
   prof_begin(prof, FF_STAGE_GEMM1, s);
-  hipLaunchKernelGGL(ff_gemv1_kernel, dim3((n_extent + 31) / 32 * (32 / kGemv1Pos), p.n_blocks), dim3(kGemv1Waves * 64),
-                     gemv1_lds(nt, p.d_model), s, p, gemv1_steps(p.d_model));
+  hipLaunchKernelGGL(fn, dim3(groups1, p.n_blocks), dim3(nw * 64),
+                     gemv1_lds(nw, nt, p.d_model), s, p, gemv1_steps(nw, p.d_model));
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_GEMM2, s);
   hipLaunchKernelGGL(ff_gemv2_kernel, dim3(cols, p.n_chunks, p.n_blocks), dim3(kGemvWaves * 64), 0, s, p);

@@ -262,7 +262,20 @@ static void check_few_tokens() {
       ++g_calls;
       CHECK((ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess) == fits && g_log.size() == (fits ? 2 : 0), "%d tokens of %d: %zu launches", nt, dm, g_log.size());
       for (const Launch &l : g_log) CHECK(l.lds <= kLds && l.grid > 0, "%d tokens of %d", nt, dm);
+      // (the first kernel's copy of the tokens, then 1 KB of sums per wavefront)
+      if (fits) CHECK(g_log[0].lds >= (size_t)nt * dm * 2 && g_log[0].lds >= g_log[0].threads * 16, "%d tokens of %d", nt, dm);
     }
+  // wavefronts of the first kernel by its workgroups, one for 16 positions of a list, and the rows' length
+  struct { int T, block, dm, k; unsigned threads; } calls[] = {
+      {1, 1, 4096, 7168, 256}, {1, 1, 4096, 3584, 512}, {1, 1, 4096, 1434, 1024}, {1, 1, 4096, 14336, 512}, {1, 1, 2048, 2048, 512},
+      {1, 1, 2048, 8192, 256}, {8, 8, 4096, 7168, 256}, {8, 8, 4096, 14336, 512}, {8, 8, 8192, 14336, 1024}, {4, 1, 8192, 2048, 256}};
+  for (const auto &c : calls) {
+    GemvParams p = {};
+    p.T = c.T; p.block = c.block; p.n_blocks = (c.T + c.block - 1) / c.block; p.d_model = c.dm; p.d_ffn = p.k_stride = 18944; p.idx = g_idx; p.part = g_room;
+    p.k.uniform = p.k.k_max = p.k.k_base = c.k;
+    g_log.clear();
+    CHECK(ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess && g_log[0].threads == c.threads, "%d tokens of %d, K %d: %u threads", c.T, c.dm, c.k, g_log[0].threads);
+  }
   g_few = false;
 }
 

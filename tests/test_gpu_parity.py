@@ -941,7 +941,8 @@ def test_few_token_calls_take_the_gemv_path(ctx):
 
 @pytest.mark.parametrize("d_model,d_ffn,T,block,rc,ks", [
     (128, 640, 1, 1, 0, [1]), (128, 640, 8, 8, 8, [31]), (640, 4096, 7, 3, 24, [33, 4000, 15]), (640, 4096, 8, 2, 0, [512, 513, 2048, 16]),
-    (1152, 1064, 5, 5, 40, [1064]), (4224, 4096, 3, 1, 64, [2049, 4096, 256]), (8192, 520, 8, 8, 8, [96]), (11648, 264, 7, 7, 8, [96])])
+    (1152, 1064, 5, 5, 40, [1064]), (4224, 4096, 3, 1, 64, [2049, 4096, 256]), (8192, 520, 8, 8, 8, [96]), (11648, 264, 7, 7, 8, [96]),
+    (3200, 520, 5, 5, 8, [96])])
 def test_few_token_kernels_at_their_edges(ctx, d_model, d_ffn, T, block, rc, ks):
     """The few-token kernels where their splits end: channels that some wavefronts have none or fewer of, lists of one position,
     ends inside and on groups of 16 and 32 and chunks that hold nothing for the shorter lists, compensator units in a group
