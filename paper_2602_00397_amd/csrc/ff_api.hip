@@ -352,6 +352,9 @@ ff_status run_ffn(ff_ctx *ctx, const ff_shape &s, const Layout &L, const void *x
     a.k.uniform = L.mu_kmax;
     a.k.k_max = L.mu_kmax;
     a.k.k_base = L.mu_kmax;
+    double none = 1.0;
+    for (int i = 0; i < std::min(L.merge_g, (s.n_tokens + block - 1) / block); ++i) none *= 1.0 - (double)ks.k_max / s.d_ffn;
+    a.k.k_likely = (int)((1.0 - none) * s.d_ffn);
   }
   FF_HIP(ctx, ff_launch_gemm1(a, g1v, g1split, ctx->gemm1_heavy_tiles, ctx->stream));
   prof_end(&ctx->prof, ctx->stream);

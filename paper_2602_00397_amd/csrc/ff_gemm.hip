@@ -1564,7 +1564,10 @@ static bool gemm1_direct_addresses(const Gemm1Params &p) {
 // more than their share (0.52, 0.33 and 0.24 for a half, a quarter and an eighth), but fill the chip where a call has
 // too few big tiles or would start a last round with a few of them.
 struct Gemm1Cost { int variant; double round; };
-constexpr Gemm1Cost kGemm1Short[] = {{kGemm1Direct64, 0.74}, {5, 0.90}, {kRemainderVariant, 0.27}, {10, 0.22}};   // blocks up to 64 tokens
+// One block of up to 64 tokens shares its rows with nobody: a round of 128 x 128 tiles whose lower half is empty waits for fewer
+// bytes than two of 64 x 64 (3584/18944, list of all neurons, 61 tokens 74.5 -> 65.5 us, 30 tokens 69.8 -> 60.9; where one round
+// of the smaller tiles is enough they win by far: K 14208 59.0 against 40.9; of merged lists only the likely length says so).
+constexpr Gemm1Cost kGemm1Short[] = {{kGemm1Direct64, 0.74}, {5, 0.90}, {0, 0.52}, {kRemainderVariant, 0.27}, {10, 0.22}};   // blocks up to 64 tokens
 constexpr Gemm1Cost kGemm1Mid[] = {{0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};                      // up to 255
 constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};           // 256 and more, and without a list
 
@@ -1582,10 +1585,11 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     // one block, 64 x 256 92 -> 64 x 32 26; K 3584, ten blocks of 64, 64 x 256 114 -> 64 x 64 100; 1100 tokens in blocks
     // of 256, 256 x 128 216 -> 128 x 128 178; dense 3584/18944, 300 tokens, 256 x 128 190 -> 128 x 128 110.)
     const Gemm1Cost *tab = p.block > 64 ? (p.block >= 256 ? kGemm1Long : kGemm1Mid) : kGemm1Short;
-    const int n_tab = p.block >= 256 || p.block <= 64 ? 4 : 3;
+    const int n_tab = p.block >= 256 ? 4 : p.block > 64 ? 3 : 5;
     double best = 0.0;
     for (int i = 0; i < n_tab; ++i) {
       const Variant &v = kGemm1[tab[i].variant];
+      if (tab == kGemm1Short && tab[i].variant == 0 && (p.n_blocks > 1 || (p.k.k_likely > 0 && p.k.k_likely + p.rc <= kNumCU * kGemm1[kRemainderVariant].bn))) continue;
       if (v.lds > g_lds_limit || (gemm1_direct(tab[i].variant) && !gemm1_direct_addresses(p))) continue;
       // without a list the blocks mean nothing: token tiles of this variant's height
       const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);

@@ -86,6 +86,8 @@ struct KSpec {
   int32_t k_base = 0;
   int32_t n_heavy = 0;
   int32_t heavy[kMaxHeavy] = {0, 0, 0, 0, 0, 0, 0, 0};
+  // lengths that only the device knows (merged lists; k_max bounds them): about how long they are, were the lists independent
+  int32_t k_likely = 0;
 };
 
 // Stage timing hooks: begin/end bracket a stage's launches with events when the

@@ -58,13 +58,13 @@ constexpr int kLds = 160 * 1024;
 static int32_t g_idx[1];      // stands for a list: the launchers only ask whether there is one
 
 // n_heavy: how many blocks have k_heavy positions instead of k; -1: lengths that only the device knows, k bounds them (merged
-// lists)
+// lists), about k_heavy
 struct Shape { int T, block, d_model, d_ffn, rc, k, k_heavy, n_heavy; };
 
 static KSpec lists(const Shape &s, int n_blocks) {
   KSpec k;
   k.uniform = k.k_max = k.k_base = s.k;
-  if (s.n_heavy < 0) k.per_block = g_idx;
+  if (s.n_heavy < 0) { k.per_block = g_idx; k.k_likely = s.k_heavy; }
   if (s.n_heavy > 0 && s.k_heavy > s.k && n_blocks > s.n_heavy) {
     k.per_block = g_idx;
     k.k_max = s.k_heavy;
@@ -152,6 +152,22 @@ static void check_gemm1_splits() {
     CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && g_log.size() == c.launches, "T %d block %d K %d: %zu launches", c.s.T, c.s.block, c.s.k, g_log.size());
     if (c.launches > 1 && g_log.size() > 1) CHECK(g_log[1].g1.rem_bn == 256 && g_log[1].grid == c.rem_grid, "T %d K %d: grid %u", c.s.T, c.s.k, g_log[1].grid);
   }
+}
+
+// Gate/up: tiles of one short block, which reads every row of its list once: two rounds of 64 x 64 tiles lose to one of 128 x 128
+// that is half empty; not so with a second block.
+static void check_gemm1_short_block() {
+  struct { Shape s; int variant; } calls[] = {
+      {{61, 128, 3584, 18944, 64, 18944, 17760, -1}, 0}, {{61, 128, 3584, 18944, 64, 18944, 14208, -1}, 7}, {{64, 64, 3584, 18944, 64, 18944, 0, 0}, 0}, {{40, 64, 128, 17024, 64, 17000, 0, 0}, 0},
+      {{61, 128, 128, 17024, 64, 17024, 16896, -1}, 0}, {{64, 64, 3584, 18944, 64, 9472, 0, 0}, 7},  {{30, 128, 4096, 14336, 64, 7168, 0, 0}, 10}};
+  for (const auto &c : calls) {
+    gemm1(c.s, true, c.variant, 0, -1);
+    const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
+    CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && g_log.size() == 1 && g_log[0].fn == fn, "T %d block %d K %d", c.s.T, c.s.block, c.s.k);
+  }
+  gemm1({64, 64, 3584, 18944, 64, 18944, 0, 0}, true, 0, 0, -1);
+  const void *fn = g_log[0].fn;
+  CHECK(gemm1({122, 64, 3584, 18944, 64, 18944, 0, 0}, true, -1, -1, -1) == hipSuccess && g_log[0].fn != fn, "two blocks");
 }
 
 // Down: the tiles with the weights in registers (5 to 8) form 32-bit offsets into W_down and H.  Where those do not
@@ -314,6 +330,7 @@ int main() {
             for (int heavy : {-1, 0, 2}) check_gemm1({T, block, dm, 14336, rc, k, 14336, heavy});
   check_gemm1_addresses();
   check_gemm1_splits();
+  check_gemm1_short_block();
   check_gemm2_addresses();
   check_gemm2_routes();
   check_gemm2_row_sources();

@@ -366,6 +366,20 @@ def test_short_blocks_run_on_merged_lists(ctx, block):
         ctx.set_option("merge_blocks", -1)
 
 
+@pytest.mark.parametrize("n_tokens,block,k", [(61, 16, 12000), (40, 64, 17000), (9, 64, 16448)])
+def test_one_short_block_with_long_lists(ctx, n_tokens, block, k):
+    """At most 64 tokens that are one block, or one group of merged lists, of more positions than 256 tiles of 64 have: 128 x 128
+    gate/up tiles whose lower half is empty (csrc/ff_launch_checks.hip holds that choice).  Oracle, bars, bf16 storage."""
+    c = Case(W.Shape("shortlong", 128, 17024, n_tokens, block, 8, 64))
+    ks = [k] * c.n_blocks
+    ref = c.oracle_layer(ks)
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=17024)
+    _assert_indices(idx, ref.indices, ks)
+    ctx.ensure_workspace(c.shape, k)
+    ctx._ws.fill_(0xFF)
+    _check_both(c, ctx, idx, ks, ref.y, f"{n_tokens} tokens in blocks of {block}, K {k}")
+
+
 def test_sizes_at_the_documented_limits(ctx):
     """The largest values the header allows: 4096 compensator units (far more than selected neurons), the
     most blocks a call takes (16384 one-token blocks), and 4096-token blocks with softmax pooling plus a
