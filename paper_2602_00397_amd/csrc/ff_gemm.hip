@@ -586,7 +586,7 @@ void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX)
   constexpr int NF = 4 * MT, TR0 = NF / 2;
   constexpr int NEWER = 2 + 2 * ((NF - D) / MT) + (NBUF - 2) * (8 + LA);
   static_assert(NBUF < S && (NF - D) % MT == 0, "ring of X");
-  // END: the steps behind the unrolled loop.  Their loads would be for steps that do not exist, so there are none, and the wait
+  // END: the steps behind the unrolled loop of three buffers.  Their loads would be for steps that do not exist, so there are none, and the wait
   // for X cannot count on them.
   auto step = [&](int kt, auto buf_tag, auto fast_tag, auto end_tag) __attribute__((always_inline)) {
     constexpr int buf = decltype(buf_tag)::value;
@@ -640,8 +640,10 @@ void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX)
       step(kt + 1, b1, fast_tag, std::false_type{});
       if (NBUF == 3) step(kt + 2, b2, fast_tag, std::false_type{});
     }
-    if (kt < nk) step(kt, b0, fast_tag, std::true_type{});
-    if (NBUF == 3 && kt + 1 < nk) step(kt + 1, b1, fast_tag, std::true_type{});
+    if constexpr (NBUF == 3) {                         // (d_model is a multiple of 128: two buffers leave no step over)
+      if (kt < nk) step(kt, b0, fast_tag, std::true_type{});
+      if (kt + 1 < nk) step(kt + 1, b1, fast_tag, std::true_type{});
+    }
   };
   if (fast) run(std::true_type{}); else run(std::false_type{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies requested past the end
