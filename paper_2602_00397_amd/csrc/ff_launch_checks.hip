@@ -224,6 +224,28 @@ static void check_gemm2_routes() {
   }
 }
 
+// Down: the longest list whose row-id table fits beside the ring of a tile with the weights in registers.  One position more and
+// the tile is refused where it is forced, and not taken where it is not.
+static void check_gemm2_row_table() {
+  const int tiles[][2] = {{5, 49152}, {6, 65536}, {7, 16384}, {8, 49152}};
+  for (const auto &t : tiles)
+    for (int more = 0; more <= (t[1] < 65536); ++more)
+      for (int T : {24, 300, 4096}) {
+        const Shape s = {T, 128, 1024, 65528, 8, t[1] - 8 + more, 0, 0};
+        DownOptions o;
+        o.variant = t[0];
+        o.nsplit = o.ksplit = 0;
+        const hipError_t e = gemm2(s, true, o, true);
+        CHECK((e == hipSuccess) == !more && g_log.empty() == (more != 0), "tile %d, list of %d", t[0], s.k + 8);
+        for (const Launch &l : g_log) CHECK(l.lds <= kLds, "tile %d, list of %d", t[0], s.k + 8);
+        const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
+        if (more) { Shape s0 = s; --s0.k; gemm2(s0, true, o, true); fn = g_log[0].fn; }
+        o.variant = -1;
+        CHECK(gemm2(s, true, o, true) == hipSuccess && !g_log.empty(), "T %d, list of %d", T, s.k + 8);
+        for (const Launch &l : g_log) CHECK(l.lds <= kLds && !(more && l.fn == fn), "T %d, list of %d", T, s.k + 8);
+      }
+}
+
 // A forced source of the row ids: the library chooses among the tiles that have it, and refuses only where none does.
 static void check_gemm2_row_sources() {
   for (int T : {9, 300, 2000, 8192, 20000})
@@ -333,6 +355,7 @@ int main() {
   check_gemm1_short_block();
   check_gemm2_addresses();
   check_gemm2_routes();
+  check_gemm2_row_table();
   check_gemm2_row_sources();
   check_gemm2_room();
   check_few_tokens();

@@ -731,11 +731,12 @@ def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
     _check_both(c, ctx, idx, ks, ref.y, f"all of {d_ffn} neurons and 24 units, {n_tokens} tokens")
 
 
-@pytest.mark.parametrize("variant", [5, 6])
-def test_largest_row_ids_and_longest_lists_in_registers(ctx, variant):
+@pytest.mark.parametrize("variant,longest", [(5, 49152), (6, 65536), (7, 16384), (8, 49152)])
+def test_largest_row_ids_and_longest_lists_in_registers(ctx, variant, longest):
     """The row-id table of the tiles with the weights in registers: ids up to 65535 (the last compensator unit behind 65528
-    neurons), and the longest list whose table fits beside the 128 x 512 tile (49152 positions); one unit more, or one
-    neuron more on the list, and a forced tile is an error while the library takes another."""
+    neurons), and the longest list whose table fits beside the tile (two bytes a position in what the ring leaves of
+    160 KB, or all 65528 neurons); one unit more, or one neuron more on the list, and a forced tile is an error while the
+    library takes another."""
     def layer(d_ffn, ks):
         c = Case(W.Shape("regid", 128, d_ffn, 60, 24, 8, 8))
         ref = c.oracle_layer(ks)
@@ -750,12 +751,13 @@ def test_largest_row_ids_and_longest_lists_in_registers(ctx, variant):
             for option in ("gemm2_variant", "gemm2_nsplit", "gemm2_ksplit"):
                 ctx.set_option(option, -1)
 
-    layer(65528, [40000, 49144, 17])
+    k = min(40000, longest - 8)
+    layer(65528, [k, longest - 8, 17])
     with pytest.raises(B.FFError):
-        layer(65536, [40000, 100, 17])
-    if variant == 5:
+        layer(65536, [k, 100, 17])
+    if longest < 65536:
         with pytest.raises(B.FFError):
-            layer(65528, [40000, 49145, 17])
+            layer(65528, [k, longest - 7, 17])
 
 
 @pytest.mark.parametrize("n_tokens,block", [(256, 64), (6, 4)])
@@ -1102,12 +1104,13 @@ def test_exact_ties_on_gpu(ctx):
     assert idx.cpu().tolist() == [[0, 1, 2, 3, 4]] * 2
 
 
-@pytest.mark.parametrize("df", [2048, 20480, 28672, 40960, 147456])
+@pytest.mark.parametrize("df", [2048, 8184, 14328, 20480, 28672, 40960, 147456])
 def test_heavy_ties_at_the_threshold(ctx, df):
     # 1500 scores are exactly equal and the K-th largest lies among them: the bucket holding the
-    # threshold overflows the ranking step and the radix path decides.  The sizes take the five
-    # top-K kernels: keys in 16, 24 or 32 registers per thread; beyond 32768 neurons the general kernel,
-    # with a class byte per key in LDS for the compaction and, at 147456, without it.
+    # threshold overflows the ranking step and the radix path decides.  The sizes take the seven
+    # top-K kernels: scores in 4, 8, 16, 24 or 32 registers per thread (8 and 16 also keep masks of the scores above
+    # the threshold's bucket); beyond 32768 neurons the general kernel, with a class byte per score in LDS for the
+    # compaction and, at 147456, without it.
     dm, T, r = 128, 64, 8
     ic = W.integer_valued_case(dm, df, T, r, seed=11)
     w2 = ic["w2"].copy()
@@ -1134,7 +1137,31 @@ def test_heavy_ties_at_the_threshold(ctx, df):
     _assert_indices(idx, [O.select_topk(s2[b], ks[b]) for b in range(2)], ks)
 
 
-@pytest.mark.parametrize("df", [2048, 20480, 28672, 40960])
+@pytest.mark.parametrize("df", [2048, 8184, 14328, 20480, 28672, 40960])
+@pytest.mark.parametrize("n_tied", [40, 300, 700])
+def test_ties_over_many_rows_at_the_threshold(ctx, df, n_tied):
+    """Equal scores all over the block, in most wavefronts' rows, the K-th largest among them: too few to overflow their
+    bucket (1024), ranked by every wavefront for itself (40, with what else is equal at most 64 up to 14328 neurons) or by the
+    whole workgroup; the lowest indices among them are kept."""
+    dm, T, r = 128, 64, 8
+    ic = W.integer_valued_case(dm, df, T, r, seed=23)
+    w2 = ic["w2"].copy()
+    at = np.unique(np.linspace(3, df - 2, n_tied).astype(int))
+    w2[:, at] = w2[:, at[:1]]
+    s = O.predictor_scores(_f32(ic["x"]), None, _f32(ic["w1"]), _f32(w2))
+    shape = B.Shape(dm, df, T, 64, r, 0)
+    xd, w1d, w2d = (B.to_device_bf16(a, DEV) for a in (ic["x"], ic["w1"], w2))
+    pred = B.Predictor(None, w1d.data_ptr(), w2d.data_ptr())
+    ctx.ensure_workspace(shape, df)
+    n_above, n_equal = int((s > s[at[0]]).sum()), int((s == s[at[0]]).sum())
+    assert n_tied <= n_equal <= 1024 and (n_equal <= 64 or n_tied > 40 or df > 14328)
+    for k in sorted({max(1, n_above), n_above + 1, n_above + n_tied // 2, min(df, n_above + n_tied), min(df, n_above + n_tied + 1)}):
+        idx = torch.empty((1, k), dtype=torch.int32, device=DEV)
+        ctx.predict(shape, xd, pred, [k], k, idx, None)
+        np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
+
+
+@pytest.mark.parametrize("df", [2048, 8184, 14328, 20480, 28672, 40960])
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -110, 2.0 ** 80])
 def test_scores_that_fp32_cannot_tell_apart(ctx, df, scale):
     """The bucket map of the top-K kernels works on fp32 roundings: scores 2^26 + 0 .. 255 (fp32 steps of 8 there), and the
@@ -1157,7 +1184,7 @@ def test_scores_that_fp32_cannot_tell_apart(ctx, df, scale):
         np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
 
 
-@pytest.mark.parametrize("df", [2048, 20480, 28672, 40960])
+@pytest.mark.parametrize("df", [2048, 8184, 14328, 20480, 28672, 40960])
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -130, 2.0 ** 80])
 def test_scores_in_a_narrow_range(ctx, df, scale):
     """Scores 2^26 + 0 .. 65535, few of them equal: a range of 2^-10 of their size, which top-K cuts into buckets in fp64."""
@@ -1177,12 +1204,12 @@ def test_scores_in_a_narrow_range(ctx, df, scale):
         np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
 
 
-@pytest.mark.parametrize("df", [2048, 40960])
+@pytest.mark.parametrize("df", [2048, 8184, 14328, 20480, 28672, 40960])
 def test_scores_that_are_not_finite_still_give_a_valid_list(ctx, df):
     """Scores are expected to be finite.  If they are not (an infinity among the hidden states makes
     every score of its block NaN or infinite), the list written is still exactly K distinct, ascending,
     in-range indices with a -1 tail, and nothing is written past the row; the other block is unaffected.
-    2048 neurons take the register kernel, 40960 the general one."""
+    The kernels with scores in 4 to 32 registers, and the general one."""
     dm, T, r = 128, 128, 8
     ic = W.integer_valued_case(dm, df, T, r, seed=3)
     x_bits = ic["x"].copy()
