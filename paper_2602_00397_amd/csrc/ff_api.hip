@@ -331,6 +331,7 @@ ff_status run_ffn(ff_ctx *ctx, const ff_shape &s, const Layout &L, const void *x
   a.n_blocks = (s.n_tokens + block - 1) / block;
   a.rc = rc; a.comp_act = comp ? comp->act : FF_ACT_SILU; a.k_stride = k_stride; a.hs = L.hs;
   a.k = ks;
+  int k_likely = 0;
   prof_begin(&ctx->prof, FF_STAGE_GEMM1, ctx->stream);
   if (merge && L.merge_g > 1 && indices != nullptr) {
     // the lists of every merge_g neighbouring blocks become one list over 128 tokens; both GEMMs then
@@ -352,11 +353,11 @@ ff_status run_ffn(ff_ctx *ctx, const ff_shape &s, const Layout &L, const void *x
     a.k.uniform = L.mu_kmax;
     a.k.k_max = L.mu_kmax;
     a.k.k_base = L.mu_kmax;
-    double none = 1.0;
+    double none = 1.0;   // (were the lists independent)
     for (int i = 0; i < std::min(L.merge_g, (s.n_tokens + block - 1) / block); ++i) none *= 1.0 - (double)ks.k_max / s.d_ffn;
-    a.k.k_likely = (int)((1.0 - none) * s.d_ffn);
+    k_likely = (int)((1.0 - none) * s.d_ffn);
   }
-  FF_HIP(ctx, ff_launch_gemm1(a, g1v, g1split, ctx->gemm1_heavy_tiles, ctx->stream));
+  FF_HIP(ctx, ff_launch_gemm1(a, g1v, g1split, ctx->gemm1_heavy_tiles, k_likely, ctx->stream));
   prof_end(&ctx->prof, ctx->stream);
   Gemm2Params g;
   g.h = a.h;

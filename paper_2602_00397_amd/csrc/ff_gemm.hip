@@ -1573,7 +1573,7 @@ constexpr Gemm1Cost kGemm1Short[] = {{kGemm1Direct64, 0.74}, {5, 0.90}, {0, 0.52
 constexpr Gemm1Cost kGemm1Mid[] = {{0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};                      // up to 255
 constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};           // 256 and more, and without a list
 
-hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, hipStream_t s) {
+hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, int k_likely, hipStream_t s) {
   Gemm1Params p = p_in;
   if (p.idx != nullptr) p.block = std::min(p.block, p.T);   // (one short block: tiles for the tokens that there are)
   p.off32 = gemm1_direct_addresses(p);
@@ -1591,7 +1591,7 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     double best = 0.0;
     for (int i = 0; i < n_tab; ++i) {
       const Variant &v = kGemm1[tab[i].variant];
-      if (tab == kGemm1Short && tab[i].variant == 0 && (p.n_blocks > 1 || (p.k.k_likely > 0 && p.k.k_likely + p.rc <= kNumCU * kGemm1[kRemainderVariant].bn))) continue;
+      if (tab == kGemm1Short && tab[i].variant == 0 && (p.n_blocks > 1 || (k_likely > 0 && k_likely + p.rc <= kNumCU * kGemm1[kRemainderVariant].bn))) continue;
       if (v.lds > g_lds_limit || (gemm1_direct(tab[i].variant) && !gemm1_direct_addresses(p))) continue;
       // without a list the blocks mean nothing: token tiles of this variant's height
       const long V = p.idx == nullptr ? (p.T + v.bm - 1) / v.bm : (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);

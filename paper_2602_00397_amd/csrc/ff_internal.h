@@ -86,8 +86,6 @@ struct KSpec {
   int32_t k_base = 0;
   int32_t n_heavy = 0;
   int32_t heavy[kMaxHeavy] = {0, 0, 0, 0, 0, 0, 0, 0};
-  // lengths that only the device knows (merged lists; k_max bounds them): about how long they are, were the lists independent
-  int32_t k_likely = 0;
 };
 
 // Stage timing hooks: begin/end bracket a stage's launches with events when the
@@ -211,7 +209,8 @@ struct Gemm2Params {
 // there are such positions.
 // heavy_tiles: where the positions of a few much longer lists beyond the common length go when the launch is
 // split: -1 = the launcher decides, 0 = tiles of the main launch, 1 = a launch of their own with 128 x 64 tiles.
-hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int heavy_tiles, hipStream_t s);
+// k_likely: where only the device knows the lists' lengths (merged lists; p.k bounds them), about how long they are; else 0.
+hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int heavy_tiles, int k_likely, hipStream_t s);
 // split (gemm2): whether the last output-column tiles of every block go to a second launch with
 // half-width tiles when that saves a mostly empty last round of workgroups: -1 = the launcher decides
 // (never with a forced variant or lists of unequal length), 0 = never, 1 = whenever there are two

@@ -64,7 +64,7 @@ struct Shape { int T, block, d_model, d_ffn, rc, k, k_heavy, n_heavy; };
 static KSpec lists(const Shape &s, int n_blocks) {
   KSpec k;
   k.uniform = k.k_max = k.k_base = s.k;
-  if (s.n_heavy < 0) { k.per_block = g_idx; k.k_likely = s.k_heavy; }
+  if (s.n_heavy < 0) k.per_block = g_idx;
   if (s.n_heavy > 0 && s.k_heavy > s.k && n_blocks > s.n_heavy) {
     k.per_block = g_idx;
     k.k_max = s.k_heavy;
@@ -82,7 +82,7 @@ static hipError_t gemm1(const Shape &s, bool list, int variant, int split, int h
   g_log.clear();
   g_down = false;
   ++g_calls;
-  return ff_launch_gemm1(p, variant, split, heavy_tiles, nullptr);
+  return ff_launch_gemm1(p, variant, split, heavy_tiles, s.n_heavy < 0 ? s.k_heavy : 0, nullptr);
 }
 struct DownOptions { int variant = -1, split = -1, row_mode = -1, ksplit = -1, nsplit = -1; };
 static float g_room[1];       // stands for the workspace's room for partial sums: never touched
