@@ -353,9 +353,10 @@ ff_status run_ffn(ff_ctx *ctx, const ff_shape &s, const Layout &L, const void *x
     a.k.uniform = L.mu_kmax;
     a.k.k_max = L.mu_kmax;
     a.k.k_base = L.mu_kmax;
-    double none = 1.0;   // (were the lists independent)
-    for (int i = 0; i < std::min(L.merge_g, (s.n_tokens + block - 1) / block); ++i) none *= 1.0 - (double)ks.k_max / s.d_ffn;
-    k_likely = (int)((1.0 - none) * s.d_ffn);
+    // (predicted lists overlap: g of them hold what some 1 + (g - 1) / 2 independent ones would, at half of the neurons each 0.69
+    // of all for two, 0.85 for four and 0.94 for eight)
+    const int g = std::min(L.merge_g, (s.n_tokens + block - 1) / block);
+    k_likely = (int)((1.0 - std::pow(1.0 - (double)ks.k_max / s.d_ffn, 0.5 * (g + 1))) * s.d_ffn);
   }
   FF_HIP(ctx, ff_launch_gemm1(a, g1v, g1split, ctx->gemm1_heavy_tiles, k_likely, ctx->stream));
   prof_end(&ctx->prof, ctx->stream);

@@ -1538,10 +1538,10 @@ static hipError_t launch_variant(const Variant &v, const void *fn, const void *p
 }
 
 // Rounds of workgroups (one per CU) that V x N tiles take on the busiest XCD under the mapping that
-// launch_variant will use.
-static long xcd_rounds(long V, long N) {
+// launch_variant will use, behind `first` tiles that all XCDs share.
+static long xcd_rounds(long V, long N, long first = 0) {
   const int xs = xcd_groups(V, N, Share{});   // (what is shared takes no grid of more rounds)
-  const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs));
+  const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N + (8 >> xs) - 1) / (8 >> xs)) + (first + 7) / 8;
   return (tiles + kNumCU / 8 - 1) / (kNumCU / 8);
 }
 
@@ -1660,8 +1660,14 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     // with the weights in registers leave, and rounds over the whole chip, gate/up us -> this: 64-token blocks of 4096/14336, 4096
     // tokens, K 7168 626 -> 595, K 5120 478 -> 452, 2103 tokens, K 3584 238 -> 208; 2048/8192, 2785 tokens, K 4096 160 -> 139;
     // 128-token blocks of 4096/14336, 2795 tokens, K 7168 339 -> 324.  Of 90 calls that it changes the least favoured: 423 -> 430.)
-    const long vb = (long)p.n_blocks * ((p.block + v.bm - 1) / v.bm);
-    const long rounds_all = xcd_rounds(vb, n_full + 1), rounds_full = xcd_rounds(vb, n_full);
+    // With a few longer lists the ends of those are tiles in front of the others (4096/14336, both ends dense, 1907 tokens in blocks
+    // of 64, K 10752, split without counting them 490 -> 505), or, with tiles of 128 tokens, a third launch that a split has to
+    // pay for too, so there the whole chip's count has to fall (2048/8192, 1845 tokens in blocks of 128, K 4096: 96 -> 112).
+    const long mt = (p.block + v.bm - 1) / v.bm, vb = (long)p.n_blocks * mt;
+    const bool third = ragged && v.bm >= kGemm1[kHeavySurplusVariant].bm;
+    const long ends = (long)p.k.n_heavy * mt * (n_extent / v.bn - n_full);
+    auto rounds = [&](long n) { return third ? (vb * n + kNumCU - 1) / kNumCU : xcd_rounds(vb, n, ends); };
+    const long rounds_all = rounds(n_full + 1), rounds_full = rounds(n_full);
     do_split = split > 0 || (rounds_full < rounds_all && 2 * (base_extent % v.bn) <= v.bn);
   }
   const int heavy = p.k.n_heavy;

@@ -147,6 +147,8 @@ static void check_gemm1_splits() {
       {{4096, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 64}, {{4096, 64, 4096, 14336, 64, 5120, 0, 0}, 2, 64},   // 7 and 5 whole rounds
       {{2126, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 40}, {{3000, 64, 2048, 8192, 64, 4096, 0, 0}, 2, 48},    // by the busiest XCD's count
       {{4096, 64, 4096, 14336, 64, 3584, 0, 0}, 1, 0},  {{3000, 64, 4096, 14336, 64, 7168, 0, 0}, 1, 0},    // 3.5 and 5.1 rounds
+      {{1845, 128, 2048, 8192, 32, 4096, 8192, 2}, 1, 0},  {{3732, 64, 2048, 8192, 32, 4096, 8192, 2}, 1, 0},    // two longer lists
+      {{1907, 64, 4096, 14336, 64, 10752, 14336, 2}, 1, 0},
       {{8192, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 128}};
   for (const auto &c : calls) {
     CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && g_log.size() == c.launches, "T %d block %d K %d: %zu launches", c.s.T, c.s.block, c.s.k, g_log.size());
