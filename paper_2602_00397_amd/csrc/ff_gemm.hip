@@ -1634,14 +1634,14 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     p.block = v.bm;
     p.n_blocks = (p.T + v.bm - 1) / v.bm;
   }
-  // One or two blocks: tiles in step ask for the same channels of all their rows at once, which lie a power of two apart as a
-  // rule, and how much that costs depends on where the matrices lie in memory.  From different places on, 4096/14336, list of
-  // 14193, 30 tokens: 57.6 -> 47.4 us in one process, 45.5 -> 46.0 in another; 256 tokens in two blocks, K 10752, 80.0 -> 74.8 and
-  // 74.8 -> 74.6 (at worst: two merged lists of 3584/18944, 141 -> 147).  More blocks share rows, and lose: three blocks of
-  // 3584/18944, K 9472, 66.9 -> 84.9, four of 4096/14336, K 10752, 124 -> 155, five 121 -> 169.  (A start by the tile's position,
-  // the same for all blocks, is as good with one block, gains nothing with two and still loses from three on.  The tiles with the
-  // weights in registers do not have it.)
-  p.spread = p.idx != nullptr && p.block <= v.bm && p.n_blocks <= 2;
+  // One or two blocks with rows a multiple of 4 KB apart: tiles in step ask for the same channels of all their rows at once, and
+  // how much that costs depends on where the matrices lie in memory.  From different places on, 4096/14336, list of 14193, 30
+  // tokens: 57.6 -> 47.4 us in one process, 45.5 -> 46.0 in another; 256 tokens in two blocks, K 10752, 80.0 -> 74.8 and 74.8 ->
+  // 74.6.  Other rows gain nothing, and two blocks lose where they share most rows (two merged lists of 3584/18944 139 -> 145); more
+  // blocks lose anyhow: three of 3584/18944, K 9472, 66.9 -> 84.9, four of 4096/14336, K 10752, 124 -> 155, five 121 -> 169.
+  // (A start by the tile's position, the same for all blocks, is as good with one block, gains nothing with two and still loses
+  // from three on.  The tiles with the weights in registers do not have it.)
+  p.spread = p.idx != nullptr && p.block <= v.bm && p.n_blocks <= 2 && p.d_model % 2048 == 0;
   Gemm1Params q = p;
   q.full_only = 0;
   q.rem_bn = 0;
