@@ -12,6 +12,8 @@
 // a fixed order, so results are reproducible.
 // The products are MFMAs with weight rows on one side and the tokens, repeated to fill an operand, on the
 // other: with multiply-adds the arithmetic of several tokens and its lane reductions took longer than the loads.
+#include <algorithm>
+
 #include "ff_internal.h"
 
 namespace {
@@ -331,10 +333,13 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   const int nt = p.block < p.T ? p.block : p.T;
   const int n_extent = p.k.k_max + p.rc;
   p.counter = reinterpret_cast<int32_t *>(p.part + (size_t)kGemvChunks * p.T * p.d_model);
-  // gemv2: two workgroups per CU, as far as each of their wavefronts has a group of 32 positions
+  // gemv2: two workgroups per CU where each of their wavefronts then has two groups of 32 positions, the number that it keeps on
+  // their way, else at most one: more chunks are more partial sums to add up (one token, two workgroups per CU with one group for
+  // a wavefront, us -> this: 2048/8192 dense 16.4 -> 13.2, K 4096 12.2 -> 9.9; 4096/14336, K 3584 12.2 -> 11.2; 3584/18944,
+  // K 4736, with two groups and 280 workgroups 13.6, this way 12.4)
   const int cols = p.d_model / kGemv2Cols, groups = (n_extent + 31) / 32;
-  int nc = 512 / (cols * p.n_blocks);
-  if (nc > (groups + kGemvWaves - 1) / kGemvWaves) nc = (groups + kGemvWaves - 1) / kGemvWaves;
+  const int most = 512 / (cols * p.n_blocks), full = (groups + 2 * kGemvWaves - 1) / (2 * kGemvWaves);
+  const int nc = most <= full ? most : std::min(full, 256 / (cols * p.n_blocks));
   p.n_chunks = nc < 1 ? 1 : (nc > kGemvChunks ? kGemvChunks : nc);
   const int groups1 = (n_extent + 31) / 32 * (32 / kGemv1Pos);
   const int nw = gemv1_waves((long)groups1 * p.n_blocks, nt, p.d_model, lds_limit);
