@@ -334,9 +334,9 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   const int n_extent = p.k.k_max + p.rc;
   p.counter = reinterpret_cast<int32_t *>(p.part + (size_t)kGemvChunks * p.T * p.d_model);
   // gemv2: two workgroups per CU where each of their wavefronts then has two groups of 32 positions, the number that it keeps on
-  // their way, else at most one: more chunks are more partial sums to add up (one token, two workgroups per CU with one group for
-  // a wavefront, us -> this: 2048/8192 dense 16.4 -> 13.2, K 4096 12.2 -> 9.9; 4096/14336, K 3584 12.2 -> 11.2; 3584/18944,
-  // K 4736, with two groups and 280 workgroups 13.6, this way 12.4)
+  // their way, else at most one: more chunks are more partial sums to add up.  One token, two workgroups per CU down to one group
+  // for a wavefront, us -> this: 2048/8192 dense 16.3 -> 13.1, K 4096 11.9 -> 9.9; 4096/14336, K 7168 15.7 -> 14.8, K 3584 12.1 ->
+  // 11.1; 3584/18944, K 4736 13.0 -> 12.3 (with two groups and 280 workgroups 13.6)
   const int cols = p.d_model / kGemv2Cols, groups = (n_extent + 31) / 32;
   const int most = 512 / (cols * p.n_blocks), full = (groups + 2 * kGemvWaves - 1) / (2 * kGemvWaves);
   const int nc = most <= full ? most : std::min(full, 256 / (cols * p.n_blocks));

@@ -24,7 +24,7 @@ static int g_fail = 0, g_calls = 0;
 static bool g_down = false, g_few = false;   // whose launches are being recorded
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
-  Launch l = {fn, grid.x, block.x, lds, {}, {}, {}};
+  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, {}};
   if (g_few) memcpy(static_cast<void *>(&l.gv), args[0], sizeof(l.gv));
   else if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
   else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
@@ -305,16 +305,20 @@ static void check_few_tokens() {
       // (the first kernel's copy of the tokens, then 1 KB of sums per wavefront)
       if (fits) CHECK(g_log[0].lds >= (size_t)nt * dm * 2 && g_log[0].lds >= g_log[0].threads * 16, "%d tokens of %d", nt, dm);
     }
-  // wavefronts of the first kernel by its workgroups, one for 16 positions of a list, and the rows' length
-  struct { int T, block, dm, k; unsigned threads; } calls[] = {
-      {1, 1, 4096, 7168, 256}, {1, 1, 4096, 3584, 512}, {1, 1, 4096, 1434, 1024}, {1, 1, 4096, 14336, 512}, {1, 1, 2048, 2048, 512},
-      {1, 1, 2048, 8192, 256}, {8, 8, 4096, 7168, 256}, {8, 8, 4096, 14336, 512}, {8, 8, 8192, 14336, 1024}, {4, 1, 8192, 2048, 256}};
+  // wavefronts of the first kernel by its workgroups, one for 16 positions of a list, and the rows' length; workgroups of the
+  // second: two per CU, else as many as have 512 positions each, up to one per CU
+  struct { int T, block, dm, k; unsigned threads, grid2; } calls[] = {
+      {1, 1, 4096, 7168, 256, 256}, {1, 1, 4096, 3584, 512, 224}, {1, 1, 4096, 1434, 1024, 96}, {1, 1, 4096, 14336, 512, 512},
+      {1, 1, 2048, 2048, 512, 64}, {1, 1, 2048, 8192, 256, 256}, {1, 1, 2048, 16385, 256, 512}, {1, 1, 3584, 4736, 256, 252},
+      {8, 8, 4096, 7168, 256, 256}, {8, 8, 4096, 14336, 512, 512}, {8, 8, 8192, 14336, 1024, 512}, {4, 1, 8192, 2048, 256, 512},
+      {8, 1, 16384, 2048, 1024, 1024}, {1, 1, 256, 18944, 256, 74}};
   for (const auto &c : calls) {
     GemvParams p = {};
     p.T = c.T; p.block = c.block; p.n_blocks = (c.T + c.block - 1) / c.block; p.d_model = c.dm; p.d_ffn = p.k_stride = 18944; p.idx = g_idx; p.part = g_room;
     p.k.uniform = p.k.k_max = p.k.k_base = c.k;
     g_log.clear();
-    CHECK(ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess && g_log[0].threads == c.threads, "%d tokens of %d, K %d: %u threads", c.T, c.dm, c.k, g_log[0].threads);
+    CHECK(ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess && g_log[0].threads == c.threads && g_log[1].grid == c.grid2, "%d tokens of %d, K %d: %u threads, then %u workgroups", c.T, c.dm, c.k,
+          g_log[0].threads, g_log[1].grid);
   }
   g_few = false;
 }
