@@ -137,23 +137,30 @@ struct TopkMap {
   bool none, fine;       // no buckets; buckets of the fp64 scores
   float lo, scale;
   double lo64, scale64;
-  __host__ __device__ __forceinline__ int bucket(float s) const { return clamp((int)((s - lo) * scale)); }
+  static __host__ __device__ __forceinline__ int bucket(float s, float lo, float scale) { return clamp((int)((s - lo) * scale)); }
+  __host__ __device__ __forceinline__ int bucket(float s) const { return bucket(s, lo, scale); }
   __host__ __device__ __forceinline__ int bucket64(double s) const { return clamp((int)((s - lo64) * scale64)); }
   static __host__ __device__ __forceinline__ int clamp(int b) { return b < 0 ? 0 : (b < TOPK_BUCKETS ? b : TOPK_BUCKETS - 1); }
 };
+// whether fp32 roundings between lo and hi are fine enough for the buckets (the limits keep the scale, and every product with it,
+// a finite number; false for a NaN), and the scale that cuts that range into them
+__host__ __device__ __forceinline__ bool topk_fp32_range(float lo, float hi) {
+  const float range = hi - lo;
+  return range > 1e-30f && fabsf(lo) < 1e30f && range < 1e30f && range >= fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-9f;
+}
+__host__ __device__ __forceinline__ float topk_fp32_scale(float lo, float hi) { return (float)TOPK_BUCKETS / (hi - lo); }
 // [lo, hi] encloses the scores
 __host__ __device__ __forceinline__ TopkMap topk_map(double lo, double hi) {
   TopkMap m = {};
   m.lo = (float)lo;
   m.lo64 = lo;
-  const float hi_f = (float)hi, range = hi_f - m.lo;
+  const float hi_f = (float)hi;
   const double range64 = hi - lo;
-  // (the limits keep every scale, and every product with it, a finite number)
   m.none = !(range64 > 1e-300 && range64 < 1e300);
-  m.fine = !(range > 1e-30f && fabsf(m.lo) < 1e30f && range < 1e30f && range >= fmaxf(fabsf(m.lo), fabsf(hi_f)) * 0x1p-9f);
+  m.fine = !topk_fp32_range(m.lo, hi_f);
   if (m.none) return m;
   if (m.fine) m.scale64 = (double)TOPK_BUCKETS / range64;
-  else m.scale = (float)TOPK_BUCKETS / range;
+  else m.scale = topk_fp32_scale(m.lo, hi_f);
   return m;
 }
 

@@ -5,6 +5,7 @@
 #include "ff_internal.h"
 
 #include <algorithm>
+#include <utility>
 
 namespace {
 
@@ -412,16 +413,101 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return dpp_add_step<0x143, 0xc>(v);   // lane 31 into rows 2 and 3
 }
 
+constexpr int TOPK_FEW = 16;   // candidates that are ranked by fours of lanes
+
 // LDS of the threshold search, shared by both top-K kernels
 struct TopkShared {
-  __align__(16) unsigned int hist[TOPK_BUCKETS];   // also the 256-bin histogram of the radix path
-  double cand[TOPK_CAND];
+  __align__(16) unsigned int no_bucket[64];        // in front of the histogram: what buckets -1 .. -64 count
+  unsigned int hist[TOPK_BUCKETS];                 // also the 256-bin histogram of the radix path
+  double cand[TOPK_CAND + TOPK_FEW];
   int wsum[16];
   unsigned int wtot[4];
   unsigned int sel_bin, sel_rem, n_cand;
   double theta;
-  int ties;
+  int ties, n_ties;
 };
+
+// The bucket that holds the K-th largest score, and which of its scores that is (sh.sel_bin, sh.sel_rem), from a full histogram.
+__device__ __forceinline__ void topk_find_bucket(TopkShared &sh, int K) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = scores in higher buckets
+  const uint4 h4 = *reinterpret_cast<const uint4 *>(&sh.hist[TOPK_BUCKETS - 4 - 4 * tid]);
+  const int h[4] = {(int)h4.w, (int)h4.z, (int)h4.y, (int)h4.x};
+  const int local = (h[0] + h[1]) + (h[2] + h[3]);
+  const int inc = wave_incl_scan(local);
+  if (lane == 63) sh.wsum[wave] = inc;
+  __syncthreads();
+  const int w = lane < 16 ? sh.wsum[lane] : 0;                // every wavefront scans the 16 totals itself
+  int above = __builtin_amdgcn_readlane(wave_incl_scan(w) - w, wave) + inc - local;
+  if (above < K && K <= above + local) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (above < K && K <= above + h[q]) { sh.sel_bin = (unsigned int)(TOPK_BUCKETS - 1 - (4 * tid + q)); sh.sel_rem = (unsigned int)(K - above); }
+      above += h[q];
+    }
+  }
+  __syncthreads();
+}
+
+// The need-th largest of the c candidates, how many of its equals are kept, and how many there are.  (sh.cand has NaN, which
+// compares with nothing, behind the last one: topk_pad, before the barrier that everybody's candidates need anyway.)
+__device__ __forceinline__ void topk_pad(TopkShared &sh, int c) {
+  if (threadIdx.x < TOPK_FEW) sh.cand[c + (int)threadIdx.x] = __longlong_as_double(0x7ff8000000000000ll);
+}
+__device__ __forceinline__ void topk_rank(TopkShared &sh, int c, int need, double &theta, int &ties_taken, int &n_ties) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  // rank of candidate i among the c; the need-th largest has n_gt < need <= n_gt + n_eq (all holders of its value agree)
+  auto rank = [&](double mine, int &n_gt, int &n_eq) __attribute__((always_inline)) {
+    n_gt = n_eq = 0;
+#pragma unroll 1
+    for (int j0 = 0; j0 < c; j0 += 8) {          // eight reads in flight (more than that spill)
+      double o[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) o[u] = sh.cand[j0 + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        n_gt += o[u] > mine;
+        n_eq += o[u] == mine;
+      }
+    }
+  };
+  int n_gt, n_eq;
+  if (c <= 64) {                                 // every wavefront finds it itself
+    double mine;
+    if (c <= TOPK_FEW) {                         // lanes 4 i .. 4 i + 3 hold candidate i against four of the others each
+      mine = sh.cand[lane >> 2];
+      int both = 0;
+#pragma unroll
+      for (int u = 0; u < TOPK_FEW / 4; ++u) {
+        const double o = sh.cand[(lane & 3) * (TOPK_FEW / 4) + u];
+        both += (o > mine ? 1 : 0) + (o == mine ? 65536 : 0);
+      }
+      both += __builtin_amdgcn_update_dpp(0, both, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
+      both += __builtin_amdgcn_update_dpp(0, both, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
+      n_gt = both & 0xffff;
+      n_eq = both >> 16;
+    } else {
+      mine = lane < c ? sh.cand[lane] : sh.cand[c];
+      rank(mine, n_gt, n_eq);
+    }
+    const int src = __ffsll((unsigned long long)__ballot(n_gt < need && need <= n_gt + n_eq)) - 1;
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(mine);
+    const unsigned int b0 = __builtin_amdgcn_readlane((unsigned int)bits, src), b1 = __builtin_amdgcn_readlane((unsigned int)(bits >> 32), src);
+    theta = __longlong_as_double((long long)(((unsigned long long)b1 << 32) | b0));
+    ties_taken = need - __builtin_amdgcn_readlane(n_gt, src);
+    n_ties = __builtin_amdgcn_readlane(n_eq, src);
+  } else {
+    if (tid < c) {
+      const double mine = sh.cand[tid];
+      rank(mine, n_gt, n_eq);
+      if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; sh.n_ties = n_eq; }
+    }
+    __syncthreads();
+    theta = sh.theta;
+    ties_taken = sh.ties;
+    n_ties = sh.n_ties;
+  }
+}
 
 // The K-th largest score theta and the number of scores equal to theta that are kept, found exactly by the 1024 threads of a
 // workgroup.  each(fn) calls fn(score, score rounded to fp32) once for every score the calling thread owns; gather(bucket_of,
@@ -429,9 +515,6 @@ struct TopkShared {
 // encloses the scores (it only shapes the bucket map); need_radix skips the buckets.  Scores are compared as numbers (-0 ==
 // +0), except where the radix path had to order them: it returns true, and theta as a key.  A chain of latencies, so: a
 // prefix sum whose 16 totals every wavefront scans itself, candidates that every wavefront ranks itself, no 64-bit keys.
-// (Against three barriers in the prefix sum, a ranking for all by one wavefront's threads, compaction in two rounds and rows
-// of keys for 16384 scores whatever their number, us between events: one block of 14336 scores 14.1 -> 12.8, blocks of 8192
-// 14.0 -> 10.2, of 688 13.3 -> 7.9, of 18944 19.4 -> 18.3, of 28672 25.5 -> 23.3.)
 // (Buckets of the fp32 roundings, against fp64 arithmetic on every score: one block of 14336 1.8 us less; scores whose range is
 // 2^-14 of their size, which fp32 has no steps for: 12.6 us in fp64 buckets, 30.2 on the radix path.)
 // On entry sh.hist is zero, sh.n_cand is 0 and a barrier has been passed.
@@ -446,62 +529,16 @@ __device__ __forceinline__ bool topk_threshold(TopkShared &sh, int K, double lo_
   auto by_buckets = [&](auto bucket_of) __attribute__((always_inline)) -> bool {
     each([&](double v, float s) { atomicAdd(&sh.hist[bucket_of(v, s)], 1u); });
     __syncthreads();
-    // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = scores in higher buckets
-    const uint4 h4 = *reinterpret_cast<const uint4 *>(&sh.hist[TOPK_BUCKETS - 4 - 4 * tid]);
-    const int h[4] = {(int)h4.w, (int)h4.z, (int)h4.y, (int)h4.x};
-    const int local = (h[0] + h[1]) + (h[2] + h[3]);
-    const int inc = wave_incl_scan(local);
-    if (lane == 63) sh.wsum[wave] = inc;
-    __syncthreads();
-    const int w = lane < 16 ? sh.wsum[lane] : 0;                // every wavefront scans the 16 totals itself
-    int above = __builtin_amdgcn_readlane(wave_incl_scan(w) - w, wave) + inc - local;
-    if (above < K && K <= above + local) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (above < K && K <= above + h[q]) { sh.sel_bin = (unsigned int)(TOPK_BUCKETS - 1 - (4 * tid + q)); sh.sel_rem = (unsigned int)(K - above); }
-        above += h[q];
-      }
-    }
-    __syncthreads();
+    topk_find_bucket(sh, K);
     const int tb = __builtin_amdgcn_readfirstlane((int)sh.sel_bin);
     const int need = __builtin_amdgcn_readfirstlane((int)sh.sel_rem);   // rank of theta inside bucket tb (1 = largest)
     const int c = __builtin_amdgcn_readfirstlane((int)sh.hist[tb]);
     if (c > TOPK_CAND) return false;              // uniform: every thread reads the same hist[tb]
+    topk_pad(sh, c);
     gather(bucket_of, tb, [&](double v) { sh.cand[atomicAdd(&sh.n_cand, 1u)] = v; });
     __syncthreads();
-    // rank of candidate i among the c; the need-th largest has n_gt < need <= n_gt + n_eq (all holders of its value agree)
-    auto rank = [&](double mine, int &n_gt, int &n_eq) __attribute__((always_inline)) {
-      n_gt = n_eq = 0;
-      for (int j0 = 0; j0 < c; j0 += 8) {          // eight reads in flight
-        double o[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) o[u] = sh.cand[min(j0 + u, c - 1)];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          n_gt += j0 + u < c && o[u] > mine;
-          n_eq += j0 + u < c && o[u] == mine;
-        }
-      }
-    };
-    int n_gt, n_eq;
-    if (c <= 64) {                                 // every wavefront finds it itself
-      const double mine = sh.cand[min(lane, c - 1)];
-      rank(mine, n_gt, n_eq);
-      const int src = __ffsll((unsigned long long)__ballot(lane < c && n_gt < need && need <= n_gt + n_eq)) - 1;
-      const unsigned long long bits = (unsigned long long)__double_as_longlong(mine);
-      const unsigned int b0 = __builtin_amdgcn_readlane((unsigned int)bits, src), b1 = __builtin_amdgcn_readlane((unsigned int)(bits >> 32), src);
-      theta = __longlong_as_double((long long)(((unsigned long long)b1 << 32) | b0));
-      ties_taken = need - __builtin_amdgcn_readlane(n_gt, src);
-    } else {
-      if (tid < c) {
-        const double mine = sh.cand[tid];
-        rank(mine, n_gt, n_eq);
-        if (n_gt < need && need <= n_gt + n_eq) { sh.theta = mine; sh.ties = need - n_gt; }
-      }
-      __syncthreads();
-      theta = sh.theta;
-      ties_taken = sh.ties;
-    }
+    int n_ties;
+    topk_rank(sh, c, need, theta, ties_taken, n_ties);
     return true;
   };
   // (the rare map's code out of the way: between the other's passes it made every call 0.5 to 1.4 us longer)
@@ -667,157 +704,233 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
   for (int i = K + tid; i < k_stride; i += 1024) out[i] = -1;
 }
 
-// min or max of a 32-bit value over the wavefront with data-parallel-primitive lane exchanges inside
-// the rows of 16 lanes (xor 1, xor 2, mirror in 8, mirror in 16) and four lane reads across the rows
-template <bool MAX, int CTRL>
-__device__ __forceinline__ unsigned int dpp_minmax_step(unsigned int v) {
-  const unsigned int o = (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
-  return MAX ? max(v, o) : min(v, o);
+// min over each row of 16 lanes, by data-parallel-primitive lane exchanges
+template <int CTRL>
+__device__ __forceinline__ unsigned int dpp_min_step(unsigned int v) {
+  return min(v, (unsigned int)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false));
 }
-template <bool MAX>
-__device__ __forceinline__ unsigned int wave_minmax_u32(unsigned int v) {
-  v = dpp_minmax_step<MAX, 0xB1>(v);    // quad_perm [1,0,3,2]
-  v = dpp_minmax_step<MAX, 0x4E>(v);    // quad_perm [2,3,0,1]
-  v = dpp_minmax_step<MAX, 0x141>(v);   // row_half_mirror
-  v = dpp_minmax_step<MAX, 0x140>(v);   // row_mirror
-  const unsigned int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
-  const unsigned int c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
-  return MAX ? max(max(a, b), max(c, d)) : min(min(a, b), min(c, d));
+__device__ __forceinline__ unsigned int row_min_u32(unsigned int v) {
+  v = dpp_min_step<0xB1>(v);    // quad_perm [1,0,3,2]
+  v = dpp_min_step<0x4E>(v);    // quad_perm [2,3,0,1]
+  v = dpp_min_step<0x141>(v);   // row_half_mirror
+  return dpp_min_step<0x140>(v);   // row_mirror
 }
 
 // The same selection for d_ffn <= 1024 * ROWS with every score in a register.  Wavefront w owns the consecutive indices
-// [64 w R, 64 (w + 1) R), R = ceil(d_ffn / 1024) rows of 64, so the scores are read with all loads in flight, no pass reads them
-// back from LDS, and the rank of a kept index among the kept ones is a scan over 16 per-wavefront totals plus counts over
-// earlier rows and lower lanes (ballots).
+// [64 w ROWS, 64 (w + 1) ROWS), read with all loads in flight, no pass reads them back, and the rank of a kept index among the
+// kept ones is a scan over 16 per-wavefront totals plus counts over earlier rows and lower lanes (ballots).
+// What binds it is the issue of vector instructions: with 16 wavefronts on four SIMDs one instruction per row of 64 scores costs
+// 16 cycles.  So: the range from the fp32 roundings, minimum and maximum of two rows an instruction; the bucket of a score is
+// kept beside it, for two compares per row in each later pass; an index past the end has a bucket below all others, where no
+// pass looks (slots in front of the histogram count them), so no pass asks whether an index is valid; scores are looked at
+// again only in rows that hold a candidate of the threshold's bucket.  (Kernel alone, back to back, us, with keys, valid
+// indices and buckets formed again in every pass -> this: one block of 688 5.8 -> 3.4, 4096 6.7 -> 4.0, 8192 7.8 -> 5.1, 14336
+// 11.6 -> 6.9, 18944 16.8 -> 9.0; 64 blocks of 14336 11.9 -> 7.7.  Of one block of 14336 a third is the scores' way to the CU.)
+// Whatever the roundings cannot order (a range too narrow or too wide for fp32, NaN or infinite scores, a bucket with too many
+// ties) goes through topk_threshold, as in the kernel above.
 template <int ROWS>
 __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restrict__ scores,
                                                            int32_t *__restrict__ indices, int d_ffn,
                                                            int k_stride, KSpec ks) {
   __shared__ TopkShared sh;
-  __shared__ unsigned int red_lo[16], red_hi[16];
+  __shared__ unsigned int red[32];      // every wavefront's ends of the score range
   __shared__ int2 cnt[16];              // scores above theta and equal to it, per wavefront
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = blockIdx.x;
   const double *sc = scores + (size_t)b * d_ffn;
   int32_t *out = indices + (size_t)b * k_stride;
-  int K = ks.per_block ? ks.per_block[b] : ks.uniform;
-  K = max(1, min(K, min(d_ffn, k_stride)));
-  const int R = (d_ffn + 1023) / 1024;
-  const int i0 = wave * R * 64 + lane;   // this thread's index in row 0
+  int i0 = wave * ROWS * 64 + lane;         // this thread's index in row 0
 
-  // An index past the end repeats the last score and is masked by `valid`.  The score range only
-  // shapes the bucket map, so bounds that enclose it are as good as the exact ends: the high words of
-  // the smallest and largest key, which cost 32-bit wavefront reductions.
+  // An index past the end repeats the last score, which leaves the range as it is.
   double v[ROWS];
-  // The fp32 roundings are kept beside them as far as the 128 registers of 1024 threads reach; 24 and 32 rows round each time
-  // (of a copy that the compiler cannot follow: it would keep the roundings, and the buckets, in scratch memory).
-  constexpr bool KEEP = ROWS <= 16;
-  float score[ROWS];
-  unsigned int lo_w = 0xffffffffu, hi_w = 0u;
-#pragma unroll
-  for (int u = 0; u < ROWS; ++u) v[u] = sc[min(i0 + u * 64, d_ffn - 1)];
-  *reinterpret_cast<uint4 *>(&sh.hist[4 * tid]) = make_uint4(0, 0, 0, 0);
-  if (tid == 0) sh.n_cand = 0;
 #pragma unroll
   for (int u = 0; u < ROWS; ++u) {
-    if (KEEP) score[u] = (float)v[u];
-    const unsigned int hw = (unsigned int)((unsigned long long)__double_as_longlong(v[u]) >> 32);
-    const unsigned int key = hw ^ ((unsigned int)((int)hw >> 31) | 0x80000000u);   // unsigned order = score order
-    lo_w = min(lo_w, key);
-    hi_w = max(hi_w, key);
+    v[u] = *reinterpret_cast<const double *>(reinterpret_cast<const char *>(sc) + (uint32_t)min(i0 + u * 64, d_ffn - 1) * 8u);
+    if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);
   }
-  auto valid = [&](int u) -> bool { return u < R && i0 + u * 64 < d_ffn; };
-  lo_w = wave_minmax_u32<false>(lo_w);
-  hi_w = wave_minmax_u32<true>(hi_w);
-  if (lane == 0) { red_lo[wave] = lo_w; red_hi[wave] = hi_w; }
-  __syncthreads();
-  lo_w = wave_minmax_u32<false>(red_lo[lane & 15]);
-  hi_w = wave_minmax_u32<true>(red_hi[lane & 15]);
-  const double lo_v = key_score((unsigned long long)lo_w << 32);
-  const double hi_v = key_score(((unsigned long long)hi_w << 32) | 0xffffffffull);
-  const bool need_radix = !(hi_v > lo_v);   // no ordered range to cut into buckets (not finite)
-  double theta = 0.0;
-  unsigned long long theta_key = 0;
-  int ties_taken;
+  int K = ks.per_block ? ks.per_block[b] : ks.uniform;
+  K = max(1, min(K, min(d_ffn, k_stride)));
   static_assert(TOPK_BUCKETS == 4 * 1024, "a thread clears and scans four buckets");
-  // A row's scores in higher buckets than the threshold's are above it, those in lower ones below; only rows that hold a
-  // candidate have to be compared with theta afterwards.  (One block of 14336 scores: 1.3 us less than comparing every score
-  // twice, of 8192 0.5 us; with few rows there is nothing to save, and more rows than 16 do not leave the registers.)
-  constexpr bool MASKS = ROWS == 8 || ROWS == 16;
-  unsigned long long m_gt[ROWS];
-  unsigned int open_rows = 0;
-  const bool by_key = topk_threshold(sh, K, lo_v, hi_v, need_radix,
-                                     [&](auto fn) __attribute__((always_inline)) {
+  *reinterpret_cast<uint4 *>(&sh.hist[4 * tid]) = make_uint4(0, 0, 0, 0);
+  if (tid == 0) sh.n_cand = 0;
+  int bk[ROWS];                          // roundings, then buckets
+  float lo = (float)v[0], hi = lo;
 #pragma unroll
-                                       for (int u = 0; u < ROWS; ++u)
-                                         if (valid(u)) {
-                                           double x = v[u];
-                                           if (!KEEP) asm volatile("" : "+v"(x));
-                                           fn(x, KEEP ? score[u] : (float)x);
-                                         }
-                                     },
-                                     [&](auto bucket_of, int tb, auto append) __attribute__((always_inline)) {
-#pragma unroll
-                                       for (int u = 0; u < ROWS; ++u) {
-                                         double x = v[u];
-                                         if (!KEEP) asm volatile("" : "+v"(x));
-                                         const int bk = bucket_of(x, KEEP ? score[u] : (float)x);
-                                         const bool is_cand = valid(u) && bk == tb;
-                                         if (MASKS) {
-                                           m_gt[u] = __ballot(valid(u) && bk > tb);
-                                           if (__ballot(is_cand)) open_rows |= 1u << u;
-                                         }
-                                         if (is_cand) append(x);
-                                       }
-                                     },
-                                     theta, theta_key, ties_taken);
-  // ordered compaction
-  auto below = [&](unsigned long long m) -> int {                             // set bits in lower lanes
-    return (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+  for (int u = 0; u < ROWS; ++u) {
+    const float r = (float)v[u];
+    bk[u] = __float_as_int(r);
+    if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    lo = __builtin_elementwise_minimum(lo, r);     // (these keep a NaN)
+    hi = __builtin_elementwise_maximum(hi, r);
+  }
+  asm("" : "+v"(i0));                   // (the rows' indices are formed again where they are used: no registers for them in between)
+  auto order = [](float x) __attribute__((always_inline)) -> unsigned int {     // unsigned order = score order, NaN at either end
+    const unsigned int u = __float_as_uint(x);
+    return u ^ ((unsigned int)((int)u >> 31) | 0x80000000u);
   };
-  auto compact = [&](auto above, auto equal) __attribute__((always_inline)) {
-    int n_gt = 0, n_eq = 0;
-#pragma unroll
-    for (int u = 0; u < ROWS; ++u)
-      if (MASKS ? (open_rows >> u) & 1u : u < R) {
-        const unsigned long long m = __ballot(valid(u) && above(v[u]));
-        if (MASKS) m_gt[u] = m;
-        else n_gt += __popcll(m);
-        n_eq += __popcll(__ballot(valid(u) && equal(v[u])));
-      }
-    if (MASKS) {
-#pragma unroll
-      for (int u = 0; u < ROWS; ++u) n_gt += __popcll(m_gt[u]);
-    }
+  auto value = [](unsigned int u) __attribute__((always_inline)) -> float { return __uint_as_float((u >> 31) ? (u & 0x7fffffffu) : ~u); };
+  // both ends as minima, of the order and of its complement: the halves of the wavefront take one each
+  auto ends = [&](unsigned int of_lo, unsigned int of_hi, unsigned int &l, unsigned int &h) __attribute__((always_inline)) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(of_lo, ~of_hi, false, false);
+    unsigned int m = min(sw[0], sw[1]);
+    m = row_min_u32(m);
+    l = min(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16));
+    h = min(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48));
+    if (lane == 0) { red[wave] = l; red[16 + wave] = h; }
+    __syncthreads();
+    m = row_min_u32(red[lane & 31]);
+    l = __builtin_amdgcn_readlane(m, 0);
+    h = ~__builtin_amdgcn_readlane(m, 16);
+  };
+  unsigned int lo_w, hi_w;
+  ends(order(lo), order(hi), lo_w, hi_w);
+  lo = value(lo_w);
+  hi = value(hi_w);
+  auto below = [&](unsigned long long m, int from) __attribute__((always_inline)) -> int {   // from + set bits in lower lanes
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, (unsigned int)from));
+  };
+  // kept scores and ties of lower wavefronts, from every wavefront's totals (every wavefront scans the 16 pairs itself)
+  auto before = [&](int n_gt, int n_eq, int ties_taken, int &pos, int &eq_seen) __attribute__((always_inline)) {
     if (lane == 0) cnt[wave] = make_int2(n_gt, n_eq);
     __syncthreads();
-    // every wavefront scans the 16 pairs itself: lane l < 16 holds wavefront l's totals
     const int2 mine = lane < 16 ? cnt[lane] : make_int2(0, 0);
     const int e_before = wave_incl_scan(mine.y) - mine.y;
     const int kept = mine.x + max(0, min(mine.y, ties_taken - e_before));
-    int eq_seen = __builtin_amdgcn_readlane(e_before, wave);                    // ties at lower indices
-    int pos = __builtin_amdgcn_readlane(wave_incl_scan(kept) - kept, wave);     // kept at lower indices
+    eq_seen = __builtin_amdgcn_readlane(e_before, wave);
+    pos = __builtin_amdgcn_readlane(wave_incl_scan(kept) - kept, wave);
+  };
+
+  bool done = false, found = false;
+  double theta = 0.0;
+  int ties_taken = 0, pos, eq_seen;
+  if (__builtin_expect(topk_fp32_range(lo, hi), 1)) {
+    const float scale = topk_fp32_scale(lo, hi);
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) bk[u] = TopkMap::bucket(__int_as_float(bk[u]), lo, scale);
+    if ((wave + 1) * ROWS * 64 > d_ffn) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) bk[u] = i0 + u * 64 < d_ffn ? bk[u] : ~lane;
+    }
+    unsigned int *hist = sh.hist;
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) atomicAdd(hist + bk[u], 1u);
+    __syncthreads();
+    topk_find_bucket(sh, K);
+    int tb = __builtin_amdgcn_readfirstlane((int)sh.sel_bin);
+    const int need = __builtin_amdgcn_readfirstlane((int)sh.sel_rem);   // rank of theta inside bucket tb (1 = largest)
+    const int c = __builtin_amdgcn_readfirstlane((int)sh.hist[tb]);
+    if (c <= TOPK_CAND) {                       // (uniform: every thread reads the same)
+      topk_pad(sh, c);
+      unsigned int open_rows = 0;               // rows that hold a candidate
+      int n_gt = 0;
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        n_gt += __popcll(__ballot(bk[u] > tb));
+        if (__ballot(bk[u] == tb)) {
+          open_rows |= 1u << u;
+          if (bk[u] == tb) sh.cand[atomicAdd(&sh.n_cand, 1u)] = v[u];
+        }
+      }
+      __syncthreads();
+      // (the compiler would keep these passes' conditions for the next ones, in more scalar registers than there are)
+      open_rows = __builtin_amdgcn_readfirstlane(open_rows);
+      asm volatile("" : "+s"(tb));
+      int n_ties;
+      topk_rank(sh, c, need, theta, ties_taken, n_ties);
+      if (__builtin_expect(ties_taken == n_ties, 1)) {       // all that equal theta are kept (else: by their order, below)
+        // candidates that are kept move to the bucket above
+        if (open_rows) {
+#pragma unroll
+          for (int u = 0; u < ROWS; ++u)
+            if ((open_rows >> u) & 1u) {
+              const bool kept = bk[u] == tb && v[u] >= theta;
+              n_gt += __popcll(__ballot(kept));
+              bk[u] += kept;
+            }
+        }
+        before(n_gt, 0, 0, pos, eq_seen);
+        asm volatile("" : "+s"(tb));
+        // (K of them together, so nothing is written past the list)
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+          const unsigned long long m = __ballot(bk[u] > tb);
+          const uint32_t at = (uint32_t)below(m, pos) * 4u;
+          if (bk[u] > tb) *reinterpret_cast<int32_t *>(reinterpret_cast<char *>(out) + at) = i0 + u * 64;
+          pos += __popcll(m);
+        }
+        done = true;
+      }
+      found = true;
+    }
+    if (!done) __syncthreads();                 // (the histogram has been read)
+  }
+  if (__builtin_expect(!done, 0)) {
+    // (what the compiler cannot follow: it would keep conditions, roundings and keys of earlier passes, in scratch memory)
+    auto valid = [&](int u) __attribute__((always_inline)) -> bool {
+      int i = i0;
+      asm volatile("" : "+v"(i));
+      return i + u * 64 < d_ffn;
+    };
+    auto score = [&](int u) __attribute__((always_inline)) -> double {
+      double x = v[u];
+      asm volatile("" : "+v"(x));
+      return x;
+    };
+    unsigned long long theta_key = 0;
+    if (!found) {
+      // as in the general kernel: buckets of the fp64 scores where they have an ordered range, else keys
+      unsigned int lo64 = 0xffffffffu, hi64 = 0u;      // the high words of the smallest and the largest key enclose the scores
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        const unsigned int hw = (unsigned int)((unsigned long long)__double_as_longlong(v[u]) >> 32);
+        const unsigned int key = hw ^ ((unsigned int)((int)hw >> 31) | 0x80000000u);
+        lo64 = min(lo64, key);
+        hi64 = max(hi64, key);
+      }
+      __syncthreads();                                 // (red has been read)
+      ends(lo64, hi64, lo64, hi64);
+      const double lo_v = key_score((unsigned long long)lo64 << 32), hi_v = key_score(((unsigned long long)hi64 << 32) | 0xffffffffull);
+      const bool need_radix = topk_fp32_range(lo, hi) || !(hi_v > lo_v);   // too many ties for the buckets, or no ordered range
+      if (!topk_threshold(sh, K, lo_v, hi_v, need_radix,
+                          [&](auto fn) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int u = 0; u < ROWS; ++u) {
+                              const double x = score(u);
+                              if (valid(u)) fn(x, (float)x);
+                            }
+                          },
+                          [&](auto bucket_of, int tb, auto append) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int u = 0; u < ROWS; ++u) {
+                              const double x = score(u);
+                              if (valid(u) && bucket_of(x, (float)x) == tb) append(x);
+                            }
+                          },
+                          theta, theta_key, ties_taken))
+        found = true;
+    }
+    if (found) theta_key = score_key(theta);
+    int n_gt = 0, n_eq = 0;
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
-      if (!MASKS && u >= R) continue;
-      unsigned long long m_take = MASKS ? m_gt[u] : __ballot(valid(u) && above(v[u]));
-      if (!MASKS || ((open_rows >> u) & 1u)) {
-        const bool eq = valid(u) && equal(v[u]);
-        const unsigned long long m_eq = __ballot(eq);
-        m_take |= __ballot(eq && eq_seen + below(m_eq) < ties_taken);
-        eq_seen += __popcll(m_eq);
-      }
-      const int at = pos + below(m_take);
-      if (((m_take >> lane) & 1ull) && at < K) out[at] = i0 + u * 64;           // never past the list, whatever the scores were
-      pos += __popcll(m_take);
+      const unsigned long long key = score_key(score(u));
+      n_gt += __popcll(__ballot(valid(u) && key > theta_key));
+      n_eq += __popcll(__ballot(valid(u) && key == theta_key));
     }
-  };
-  if (__builtin_expect(by_key, 0)) {
-    open_rows = 0xffffffffu;
-    compact([&](double s) { return score_key(s) > theta_key; }, [&](double s) { return score_key(s) == theta_key; });
-  } else {
-    compact([&](double s) { return s > theta; }, [&](double s) { return s == theta; });
+    before(n_gt, n_eq, ties_taken, pos, eq_seen);
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+      const unsigned long long key = score_key(score(u));
+      const bool eq = valid(u) && key == theta_key;
+      const unsigned long long m_eq = __ballot(eq);
+      const bool take = (valid(u) && key > theta_key) || (eq && below(m_eq, eq_seen) < ties_taken);
+      const unsigned long long m = __ballot(take);
+      const int at = below(m, pos);
+      if (take && at < K) out[at] = i0 + u * 64;     // never past the list, whatever the scores were
+      eq_seen += __popcll(m_eq);
+      pos += __popcll(m);
+    }
   }
   for (int i = K + tid; i < k_stride; i += 1024) out[i] = -1;
 }
@@ -825,6 +938,16 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
 }  // namespace
 
 static int g_topk_lds_raised = 0;
+
+// the top-K kernel with 2 * half rows, 1 <= half <= 16: as few as hold the block (a row that none of its indices is in still
+// costs its share of every pass)
+typedef void (*topk_reg_t)(const double *, int32_t *, int, int, KSpec);
+template <int... H>
+static topk_reg_t topk_reg_pick(int half, std::integer_sequence<int, H...>) {
+  constexpr topk_reg_t fn[] = {ff_topk_reg_kernel<2 * H + 2>...};
+  return fn[half - 1];
+}
+static topk_reg_t topk_reg_kernel(int half) { return topk_reg_pick(half, std::make_integer_sequence<int, 16>{}); }
 
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
   const int n_slices = (p.d_model + 511) / 512;
@@ -865,14 +988,8 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   }
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_TOPK, s);
-  // (as few rows as hold the block: a row that none of its indices is in still costs its share of the loads)
-  const auto topk_reg = p.d_ffn <= 4 * 1024    ? ff_topk_reg_kernel<4>
-                        : p.d_ffn <= 8 * 1024  ? ff_topk_reg_kernel<8>
-                        : p.d_ffn <= 16 * 1024 ? ff_topk_reg_kernel<16>
-                        : p.d_ffn <= 24 * 1024 ? ff_topk_reg_kernel<24>
-                                               : ff_topk_reg_kernel<32>;
   if (p.d_ffn <= 32 * 1024) {
-    hipLaunchKernelGGL(topk_reg, dim3(p.n_blocks), dim3(1024), 0, s, p.scores, p.indices, p.d_ffn, p.k_stride, p.k);
+    hipLaunchKernelGGL(topk_reg_kernel((p.d_ffn + 2047) / 2048), dim3(p.n_blocks), dim3(1024), 0, s, p.scores, p.indices, p.d_ffn, p.k_stride, p.k);
   } else {
     // the kernel's own static arrays (bucket histogram, candidates, scan scratch) take under 26 KiB
     const size_t dyn_limit = (size_t)lds_limit - 26 * 1024;

@@ -1161,6 +1161,37 @@ def test_ties_over_many_rows_at_the_threshold(ctx, df, n_tied):
         np.testing.assert_array_equal(idx[0].cpu().numpy(), O.select_topk(s, k), err_msg=f"k={k}")
 
 
+@pytest.mark.parametrize("half", range(1, 17))
+def test_topk_at_every_row_count(ctx, half):
+    """The top-K kernel keeps 2, 4, .. 32 scores per thread: the largest block of each count (every index of every wavefront), the
+    smallest (most wavefronts past the end) and one that ends inside a row; continuous scores, and few equal ones at the threshold,
+    all or some of them kept: ranked by fours of lanes (up to 16 candidates) or one lane each (up to 64)."""
+    dm, T, r = 128, 64, 8
+    for df in (2048 * half, 2048 * (half - 1) + 8, 2048 * half - 1000):
+        rng = np.random.default_rng(df)
+        xb, w1b, w2b = (W.f32_to_bf16_bits(rng.standard_normal(n).astype(np.float32)) for n in ((T, dm), (dm, r), (r, df)))
+        shape = B.Shape(dm, df, T, 64, r, 0)
+        ctx.ensure_workspace(shape, df)
+        for n_tied in (0, 3, 14, 40):
+            w2t = w2b.copy()
+            if n_tied:
+                at = np.unique(np.linspace(0, df - 1, n_tied).astype(int))
+                w2t[:, at] = w2t[:, at[:1]]
+            s = O.predictor_scores(_f32(xb), None, _f32(w1b), _f32(w2t))
+            xd, w1d, w2d = (B.to_device_bf16(a, DEV) for a in (xb, w1b, w2t))
+            pred = B.Predictor(None, w1d.data_ptr(), w2d.data_ptr())
+            ks = (1, df // 2, df)
+            if n_tied:
+                n_above = int((s > s[0]).sum())
+                ks = (n_above + 1, min(df, n_above + 2), n_above + len(at))
+            for k in ks:
+                idx = torch.empty((1, k + 3), dtype=torch.int32, device=DEV)
+                ctx.predict(shape, xd, pred, [k], k + 3, idx, None)
+                got = idx[0].cpu().numpy()
+                np.testing.assert_array_equal(got[:k], O.select_topk(s, k), err_msg=f"df={df} n_tied={n_tied} k={k}")
+                assert (got[k:] == -1).all()
+
+
 @pytest.mark.parametrize("df", [2048, 8184, 14328, 20480, 28672, 40960])
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -110, 2.0 ** 80])
 def test_scores_that_fp32_cannot_tell_apart(ctx, df, scale):
