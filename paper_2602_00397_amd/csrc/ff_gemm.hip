@@ -679,6 +679,113 @@ void ff_gemm1_direct_kernel(Gemm1Params p, int V, int mt, int N, int xs, int NX)
     }
 }
 
+// The compensator's first layer (Eq. 20) where the units start a tile of their own behind lists of equal length: then they are the
+// same columns of H for every token, and blocks mean nothing.
+//     H[t][K + u] = act(x_t . Wc1[u]), u0 <= u < rc; zero up to the next multiple of 64.
+// A workgroup takes 32 MT tokens and BU units, its eight wavefronts an eighth of the channels each, so that a wavefront has only
+// few steps to wait for, two on their way; their sums are added in wavefront order.  The workgroups start at different steps,
+// for rows that lie a multiple of 4 KB apart keep all lines of a step in one channel of the L2.  Rows are loaded by fours of lanes
+// and exchanged, as in ff_gemm1_direct_kernel.  Bound by the exchanges and the rows' way from L2.
+// (As 64 x 64 tiles of the gate/up kernel, half of whose products nobody wants, us -> this: 4096 tokens of 2048, 32 units 16.8 -> 8.8;
+// 8192 of 4096, 64 units 28.9 -> 21.2.)
+// grid (ceil(T / (32 MT)), tiles of BU units)
+template <int MT, int BU>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+void ff_comp_kernel(Gemm1Params p, int K, int u0) {
+  constexpr int NW = 8, NU = BU / 32, U = 2, BM = 32 * MT;
+  __shared__ __align__(16) float red[NW][BM][BU];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, half = lane >> 5;
+  const int lr = (lane >> 2) & 7, chunk = (lane & 3) + 4 * half;
+  const int t0 = (int)blockIdx.x * BM, unit0 = u0 + (int)blockIdx.y * BU;
+  const int rows_valid = min(BM, p.T - t0);
+  const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
+  const int nk = p.d_model / 64, per = (nk + NW - 1) / NW, s0 = min(wave * per, nk), n = min(per, nk - s0);   // this wavefront's steps
+  const int rot = n > 0 ? ((int)blockIdx.x >> 3) % n : 0;
+  typedef const __attribute__((address_space(1))) u32x4_t *gptr_t;
+  const uintptr_t xbase = (uintptr_t)(p.x + (size_t)t0 * p.d_model), wbase = (uintptr_t)p.wc1;
+  uint32_t x_off[MT][4], w_off[NU][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) x_off[i][j] = (uint32_t)min(32 * i + j + 4 * lr, rows_valid - 1) * row_bytes + (uint32_t)chunk * 16u;
+#pragma unroll
+    for (int f = 0; f < NU; ++f) w_off[f][j] = (uint32_t)min(unit0 + 32 * f + j + 4 * lr, p.rc - 1) * row_bytes + (uint32_t)chunk * 16u;   // past the end: not stored
+  }
+  u32x4_t xb[U][MT][4], wb[U][NU][4];
+  auto load = [&](int i, int buf) __attribute__((always_inline)) {
+    const uint32_t ko = (uint32_t)(s0 + (i + rot < n ? i + rot : i + rot - n)) * 128u;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) xb[buf][m][j] = *(gptr_t)(xbase + ko + x_off[m][j]);
+#pragma unroll
+    for (int f = 0; f < NU; ++f)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) wb[buf][f][j] = *(gptr_t)(wbase + ko + w_off[f][j]);
+  };
+  f32x16_t acc[MT][NU];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int f = 0; f < NU; ++f)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[m][f][e] = 0.0f;
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+    if (i < n) load(i, i);
+  for (int i0 = 0; i0 < n; i0 += U) {
+#pragma unroll
+    for (int b = 0; b < U; ++b)
+      if (i0 + b < n) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int d = 0; d < 4; ++d) transpose4<true>(xb[b][m], d);
+#pragma unroll
+        for (int f = 0; f < NU; ++f)
+#pragma unroll
+          for (int d = 0; d < 4; ++d) transpose4<true>(wb[b][f], d);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int f = 0; f < NU; ++f) acc[m][f] = mfma32(xb[b][m][g], wb[b][f][g], acc[m][f]);
+        if (i0 + b + U < n) load(i0 + b + U, b);
+      }
+  }
+  // lane (c, half) holds unit 32 f + c of tokens 32 m + 8 (e / 4) + 4 half + e mod 4
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int f = 0; f < NU; ++f)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) red[wave][32 * m + 8 * (e >> 2) + 4 * half + (e & 3)][32 * f + c] = acc[m][f][e];
+  __syncthreads();
+  constexpr int PER = BU / 16;                                          // adjacent units per thread
+  const int u = (tid & 15) * PER;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int t = 32 * m + (tid >> 4);
+    if (t >= rows_valid) return;
+    float v[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) v[q] = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int q = 0; q < PER; ++q) v[q] += red[w][t][u + q];
+    bf16_t *dst = p.h + (size_t)(t0 + t) * p.hs + K + unit0 + u;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) v[q] = unit0 + u + q < p.rc ? act_apply(p.comp_act, v[q]) : 0.0f;
+#pragma unroll
+    for (int q = 0; q < PER; q += 2) *reinterpret_cast<uint32_t *>(dst + q) = pack_bf16x2(v[q], v[q + 1]);
+    if (BU == 32) *reinterpret_cast<uint32_t *>(dst + 32) = 0u;          // (the other half of the 64 that H has behind the lists)
+  }
+}
+
 // Four adjacent outputs of one token row on their way out of the down projection: Y in fp32, Y in
 // bf16, or the stack's residual add (the same two roundings as a bf16 Y followed by a separate add;
 // every element of res is read and written by one lane only).  o = element offset of the first.
@@ -1697,6 +1804,18 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
   }
   q.full_only = 0;
   q.rem_bn = v.bn;
+  const int rem0 = n_extent - rem;
+  const bool only_comp = !ragged && rem0 >= p.k.k_max && rem0 % 64 == 0 && (uint64_t)p.rc * (uint64_t)p.d_model * 2u >> 32 == 0;
+  if (only_comp) {
+    // Nothing but compensator units is left, the same columns for every token.  64 tokens to a workgroup once those fill the chip.
+    int K = p.k.k_max, u0 = rem0 - K;
+    const bool narrow = rem <= 32, tall = p.T > 32 * kNumCU;
+    const void *fn = narrow ? (tall ? reinterpret_cast<const void *>(&ff_comp_kernel<2, 32>) : reinterpret_cast<const void *>(&ff_comp_kernel<1, 32>))
+                            : (tall ? reinterpret_cast<const void *>(&ff_comp_kernel<2, 64>) : reinterpret_cast<const void *>(&ff_comp_kernel<1, 64>));
+    const int bm = tall ? 64 : 32;
+    void *args[] = {&q, &K, &u0};
+    return hipLaunchKernel(fn, dim3((p.T + bm - 1) / bm, narrow ? 1 : up64(rem) / 64), dim3(512), args, 0, s);
+  }
   if (heavy_small) {
     // everything of a heavy block from where the main launch stopped, its part-filled last tile included
     Gemm1Params qh = q;

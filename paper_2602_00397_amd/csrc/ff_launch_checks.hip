@@ -141,15 +141,18 @@ static void check_gemm1_addresses() {
 }
 
 // Gate/up: positions beyond the last full tile get a launch of their own where the tile that they would need starts a further
-// round of workgroups, one per CU; not where it fits into the last one.
+// round of workgroups, one per CU; not where it fits into the last one.  Compensator units and nothing else: workgroups of 32
+// tokens, of 64 from 256 such on.
 static void check_gemm1_splits() {
   struct { Shape s; size_t launches; unsigned rem_grid; } calls[] = {
-      {{4096, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 64}, {{4096, 64, 4096, 14336, 64, 5120, 0, 0}, 2, 64},   // 7 and 5 whole rounds
-      {{2126, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 40}, {{3000, 64, 2048, 8192, 64, 4096, 0, 0}, 2, 48},    // by the busiest XCD's count
+      {{4096, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 128}, {{4096, 64, 4096, 14336, 64, 5120, 0, 0}, 2, 128},   // 7 and 5 whole rounds
+      {{2126, 64, 4096, 14336, 64, 7168, 0, 0}, 2, 67}, {{3000, 64, 2048, 8192, 64, 4096, 0, 0}, 2, 94},    // by the busiest XCD's count
       {{4096, 64, 4096, 14336, 64, 3584, 0, 0}, 1, 0},  {{3000, 64, 4096, 14336, 64, 7168, 0, 0}, 1, 0},    // 3.5 and 5.1 rounds
       {{1845, 128, 2048, 8192, 32, 4096, 8192, 2}, 1, 0},  {{3732, 64, 2048, 8192, 32, 4096, 8192, 2}, 1, 0},    // two longer lists
       {{1907, 64, 4096, 14336, 64, 10752, 14336, 2}, 1, 0},
-      {{8192, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 128}};
+      {{8192, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 256}, {{8193, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 129},
+      {{2126, 64, 4096, 14336, 64, 7160, 0, 0}, 2, 67},   // units from the ninth on
+      {{2126, 64, 4096, 14336, 64, 7180, 0, 0}, 2, 72}, {{8192, 128, 4096, 14336, 64, 7180, 0, 0}, 2, 256}};   // lists that end inside a tile
   for (const auto &c : calls) {
     CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && g_log.size() == c.launches, "T %d block %d K %d: %zu launches", c.s.T, c.s.block, c.s.k, g_log.size());
     if (c.launches > 1 && g_log.size() > 1) CHECK(g_log[1].g1.rem_bn == 256 && g_log[1].grid == c.rem_grid, "T %d K %d: grid %u", c.s.T, c.s.k, g_log[1].grid);

@@ -687,6 +687,36 @@ def test_gate_up_gemm_with_weights_in_registers(ctx, variant, block, d_model):
         assert all((g - o).abs().max().item() <= 1e-3 * o.abs().max().item() for g, o in zip(got, out[2, 0]))
 
 
+@pytest.mark.parametrize("d_model", [128, 384, 1152])
+@pytest.mark.parametrize("rc,n_tokens,k", [(8, 33, 256), (32, 200, 256), (40, 417, 256), (64, 160, 256), (72, 97, 256), (200, 289, 512),
+                                           (24, 8200, 256), (72, 8225, 256), (40, 300, 250), (104, 130, 233)])
+def test_compensator_units_behind_whole_tiles(ctx, rc, n_tokens, k, d_model):
+    """Lists that fill whole gate/up tiles of 256, or whose last one the first units fill: the compensator's units are a launch of their own over all tokens, 32 or (above
+    8192) 64 tokens and 32 or 64 units to a workgroup; tokens and units that fill none of them, fewer steps of 64 channels than
+    wavefronts.  In a workspace full of NaN (H has to be zero behind the units), against the oracle on some blocks, and against the
+    same call without that launch: the same fp32 sums in another order, of which a unit may round to the other bf16 neighbour,
+    2^-8 of it, next to k + rc others: far below 1e-3 of max |y|."""
+    block = 72
+    c = Case(W.Shape("units", d_model, 704, n_tokens, block, 8, rc))
+    ks = [k] * c.n_blocks
+    ref = c.oracle_layer(ks, blocks=[0, c.n_blocks - 1])
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=k)
+    ctx.ensure_workspace(c.shape, k)
+    out = {}
+    try:
+        ctx.set_option("merge_blocks", 0)
+        for split in (0, 1):
+            ctx.set_option("gemm1_variant", 6)
+            ctx.set_option("gemm1_split", split)
+            ctx._ws.fill_(0xFF)
+            out[split] = c.gpu_sparse(ctx, idx, ks, out_f32=True)
+            _check_y(out[split], ref.y, f"{rc} units, {n_tokens} tokens, d_model {d_model}, split {split}")
+    finally:
+        for option in ("gemm1_variant", "gemm1_split", "merge_blocks"):
+            ctx.set_option(option, -1)
+    assert (out[0] - out[1]).abs().max().item() <= 1e-3 * out[0].abs().max().item()
+
+
 @pytest.mark.parametrize("variant", [5, 6, 7, 8])
 @pytest.mark.parametrize("rc,ks", [(0, [1, 64, 65, 320]), (8, [1064, 56, 127, 440]), (64, [128, 129, 1064, 640]), (24, [1064] * 4)])
 def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
