@@ -1485,6 +1485,152 @@ void ff_gemm2_direct_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
     }
 }
 
+// The same product for calls with few tokens or columns: 64 x 64 tiles, whose eight wavefronts take the list's groups of 32
+// positions in turn and wait for nobody until they add up at the end (in wavefront order).  Each copies H of its group into LDS of
+// its own and loads its rows into registers as above, the next group's while this one's products are formed; two workgroups on a
+// CU, so that four wavefronts of a SIMD wait in turn.  The tiles above pass a barrier every 64 positions, and cut into pieces that
+// fill the chip they write and read partial sums for as long as the products take.  What binds this one is the latency of
+// each group's loads, and, with many tiles, that a row is fetched once for every 64 tokens.
+// Whole calls of ff_sparse_ffn, half of the neurons, us, without this tile and with it: 256 tokens of 256/688 17.0 -> 14.1; 2048/8192,
+// 9 tokens 25.9 -> 22.7, 64 28.9 -> 26.3, 256 in one block 44.4 -> 41.7; 4096/14336, 9 tokens 51.7 -> 45.6, 30 51.6 -> 48.0, 64 60.6
+// -> 55.9.  Forced, 100 tokens of 4096/14336 86.5 -> 88.4 and 700 of 2048/8192 93.6 -> 104.
+// RM 0: the identity list; 1: the tile's list in an LDS table of 16-bit ids.
+constexpr int kSplitWaves = 8;
+template <int RM>
+__global__ __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
+void ff_gemm2_ksplit_kernel(Gemm2Params p, int V, int mt, int N, int xs) {
+  constexpr int NW = kSplitWaves, MT = 4, BM = MT * 16, BN = 64, STAGE = BM * 64;
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, q = lane >> 4;
+  const Gemm2Tile tl = gemm2_tile<BM, BN, 64>(p, V, mt, N, xs);
+  if (!tl.valid) return;
+  const int Kb = tl.Kb, ntot = tl.ntot, kofs = tl.kofs, nh = 2 * tl.nk;
+  uint16_t *tab = reinterpret_cast<uint16_t *>(smem + 2 * NW * STAGE);
+  if (RM == 1) {
+    // eight list entries per thread in flight at a time (left to itself the loop waits for every load)
+    const int32_t *gl = p.idx + (size_t)tl.b * p.k_stride;
+    constexpr int U = 8;
+    for (int i0 = tid; i0 < nh * 32; i0 += U * NW * 64) {
+      int raw[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) raw[u] = gl[min(kofs + i0 + u * NW * 64, Kb - 1)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * NW * 64, pos = kofs + i;
+        if (i < nh * 32) tab[i] = (uint16_t)(pos < Kb ? min(max(raw[u], 0), p.d_ffn - 1) : (pos < ntot ? p.d_ffn + (pos - Kb) : 0));
+      }
+    }
+    __syncthreads();
+  }
+  // H: copy i of a group covers rows 16 i .. + 15, 64 bytes of each
+  const uint64_t a_base = (uint64_t)(uintptr_t)(p.h + (size_t)tl.t0 * p.hs + kofs);
+  uint32_t a_off[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int row = 16 * i + lane / 4;
+    a_off[i] = (uint32_t)(min(row, tl.rows_valid - 1) * p.hs + ((lane & 3) ^ swz<32>(row)) * 8) * 2u;
+  }
+  const uint32_t lds0 = lds_addr_of(smem) + (uint32_t)wave * (2 * STAGE);
+  const uint8_t *mine = smem + wave * (2 * STAGE) + c * 64 + ((q ^ swz<32>(c)) << 4);   // (row 16 m + c: the same swizzle)
+  const int hi = c >> 3;                                                  // which of a pair of rows this lane loads
+  const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
+  const uint32_t col_bytes = (uint32_t)(min(tl.n0, p.d_model - BN) + 8 * (c & 7)) * 2u;
+  typedef const __attribute__((address_space(1))) u32x4_t *gptr_t;
+  typedef const __attribute__((address_space(1))) uint8_t *gbyte_t;
+  const uint32_t lane_off = (8u * (uint32_t)q + (uint32_t)hi) * row_bytes + col_bytes;
+  u32x4_t wb[4];
+  // group h's copies and rows (FAST: all of its positions are W_down rows; the launcher has checked that their offsets fit 32 bits)
+  auto request = [&](int h, uint32_t slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) gload_lds16_off(a_base + (uint64_t)(uint32_t)h * 64u, a_off[i], lds0 + slot * STAGE + (uint32_t)i * 1024u);
+    u32x4_t ids = {0, 0, 0, 0};
+    if (RM == 1) ids = *reinterpret_cast<const u32x4_t *>(tab + h * 32 + 8 * q);
+    const int pos0 = kofs + h * 32;
+    if (pos0 + 32 <= Kb) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (RM == 1) wb[i] = *(gptr_t)((uintptr_t)p.wd + (__umul24((ids[i] >> (16 * hi)) & 0xffffu, row_bytes) + col_bytes));
+        else {
+          const gbyte_t row0 = (gbyte_t)(uintptr_t)p.wd + (size_t)(uint32_t)(pos0 + 2 * i) * row_bytes;   // scalar
+          wb[i] = *(gptr_t)(row0 + lane_off);
+        }
+      }
+    } else {
+      int pos8 = pos0 + 8 * q + hi;
+      asm volatile("" : "+v"(pos8));                                      // (nothing of this ahead of the loop: no registers for it)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int pos = pos8 + 2 * i;
+        const uint32_t r = RM == 1 ? (ids[i] >> (16 * hi)) & 0xffffu : (uint32_t)(pos < Kb ? min(pos, p.d_ffn - 1) : (pos < ntot ? p.d_ffn + (pos - Kb) : 0));
+        const uintptr_t base = r < (uint32_t)p.d_ffn ? (uintptr_t)p.wd : (uintptr_t)p.wc2 - (size_t)p.d_ffn * row_bytes;
+        wb[i] = *(gptr_t)(base + (size_t)r * row_bytes + col_bytes);
+      }
+    }
+  };
+  f32x4_t acc[MT][4];                         // [token tile][f]
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int f = 0; f < 4; ++f) acc[i][f] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t slot = 0;
+  if (wave < nh) request(wave, 0);
+  for (int h = wave; h < nh; h += NW) {
+    // everything of group h has landed (a wavefront reads what it copied itself: no barrier)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    u32x4_t bf[4];
+    // rows 2 i and 2 i + 1 lie in lanes c and c ^ 8, as in ff_gemm2_direct_kernel
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      constexpr int ROR8 = 0x128;
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const uint32_t lo = wb[i][d], up = wb[i][2 + d];
+        const uint32_t ev = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)up, ROR8, 0xf, 0xc, false);
+        const uint32_t od = (uint32_t)__builtin_amdgcn_update_dpp((int)up, (int)lo, ROR8, 0xf, 0x3, false);
+        bf[2 * d][i] = __builtin_amdgcn_perm(od, ev, 0x05040100u);
+        bf[2 * d + 1][i] = __builtin_amdgcn_perm(od, ev, 0x07060302u);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // (the other place's last reader was the group before, whose products are out)
+    if (h + NW < nh) request(h + NW, slot ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4_t af[2];
+    af[0] = *reinterpret_cast<const u32x4_t *>(mine + slot * STAGE);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      if (m + 1 < MT) af[(m + 1) & 1] = *reinterpret_cast<const u32x4_t *>(mine + slot * STAGE + (m + 1) * 1024);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) acc[m][f] = mfma16(af[m & 1], bf[f], acc[m][f]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    slot ^= 1;
+  }
+  // the wavefronts' sums, in order, 16 rows at a time: lane (c, q) holds columns 8 (c mod 8) + 4 (c / 8) + f of rows 4 q + e
+  float4 *red = reinterpret_cast<float4 *>(smem);                        // [wave][16 rows][16 columns of four]
+  const int col4 = 2 * (c & 7) + hi;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    __syncthreads();                                                     // the copies' LDS, or the last rows, are free
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[(wave * 16 + 4 * q + e) * 16 + col4] = make_float4(acc[m][0][e], acc[m][1][e], acc[m][2][e], acc[m][3][e]);
+    __syncthreads();
+    const int rowl = 16 * m + (tid >> 4);
+    if (tid < 256 && rowl < tl.rows_valid && tl.n0 < p.d_model) {
+      float4 v = red[tid];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        const float4 o = red[w * 256 + tid];
+        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+      }
+      gemm2_store<BM>(p, tl, rowl, tl.n0 + 4 * (tid & 15), v);
+    }
+  }
+}
+
 // ---- variant tables --------------------------------------------------------
 struct Variant {
   const void *fn;
@@ -1516,6 +1662,10 @@ template <int MT, int KG = 1>
 Variant g2d() {
   return Variant{reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 0, KG>), MT * 16, kDirectWaves / KG * 64, kDirectWaves * 64,
                  kDirectStages * KG * MT * 16 * 128, {reinterpret_cast<const void *>(&ff_gemm2_direct_kernel<MT, 1, KG>), nullptr, nullptr}};
+}
+Variant g2k() {
+  return Variant{reinterpret_cast<const void *>(&ff_gemm2_ksplit_kernel<0>), 64, 64, kSplitWaves * 64, 2 * kSplitWaves * 64 * 64,
+                 {reinterpret_cast<const void *>(&ff_gemm2_ksplit_kernel<1>), nullptr, nullptr}};
 }
 constexpr int kIdRingBytes = 8 * 256;   // row-id mode 3: eight stages of 64 raw list entries
 
@@ -1551,6 +1701,7 @@ const Variant kGemm2[] = {
     g2d<4>(),                 // 6: 64 x 512, weights in registers
     g2d<8, 2>(),              // 7: 128 x 256, weights in registers, 2 k-groups (128 KB)
     g2d<4, 2>(),              // 8: 64 x 256, the same (64 KB)
+    g2k(),                    // 9: 64 x 64, weights in registers, 8 wavefronts that take groups of 32 positions in turn (64 KB)
 };
 constexpr int kNumGemm1 = sizeof(kGemm1) / sizeof(Variant);
 constexpr int kNumGemm2 = sizeof(kGemm2) / sizeof(Variant);
@@ -1658,7 +1809,7 @@ constexpr int kRemainderVariant = 7;
 constexpr int kHeavySurplusVariant = 8;
 constexpr int kWide128 = 6;
 constexpr int kGemm1Direct128 = 11, kGemm1Direct64 = 12;   // the gate/up tiles with the weights in registers
-constexpr int kDirect128 = 5, kDirect64 = 6, kDirect128Narrow = 7, kDirect64Narrow = 8;   // the down-GEMM tiles
+constexpr int kDirect128 = 5, kDirect64 = 6, kDirect128Narrow = 7, kDirect64Narrow = 8, kSplit64 = 9;   // the down-GEMM tiles
 constexpr int kHalf128Wide = 4;     // the 128 x 256 down-GEMM tile with eight wavefronts (144 KB)
 
 static bool gemm1_direct(int variant) { return variant >= kGemm1Direct128; }
@@ -1855,13 +2006,15 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 // a few workgroups on the chip, or all of it busy).  The tiles with the weights in registers run a step of 128 x 512 in 1.6 us
 // with the chip full (1.32 PFLOP/s dense), one of 64 x 512 in 1.1 to 1.24; alone on the chip they wait for their loads.  The
 // tiles of 256 columns serve calls with few columns and blocks (2048/8192, K 4096, 32 blocks of 128, one round: 75.9 us with both
-// operands in LDS, 66.5 with the weights in registers; 256 tokens of the smallest configuration 13.7 cut in pieces, 11.7 as 64 x 256).
+// operands in LDS, 66.5 with the weights in registers).  The 64 x 64 tiles: see their kernel; with one or two tiles of tokens, one
+// on each CU, a step takes 0.25 to 0.3, with four 0.35 to 0.45 (200 tokens of 4096/14336, K 3584: at 0.33 throughout they would be
+// taken, 65.8 -> 68.3; at 0.41 the gains of 3 to 8% on 9 to 100 tokens of 4096/14336 would be lost).
 // The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
 struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
-                                     {kDirect128Narrow, 0.8, 0.95, 9.0}, {kDirect64Narrow, 0.45, 1.1, 6.0},
+                                     {kDirect128Narrow, 0.8, 0.95, 9.0}, {kDirect64Narrow, 0.45, 1.1, 6.0}, {kSplit64, 0.25, 0.33, 5.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
-static bool gemm2_direct(int variant) { return variant >= kDirect128 && variant <= kDirect64Narrow; }
+static bool gemm2_direct(int variant) { return variant >= kDirect128; }
 // Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
 // product of two 24-bit numbers in 32 bits, a token's offset into a tile of H has 32 bits too.
 static bool gemm2_direct_addresses(const Gemm2Params &p) {
@@ -1956,8 +2109,10 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
         const int xs = xcd_groups(V, N * n, n > 1 ? Share{} : share_of(v, p, false));
         const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N * n + (8 >> xs) - 1) / (8 >> xs));   // of the busiest XCD
         const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
-        double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * g.full);
-        if (busy > 0.0) cost += g.fixed + steps * (g.idle + (g.full - g.idle) * busy);
+        // (64 x 64 tiles fetch every row once for each 64 tokens: more than two such tiles of tokens make each other wait)
+        const double full = g.variant == kSplit64 && V > 2 ? 0.37 : g.full;
+        double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * full);
+        if (busy > 0.0) cost += g.fixed + steps * (g.idle + (full - g.idle) * busy);
         if (n > 1) cost += 3.0 + (double)n * (double)per_piece / 3.3e6;
         if (heavy_cut) {
           const long heavy = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;

@@ -175,18 +175,18 @@ static void check_gemm1_short_block() {
   CHECK(gemm1({122, 64, 3584, 18944, 64, 18944, 0, 0}, true, -1, -1, -1) == hipSuccess && g_log[0].fn != fn, "two blocks");
 }
 
-// Down: the tiles with the weights in registers (5 to 8) form 32-bit offsets into W_down and H.  Where those do not
+// Down: the tiles with the weights in registers (5 to 9) form 32-bit offsets into W_down and H.  Where those do not
 // reach, the library takes another tile and a forced one is an error, cut along the list or not.
 static void check_gemm2_addresses() {
   std::set<const void *> in_registers;
-  for (int variant : {5, 6, 7, 8})
+  for (int variant : {5, 6, 7, 8, 9})
     for (bool list : {false, true}) {
       DownOptions o;
       o.variant = variant;
       CHECK(gemm2({700, 128, 256, 1024, 32, 512, 0, 0}, list, o, true) == hipSuccess && g_log.size() == 1, "tile %d", variant);
       for (const Launch &l : g_log) in_registers.insert(l.fn);
     }
-  CHECK(in_registers.size() == 8, "%zu kernels", in_registers.size());
+  CHECK(in_registers.size() == 10, "%zu kernels", in_registers.size());
   // rows of 16 MiB; a matrix of 4 GiB, and just below; H of 2^24 positions
   struct { Shape s; bool ok, ok_list; } sizes[] = {{{20, 10, 8388608, 8, 0, 8, 0, 0}, false, false},
                                                   {{20, 10, 8388608 - 128, 8, 0, 8, 0, 0}, true, true},
@@ -203,7 +203,7 @@ static void check_gemm2_addresses() {
         const bool may = list ? z.ok_list : z.ok;
         for (const Launch &l : g_log)
           CHECK(may || !in_registers.count(l.fn), "d_model %d d_ffn %d list %d", z.s.d_model, z.s.d_ffn, list);
-        for (int variant : {5, 6, 7, 8}) {
+        for (int variant : {5, 6, 7, 8, 9}) {
           o.variant = variant;
           const hipError_t e = gemm2(z.s, list, o, true);
           CHECK((e == hipSuccess) == may && g_log.empty() == !may, "d_model %d d_ffn %d list %d tile %d nsplit %d", z.s.d_model, z.s.d_ffn, list, variant, nsplit);
@@ -216,8 +216,8 @@ static void check_gemm2_routes() {
   struct { Shape s; bool list; int variant, row_mode; bool cut; } routes[] = {
       {{9000, 256, 1024, 1064, 24, 1064, 0, 0}, false, 5, -1, false},   // the identity list with compensator rows behind it
       {{150, 256, 4096, 4096, 24, 4096, 0, 0}, false, 6, -1, true},
-      {{60, 256, 2048, 4096, 24, 4096, 0, 0}, false, 8, -1, true},
-      {{256, 256, 256, 344, 24, 344, 0, 0}, false, 8, -1, false},
+      {{60, 256, 2048, 4096, 24, 4096, 0, 0}, false, 9, -1, true},
+      {{256, 256, 256, 344, 24, 344, 0, 0}, false, 9, -1, false},
       {{3000, 64, 512, 65536, 16, 3000, 0, 0}, true, 3, 2, true}};     // ids of more than 16 bits: scalar loads
   for (const auto &r : routes) {
     CHECK(gemm2(r.s, r.list, DownOptions(), true) == hipSuccess && !g_log.empty(), "T %d", r.s.T);
@@ -232,7 +232,7 @@ static void check_gemm2_routes() {
 // Down: the longest list whose row-id table fits beside the ring of a tile with the weights in registers.  One position more and
 // the tile is refused where it is forced, and not taken where it is not.
 static void check_gemm2_row_table() {
-  const int tiles[][2] = {{5, 49152}, {6, 65536}, {7, 16384}, {8, 49152}};
+  const int tiles[][2] = {{5, 49152}, {6, 65536}, {7, 16384}, {8, 49152}, {9, 49152}};
   for (const auto &t : tiles)
     for (int more = 0; more <= (t[1] < 65536); ++more)
       for (int T : {24, 300, 4096}) {

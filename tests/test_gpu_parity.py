@@ -717,11 +717,12 @@ def test_compensator_units_behind_whole_tiles(ctx, rc, n_tokens, k, d_model):
     assert (out[0] - out[1]).abs().max().item() <= 1e-3 * out[0].abs().max().item()
 
 
-@pytest.mark.parametrize("variant", [5, 6, 7, 8])
+@pytest.mark.parametrize("variant", [5, 6, 7, 8, 9])
 @pytest.mark.parametrize("rc,ks", [(0, [1, 64, 65, 320]), (8, [1064, 56, 127, 440]), (64, [128, 129, 1064, 640]), (24, [1064] * 4)])
 def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
-    """The down-GEMM tiles that load the gathered rows straight into registers (128 x 512, 64 x 512, and 256 columns in two
-    k-groups, of which one has a step less where their number is odd): lists of one to seventeen steps of 64, ends inside a step, steps that hold neurons and compensator units, the identity list
+    """The down-GEMM tiles that load the gathered rows straight into registers (128 x 512, 64 x 512, 256 columns in two
+    k-groups, of which one has a step less where their number is odd, and 64 x 64 with eight wavefronts that take groups of 32
+    positions in turn, some of them none): lists of one to seventeen steps of 64, ends inside a step, steps that hold neurons and compensator units, the identity list
     of the dense call, a short last block, columns that fill no whole tile; whole lists, and all of them cut into 2, 5
     and 16 pieces, some of which hold nothing.  Against the oracle at the stated bars and against the tile with both
     operands in LDS (other order of the same fp32 sums: 1e-5)."""
@@ -751,8 +752,8 @@ def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
                                                     (256, 344, 256)])
 def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
     """Lists that hold every neuron are the identity list, with the compensator's rows behind it: calls for which the down
-    GEMM takes the 128 x 512 tile, (the second: a tile with both operands in LDS), the 64 x 512 and the 64 x 256 tile cut into
-    pieces and the 64 x 256 tile whole, with the weights in registers
+    GEMM takes the 128 x 512 tile, (the second: a tile with both operands in LDS), the 64 x 512 and the 64 x 64 tile cut into
+    pieces and the 64 x 64 tile whole, with the weights in registers
     (csrc/ff_launch_checks.hip holds that choice)."""
     c = Case(W.Shape("keepall", d_model, d_ffn, n_tokens, 256, 8, 24))
     ks = [d_ffn] * c.n_blocks
@@ -761,7 +762,7 @@ def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
     _check_both(c, ctx, idx, ks, ref.y, f"all of {d_ffn} neurons and 24 units, {n_tokens} tokens")
 
 
-@pytest.mark.parametrize("variant,longest", [(5, 49152), (6, 65536), (7, 16384), (8, 49152)])
+@pytest.mark.parametrize("variant,longest", [(5, 49152), (6, 65536), (7, 16384), (8, 49152), (9, 49152)])
 def test_largest_row_ids_and_longest_lists_in_registers(ctx, variant, longest):
     """The row-id table of the tiles with the weights in registers: ids up to 65535 (the last compensator unit behind 65528
     neurons), and the longest list whose table fits beside the tile (two bytes a position in what the ring leaves of
