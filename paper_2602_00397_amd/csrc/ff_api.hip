@@ -265,6 +265,12 @@ ff_status run_predict(ff_ctx *ctx, const ff_shape &s, const Layout &L, const voi
   p.z = reinterpret_cast<double *>(base + L.z);
   p.hpart = reinterpret_cast<double *>(base + L.hpart);
   p.scores = scores_opt ? scores_opt : reinterpret_cast<double *>(base + L.scores);
+  // narrower slices: no part of what a call needs, used where scratch has the room
+  const size_t fine_at = up(L.total, 256), have = scratch_base ? (size_t)FF_STATIC_SCRATCH_BYTES : ctx->ws_bytes;
+  if (have > fine_at) {
+    p.hpart_fine = reinterpret_cast<double *>(base + fine_at);
+    p.hpart_fine_bytes = have - fine_at;
+  }
   p.k = ks;
   p.k_stride = k_stride;
   p.indices = indices;
@@ -524,7 +530,8 @@ ff_status ff_workspace_bytes(const ff_shape *shape, int32_t k_max, size_t *bytes
   // (with room for the merged lists of short blocks, whether or not a call will use them)
   *bytes = std::max(make_layout(*shape, k_max).total,
                     make_layout(*shape, k_max, false, merge_factor(*shape, 160 * 1024)).total) +
-           ff_gemm2_split_bytes(shape->n_tokens, shape->d_model);
+           std::max(ff_gemm2_split_bytes(shape->n_tokens, shape->d_model),
+                    ff_pool_fine_bytes(shape->d_model, (int)(((size_t)shape->n_tokens + shape->block - 1) / shape->block), shape->r_pred));
   return FF_OK;
 }
 

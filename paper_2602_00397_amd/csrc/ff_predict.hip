@@ -203,6 +203,159 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
   }
 }
 
+// Pooling for calls whose blocks are few but not short.  Above, every workgroup of 512 channels, several of which share a slice's
+// outputs, converts and adds all rows in fp64, a wavefront every fourth of them, waits for two rounds of W1 behind that, and then one
+// thread adds up to 128 partial sums of an output.  Here a workgroup has 8 LW channels, LW lanes to a row, all rows of
+// a block of 128 on their way at once and W1's with them; the rows' sums go through lanes, then wavefronts, in fixed order, the
+// outputs' in eights.  Bound by latency: (the logits, the weights' exponentials,) one round of loads, five to eight barriers.  The price is
+// paid by the scores kernel, which adds up four or two times as many slices.  (ff_predict alone, us, the kernel above -> this:
+// softmax: 100 tokens of 4096/14336 23.2 -> 21.4, 2000 30.8 -> 29.3, 700 of 2048/8192 23.1 -> 19.6, 4096 27.0 -> 23.9, one block of 300
+// 27.4 -> 19.0, one of 4096 tokens of 4096/14336 165 -> 57; the mean: 700 of 2048/8192 17.1 -> 15.4, 250 of 4096/14336 17.7 ->
+// 16.6, blocks of 256 tokens of 3584/18944 28.9 -> 25.0, one block of 4096 of 4096/14336 107 -> 45.)
+// grid (slices of 8 LW channels, n_blocks)
+constexpr int kPoolFineThreads = 512;
+template <bool SOFTMAX, int LW>
+__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf16_t *__restrict__ x,
+                                                                       const double *__restrict__ z,
+                                                                       const bf16_t *__restrict__ w1,
+                                                                      double *__restrict__ hpart, int T,
+                                                                      int d_model, int Nb, int r) {
+  constexpr int NT = kPoolFineThreads, NW = NT / 64, CH = 8 * LW, RPW = 64 / LW, STEP = NW * RPW, U = LW / 4, WU = LW / 4;
+  __shared__ double red1[2 * NW];
+  // Nb <= 4096 weights; rows' sums [wavefront][channel]; the outputs' [8][thread] and [group][output]
+  __shared__ __align__(16) double ps[8 * NT];
+  double *p_s = ps;
+  __shared__ double a_s[CH];               // this workgroup's pooled channels
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int b = blockIdx.y, t0 = b * Nb, n = min(T, t0 + Nb) - t0;
+  const int c_base = blockIdx.x * CH, n_ch = min(CH, d_model - c_base);
+  const int sub = lane / LW, c8 = 8 * (lane % LW);
+  const bf16_t *xc = x + (size_t)t0 * d_model + c_base + min(c8, n_ch - 8);   // (channels past d_model: not used)
+  const int row0 = wave * RPW + sub;
+  uint4 v[U];
+  auto load_rows = [&](int i) __attribute__((always_inline)) {     // past the end: the last row again, not added
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4 *>(xc + (size_t)min(i + u * STEP, n - 1) * d_model);
+  };
+  const double z0 = SOFTMAX ? z[t0 + min(tid, n - 1)] : 0.0;
+  load_rows(row0);
+  // thread (cl, o) takes the outputs 8 o .. 8 o + 7 over the channels cl, cl + CL, ...
+  const int n_oct = r >> 3;                                     // <= 128
+  const int o_bits = n_oct > 1 ? 32 - __builtin_clz(n_oct - 1) : 0, o_ceil = 1 << o_bits, CL = NT >> o_bits;
+  const int o = tid & (o_ceil - 1), cl = tid >> o_bits;
+  const bf16_t *wp = w1 + (size_t)c_base * r + 8 * min(o, n_oct - 1);
+  uint4 wv[WU];
+  auto load_w1 = [&](int cq) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < WU; ++u) wv[u] = *reinterpret_cast<const uint4 *>(wp + (size_t)min(cq + u * CL, n_ch - 1) * r);
+  };
+  load_w1(cl);
+  __builtin_amdgcn_sched_barrier(0);
+  if (SOFTMAX) {
+    double m = -INFINITY;
+    for (int i = tid; i < n; i += NT) m = fmax(m, i == tid ? z0 : z[t0 + i]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+    if (lane == 0) red1[wave] = m;
+    __syncthreads();
+    m = red1[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmax(m, red1[w]);
+    double part = 0.0;
+    for (int i = tid; i < n; i += NT) {
+      const double e = exp((i == tid ? z0 : z[t0 + i]) - m);
+      p_s[i] = e;
+      part += e;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+    if (lane == 0) red1[NW + wave] = part;
+    __syncthreads();
+    double s = red1[NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red1[NW + w];
+    for (int i = tid; i < n; i += NT) p_s[i] = p_s[i] / s;
+    __syncthreads();
+  }
+  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int i = row0; i < n; i += U * STEP) {
+    if (i > row0) load_rows(i);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u * STEP < n) {
+        double xv[8];
+        unpack8(v[u], xv);
+        const double w = SOFTMAX ? p_s[i + u * STEP] : 1.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = SOFTMAX ? fma(w, xv[j], acc[j]) : acc[j] + xv[j];
+      }
+  }
+#pragma unroll
+  for (int off = LW; off < 64; off <<= 1)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], off);
+  if (SOFTMAX) __syncthreads();            // (the weights have been read)
+  if (sub == 0) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) *reinterpret_cast<double2 *>(&ps[wave * CH + c8 + j]) = make_double2(acc[j], acc[j + 1]);
+  }
+  __syncthreads();
+  if (tid < CH) {
+    double tot = ps[tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) tot += ps[w * CH + tid];
+    a_s[tid] = SOFTMAX ? tot : tot / (double)n;
+  }
+  __syncthreads();
+  double acc8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int cq = cl; cq < n_ch; cq += WU * CL) {
+    if (cq > cl) {
+      load_w1(cq);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < WU; ++u)
+      if (cq + u * CL < n_ch) {
+        double wd[8];
+        unpack8(wv[u], wd);
+        const double av = a_s[cq + u * CL];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc8[q] = fma(av, wd[q], acc8[q]);
+      }
+  }
+  // ps[q][cl][o]; an output's CL sums are added in eights, then those
+#pragma unroll
+  for (int q = 0; q < 8; ++q) ps[q * NT + tid] = acc8[q];
+  __syncthreads();
+  double *dst = hpart + ((size_t)b * gridDim.x + blockIdx.x) * r;
+  const int cols = 8 << o_bits, per = min(8, CL), G = CL / per;     // cols * G = 8 NT / per
+  double sum[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {                                    // (cols = 1024: two outputs a thread)
+    const int e = tid + h * NT, j = e & (cols - 1), g = e / cols;
+    sum[h] = 0.0;
+    if (g < G) {
+      const double *src = &ps[(j >> o_bits) * NT + g * per * o_ceil + (j & (o_ceil - 1))];
+      for (int q = 0; q < per; ++q) sum[h] += src[q * o_ceil];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = tid + h * NT;
+    if (e < cols * G) ps[e] = sum[h];
+  }
+  __syncthreads();
+  for (int j = tid; j < cols; j += NT) {
+    const int oo = j & (o_ceil - 1);
+    if (oo < n_oct) {
+      double tot = 0.0;
+      for (int g = 0; g < G; ++g) tot += ps[g * cols + j];
+      dst[8 * oo + (j >> o_bits)] = tot;
+    }
+  }
+}
+
 // ---- Eq. 13 in float64 ---------------------------------------------------------------------
 // The first layer (long contraction over d_model, few outputs) is cut into slices of 512 channels that
 // ride along with the pooling kernel above; the second (short contraction, d_ffn outputs) takes MLP_BB
@@ -317,7 +470,15 @@ __global__ __launch_bounds__(THREADS) void ff_scores_split_kernel(const double *
     if (i < nb) {
       const double *src = hpart + (size_t)(b0 + i) * n_slices * r + j;
       int s = 0;
-      for (; s + 8 <= n_slices; s += 8) {      // eight loads in flight, added in slice order
+      for (; s + 16 <= n_slices; s += 16) {    // (finer slices) sixteen, then eight loads in flight, added in slice order
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = src[(size_t)(s + u) * r];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc += v[u];
+      }
+      for (; s + 8 <= n_slices; s += 8) {
         double v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(s + u) * r];
@@ -949,8 +1110,21 @@ static topk_reg_t topk_reg_pick(int half, std::integer_sequence<int, H...>) {
 }
 static topk_reg_t topk_reg_kernel(int half) { return topk_reg_pick(half, std::make_integer_sequence<int, 16>{}); }
 
+// Lanes to a row of ff_pool_fine_kernel (0: it does not apply).  128 channels to a workgroup as long as a workgroup of the scores kernel
+// then has at most 4096 partial sums to add, else 256 (1200 tokens of 3584/18944 in blocks of 256 favour 128, 29.6 against 30.5 us,
+// 2000 of 4096/14336 256, 21.4 against 23.2).
+static int pool_fine_lanes(int d_model, int n_blocks, int r) {
+  if ((d_model + 511) / 512 * n_blocks > 128 || r <= 0 || r % 8 != 0) return 0;
+  return (n_blocks <= 2 ? 1 : MLP_BB) * r * ((d_model + 127) / 128) <= 4096 ? 16 : 32;
+}
+size_t ff_pool_fine_bytes(int d_model, int n_blocks, int r) {
+  const int ch = 8 * pool_fine_lanes(d_model, n_blocks, r);
+  return ch == 0 ? 0 : (size_t)n_blocks * ((d_model + ch - 1) / ch) * r * sizeof(double);
+}
+
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
-  const int n_slices = (p.d_model + 511) / 512;
+  int n_slices = (p.d_model + 511) / 512;
+  double *hpart = p.hpart;
   // Few blocks: the first layer's outputs are shared out over up to 8 workgroups per slice (each pools the slice again),
   // at least 32 outputs each, until there is one for every CU (d_model 4096, r 128: one token 7.5 -> 5.3 us, a block of
   // 100 9.0 -> 7.5, 16 blocks 12.8 -> 11.6).  How many share them decides which channels are summed together first, so the
@@ -958,15 +1132,23 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   int oz = 256 / (n_slices * p.n_blocks);
   oz = std::max(1, std::min({oz, 8, p.r / 32}));
   prof_begin(prof, FF_STAGE_POOL, s);
-  if (p.q_pred) {
-    hipLaunchKernelGGL(ff_logits_kernel, dim3((p.T + 3) / 4), dim3(256), 0, s, p.x, p.q_pred, p.z,
-                       p.T, p.d_model);
+  // Short blocks' rows are few loads anyhow, and the scores kernel's further slices cost 0.5 to 1 us (softmax: 160 tokens of 3584/18944 in
+  // blocks of 32 27.1 -> 27.6, 256 of 256/688 in blocks of 64 16.5 -> 16.2; the mean: 64 tokens of 4096/14336 16.7 -> 17.1, 100 16.7 -> 16.4).
+  const size_t fine_bytes = std::min(p.T, p.block) >= (p.q_pred ? 64 : 96) ? ff_pool_fine_bytes(p.d_model, p.n_blocks, p.r) : 0;
+  if (p.q_pred) hipLaunchKernelGGL(ff_logits_kernel, dim3((p.T + 3) / 4), dim3(256), 0, s, p.x, p.q_pred, p.z, p.T, p.d_model);
+  if (fine_bytes > 0 && p.hpart_fine_bytes >= fine_bytes) {
+    const int lw = pool_fine_lanes(p.d_model, p.n_blocks, p.r);
+    hpart = p.hpart_fine;
+    n_slices = (p.d_model + 8 * lw - 1) / (8 * lw);
+    hipLaunchKernelGGL(lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>) : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>), dim3(n_slices, p.n_blocks), dim3(kPoolFineThreads), 0, s,
+                       p.x, p.q_pred ? p.z : nullptr, p.w1, hpart, p.T, p.d_model, p.block, p.r);
+  } else if (p.q_pred) {
     hipLaunchKernelGGL(ff_pool_kernel<true>, dim3(n_slices, p.n_blocks, oz), dim3(256),
-                       (size_t)p.block * sizeof(double), s, p.x, p.z, p.w1, p.hpart, p.T, p.d_model,
+                       (size_t)p.block * sizeof(double), s, p.x, p.z, p.w1, hpart, p.T, p.d_model,
                        p.block, p.r);
   } else {
     hipLaunchKernelGGL(ff_pool_kernel<false>, dim3(n_slices, p.n_blocks, oz), dim3(256),
-                       0, s, p.x, (const double *)nullptr, p.w1, p.hpart, p.T, p.d_model, p.block, p.r);
+                       0, s, p.x, (const double *)nullptr, p.w1, hpart, p.T, p.d_model, p.block, p.r);
   }
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_MLP, s);
@@ -977,13 +1159,13 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   // 64 blocks at d_ffn 14336 take 21.4 us as they are, 23.0 this way: every workgroup forms the hidden units again.)
   if (p.n_blocks <= 2) {
     hipLaunchKernelGGL((ff_scores_split_kernel<1, 32, 1024>), dim3((p.d_ffn + 127) / 128, p.n_blocks), dim3(1024),
-                       (size_t)p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);
+                       (size_t)p.r * sizeof(double), s, hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);
   } else if (n_groups * ((p.d_ffn + 1023) / 1024) <= 128) {
     hipLaunchKernelGGL((ff_scores_split_kernel<MLP_BB, 64, 512>), dim3((p.d_ffn + 255) / 256, n_groups), dim3(512),
-                       (size_t)MLP_BB * p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);
+                       (size_t)MLP_BB * p.r * sizeof(double), s, hpart, p.w2, p.scores, p.n_blocks, p.r, n_slices, p.d_ffn);
   } else {
     hipLaunchKernelGGL(ff_scores_kernel, dim3((p.d_ffn + 1023) / 1024, n_groups), dim3(256),
-                       (size_t)MLP_BB * p.r * sizeof(double), s, p.hpart, p.w2, p.scores, p.n_blocks, p.r,
+                       (size_t)MLP_BB * p.r * sizeof(double), s, hpart, p.w2, p.scores, p.n_blocks, p.r,
                        n_slices, p.d_ffn);
   }
   prof_end(prof, s);

@@ -1096,6 +1096,44 @@ def test_predictor_few_blocks(ctx, n_blocks, df, r):
     _assert_indices(idx, ref.indices, ks)
 
 
+@pytest.mark.parametrize("with_q", [False, True])
+@pytest.mark.parametrize("dm,r,T,block", [(128, 8, 96, 96), (640, 32, 257, 128), (640, 264, 385, 128), (1152, 72, 300, 300), (384, 1024, 97, 128),
+                                          (896, 40, 1111, 100), (2048, 16, 3001, 96), (1664, 520, 130, 129), (256, 64, 4096, 4096)])
+def test_pooling_of_few_long_blocks(ctx, dm, r, T, block, with_q):
+    """Narrow channel slices: one or several blocks, the last one short, both slice widths (the last slice part-filled), up to more
+    rows than are loaded at once, 8 to 1024 outputs; and the smallest workspace that a call accepts, which leaves no room for
+    them.  Scores to 1e-12 of the oracle's (fp64 sums in another order), lists bit-exact."""
+    df = 264
+    shp = W.Shape(f"long{dm}_{r}", dm, df, T, block, r, 8)
+    c = Case(shp, with_q=with_q, seed=11 + dm + r)
+    ks = [max(1, df // 3)] * c.n_blocks
+    ref = c.oracle_layer(ks, compute_ffn=False)
+    q = _f32(c.lt.q_pred) if with_q else None
+    x = _f32(c.x_bits)
+    ref_s = np.stack([O.predictor_scores(x[b * block:min(T, (b + 1) * block)], q, c.host("w1"), c.host("w2")) for b in range(c.n_blocks)])
+    small = B.Context(0)
+    try:
+        idx, sc = c.gpu_predict(ctx, ks, k_stride=max(ks), scores=True)
+        lo, hi = 0, B.workspace_bytes(c.shape, max(ks))         # bytes that are refused, bytes that are enough
+        ws = torch.empty(hi, dtype=torch.uint8, device=DEV)
+        idx_s, sc_s = torch.empty_like(idx), torch.empty_like(sc)
+        while hi - lo > 256:
+            mid = (lo + hi) // 512 * 256
+            small.set_workspace(ws[:mid])
+            try:
+                small.predict(c.shape, c.x, c.pred, ks, max(ks), idx_s, sc_s)
+                hi = mid
+            except B.FFError:
+                lo = mid
+        small.set_workspace(ws[:hi])
+        small.predict(c.shape, c.x, c.pred, ks, max(ks), idx_s, sc_s)
+        for i, s, what in ((idx, sc, "room for them"), (idx_s, sc_s, "smallest workspace")):
+            np.testing.assert_allclose(s.cpu().numpy(), ref_s, rtol=1e-12, atol=1e-13 * np.abs(ref_s).max(), err_msg=what)
+            _assert_indices(i, ref.indices, ks)
+    finally:
+        small.close()
+
+
 def test_diagnostic_calls(ctx):
     a = torch.arange(1 << 20, dtype=torch.int32, device=DEV)
     b = torch.zeros_like(a)
