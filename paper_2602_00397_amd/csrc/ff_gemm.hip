@@ -1738,12 +1738,13 @@ constexpr int kNumCU = 256;
 // (Gate/up launch, always eight groups against this rule: 4096/14336, K 7168, 128-token blocks: 1 block 130 -> 69 us,
 // 4 blocks 141 -> 79, 12 blocks 241 -> 192; 65 blocks of 77: 938 -> 894; 64 blocks unchanged; 3584/18944 dense, 300
 // tokens: 459 -> 185, 9001 tokens 2264 -> 2038, and the down launch 1715 -> 1260.)
-// Among grids of no more rounds, the one that fetches less from beyond an XCD's L2: an XCD holds 32 tiles at a time, as many
+// Among grids of no more rounds, or all of one round, the one that fetches less from beyond an XCD's L2: an XCD holds 32 tiles at a time, as many
 // of its blocks as it has and the rest tiles of the same block.  A weight line is fetched once for those of its resident
 // blocks that keep the neuron, a line of X once for the resident tiles of its block, so more blocks and fewer tiles pay where
 // blocks are short and lists sparse.  Fewer groups of blocks have to save a sixth of it.  (4096/14336, eight groups against
 // this: 64 blocks of 64, K 3584: gate/up 343 -> 333 us, down 147 -> 138; 64 blocks of 128, K 7168: down 397 -> 389; 2048/8192,
-// 32 blocks of 128, K 4096: both 1% less.)
+// 32 blocks of 128, K 4096: both 1% less; eight blocks of 128, K 7168, one round of 128 x 256: the call 230 -> 203, 15 of K 3584
+// 189 -> 175.)  Two blocks in one round stay apart: they would share too little (256 tokens of 4096/14336 79.6 -> 83.5).
 struct Share {
   int w_rows, x_rows;   // a tile's rows (or their pieces) of weights and of X or H, in proportion to the bytes
   double keep;          // share of the neurons on a list; 0: tiles that share nothing to speak of
@@ -1759,7 +1760,7 @@ static int xcd_groups(long V, long N, const Share &sh) {
     if (xs == 3) best_cost = cost[xs] * 31.0 / 32.0;
     else if (cost[xs] < best_cost) { best = xs; best_cost = cost[xs]; }
   }
-  if (sh.keep <= 0.0 || cost[best] <= 1.0) return best;
+  if (sh.keep <= 0.0 || (cost[best] <= 1.0 && V <= 2)) return best;
   auto fetch = [&](int xs) {
     const long blocks = std::min<long>((V + (1 << xs) - 1) >> xs, kNumCU / 8);
     const long tiles = std::min<long>((N + (8 >> xs) - 1) / (8 >> xs), std::max<long>(1, kNumCU / 8 / blocks));
@@ -1767,9 +1768,9 @@ static int xcd_groups(long V, long N, const Share &sh) {
     for (long l = 0; l < std::max<long>(1, blocks / sh.mt); ++l) none *= 1.0 - sh.keep;
     return sh.w_rows * (1.0 - none) / ((double)blocks * sh.keep) + (double)sh.x_rows / (double)tiles;
   };
-  const int rounds_best = best;
+  const double rounds_best = std::max(1.0, cost[best]);
   for (int xs = best - 1; xs >= 0; --xs)
-    if (cost[xs] <= cost[rounds_best] && fetch(xs) < fetch(best) * 5.0 / 6.0) best = xs;
+    if (cost[xs] <= rounds_best && fetch(xs) < fetch(best) * 5.0 / 6.0) best = xs;
   return best;
 }
 // what the tiles of variant v share in a launch of these parameters
@@ -1831,6 +1832,9 @@ constexpr Gemm1Cost kGemm1Short[] = {{kGemm1Direct64, 0.74}, {5, 0.90}, {0, 0.52
 constexpr Gemm1Cost kGemm1Mid[] = {{0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};                      // up to 255
 constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};           // 256 and more, and without a list
 
+// The 128 x 256 tile's round where it competes with 128 x 128 for lists of equal length: two of those take 1.08 of it (fitted to 46 calls).
+constexpr double kWideRound = 0.96;
+
 hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, int k_likely, hipStream_t s) {
   Gemm1Params p = p_in;
   if (p.idx != nullptr) p.block = std::min(p.block, p.T);   // (one short block: tiles for the tokens that there are)
@@ -1861,27 +1865,43 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
     }
     if (variant < 0) return hipErrorInvalidValue;
     if (p.block > 64 && p.block < 256) {
-      // The 128 x 256 tile (with the weights in registers where it can address them) moves fewer bytes per FLOP; its part-filled last tile goes to the remainder
-      // launch (with lists of unequal length every block's own).  In rounds of it: whole rounds of full wide
-      // tiles plus 0.22 per round of remainder tiles, plus the launch of the few much longer lists' ends (half a
-      // round of tiles at most, 0.4; else further wide tiles).  (Measured, wide
-      // against 128 x 128: 4096/14336 x 64 blocks K 7168 0.888 / 0.916 ms, K 7300 0.895 / 0.920, K 3584 -- 3.5
-      // rounds of wide tiles -- 0.520 / 0.490; 16 blocks of 7168 with the first and last dense 0.332 / 0.267;
-      // 3584/18944 x 128 blocks K 13126 2.75 / 2.86; 2048/8192 x 32 blocks K 4200 0.155 / 0.172.)
+      // The 128 x 256 tile (with the weights in registers where it can address them) moves fewer bytes per FLOP.  It takes lists whole, or
+      // leaves its part-filled last tile to the remainder launch (with lists of unequal length every block's own): 0.03 rounds and 0.15 per 8192
+      // tokens if that is compensator units alone, nothing if half a tile of them (they cost the main launch as much), else 0.22 per round
+      // of remainder tiles.  Rounds are those of the busiest XCD: a whole chip's count took 252 tiles of 18 blocks for one round, and no XCD split
+      // of them is.  (ff_sparse_ffn, us, lists cut and rounds of the whole chip -> this: 4096/14336: 700 tokens, K 7168 182 -> 173, 2000 356 ->
+      // 338; 2200, K 3584 311 -> 232; 1400, K 5734 315 -> 257; 2900 478 -> 431; 2000, K 10752 515 -> 500; 3584/18944: 480 tokens, K
+      // 9472 170 -> 156, 4000 771 -> 740; 1600, K 4736 282 -> 227; 2048/8192: 900 tokens, K 4096 92 -> 91; 2050, K 2048 107 -> 89.  Of
+      // 70 calls from 200 to 11000 tokens 3 chose a tile more than 2% slower than the fastest: 5, 6 and 7%.)
+      // A few much longer lists: the launch of their ends besides (half a round of tiles at most, 0.4; else further wide tiles).
+      // (Measured, wide against 128 x 128: 4096/14336, 16 blocks of 7168 with the first and last dense 0.332 / 0.267 ms.)
       const int wide = gemm1_direct_addresses(p) ? kGemm1Direct128 : kWide128;
       const Variant &w = kGemm1[wide];
-      const int rem_w = base_extent % w.bn;
-      const long wide_full = (long)p.n_blocks * (base_extent / w.bn);
-      const long rem_wgs = (long)p.n_blocks * 2 * ((rem_w + 63) / 64);
-      const long surplus = (long)p.k.n_heavy * (n_extent / w.bn - base_extent / w.bn);
-      const bool surplus_own = surplus > 0 && 2 * surplus <= kNumCU;
-      const double cost_wide = (double)((wide_full + (surplus_own ? 0 : surplus) + kNumCU - 1) / kNumCU) + (surplus_own ? 0.4 : 0.0) +
-                               0.22 * (double)((rem_wgs + kNumCU - 1) / kNumCU);
-      // (merged lists: only a bound of their lengths is known here)
-      const bool unknown = ragged && p.k.n_heavy == 0;
-      if (split != 0 && w.lds <= g_lds_limit && base_extent >= w.bn && (unknown || cost_wide <= best) && wide_full >= 224) {
-        variant = wide;
-        if (rem_w > 0 || ragged) split = 1;
+      const int n_full = base_extent / w.bn, rem_w = base_extent % w.bn;
+      if (w.lds > g_lds_limit) {
+      } else if (!ragged) {
+        const long V = (long)p.n_blocks * ((p.block + w.bm - 1) / w.bm);
+        const bool behind = n_full * w.bn >= p.k.k_max && n_full * w.bn % 64 == 0;      // nothing but compensator units is left
+        const double rest = rem_w == 0 || (behind && rem_w <= 32) ? 0.0 : behind ? 0.03 + 0.15 * p.T / 8192.0 : 0.22 * (double)((2 * V * ((rem_w + 63) / 64) + kNumCU - 1) / kNumCU);
+        const double whole = (double)xcd_rounds(V, (up64(base_extent) + w.bn - 1) / w.bn);
+        const double cut = n_full == 0 ? 1e30 : (double)xcd_rounds(V, n_full) + rest;
+        if (kWideRound * (split == 0 ? whole : split > 0 ? cut : std::min(whole, cut)) <= best) {
+          variant = wide;
+          if (split < 0) split = rem_w > 0 && cut <= whole;
+        }
+      } else {
+        const long wide_full = (long)p.n_blocks * n_full;
+        const long rem_wgs = (long)p.n_blocks * 2 * ((rem_w + 63) / 64);
+        const long surplus = (long)p.k.n_heavy * (n_extent / w.bn - n_full);
+        const bool surplus_own = surplus > 0 && 2 * surplus <= kNumCU;
+        const double cost_wide = (double)((wide_full + (surplus_own ? 0 : surplus) + kNumCU - 1) / kNumCU) + (surplus_own ? 0.4 : 0.0) +
+                                 0.22 * (double)((rem_wgs + kNumCU - 1) / kNumCU);
+        // (merged lists: only a bound of their lengths is known here)
+        const bool unknown = p.k.n_heavy == 0;
+        if (split != 0 && n_full > 0 && (unknown || cost_wide <= best) && wide_full >= 224) {
+          variant = wide;
+          split = 1;
+        }
       }
     }
   }

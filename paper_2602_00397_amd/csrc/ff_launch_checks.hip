@@ -150,12 +150,30 @@ static void check_gemm1_splits() {
       {{4096, 64, 4096, 14336, 64, 3584, 0, 0}, 1, 0},  {{3000, 64, 4096, 14336, 64, 7168, 0, 0}, 1, 0},    // 3.5 and 5.1 rounds
       {{1845, 128, 2048, 8192, 32, 4096, 8192, 2}, 1, 0},  {{3732, 64, 2048, 8192, 32, 4096, 8192, 2}, 1, 0},    // two longer lists
       {{1907, 64, 4096, 14336, 64, 10752, 14336, 2}, 1, 0},
-      {{8192, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 256}, {{8193, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 129},
+      {{8192, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 256}, {{9153, 128, 4096, 14336, 64, 7168, 0, 0}, 2, 144},
       {{2126, 64, 4096, 14336, 64, 7160, 0, 0}, 2, 67},   // units from the ninth on
       {{2126, 64, 4096, 14336, 64, 7180, 0, 0}, 2, 72}, {{8192, 128, 4096, 14336, 64, 7180, 0, 0}, 2, 256}};   // lists that end inside a tile
   for (const auto &c : calls) {
     CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && g_log.size() == c.launches, "T %d block %d K %d: %zu launches", c.s.T, c.s.block, c.s.k, g_log.size());
     if (c.launches > 1 && g_log.size() > 1) CHECK(g_log[1].g1.rem_bn == 256 && g_log[1].grid == c.rem_grid, "T %d K %d: grid %u", c.s.T, c.s.k, g_log[1].grid);
+  }
+}
+
+// Gate/up: the 128 x 256 tile (11) against the 128 x 128 one (0) goes by the rounds of the busiest XCD, lists whole or their
+// ends in a launch of their own.
+static void check_gemm1_wide() {
+  struct { Shape s; bool wide; size_t launches; } calls[] = {
+      {{2200, 128, 4096, 14336, 64, 3584, 0, 0}, false, 2},   // 252 tiles that no split over the XCDs takes in one round
+      {{2000, 128, 4096, 14336, 64, 7168, 0, 0}, true, 1},    // two rounds either way: whole
+      {{1000, 128, 4096, 14336, 64, 7168, 0, 0}, true, 1},   {{1200, 128, 4096, 14336, 64, 7168, 0, 0}, false, 1},
+      {{900, 128, 2048, 8192, 32, 4096, 0, 0}, true, 2},      // half a tile of units: cut
+      {{4500, 128, 4096, 14336, 64, 7168, 0, 0}, true, 2},    // whole: a fifth round
+      {{2800, 200, 4096, 14336, 64, 7168, 0, 0}, false, 1}};  // two token tiles to a block
+  for (const auto &c : calls) {
+    gemm1(c.s, true, 11, 0, -1);
+    const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
+    CHECK(gemm1(c.s, true, -1, -1, -1) == hipSuccess && (g_log[0].fn == fn) == c.wide && g_log.size() == c.launches, "T %d K %d", c.s.T, c.s.k);
+    for (int split : {0, 1}) CHECK(gemm1(c.s, true, -1, split, -1) == hipSuccess && g_log.size() <= (split ? 2u : 1u), "T %d K %d split %d", c.s.T, c.s.k, split);
   }
 }
 
@@ -361,6 +379,7 @@ int main() {
             for (int heavy : {-1, 0, 2}) check_gemm1({T, block, dm, 14336, rc, k, 14336, heavy});
   check_gemm1_addresses();
   check_gemm1_splits();
+  check_gemm1_wide();
   check_gemm1_short_block();
   check_gemm2_addresses();
   check_gemm2_routes();
