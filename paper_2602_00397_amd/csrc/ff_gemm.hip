@@ -2029,10 +2029,14 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 // operands in LDS, 66.5 with the weights in registers).  The 64 x 64 tiles: see their kernel; with one or two tiles of tokens, one
 // on each CU, a step takes 0.25 to 0.3, with four 0.35 to 0.45 (200 tokens of 4096/14336, K 3584: at 0.33 throughout they would be
 // taken, 65.8 -> 68.3; at 0.41 the gains of 3 to 8% on 9 to 100 tokens of 4096/14336 would be lost).
+// (The figures of the tiles in registers of 512, 256 and, below 128 tokens, 256 columns are fitted to every tile and cut of 127 calls.  Calls, us,
+// by the figures before, 1.25 .. 1.6, 0.8 .. 0.95 and 0.45 .. 1.1 a step, and by these: 2048/8192, 1350 tokens 117 -> 111, first and
+// last block dense 520 122 -> 110, 850 138 -> 127, 4096 298 -> 285, dense 850 105 -> 98; 4096/14336, 2300 in blocks of 64 602 -> 574; 3584/18944,
+// both ends dense 520 349 -> 323.  Of 244 calls from 12 to 16000 tokens the geometric mean is 1.005.)
 // The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
 struct Gemm2Cost { int variant; double idle, full, fixed; };
-constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.25, 1.6, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
-                                     {kDirect128Narrow, 0.8, 0.95, 9.0}, {kDirect64Narrow, 0.45, 1.1, 6.0}, {kSplit64, 0.25, 0.33, 5.0},
+constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.15, 1.7, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
+                                     {kDirect128Narrow, 0.61, 0.95, 9.0}, {kDirect64Narrow, 0.53, 0.69, 8.7}, {kSplit64, 0.25, 0.33, 5.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
 static bool gemm2_direct(int variant) { return variant >= kDirect128; }
 // Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
@@ -2130,9 +2134,11 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
         const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N * n + (8 >> xs) - 1) / (8 >> xs));   // of the busiest XCD
         const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
         // (64 x 64 tiles fetch every row once for each 64 tokens: more than two such tiles of tokens make each other wait)
-        const double full = g.variant == kSplit64 && V > 2 ? 0.37 : g.full;
-        double cost = (double)(tiles / (kNumCU / 8)) * (g.fixed + steps * full);
-        if (busy > 0.0) cost += g.fixed + steps * (g.idle + (full - g.idle) * busy);
+        // (one or two tiles of 64 tokens share no rows between the 64 x 256 ones of a column: a full chip of those runs at HBM's rate)
+        const bool alone = g.variant == kDirect64Narrow && V <= 2;
+        const double full = g.variant == kSplit64 && V > 2 ? 0.37 : alone ? 1.1 : g.full, idle = alone ? 0.45 : g.idle, fixed = alone ? 6.0 : g.fixed;
+        double cost = (double)(tiles / (kNumCU / 8)) * (fixed + steps * full);
+        if (busy > 0.0) cost += fixed + steps * (idle + (full - idle) * busy);
         if (n > 1) cost += 3.0 + (double)n * (double)per_piece / 3.3e6;
         if (heavy_cut) {
           const long heavy = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;

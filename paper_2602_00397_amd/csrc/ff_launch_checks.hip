@@ -233,7 +233,8 @@ static void check_gemm2_addresses() {
 static void check_gemm2_routes() {
   struct { Shape s; bool list; int variant, row_mode; bool cut; } routes[] = {
       {{9000, 256, 1024, 1064, 24, 1064, 0, 0}, false, 5, -1, false},   // the identity list with compensator rows behind it
-      {{150, 256, 4096, 4096, 24, 4096, 0, 0}, false, 6, -1, true},
+      {{150, 256, 4096, 4096, 24, 4096, 0, 0}, false, 8, -1, true},
+      {{160, 256, 4096, 8192, 24, 8192, 0, 0}, false, 6, -1, true},
       {{60, 256, 2048, 4096, 24, 4096, 0, 0}, false, 9, -1, true},
       {{256, 256, 256, 344, 24, 344, 0, 0}, false, 9, -1, false},
       {{3000, 64, 512, 65536, 16, 3000, 0, 0}, true, 3, 2, true}};     // ids of more than 16 bits: scalar loads

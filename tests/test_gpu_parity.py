@@ -749,11 +749,11 @@ def test_down_gemm_with_weights_in_registers(ctx, variant, rc, ks):
 
 
 @pytest.mark.parametrize("d_model,d_ffn,n_tokens", [(1024, 1064, 9000), (2048, 4096, 300), (4096, 4096, 150), (2048, 4096, 60),
-                                                    (256, 344, 256)])
+                                                    (256, 344, 256), (4096, 8192, 160)])
 def test_every_neuron_kept_next_to_a_compensator(ctx, d_model, d_ffn, n_tokens):
     """Lists that hold every neuron are the identity list, with the compensator's rows behind it: calls for which the down
-    GEMM takes the 128 x 512 tile, (the second: a tile with both operands in LDS), the 64 x 512 and the 64 x 64 tile cut into
-    pieces and the 64 x 64 tile whole, with the weights in registers
+    GEMM takes the 128 x 512 tile, (the second: a tile with both operands in LDS), the 64 x 256 and the 64 x 64 tile cut into
+    pieces, the 64 x 64 tile whole and the 64 x 512 tile cut into pieces, with the weights in registers
     (csrc/ff_launch_checks.hip holds that choice)."""
     c = Case(W.Shape("keepall", d_model, d_ffn, n_tokens, 256, 8, 24))
     ks = [d_ffn] * c.n_blocks
