@@ -17,6 +17,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's first plain arguments come in scalar registers instead of being its first load (ff_predict, three dependent
+    # launches: one token of 4096/14336 16.0 -> 15.2 us, 100 tokens 16.8 -> 16.0; the smallest configuration's call 27.9 -> 27.4)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
     "-Wno-unused-command-line-argument",
 ]
