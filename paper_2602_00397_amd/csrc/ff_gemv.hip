@@ -33,11 +33,9 @@ __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, f3
 __device__ __forceinline__ f32x16_t mfma32(const u32x4_t &a, const u32x4_t &b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-// list length of block b; without a list (dense: position p is row p) the pitch does not bound it
-__device__ __forceinline__ int gv_block_k(const GemvParams &p, int b) {
-  int K = p.k.per_block ? p.k.per_block[b] : p.k.uniform;
-  K = max(1, min(K, p.d_ffn));
-  return p.idx ? min(K, p.k_stride) : K;
+// list length of block b, at most cap
+__device__ __forceinline__ int gv_block_k(const int32_t *per_block, int uniform, int cap, int b) {
+  return max(1, min(per_block ? per_block[b] : uniform, cap));
 }
 __device__ __forceinline__ float gv_act(int act, float g) {
   if (act == FF_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
@@ -54,23 +52,26 @@ __device__ __forceinline__ float gv_act(int act, float g) {
 // end next to each other (a dense token, 8 wavefronts: with 4 steps 54.5 us, with 2 52.6).  How many wavefronts: gemv1_waves.
 // With multiply-adds, a wavefront per position, a dense token of 4096/14336 took 44.5 us (now 45.5), one on a list of 7168 23.2
 // (22.6), one on 4096 positions of 8192/28672 86.1 (87.5), five tokens on 4096 positions of 2048/8192 19.5 (12.3).
+// What the first loads' addresses need comes as plain arguments, which are in scalar registers at the start (five tokens on a kept list
+// of 2048/8192, both kernels 19.6 -> 19.1 us).
 // grid (groups of 16 positions, n_blocks), LDS = gemv1_lds.
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : 6)))
-void ff_gemv1_kernel(GemvParams p, int steps) {
+void ff_gemv1_kernel(const int32_t *idx, const int32_t *per_block, const bf16_t *x, int uniform, int cap, int k_stride, int rc, int T, int block,
+                     int d_model, int steps, GemvParams p) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, half = lane >> 5;
   const int b = blockIdx.y;
-  const int t0 = b * p.block;
-  const int nt = min(p.T, t0 + p.block) - t0;          // <= kGemvMaxTokens by the launcher's check
-  const int Kb = gv_block_k(p, b);
-  const int ntot = Kb + p.rc;
+  const int t0 = b * block;
+  const int nt = min(T, t0 + block) - t0;          // <= kGemvMaxTokens by the launcher's check
+  const int Kb = gv_block_k(per_block, uniform, cap, b);
+  const int ntot = Kb + rc;
   const int pos0 = blockIdx.x * kGemv1Pos;
   // (the counters of the next kernel's column groups start at zero)
   if (blockIdx.x == 0)
-    for (int i = tid; i < p.d_model / kGemv2Cols; i += NW * 64) p.counter[b * (p.d_model / kGemv2Cols) + i] = 0;
+    for (int i = tid; i < d_model / kGemv2Cols; i += NW * 64) p.counter[b * (d_model / kGemv2Cols) + i] = 0;
   if (pos0 >= (ntot + 31) / 32 * 32) return;
   // load j of a step: chunk (lane mod 4) + 4 (lane / 32) of row j + 4 (lane / 4 mod 8), gate rows in front of the up rows
   // (positions past the list's end: the last one's rows again; H is written as zero there)
@@ -79,24 +80,24 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int pos = min(pos0 + j + 4 * ((lane >> 2) & 3), ntot - 1);
-    entry[j] = p.idx ? p.idx[(size_t)b * p.k_stride + min(pos, Kb - 1)] : pos;
+    entry[j] = idx ? idx[(size_t)b * k_stride + min(pos, Kb - 1)] : pos;
   }
   const int ch0 = wave * steps * 64;                             // this wavefront's first channel
-  const int n = max(0, min(p.d_model - ch0, steps * 64)) / 64;   // its steps
+  const int n = max(0, min(d_model - ch0, steps * 64)) / 64;   // its steps
   const int pitch = n * 128;                                     // bytes per token in LDS
-  uint8_t *xs = smem + (size_t)nt * min(ch0, p.d_model) * 2;
+  uint8_t *xs = smem + (size_t)nt * min(ch0, d_model) * 2;
   const int nc = n * 8;                                          // 16-byte chunks per token
   for (int t = 0; t < nt; ++t)
     for (int c0 = 0; c0 < nc; c0 += 64)
       if (c0 + lane < nc)
-        gload_lds16(p.x + (size_t)(t0 + t) * p.d_model + ch0 + ((c0 + lane) ^ t) * 8, lds_addr_of(xs) + (uint32_t)(t * pitch + c0 * 16));
+        gload_lds16(x + (size_t)(t0 + t) * d_model + ch0 + ((c0 + lane) ^ t) * 8, lds_addr_of(xs) + (uint32_t)(t * pitch + c0 * 16));
   __builtin_amdgcn_sched_barrier(0);
   const bf16_t *rows[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int pos = min(pos0 + j + 4 * ((lane >> 2) & 3), ntot - 1);
-    const bf16_t *row = pos < Kb ? (up ? p.wu : p.wg) + (size_t)min(max(entry[j], 0), p.d_ffn - 1) * p.d_model
-                                 : p.wc1 + (size_t)(pos - Kb) * p.d_model;
+    const bf16_t *row = pos < Kb ? (up ? p.wu : p.wg) + (size_t)min(max(entry[j], 0), p.d_ffn - 1) * d_model
+                                 : p.wc1 + (size_t)(pos - Kb) * d_model;
     rows[j] = row + ch0 + ((lane & 3) + 4 * half) * 8;
   }
   constexpr int U = 2;
@@ -152,7 +153,7 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
   }
   const int pos = pos0 + pp;
   float hv = pos < Kb ? gv_act(FF_ACT_SILU, g) * u : (pos < ntot ? gv_act(p.comp_act, g) : 0.0f);
-  if (p.mask != nullptr && pos < Kb && !(((uint32_t)p.mask[(size_t)b * p.k_stride + pos] >> (t / p.sub_block)) & 1u)) hv = 0.0f;   // not selected for this token
+  if (p.mask != nullptr && pos < Kb && !(((uint32_t)p.mask[(size_t)b * k_stride + pos] >> (t / p.sub_block)) & 1u)) hv = 0.0f;   // not selected for this token
   p.h[(size_t)(t0 + t) * p.hs + pos] = f32_to_bf16(hv);
 }
 
@@ -166,7 +167,8 @@ void ff_gemv1_kernel(GemvParams p, int steps) {
 // token on 7168 of 4096/14336 19.0 and 15.9, dense 31.2 and 27.0; eight tokens of a list each 39.2 and 23.7.)
 // grid (d_model / 128, n_chunks, n_blocks)
 __global__ __launch_bounds__(kGemvWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
-void ff_gemv2_kernel(GemvParams p) {
+void ff_gemv2_kernel(const int32_t *idx, const int32_t *per_block, const bf16_t *h, int uniform, int cap, int k_stride, int rc, int T, int block,
+                     int hs, int n_chunks, GemvParams p) {
   constexpr int PITCH = kGemv2Cols + 4;
   __shared__ __align__(16) float red[kGemvWaves][kGemvMaxTokens][PITCH];
   __shared__ int last_s;
@@ -174,16 +176,16 @@ void ff_gemv2_kernel(GemvParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, q = lane >> 4;
   const int b = blockIdx.z, ch = blockIdx.y;
-  const int t0 = b * p.block;
-  const int nt = min(p.T, t0 + p.block) - t0;
-  const int Kb = gv_block_k(p, b);
-  const int ntot = Kb + p.rc;
+  const int t0 = b * block;
+  const int nt = min(T, t0 + block) - t0;
+  const int Kb = gv_block_k(per_block, uniform, cap, b);
+  const int ntot = Kb + rc;
   const int n_groups = (ntot + 31) / 32;
-  const int per = (n_groups + p.n_chunks - 1) / p.n_chunks;
+  const int per = (n_groups + n_chunks - 1) / n_chunks;
   const int g_end = min(n_groups, (ch + 1) * per);
   const int col0 = blockIdx.x * kGemv2Cols;
-  const int32_t *list = p.idx ? p.idx + (size_t)b * p.k_stride : nullptr;
-  const bf16_t *hrow = p.h + (size_t)(t0 + min(c & 7, nt - 1)) * p.hs + 8 * q;
+  const int32_t *list = idx ? idx + (size_t)b * k_stride : nullptr;
+  const bf16_t *hrow = h + (size_t)(t0 + min(c & 7, nt - 1)) * hs + 8 * q;
   const size_t lane_col = (size_t)(col0 + 8 * c);
   f32x4_t acc[8];
 #pragma unroll
@@ -256,28 +258,28 @@ void ff_gemv2_kernel(GemvParams p) {
     float s = 0.0f;
 #pragma unroll
     for (int w = 0; w < kGemvWaves; ++w) s += red[w][t][col];
-    if (p.n_chunks == 1) store(t, col0 + col, s);
-    else __hip_atomic_store(p.part + ((size_t)ch * p.T + t0 + t) * p.d_model + col0 + col, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n_chunks == 1) store(t, col0 + col, s);
+    else __hip_atomic_store(p.part + ((size_t)ch * T + t0 + t) * p.d_model + col0 + col, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (p.n_chunks == 1) return;
+  if (n_chunks == 1) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // this wavefront's sums have arrived
   __syncthreads();
   if (tid == 0)
-    last_s = __hip_atomic_fetch_add(p.counter + b * gridDim.x + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.n_chunks - 1;
+    last_s = __hip_atomic_fetch_add(p.counter + b * gridDim.x + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
   __syncthreads();
   if (!last_s) return;
   for (int v = tid; v < nt * kGemv2Cols; v += kGemvWaves * 64) {
     const int t = v / kGemv2Cols, col = v % kGemv2Cols;
     float *src = p.part + (size_t)(t0 + t) * p.d_model + col0 + col;
     float s = 0.0f;
-    for (int j0 = 0; j0 < p.n_chunks; j0 += 8) {                 // eight loads in flight, added in chunk order
+    for (int j0 = 0; j0 < n_chunks; j0 += 8) {                 // eight loads in flight, added in chunk order
       float x[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        x[j] = __hip_atomic_load(src + (size_t)min(j0 + j, p.n_chunks - 1) * p.T * p.d_model, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x[j] = __hip_atomic_load(src + (size_t)min(j0 + j, n_chunks - 1) * T * p.d_model, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        if (j0 + j < p.n_chunks) s += x[j];
+        if (j0 + j < n_chunks) s += x[j];
     }
     store(t, col0 + col, s);
   }
@@ -342,14 +344,17 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   const int nc = most <= full ? most : std::min(full, 256 / (cols * p.n_blocks));
   p.n_chunks = nc < 1 ? 1 : (nc > kGemvChunks ? kGemvChunks : nc);
   const int groups1 = (n_extent + 31) / 32 * (32 / kGemv1Pos);
+  const int cap = p.idx ? std::min(p.d_ffn, p.k_stride) : p.d_ffn;   // (without a list position p is row p, and the pitch bounds nothing)
   const int nw = gemv1_waves((long)groups1 * p.n_blocks, nt, p.d_model, lds_limit);
   const auto fn = nw == 4 ? ff_gemv1_kernel<4> : nw == 8 ? ff_gemv1_kernel<8> : ff_gemv1_kernel<16>;
   prof_begin(prof, FF_STAGE_GEMM1, s);
   hipLaunchKernelGGL(fn, dim3(groups1, p.n_blocks), dim3(nw * 64),
-                     gemv1_lds(nw, nt, p.d_model), s, p, gemv1_steps(nw, p.d_model));
+                     gemv1_lds(nw, nt, p.d_model), s, p.idx, p.k.per_block, p.x, p.k.uniform, cap, p.k_stride, p.rc, p.T, p.block, p.d_model,
+                     gemv1_steps(nw, p.d_model), p);
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_GEMM2, s);
-  hipLaunchKernelGGL(ff_gemv2_kernel, dim3(cols, p.n_chunks, p.n_blocks), dim3(kGemvWaves * 64), 0, s, p);
+  hipLaunchKernelGGL(ff_gemv2_kernel, dim3(cols, p.n_chunks, p.n_blocks), dim3(kGemvWaves * 64), 0, s, p.idx, p.k.per_block, p.h, p.k.uniform, cap,
+                     p.k_stride, p.rc, p.T, p.block, p.hs, p.n_chunks, p);
   prof_end(prof, s);
   return hipGetLastError();
 }

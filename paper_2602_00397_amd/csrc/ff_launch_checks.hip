@@ -25,7 +25,7 @@ static bool g_down = false, g_few = false;   // whose launches are being recorde
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
   Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, {}};
-  if (g_few) memcpy(static_cast<void *>(&l.gv), args[0], sizeof(l.gv));
+  if (g_few) memcpy(static_cast<void *>(&l.gv), args[11], sizeof(l.gv));   // (behind the plain arguments)
   else if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
   else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
   g_log.push_back(l);
