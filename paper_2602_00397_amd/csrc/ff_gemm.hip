@@ -2028,7 +2028,8 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 // tiles of 256 columns serve calls with few columns and blocks (2048/8192, K 4096, 32 blocks of 128, one round: 75.9 us with both
 // operands in LDS, 66.5 with the weights in registers).  The 64 x 64 tiles: see their kernel; with one or two tiles of tokens, one
 // on each CU, a step takes 0.25 to 0.3, with four 0.35 to 0.45 (200 tokens of 4096/14336, K 3584: at 0.33 throughout they would be
-// taken, 65.8 -> 68.3; at 0.41 the gains of 3 to 8% on 9 to 100 tokens of 4096/14336 would be lost).
+// taken, 65.8 -> 68.3; at 0.41 the gains of 3 to 8% on 9 to 100 tokens of 4096/14336 would be lost; at 0.37 478 tokens of 2048/8192, both
+// ends dense, 77.0 -> 78.7).
 // (The figures of the tiles in registers of 512, 256 and, below 128 tokens, 256 columns are fitted to every tile and cut of 127 calls.  Calls, us,
 // by the figures before, 1.25 .. 1.6, 0.8 .. 0.95 and 0.45 .. 1.1 a step, and by these: 2048/8192, 1350 tokens 117 -> 111, first and
 // last block dense 520 122 -> 110, 850 138 -> 127, 4096 298 -> 285, dense 850 105 -> 98; 4096/14336, 2300 in blocks of 64 602 -> 574; 3584/18944,
@@ -2038,6 +2039,15 @@ struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.15, 1.7, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
                                      {kDirect128Narrow, 0.61, 0.95, 9.0}, {kDirect64Narrow, 0.53, 0.69, 8.7}, {kSplit64, 0.25, 0.33, 5.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
+// g for V tiles of tokens, with lists of equal length and with a few longer ones alike (two blocks of 45 tokens, one dense, 4096/14336, K 3584:
+// 64 x 256 tiles by figures that did not know V, 123.8 us, 64 x 64 ones 118.8)
+static Gemm2Cost gemm2_price(Gemm2Cost g, long V) {
+  // 64 x 64 tiles fetch every row once for each 64 tokens: more than two such tiles of tokens make each other wait
+  if (g.variant == kSplit64 && V > 2) g.full = 0.365;
+  // one or two tiles of 64 tokens share no rows between the 64 x 256 ones of a column: a full chip of those runs at HBM's rate
+  if (g.variant == kDirect64Narrow && V <= 2) return {g.variant, 0.45, 1.1, 6.0};
+  return g;
+}
 static bool gemm2_direct(int variant) { return variant >= kDirect128; }
 // Whether the tiles with the weights in registers can address these matrices: a listed row's offset into W_down is the
 // product of two 24-bit numbers in 32 bits, a token's offset into a tile of H has 32 bits too.
@@ -2116,8 +2126,8 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     const int n0 = pieces;
     double best = 0.0;
     // A few much longer lists that will be cut (below): their pieces start first, on CUs that the common tiles leave idle
-    // where there are such, else ahead of everybody.  That favours the large tiles with the weights in registers, which
-    // leave the most; the others only where those do not apply.  (First and last block dense, us per call at 4096/14336,
+    // where there are such, else ahead of everybody.  That favours the tiles with the weights in registers, the large ones, which
+    // leave the most, ahead of the 64 x 64 ones; the others only where none of those applies.  (First and last block dense, us per call at 4096/14336,
     // priced without the pieces against this: 2000 tokens 502 / 471, 500 327 / 303, 2000 in blocks of 256 565 / 537, 1500 in
     // blocks of 64, K 3584 361 / 336; 64 x 512 tiles must save a tenth, since they take twice the pieces.)  Not asked: ksplit,
     // which is to change the long lists' sums and no others, hence no tile.
@@ -2133,21 +2143,18 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
         const int xs = xcd_groups(V, N * n, n > 1 ? Share{} : share_of(v, p, false));
         const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N * n + (8 >> xs) - 1) / (8 >> xs));   // of the busiest XCD
         const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
-        // (64 x 64 tiles fetch every row once for each 64 tokens: more than two such tiles of tokens make each other wait)
-        // (one or two tiles of 64 tokens share no rows between the 64 x 256 ones of a column: a full chip of those runs at HBM's rate)
-        const bool alone = g.variant == kDirect64Narrow && V <= 2;
-        const double full = g.variant == kSplit64 && V > 2 ? 0.37 : alone ? 1.1 : g.full, idle = alone ? 0.45 : g.idle, fixed = alone ? 6.0 : g.fixed;
-        double cost = (double)(tiles / (kNumCU / 8)) * (fixed + steps * full);
-        if (busy > 0.0) cost += fixed + steps * (idle + (full - idle) * busy);
+        const Gemm2Cost c = gemm2_price(g, V);
+        double cost = (double)(tiles / (kNumCU / 8)) * (c.fixed + steps * c.full);
+        if (busy > 0.0) cost += c.fixed + steps * (c.idle + (c.full - c.idle) * busy);
         if (n > 1) cost += 3.0 + (double)n * (double)per_piece / 3.3e6;
         if (heavy_cut) {
           const long heavy = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;
           const long free_pieces = std::max<long>(1, std::min<long>(kNumCU / heavy, kMaxFreePieces));
           const double piece_steps = (double)((surplus + free_pieces - 1) / free_pieces) / 64;
           if (V * N + heavy * free_pieces <= kNumCU)
-            cost = g.fixed + steps * (g.idle + (g.full - g.idle) * (double)(V * N + heavy * free_pieces) / kNumCU);
+            cost = c.fixed + steps * (c.idle + (c.full - c.idle) * (double)(V * N + heavy * free_pieces) / kNumCU);
           else
-            cost += (double)((heavy * free_pieces + kNumCU - 1) / kNumCU) * (g.fixed + piece_steps * g.full);
+            cost += (double)((heavy * free_pieces + kNumCU - 1) / kNumCU) * (c.fixed + piece_steps * c.full);
         }
         if (variant < 0 || cost < best * (heavy_cut ? 0.9 : 0.98)) { variant = g.variant; pieces = n; best = cost; }
       }

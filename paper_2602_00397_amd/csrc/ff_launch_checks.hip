@@ -248,6 +248,20 @@ static void check_gemm2_routes() {
   }
 }
 
+// Down: which tile the prices choose.
+static void check_gemm2_prices() {
+  struct { Shape s; bool list; int variant; } calls[] = {
+      // two token tiles of 64, one list longer: priced for two like lists of equal length
+      {{90, 48, 4096, 14336, 64, 3584, 14336, 1}, true, 9}, {{100, 50, 3584, 18944, 64, 4736, 18944, 1}, true, 9}};
+  for (const auto &c : calls) {
+    DownOptions o;
+    o.variant = c.variant;
+    gemm2(c.s, c.list, o, true);
+    const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
+    CHECK(gemm2(c.s, c.list, DownOptions(), true) == hipSuccess && !g_log.empty() && g_log[0].fn == fn, "T %d block %d d_model %d K %d, not tile %d", c.s.T, c.s.block, c.s.d_model, c.s.k, c.variant);
+  }
+}
+
 // Down: the longest list whose row-id table fits beside the ring of a tile with the weights in registers.  One position more and
 // the tile is refused where it is forced, and not taken where it is not.
 static void check_gemm2_row_table() {
@@ -384,6 +398,7 @@ int main() {
   check_gemm1_short_block();
   check_gemm2_addresses();
   check_gemm2_routes();
+  check_gemm2_prices();
   check_gemm2_row_table();
   check_gemm2_row_sources();
   check_gemm2_room();
