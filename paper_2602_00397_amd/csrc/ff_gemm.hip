@@ -2030,18 +2030,40 @@ static Variant with_rows(Variant v, const Gemm2Params &p, int row_mode, int tab_
 // on each CU, a step takes 0.25 to 0.3, with four 0.35 to 0.45 (200 tokens of 4096/14336, K 3584: at 0.33 throughout they would be
 // taken, 65.8 -> 68.3; at 0.41 the gains of 3 to 8% on 9 to 100 tokens of 4096/14336 would be lost; at 0.37 478 tokens of 2048/8192, both
 // ends dense, 77.0 -> 78.7).
-// (The figures of the tiles in registers of 512, 256 and, below 128 tokens, 256 columns are fitted to every tile and cut of 127 calls.  Calls, us,
-// by the figures before, 1.25 .. 1.6, 0.8 .. 0.95 and 0.45 .. 1.1 a step, and by these: 2048/8192, 1350 tokens 117 -> 111, first and
-// last block dense 520 122 -> 110, 850 138 -> 127, 4096 298 -> 285, dense 850 105 -> 98; 4096/14336, 2300 in blocks of 64 602 -> 574; 3584/18944,
-// both ends dense 520 349 -> 323.  Of 244 calls from 12 to 16000 tokens the geometric mean is 1.005.)
+// (The figures of the tiles in registers of 512, 256 and, below 128 tokens, 256 columns are fitted to every tile and cut of 127 calls of the
+// three larger layers.  Calls, us, by the figures before, 1.25 .. 1.6, 0.8 .. 0.95 and 0.45 .. 1.1 a step, and by these: 2048/8192, 1350 tokens
+// 117 -> 111, first and last block dense 520 122 -> 110, 850 138 -> 127, 4096 298 -> 285, dense 850 105 -> 98; 4096/14336, 2300 in blocks of 64
+// 602 -> 574; 3584/18944, both ends dense 520 349 -> 323.  Every tile and cut of 836 calls of these layers measured, from 9 to 16000 tokens:
+// the two sets of figures choose differently in 119, geometric mean 0.966, of which 8 lost more than 1%, 2% but for one of 4% and one of 7%.)
 // The last three, slower at the same tile, are what matrices of 4 GiB and more and lists too long for the row-id table get.
 struct Gemm2Cost { int variant; double idle, full, fixed; };
 constexpr Gemm2Cost kGemm2Cost[] = {{kDirect128, 1.15, 1.7, 9.0}, {kDirect64, 1.15, 1.24, 6.0}, {kHalf128Wide, 0.75, 1.1, 6.0},
                                      {kDirect128Narrow, 0.61, 0.95, 9.0}, {kDirect64Narrow, 0.53, 0.69, 8.7}, {kSplit64, 0.25, 0.33, 5.0},
                                      {0, 1.4, 2.05, 9.0}, {2, 1.25, 2.07, 9.0}, {3, 1.25, 1.45, 8.0}};
-// g for V tiles of tokens, with lists of equal length and with a few longer ones alike (two blocks of 45 tokens, one dense, 4096/14336, K 3584:
-// 64 x 256 tiles by figures that did not know V, 123.8 us, 64 x 64 ones 118.8)
-static Gemm2Cost gemm2_price(Gemm2Cost g, long V) {
+// A W_down of at most 4 MiB, an XCD's L2, is fetched once and waited for little after that, and its lists are few steps long: what it costs
+// to start a tile decides.  These figures are fitted to every tile and cut of 554 calls of 256/688, 256/1024, 256/4096, 512/1024, 512/2048,
+// 512/4096, 640/3072 and 768/2048, 100 to 16384 tokens: dense, lists of equal length, first and last block dense.  Geometric mean over each
+// call's fastest tile 1.005, by the figures above 1.033; 6 more than 1% slower than by those, the most 4% (256/688, K 516, 9000 tokens).  (256/688,
+// us, by the figures above and by these: dense 5000 tokens 26.3 -> 23.5, 7000 33.8 -> 27.5, 9566 38.4 -> 35.2; K 344, 5000 24.5 -> 20.4, 7000
+// 31 -> 23.5; K 172, 14000 26.1 -> 24.1; both ends dense, 9000 31.1 -> 29.5.  With 5.5 MiB and more the figures above choose well enough, 1.010
+// of the fastest for 1024/2816, 1.016 for 1024/4096.)
+constexpr uint64_t kXcdL2Bytes = 4 << 20;
+constexpr Gemm2Cost kGemm2CostL2[] = {{kHalf128Wide, 0.75, 1.1, 6.5}, {kDirect64Narrow, 0.55, 0.65, 6.5}, {kSplit64, 0.2, 0.2, 3.0}};
+// g for V tiles of tokens, with lists of equal length and with a few longer ones alike (two blocks of 45 tokens, one dense,
+// 4096/14336, K 3584: 64 x 256 tiles by figures that did not know V, 123.8 us, 64 x 64 ones 118.8)
+static Gemm2Cost gemm2_price(Gemm2Cost g, const Gemm2Params &p, long V, bool heavy_cut) {
+  if ((uint64_t)p.d_ffn * (uint64_t)p.d_model * 2u <= kXcdL2Bytes) {
+    for (const Gemm2Cost &c : kGemm2CostL2)
+      if (c.variant == g.variant) g = c;
+    // With one tile of 256 columns a longer call is many tiles of tokens, and the H of 64 tokens is mostly in the L2 of the XCD that the
+    // gate/up tile of their 128 ran on: another one.  (256/688, 64 x 256 against 128 x 256: K 344, 14000 tokens 34.0 / 32.5, 8200 25.1 / 24.9;
+    // K 172, three steps, 14000 24.1 / 26.1.  Blocks of 16 merged, 10956 tokens, 64 x 64 against 128 x 256: 64.5 / 61.0.)
+    if (p.d_model <= kGemm2[kDirect64Narrow].bn && p.idx != nullptr && p.block > 64 && !heavy_cut) {
+      if (g.variant == kDirect64Narrow) g.full = 1.0;
+      if (g.variant == kSplit64) g.full = 0.25;
+    }
+    return g;
+  }
   // 64 x 64 tiles fetch every row once for each 64 tokens: more than two such tiles of tokens make each other wait
   if (g.variant == kSplit64 && V > 2) g.full = 0.365;
   // one or two tiles of 64 tokens share no rows between the 64 x 256 ones of a column: a full chip of those runs at HBM's rate
@@ -2143,7 +2165,7 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
         const int xs = xcd_groups(V, N * n, n > 1 ? Share{} : share_of(v, p, false));
         const long tiles = ((V + (1 << xs) - 1) >> xs) * ((N * n + (8 >> xs) - 1) / (8 >> xs));   // of the busiest XCD
         const double steps = ((base + n - 1) / n + 63) / 64, busy = (double)(tiles % (kNumCU / 8)) / (kNumCU / 8);
-        const Gemm2Cost c = gemm2_price(g, V);
+        const Gemm2Cost c = gemm2_price(g, p, V, heavy_cut);
         double cost = (double)(tiles / (kNumCU / 8)) * (c.fixed + steps * c.full);
         if (busy > 0.0) cost += c.fixed + steps * (c.idle + (c.full - c.idle) * busy);
         if (n > 1) cost += 3.0 + (double)n * (double)per_piece / 3.3e6;

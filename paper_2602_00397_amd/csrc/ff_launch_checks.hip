@@ -252,7 +252,15 @@ static void check_gemm2_routes() {
 static void check_gemm2_prices() {
   struct { Shape s; bool list; int variant; } calls[] = {
       // two token tiles of 64, one list longer: priced for two like lists of equal length
-      {{90, 48, 4096, 14336, 64, 3584, 14336, 1}, true, 9}, {{100, 50, 3584, 18944, 64, 4736, 18944, 1}, true, 9}};
+      {{90, 48, 4096, 14336, 64, 3584, 14336, 1}, true, 9}, {{100, 50, 3584, 18944, 64, 4736, 18944, 1}, true, 9},
+      // W_down in an XCD's L2: 64 x 64, then 64 x 256; with three steps or dense on to the longest calls, with more steps and blocks of 128 tokens or
+      // more 128 x 256 there
+      {{5000, 128, 256, 688, 0, 688, 0, 0}, false, 9}, {{7000, 128, 256, 688, 0, 688, 0, 0}, false, 9}, {{9500, 128, 256, 688, 0, 688, 0, 0}, false, 8},
+      {{5000, 128, 256, 688, 16, 344, 0, 0}, true, 9}, {{7000, 256, 256, 688, 0, 344, 0, 0}, true, 9}, {{14000, 128, 256, 688, 16, 344, 0, 0}, true, 4},
+      {{14000, 128, 256, 688, 16, 172, 0, 0}, true, 8}, {{2000, 128, 256, 688, 16, 344, 688, 2}, true, 9}, {{5000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{7000, 128, 256, 688, 16, 344, 688, 2}, true, 8},
+      {{9000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{11582, 128, 256, 688, 16, 688, 0, -1}, true, 4},   // (the last of merged lists)
+      // ... and where it is not
+      {{4096, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}, {{1350, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}};
   for (const auto &c : calls) {
     DownOptions o;
     o.variant = c.variant;
@@ -260,6 +268,24 @@ static void check_gemm2_prices() {
     const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
     CHECK(gemm2(c.s, c.list, DownOptions(), true) == hipSuccess && !g_log.empty() && g_log[0].fn == fn, "T %d block %d d_model %d K %d, not tile %d", c.s.T, c.s.block, c.s.d_model, c.s.k, c.variant);
   }
+  // no tile of 512 columns for 256 or fewer, whatever the lists
+  std::set<const void *> wide;
+  for (int variant : {5, 6})
+    for (bool list : {false, true}) {
+      DownOptions o;
+      o.variant = variant;
+      gemm2({700, 128, 256, 688, 16, 344, 0, 0}, list, o, true);
+      for (const Launch &l : g_log) wide.insert(l.fn);
+    }
+  for (int T = 9; T < 20000; T += T / 8 + 1)
+    for (int block : {16, 64, 128, 200, 256})
+      for (int dm : {128, 256})
+        for (int df : {688, 4096, 14336})
+          for (int k : {df / 4, df / 2, df})
+            for (int heavy : {-1, 0, 1, 2}) {
+              const Shape s = {T, block, dm, df, 16, k, df, heavy};
+              CHECK(gemm2(s, true, DownOptions(), true) == hipSuccess && !wide.count(g_log[0].fn), "T %d block %d d_model %d K %d, %d dense", T, block, dm, k, heavy);
+            }
 }
 
 // Down: the longest list whose row-id table fits beside the ring of a tile with the weights in registers.  One position more and
