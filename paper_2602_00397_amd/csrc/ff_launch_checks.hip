@@ -259,7 +259,11 @@ static void check_gemm2_prices() {
       {{5000, 128, 256, 688, 16, 344, 0, 0}, true, 9}, {{7000, 256, 256, 688, 0, 344, 0, 0}, true, 9}, {{14000, 128, 256, 688, 16, 344, 0, 0}, true, 4},
       {{14000, 128, 256, 688, 16, 172, 0, 0}, true, 8}, {{2000, 128, 256, 688, 16, 344, 688, 2}, true, 9}, {{5000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{7000, 128, 256, 688, 16, 344, 688, 2}, true, 8},
       {{9000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{11582, 128, 256, 688, 16, 688, 0, -1}, true, 4},   // (the last of merged lists)
-      // ... and where it is not
+      // ... and where it is not; a few longer lists' pieces beside more than a round of common tiles, and beside less
+      {{2909, 64, 4096, 14336, 64, 3584, 14336, 2}, true, 6}, {{3000, 64, 3584, 18944, 64, 4736, 18944, 2}, true, 6},
+      {{11490, 256, 2048, 8192, 32, 2327, 8192, 2}, true, 5}, {{11609, 128, 2048, 8192, 32, 2048, 8192, 2}, true, 5}, {{4951, 128, 4096, 14336, 64, 7168, 14336, 2}, true, 7},
+      {{2300, 64, 3584, 18944, 64, 9472, 18944, 2}, true, 8},
+      {{1700, 64, 2048, 8192, 32, 2048, 8192, 2}, true, 6}, {{2048, 64, 2048, 8192, 32, 2048, 8192, 2}, true, 6},
       {{4096, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}, {{1350, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}};
   for (const auto &c : calls) {
     DownOptions o;
