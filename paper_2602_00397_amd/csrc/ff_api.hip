@@ -531,7 +531,7 @@ ff_status ff_workspace_bytes(const ff_shape *shape, int32_t k_max, size_t *bytes
   *bytes = std::max(make_layout(*shape, k_max).total,
                     make_layout(*shape, k_max, false, merge_factor(*shape, 160 * 1024)).total) +
            std::max(ff_gemm2_split_bytes(shape->n_tokens, shape->d_model),
-                    ff_pool_fine_bytes(shape->d_model, (int)(((size_t)shape->n_tokens + shape->block - 1) / shape->block), shape->r_pred));
+                    ff_pool_fine_bytes(shape->n_tokens, shape->block, shape->d_model, shape->r_pred, true));
   return FF_OK;
 }
 

@@ -2118,7 +2118,7 @@ size_t ff_gemm2_split_bytes(int n_tokens, int d_model) {
   long tiles = 2 * kNumCU;
   for (const Gemm2Cost &g : kGemm2Cost) {
     const Variant &v = kGemm2[g.variant];
-    tiles = std::min<long>(tiles, (long)((n_tokens + v.bm - 1) / v.bm) * ((d_model + v.bn - 1) / v.bn));
+    tiles = std::min<long>(tiles, ((long)n_tokens + v.bm - 1) / v.bm * (((long)d_model + v.bn - 1) / v.bn));
   }
   const size_t n = std::min<size_t>({kSplitCapBytes / per_piece, (size_t)(kMaxPieces - 1), (size_t)(2 * kNumCU / tiles)});
   return n >= 2 ? n * per_piece : 0;

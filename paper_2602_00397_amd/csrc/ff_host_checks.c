@@ -41,7 +41,7 @@ static void part1_no_gpu(void) {
   int32_t k = 0;
   double keep[4];
   const double imp[4] = {1.0, 2.0, 3.0, 4.0}, bad[2] = {1.0, -1.0};
-  size_t bytes = 0;
+  size_t bytes = 0, more = 0;
   ff_ctx *ctx = NULL;
   ff_shape ok = {4096, 14336, 8192, 128, 128, 64};
   ff_shape huge = {1 << 20, 1 << 30, 2147483647 - 131072, 131072, 1024, 4096};
@@ -82,6 +82,16 @@ static void part1_no_gpu(void) {
   EXPECT(ff_workspace_bytes(&ok, 0, &bytes), FF_ERR_INVALID_ARG);
   EXPECT(ff_workspace_bytes(&ok, 14337, &bytes), FF_ERR_INVALID_ARG);
   EXPECT(ff_workspace_bytes(&huge, 1 << 30, &bytes), FF_OK);   /* sizes are computed in size_t */
+  s = ok; s.n_tokens = s.block = 100; s.d_model = 65536; s.r_pred = 1 << 30;   /* (calls without a predictor ignore r_pred) */
+  EXPECT(ff_workspace_bytes(&s, 7168, &bytes), FF_OK);
+  s = ok; s.n_tokens = s.block = 100; s.d_model = 2147483520;
+  EXPECT(ff_workspace_bytes(&s, 7168, &bytes), FF_OK);
+  /* blocks too short for pooling in narrow slices: no room for those, just the first layer's 512 bytes more */
+  s = ok; s.n_tokens = 2; s.block = 1; s.r_pred = 1020;
+  EXPECT(ff_workspace_bytes(&s, 7168, &bytes), FF_OK);
+  s.r_pred = 1024;
+  EXPECT(ff_workspace_bytes(&s, 7168, &more), FF_OK);
+  if (more != bytes + 512) ++n_fail;
   s = huge; s.n_tokens = 2147483647;
   EXPECT(ff_workspace_bytes(&s, 1 << 30, &bytes), FF_ERR_SHAPE);
   s = ok; s.d_model = 100;

@@ -119,15 +119,15 @@ struct PredictParams {
   int32_t T, d_model, d_ffn, block, r, n_blocks;
   double *z;        // [T] pooling logits (softmax pooling only)
   double *hpart;    // [n_blocks][ceil(d_model / 512)][r]: the first layer's sums over slices of 512 channels
-  double *hpart_fine = nullptr;   // the same in narrower slices, for few blocks with softmax pooling, where scratch has room
+  double *hpart_fine = nullptr;   // the same in narrower slices, for few blocks that are not short, where scratch has room
   size_t hpart_fine_bytes = 0;
   double *scores;   // [n_blocks][d_ffn]
   KSpec k;
   int32_t k_stride;
   int32_t *indices;  // [n_blocks][k_stride]
 };
-// what hpart_fine takes (0: the call has no use for it)
-size_t ff_pool_fine_bytes(int d_model, int n_blocks, int r);
+// what hpart_fine takes (0: the call has no use for it; the mean's calls with a use for it are among softmax pooling's)
+size_t ff_pool_fine_bytes(int n_tokens, int block, int d_model, int r, bool softmax);
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof);
 
 // Top-K's map of scores to buckets: monotone (s1 <= s2 gives bucket(s1) <= bucket(s2)), so a key in a higher bucket is a

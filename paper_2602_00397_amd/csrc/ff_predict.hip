@@ -1112,14 +1112,17 @@ static topk_reg_t topk_reg_kernel(int half) { return topk_reg_pick(half, std::ma
 
 // Lanes to a row of ff_pool_fine_kernel (0: it does not apply).  128 channels to a workgroup as long as a workgroup of the scores kernel
 // then has at most 4096 partial sums to add, else 256 (1200 tokens of 3584/18944 in blocks of 256 favour 128, 29.6 against 30.5 us,
-// 2000 of 4096/14336 256, 21.4 against 23.2).
-static int pool_fine_lanes(int d_model, int n_blocks, int r) {
-  if ((d_model + 511) / 512 * n_blocks > 128 || r <= 0 || r % 8 != 0) return 0;
-  return (n_blocks <= 2 ? 1 : MLP_BB) * r * ((d_model + 127) / 128) <= 4096 ? 16 : 32;
+// 2000 of 4096/14336 256, 21.4 against 23.2).  Short blocks' rows are few loads anyhow, and the scores kernel's further slices cost 0.5 to
+// 1 us (softmax: 160 tokens of 3584/18944 in blocks of 32 27.1 -> 27.6, 256 of 256/688 in blocks of 64 16.5 -> 16.2; the mean: 64 tokens of
+// 4096/14336 16.7 -> 17.1, 100 16.7 -> 16.4).
+static int pool_fine_lanes(int n_tokens, int block, int d_model, int r, bool softmax) {
+  const int64_t n_blocks = ((int64_t)n_tokens + block - 1) / block, dm = d_model;   // (where room is asked for nobody has looked at r)
+  if (std::min(n_tokens, block) < (softmax ? 64 : 96) || (dm + 511) / 512 * n_blocks > 128 || r <= 0 || r > 1024 || r % 8 != 0) return 0;
+  return (n_blocks <= 2 ? 1 : MLP_BB) * r * ((dm + 127) / 128) <= 4096 ? 16 : 32;
 }
-size_t ff_pool_fine_bytes(int d_model, int n_blocks, int r) {
-  const int ch = 8 * pool_fine_lanes(d_model, n_blocks, r);
-  return ch == 0 ? 0 : (size_t)n_blocks * ((d_model + ch - 1) / ch) * r * sizeof(double);
+size_t ff_pool_fine_bytes(int n_tokens, int block, int d_model, int r, bool softmax) {
+  const size_t ch = 8 * (size_t)pool_fine_lanes(n_tokens, block, d_model, r, softmax);
+  return ch == 0 ? 0 : ((size_t)n_tokens + block - 1) / block * (((size_t)d_model + ch - 1) / ch) * r * sizeof(double);
 }
 
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
@@ -1132,12 +1135,10 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   int oz = 256 / (n_slices * p.n_blocks);
   oz = std::max(1, std::min({oz, 8, p.r / 32}));
   prof_begin(prof, FF_STAGE_POOL, s);
-  // Short blocks' rows are few loads anyhow, and the scores kernel's further slices cost 0.5 to 1 us (softmax: 160 tokens of 3584/18944 in
-  // blocks of 32 27.1 -> 27.6, 256 of 256/688 in blocks of 64 16.5 -> 16.2; the mean: 64 tokens of 4096/14336 16.7 -> 17.1, 100 16.7 -> 16.4).
-  const size_t fine_bytes = std::min(p.T, p.block) >= (p.q_pred ? 64 : 96) ? ff_pool_fine_bytes(p.d_model, p.n_blocks, p.r) : 0;
+  const size_t fine_bytes = ff_pool_fine_bytes(p.T, p.block, p.d_model, p.r, p.q_pred != nullptr);
   if (p.q_pred) hipLaunchKernelGGL(ff_logits_kernel, dim3((p.T + 3) / 4), dim3(256), 0, s, p.x, p.q_pred, p.z, p.T, p.d_model);
   if (fine_bytes > 0 && p.hpart_fine_bytes >= fine_bytes) {
-    const int lw = pool_fine_lanes(p.d_model, p.n_blocks, p.r);
+    const int lw = pool_fine_lanes(p.T, p.block, p.d_model, p.r, p.q_pred != nullptr);
     hpart = p.hpart_fine;
     n_slices = (p.d_model + 8 * lw - 1) / (8 * lw);
     hipLaunchKernelGGL(lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>) : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>), dim3(n_slices, p.n_blocks), dim3(kPoolFineThreads), 0, s,
