@@ -95,12 +95,12 @@ def build_host_checks() -> str:
 
 
 def build_launch_checks() -> str:
-    """csrc/ff_launch_checks.hip with the GEMM and few-token launchers' object files (as build() left them): the program
+    """csrc/ff_launch_checks.hip with the predictor's, the GEMMs' and the few-token launchers' object files (as build() left them): the program
     records their launches instead of making them, so it needs no GPU."""
     exe = os.path.join(OBJ, "ff_launch_checks")
     obj = os.path.join(OBJ, "ff_launch_checks.o")
     _run([HIPCC, *FLAGS, "-c", os.path.join(CSRC, "ff_launch_checks.hip"), "-o", obj])
-    _run([HIPCC, "--offload-arch=gfx950", obj, os.path.join(OBJ, "ff_gemm.o"), os.path.join(OBJ, "ff_gemv.o"), "-o", exe,
+    _run([HIPCC, "--offload-arch=gfx950", obj, *(os.path.join(OBJ, "ff_%s.o" % n) for n in ("predict", "gemm", "gemv")), "-o", exe,
           "-Wl,-rpath," + os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "lib")])
     return exe
 

@@ -1,4 +1,4 @@
-// Checks of the GEMM launchers' choices, of the few-token path's limits and of top-K's bucket map, without a GPU: this program
+// Checks of the GEMM launchers' choices, of the few-token path's limits, of the pooling kernels' and of top-K's bucket map, without a GPU: this program
 // is linked with the launchers' object files and defines hipLaunchKernel itself, so every launch is recorded instead of made.  Swept over shapes, list lengths and options, every
 // launch must fit what its kernel assumes.  Exit code 0 = all hold.
 #include <math.h>
@@ -18,14 +18,16 @@ struct Launch {
   Gemm1Params g1;
   Gemm2Params g2;
   GemvParams gv;
+  dim3 dims;
 };
 static std::vector<Launch> g_log;
 static int g_fail = 0, g_calls = 0;
-static bool g_down = false, g_few = false;   // whose launches are being recorded
+static bool g_down = false, g_few = false, g_pred = false;   // whose launches are being recorded
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
-  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, {}};
-  if (g_few) memcpy(static_cast<void *>(&l.gv), args[11], sizeof(l.gv));   // (behind the plain arguments)
+  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, {}, grid};
+  if (g_pred) {}                                                           // (plain arguments: the grid says enough)
+  else if (g_few) memcpy(static_cast<void *>(&l.gv), args[11], sizeof(l.gv));   // (behind the plain arguments)
   else if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
   else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
   g_log.push_back(l);
@@ -389,6 +391,37 @@ static void check_few_tokens() {
   g_few = false;
 }
 
+// The predictor: which calls pool in narrow slices, and how narrow, given the room that ff_pool_fine_bytes asks for; without it, or
+// elsewhere, in 512 channels.
+static void check_pooling() {
+  g_pred = true;
+  struct { int T, block, dm, r; bool softmax; unsigned slices; } calls[] = {      // slices: 0 = of 512 channels
+      {64, 64, 4096, 128, true, 32}, {63, 128, 4096, 128, true, 0}, {700, 63, 4096, 128, true, 0}, {96, 96, 4096, 128, false, 32}, {95, 128, 4096, 128, false, 0},
+      {128, 128, 4096, 136, false, 16}, {128, 128, 4096, 132, false, 0}, {100, 128, 2048, 64, true, 16},      // 4096 partial sums and more; r no multiple of 8
+      {257, 128, 2048, 64, true, 16}, {257, 128, 2048, 72, true, 8}, {257, 128, 4096, 128, false, 16},        // three blocks: the scores kernel adds for four
+      {16 * 128, 128, 4096, 64, false, 16}, {17 * 128, 128, 4096, 64, false, 0}, {128 * 128, 128, 512, 8, false, 4}, {129 * 128, 128, 512, 8, false, 0},
+      {4096, 4096, 65536, 8, true, 512}, {4096, 4096, 65664, 8, true, 0}};
+  for (const auto &c : calls)
+    for (bool room : {false, true}) {
+      PredictParams p = {};
+      p.T = c.T; p.block = c.block; p.d_model = c.dm; p.d_ffn = 688; p.r = c.r; p.n_blocks = (c.T + c.block - 1) / c.block;
+      p.q_pred = c.softmax ? reinterpret_cast<const bf16_t *>(g_idx) : nullptr;
+      p.k_stride = p.k.uniform = p.k.k_max = p.k.k_base = 344;
+      const size_t bytes = ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, c.softmax), n = (size_t)p.n_blocks * c.r * sizeof(double);
+      CHECK(bytes == c.slices * n && ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, true) >= bytes, "T %d block %d d_model %d r %d: %zu bytes", c.T, c.block, c.dm, c.r, bytes);
+      p.hpart_fine = reinterpret_cast<double *>(g_room);
+      p.hpart_fine_bytes = room ? bytes : bytes - (bytes > 0);
+      g_log.clear();
+      ++g_calls;
+      CHECK(ff_launch_predict(p, kLds, nullptr, nullptr) == hipSuccess && g_log.size() == (c.softmax ? 4u : 3u), "T %d: %zu launches", c.T, g_log.size());
+      const Launch &pool = g_log[c.softmax];
+      const bool narrow = room && c.slices > 0;
+      CHECK(pool.threads == (narrow ? 512u : 256u) && pool.dims.x == (narrow ? c.slices : (unsigned)(c.dm + 511) / 512) && pool.dims.y == (unsigned)p.n_blocks,
+            "T %d block %d d_model %d r %d softmax %d: %u x %u workgroups of %u", c.T, c.block, c.dm, c.r, c.softmax, pool.dims.x, pool.dims.y, pool.threads);
+    }
+  g_pred = false;
+}
+
 // Top-K's bucket map: monotone over the scores, and scores spread evenly over their range fill the buckets evenly, however
 // narrow the range is against the scores' size and however small or large they are.  (A bucket of more than TOPK_CAND keys
 // sends the whole block to eight passes over its scores.)
@@ -433,6 +466,7 @@ int main() {
   check_gemm2_row_sources();
   check_gemm2_room();
   check_few_tokens();
+  check_pooling();
   check_topk_map();
   printf("launch checks: %d calls, %d wrong\n", g_calls, g_fail);
   return g_fail != 0;

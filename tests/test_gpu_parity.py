@@ -595,6 +595,53 @@ def test_long_lists_cut_along_k(ctx):
         ctx.set_option("gemm2_row_mode", -1)
 
 
+@pytest.mark.parametrize("variant", [5, 6, 7, 8, 9])
+def test_long_lists_in_pieces_with_weights_in_registers(ctx, variant):
+    """The same cut on every down tile with the weights in registers: the longest list and a shorter long one that ends inside a
+    piece, in 1, 3 and 16 short pieces (some hold fewer groups than the 64 x 64 tile has wavefronts, the last ones nothing), a last
+    block of 37 tokens, columns that fill no whole tile.  Oracle, bars, bf16 storage; the other blocks' rows do not change at all,
+    those of the long lists by fp32 summation order (1e-4, as above), and do change: the cut is made."""
+    c = Case(W.Shape("kpieces", 640, 3072, 5 * 128 + 37, 128, 8, 16))
+    ks = [3072, 704, 704, 100, 704, 2900]
+    ref = c.oracle_layer(ks)
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=3072)
+    long_rows, other_rows = np.r_[0:128, 5 * 128:c.T], np.r_[128:5 * 128]
+    try:
+        ctx.set_option("gemm2_variant", variant)
+        ctx.set_option("gemm2_ksplit", 0)
+        whole = _check_both(c, ctx, idx, ks, ref.y, f"tile {variant}, long lists whole")
+        for ksplit in (1, 3, 16):
+            ctx.set_option("gemm2_ksplit", ksplit)
+            y = _check_both(c, ctx, idx, ks, ref.y, f"tile {variant}, long lists cut into {ksplit} pieces")
+            assert torch.equal(y[other_rows], whole[other_rows])
+            assert not torch.equal(y[long_rows], whole[long_rows]), "the cut was not taken"
+            assert (y[long_rows] - whole[long_rows]).abs().max().item() <= 1e-4
+    finally:
+        ctx.set_option("gemm2_variant", -1)
+        ctx.set_option("gemm2_ksplit", -1)
+
+
+@pytest.mark.parametrize("n_tokens,block", [(2000, 128), (1000, 48), (9000, 128)])
+def test_dense_ends_of_the_smallest_layer(ctx, n_tokens, block):
+    """256/688 with the first and the last block dense: by itself the launcher takes the 64 x 64 tile, then the 64 x 256 one, with the
+    long lists in pieces (csrc/ff_launch_checks.hip holds the tiles).  Some blocks against the oracle; against whole lists fp32
+    summation order on the two ends, nothing elsewhere."""
+    c = Case(dataclasses.replace(W.CONFIGS["c0"], n_tokens=n_tokens, block=block))
+    ks = [688] + [344] * (c.n_blocks - 2) + [688]
+    ref = c.oracle_layer(ks, blocks=[0, 1, c.n_blocks // 2, c.n_blocks - 1])
+    idx, _ = c.gpu_predict(ctx, ks, k_stride=688)
+    last = (c.n_blocks - 1) * block
+    try:
+        y = _check_both(c, ctx, idx, ks, ref.y, f"256/688, both ends dense, {n_tokens} tokens")
+        ctx.set_option("gemm2_ksplit", 0)
+        whole = c.gpu_sparse(ctx, idx, ks, out_f32=True)
+    finally:
+        ctx.set_option("gemm2_ksplit", -1)
+    assert torch.equal(y[block:last], whole[block:last])
+    for rows in (slice(0, block), slice(last, n_tokens)):
+        assert not torch.equal(y[rows], whole[rows]) and (y[rows] - whole[rows]).abs().max().item() <= 1e-4
+
+
 @pytest.mark.parametrize("n_tokens,block,ks", [(9, 9, [33]), (100, 128, [1000]), (150, 64, [700, 40, 1]), (300, 128, [1064, 5, 601]),
                                                (200, 32, [900] * 7), (600, 300, [513, 512])])
 def test_every_list_cut_along_k(ctx, n_tokens, block, ks):
@@ -1132,6 +1179,38 @@ def test_pooling_of_few_long_blocks(ctx, dm, r, T, block, with_q):
             _assert_indices(i, ref.indices, ks)
     finally:
         small.close()
+
+
+@pytest.mark.parametrize("T,block,with_q,narrow", [(95, 95, False, False), (96, 96, False, True), (63, 128, True, False), (64, 64, True, True),
+                                                   (17 * 96, 96, False, False), (16 * 96, 96, False, True)])
+def test_which_calls_pool_in_narrow_slices(ctx, T, block, with_q, narrow):
+    """The rule for the narrow slices at its edges (block length, 128 blocks x 512-channel slices): they add the same products in
+    another order, so a call has other last bits with room for them than in the smallest workspace exactly where it takes them.
+    ff_predict_static's own scratch has the room."""
+    c = Case(W.Shape("narrow", 4096, 264, T, block, 32, 8), with_q=with_q, seed=3 + T)
+    ks = [88] * c.n_blocks
+    _, sc = c.gpu_predict(ctx, ks, scores=True)
+    idx_s, sc_s, sc_t = torch.empty((c.n_blocks, 88), dtype=torch.int32, device=DEV), torch.empty_like(sc), torch.empty_like(sc)
+    ctx.predict_static(c.shape, c.x, c.pred, ks, 88, idx_s, sc_t)
+    small = B.Context(0)
+    try:
+        lo, hi = 0, B.workspace_bytes(c.shape, 88)             # bytes that are refused, bytes that are enough
+        ws = torch.empty(hi, dtype=torch.uint8, device=DEV)
+        while hi - lo > 256:
+            mid = (lo + hi) // 512 * 256
+            small.set_workspace(ws[:mid])
+            try:
+                small.predict(c.shape, c.x, c.pred, ks, 88, idx_s, sc_s)
+                hi = mid
+            except B.FFError:
+                lo = mid
+        small.set_workspace(ws[:hi])
+        small.predict(c.shape, c.x, c.pred, ks, 88, idx_s, sc_s)
+        torch.cuda.synchronize()
+    finally:
+        small.close()
+    assert torch.equal(sc, sc_t)
+    assert torch.equal(sc, sc_s) == (not narrow)
 
 
 def test_diagnostic_calls(ctx):
