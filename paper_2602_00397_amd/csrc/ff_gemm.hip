@@ -1833,8 +1833,10 @@ constexpr Gemm1Cost kGemm1Short[] = {{kGemm1Direct64, 0.74}, {5, 0.90}, {0, 0.52
 constexpr Gemm1Cost kGemm1Mid[] = {{0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};                      // up to 255
 constexpr Gemm1Cost kGemm1Long[] = {{3, 1.0}, {0, 0.52}, {kHeavySurplusVariant, 0.33}, {9, 0.24}};           // 256 and more, and without a list
 
-// The 128 x 256 tile's round where it competes with 128 x 128 for lists of equal length: two of those take 1.08 of it (fitted to 46 calls).
-constexpr double kWideRound = 0.96;
+// The 128 x 256 tile's round where it competes with 128 x 128 for lists of equal length: two of those take 1.10 of it (fitted to 46 calls,
+// then to 330.  At 1.08 3584/18944, K 9472, 8200 to 9500 tokens ran 22 rounds of 128 x 128 for 12: 9312 tokens 1872 -> 1755 us, 8401 1604 ->
+// 1515; of 20000 calls 79 choose another tile, in the mean 1% faster, the worst 3.5% slower, 3169 tokens in blocks of 177 821 -> 850).
+constexpr double kWideRound = 0.945;
 
 hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int heavy_tiles, int k_likely, hipStream_t s) {
   Gemm1Params p = p_in;

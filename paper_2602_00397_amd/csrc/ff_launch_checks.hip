@@ -170,7 +170,8 @@ static void check_gemm1_wide() {
       {{1000, 128, 4096, 14336, 64, 7168, 0, 0}, true, 1},   {{1200, 128, 4096, 14336, 64, 7168, 0, 0}, false, 1},
       {{900, 128, 2048, 8192, 32, 4096, 0, 0}, true, 2},      // half a tile of units: cut
       {{4500, 128, 4096, 14336, 64, 7168, 0, 0}, true, 2},    // whole: a fifth round
-      {{2800, 200, 4096, 14336, 64, 7168, 0, 0}, false, 1}};  // two token tiles to a block
+      {{2800, 200, 4096, 14336, 64, 7168, 0, 0}, false, 1},   // two token tiles to a block
+      {{9312, 128, 3584, 18944, 64, 9472, 0, 0}, true, 1}, {{8401, 128, 3584, 18944, 64, 9472, 0, 0}, true, 1}};   // 12 rounds against 22 of half the size
   for (const auto &c : calls) {
     gemm1(c.s, true, 11, 0, -1);
     const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
