@@ -43,6 +43,27 @@ __device__ __forceinline__ float gv_act(int act, float g) {
   return g;
 }
 
+// What a kernel gets: first what its first loads' addresses need, as plain arguments, two vectors of four and three pointers, in
+// scalar registers at the start (five tokens on a kept list of 2048/8192, both kernels 19.6 -> 19.1 us); then a struct of what it needs
+// besides.  Few arguments and bytes, for the launches: the smallest calls last as long as the host takes to send them (256/688, kept list, a
+// token, us: the whole parameter block and eleven plain arguments 8.62, the block alone 8.38, this 8.50; a dense one 8.30, 8.95 and 8.18).
+typedef int32_t __attribute__((ext_vector_type(4))) i32x4_t;
+struct Gemv1Args {
+  const bf16_t *wg, *wu, *wc1;
+  bf16_t *h;
+  int32_t *counter;      // [n_blocks][column groups] of the next kernel, how many chunks are done
+  const uint8_t *mask;
+  int32_t sub_block, comp_act, d_ffn, hs;
+};
+struct Gemv2Args {
+  const bf16_t *wd, *wc2;
+  float *part;
+  int32_t *counter;
+  void *y;
+  bf16_t *res;
+  int32_t d_ffn, d_model, out_f32;
+};
+
 // One workgroup per 16 list positions; its wavefronts split the channels (steps steps of 64 each), every wavefront with a ring
 // of 2 steps on their way, and their sums are added in wavefront order.  The 32 rows of an MFMA (32x32x16) are the 16 gate rows
 // and the 16 up rows; they are loaded by fours of lanes and exchanged as in the gate/up GEMM (lane by lane, as the operand wants
@@ -52,13 +73,11 @@ __device__ __forceinline__ float gv_act(int act, float g) {
 // end next to each other (a dense token, 8 wavefronts: with 4 steps 54.5 us, with 2 52.6).  How many wavefronts: gemv1_waves.
 // With multiply-adds, a wavefront per position, a dense token of 4096/14336 took 44.5 us (now 45.5), one on a list of 7168 23.2
 // (22.6), one on 4096 positions of 8192/28672 86.1 (87.5), five tokens on 4096 positions of 2048/8192 19.5 (12.3).
-// What the first loads' addresses need comes as plain arguments, which are in scalar registers at the start (five tokens on a kept list
-// of 2048/8192, both kernels 19.6 -> 19.1 us).
 // grid (groups of 16 positions, n_blocks), LDS = gemv1_lds.
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : 6)))
-void ff_gemv1_kernel(const int32_t *idx, const int32_t *per_block, const bf16_t *x, int uniform, int cap, int k_stride, int rc, int T, int block,
-                     int d_model, int steps, GemvParams p) {
+void ff_gemv1_kernel(i32x4_t lists, i32x4_t sizes, const int32_t *idx, const int32_t *per_block, const bf16_t *x, Gemv1Args p) {
+  const int uniform = lists[0], cap = lists[1], k_stride = lists[2], rc = lists[3], T = sizes[0], block = sizes[1], d_model = sizes[2], steps = sizes[3];
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -167,8 +186,8 @@ void ff_gemv1_kernel(const int32_t *idx, const int32_t *per_block, const bf16_t 
 // token on 7168 of 4096/14336 19.0 and 15.9, dense 31.2 and 27.0; eight tokens of a list each 39.2 and 23.7.)
 // grid (d_model / 128, n_chunks, n_blocks)
 __global__ __launch_bounds__(kGemvWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
-void ff_gemv2_kernel(const int32_t *idx, const int32_t *per_block, const bf16_t *h, int uniform, int cap, int k_stride, int rc, int T, int block,
-                     int hs, int n_chunks, GemvParams p) {
+void ff_gemv2_kernel(i32x4_t lists, i32x4_t sizes, const int32_t *idx, const int32_t *per_block, const bf16_t *h, Gemv2Args p) {
+  const int uniform = lists[0], cap = lists[1], k_stride = lists[2], rc = lists[3], T = sizes[0], block = sizes[1], hs = sizes[2], n_chunks = sizes[3];
   constexpr int PITCH = kGemv2Cols + 4;
   __shared__ __align__(16) float red[kGemvWaves][kGemvMaxTokens][PITCH];
   __shared__ int last_s;
@@ -265,7 +284,7 @@ void ff_gemv2_kernel(const int32_t *idx, const int32_t *per_block, const bf16_t 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // this wavefront's sums have arrived
   __syncthreads();
   if (tid == 0)
-    last_s = __hip_atomic_fetch_add(p.counter + b * gridDim.x + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
+    last_s = __hip_atomic_fetch_add(p.counter + b * (p.d_model / kGemv2Cols) + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
   __syncthreads();
   if (!last_s) return;
   for (int v = tid; v < nt * kGemv2Cols; v += kGemvWaves * 64) {
@@ -322,8 +341,7 @@ bool ff_gemv_eligible(int n_tokens, int block, int d_model, int lds_limit) {
   return n_tokens <= kGemvMaxTokens && gemv1_lds(16, nt, d_model) <= (size_t)lds_limit;
 }
 
-hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, Profiler *prof) {
-  GemvParams p = p_in;
+hipError_t ff_launch_gemv(const GemvParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
   if (!ff_gemv_eligible(p.T, p.block, p.d_model, lds_limit)) return hipErrorInvalidValue;
   if (!g_gemv_lds_raised) {
     for (const auto k : {ff_gemv1_kernel<4>, ff_gemv1_kernel<8>, ff_gemv1_kernel<16>}) {
@@ -334,7 +352,7 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   }
   const int nt = p.block < p.T ? p.block : p.T;
   const int n_extent = p.k.k_max + p.rc;
-  p.counter = reinterpret_cast<int32_t *>(p.part + (size_t)kGemvChunks * p.T * p.d_model);
+  int32_t *counter = reinterpret_cast<int32_t *>(p.part + (size_t)kGemvChunks * p.T * p.d_model);
   // gemv2: two workgroups per CU where each of their wavefronts then has two groups of 32 positions, the number that it keeps on
   // their way, else at most one: more chunks are more partial sums to add up.  One token, two workgroups per CU down to one group
   // for a wavefront, us -> this: 2048/8192 dense 16.3 -> 13.1, K 4096 11.9 -> 9.9; 4096/14336, K 7168 15.7 -> 14.8, K 3584 12.1 ->
@@ -342,19 +360,20 @@ hipError_t ff_launch_gemv(const GemvParams &p_in, int lds_limit, hipStream_t s, 
   const int cols = p.d_model / kGemv2Cols, groups = (n_extent + 31) / 32;
   const int most = 512 / (cols * p.n_blocks), full = (groups + 2 * kGemvWaves - 1) / (2 * kGemvWaves);
   const int nc = most <= full ? most : std::min(full, 256 / (cols * p.n_blocks));
-  p.n_chunks = nc < 1 ? 1 : (nc > kGemvChunks ? kGemvChunks : nc);
+  const int n_chunks = nc < 1 ? 1 : (nc > kGemvChunks ? kGemvChunks : nc);
   const int groups1 = (n_extent + 31) / 32 * (32 / kGemv1Pos);
   const int cap = p.idx ? std::min(p.d_ffn, p.k_stride) : p.d_ffn;   // (without a list position p is row p, and the pitch bounds nothing)
+  const i32x4_t lists = {p.k.uniform, cap, p.k_stride, p.rc};
   const int nw = gemv1_waves((long)groups1 * p.n_blocks, nt, p.d_model, lds_limit);
   const auto fn = nw == 4 ? ff_gemv1_kernel<4> : nw == 8 ? ff_gemv1_kernel<8> : ff_gemv1_kernel<16>;
   prof_begin(prof, FF_STAGE_GEMM1, s);
   hipLaunchKernelGGL(fn, dim3(groups1, p.n_blocks), dim3(nw * 64),
-                     gemv1_lds(nw, nt, p.d_model), s, p.idx, p.k.per_block, p.x, p.k.uniform, cap, p.k_stride, p.rc, p.T, p.block, p.d_model,
-                     gemv1_steps(nw, p.d_model), p);
+                     gemv1_lds(nw, nt, p.d_model), s, lists, (i32x4_t{p.T, p.block, p.d_model, gemv1_steps(nw, p.d_model)}), p.idx, p.k.per_block, p.x,
+                     (Gemv1Args{p.wg, p.wu, p.wc1, p.h, counter, p.mask, p.sub_block, p.comp_act, p.d_ffn, p.hs}));
   prof_end(prof, s);
   prof_begin(prof, FF_STAGE_GEMM2, s);
-  hipLaunchKernelGGL(ff_gemv2_kernel, dim3(cols, p.n_chunks, p.n_blocks), dim3(kGemvWaves * 64), 0, s, p.idx, p.k.per_block, p.h, p.k.uniform, cap,
-                     p.k_stride, p.rc, p.T, p.block, p.hs, p.n_chunks, p);
+  hipLaunchKernelGGL(ff_gemv2_kernel, dim3(cols, n_chunks, p.n_blocks), dim3(kGemvWaves * 64), 0, s, lists, (i32x4_t{p.T, p.block, p.hs, n_chunks}),
+                     p.idx, p.k.per_block, p.h, (Gemv2Args{p.wd, p.wc2, p.part, counter, p.y, p.res, p.d_ffn, p.d_model, p.out_f32}));
   prof_end(prof, s);
   return hipGetLastError();
 }

@@ -254,8 +254,6 @@ struct GemvParams {
   void *y;             // [T][d_model] bf16 or f32
   bf16_t *res;         // or nullptr: residual mode as in Gemm2Params
   int32_t T, d_model, d_ffn, block, n_blocks, rc, comp_act, k_stride, hs, out_f32;
-  int32_t n_chunks = 1;           // chosen by ff_launch_gemv, and
-  int32_t *counter = nullptr;     // [n_blocks][column groups], how many chunks are done
   // merged lists (as in Gemm1Params): position p belongs to token t iff bit (t - block start) / sub_block of
   // mask[b * k_stride + p] is set; nullptr = every position belongs to every token
   const uint8_t *mask = nullptr;

@@ -17,7 +17,6 @@ struct Launch {
   size_t lds;
   Gemm1Params g1;
   Gemm2Params g2;
-  GemvParams gv;
   dim3 dims;
 };
 static std::vector<Launch> g_log;
@@ -25,9 +24,8 @@ static int g_fail = 0, g_calls = 0;
 static bool g_down = false, g_few = false, g_pred = false;   // whose launches are being recorded
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
-  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, {}, grid};
-  if (g_pred) {}                                                           // (plain arguments: the grid says enough)
-  else if (g_few) memcpy(static_cast<void *>(&l.gv), args[11], sizeof(l.gv));   // (behind the plain arguments)
+  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, grid};
+  if (g_few || g_pred) {}                                                  // (the grid says enough)
   else if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
   else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
   g_log.push_back(l);
