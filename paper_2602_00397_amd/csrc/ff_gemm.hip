@@ -1881,18 +1881,19 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
       const int wide = gemm1_direct_addresses(p) ? kGemm1Direct128 : kWide128;
       const Variant &w = kGemm1[wide];
       const int n_full = base_extent / w.bn, rem_w = base_extent % w.bn;
-      if (w.lds > g_lds_limit) {
-      } else if (!ragged) {
+      const bool fits = w.lds <= g_lds_limit;
+      if (fits && !ragged) {
         const long V = (long)p.n_blocks * ((p.block + w.bm - 1) / w.bm);
-        const bool behind = n_full * w.bn >= p.k.k_max && n_full * w.bn % 64 == 0;      // nothing but compensator units is left
-        const double rest = rem_w == 0 || (behind && rem_w <= 32) ? 0.0 : behind ? 0.03 + 0.15 * p.T / 8192.0 : 0.22 * (double)((2 * V * ((rem_w + 63) / 64) + kNumCU - 1) / kNumCU);
+        const bool behind = n_full * w.bn >= p.k.k_max;      // nothing but compensator units is left
+        const double rest = rem_w == 0 || (behind && rem_w <= 32) ? 0.0 : behind ? 0.03 + 0.15 * p.T / 8192.0 :
+                            0.22 * (double)((2 * V * ((rem_w + 63) / 64) + kNumCU - 1) / kNumCU);
         const double whole = (double)xcd_rounds(V, (up64(base_extent) + w.bn - 1) / w.bn);
         const double cut = n_full == 0 ? 1e30 : (double)xcd_rounds(V, n_full) + rest;
         if (kWideRound * (split == 0 ? whole : split > 0 ? cut : std::min(whole, cut)) <= best) {
           variant = wide;
           if (split < 0) split = rem_w > 0 && cut <= whole;
         }
-      } else {
+      } else if (fits) {
         const long wide_full = (long)p.n_blocks * n_full;
         const long rem_wgs = (long)p.n_blocks * 2 * ((rem_w + 63) / 64);
         const long surplus = (long)p.k.n_heavy * (n_extent / w.bn - n_full);
@@ -1981,7 +1982,8 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p_in, int variant, int split, int 
   const int rem0 = n_extent - rem;
   const bool only_comp = !ragged && rem0 >= p.k.k_max && rem0 % 64 == 0 && (uint64_t)p.rc * (uint64_t)p.d_model * 2u >> 32 == 0;
   if (only_comp) {
-    // Nothing but compensator units is left, the same columns for every token.  64 tokens to a workgroup once those fill the chip.
+    // Nothing but compensator units is left, the same columns for every token.  64 tokens to a workgroup where 32 would be more
+    // workgroups than CUs.
     int K = p.k.k_max, u0 = rem0 - K;
     const bool narrow = rem <= 32, tall = p.T > 32 * kNumCU;
     const void *fn = narrow ? (tall ? reinterpret_cast<const void *>(&ff_comp_kernel<2, 32>) : reinterpret_cast<const void *>(&ff_comp_kernel<1, 32>))

@@ -238,7 +238,8 @@ hipError_t ff_launch_gemm1(const Gemm1Params &p, int variant, int split, int hea
 // n > 1 = into n pieces, fewer where split_part has no room for them.
 hipError_t ff_launch_gemm2(const Gemm2Params &p, int variant, int split, int row_mode, int ksplit, int nsplit, hipStream_t s);
 size_t ff_gemm2_split_bytes(int n_tokens, int d_model);   // room for cutting every list (0: too many tokens for that to pay)
-size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model);   // room for the launcher's own four short pieces with up to six heavy blocks, and for 16 (a forced ksplit) with two
+// room for the launcher's own four short pieces with up to six heavy blocks, and for 16 (a forced ksplit) with two
+size_t ff_gemm2_part_bytes(int n_tokens, int block, int d_model);
 hipError_t ff_gemm_init(int lds_limit);  // raises the kernels' dynamic-LDS limits; once per process
 int ff_gemm1_num_variants();
 int ff_gemm2_num_variants();

@@ -1,6 +1,6 @@
 // Checks of the GEMM launchers' choices, of the few-token path's limits, of the pooling kernels' and of top-K's bucket map, without a GPU: this program
-// is linked with the launchers' object files and defines hipLaunchKernel itself, so every launch is recorded instead of made.  Swept over shapes, list lengths and options, every
-// launch must fit what its kernel assumes.  Exit code 0 = all hold.
+// is linked with the launchers' object files and defines hipLaunchKernel itself, so every launch is recorded instead of made.
+// Swept over shapes, list lengths and options, every launch must fit what its kernel assumes.  Exit code 0 = all hold.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -182,7 +182,8 @@ static void check_gemm1_wide() {
 // that is half empty; not so with a second block.
 static void check_gemm1_short_block() {
   struct { Shape s; int variant; } calls[] = {
-      {{61, 128, 3584, 18944, 64, 18944, 17760, -1}, 0}, {{61, 128, 3584, 18944, 64, 18944, 14208, -1}, 7}, {{64, 64, 3584, 18944, 64, 18944, 0, 0}, 0}, {{40, 64, 128, 17024, 64, 17000, 0, 0}, 0},
+      {{61, 128, 3584, 18944, 64, 18944, 17760, -1}, 0}, {{61, 128, 3584, 18944, 64, 18944, 14208, -1}, 7}, {{64, 64, 3584, 18944, 64, 18944, 0, 0}, 0},
+      {{40, 64, 128, 17024, 64, 17000, 0, 0}, 0},
       {{61, 128, 128, 17024, 64, 17024, 16896, -1}, 0}, {{64, 64, 3584, 18944, 64, 9472, 0, 0}, 7},  {{30, 128, 4096, 14336, 64, 7168, 0, 0}, 10}};
   for (const auto &c : calls) {
     gemm1(c.s, true, c.variant, 0, -1);
@@ -245,7 +246,8 @@ static void check_gemm2_routes() {
     DownOptions o;
     o.variant = r.variant;
     o.row_mode = r.row_mode;
-    CHECK(gemm2(r.s, r.list, o, true) == hipSuccess && g_log[0].fn == chosen[0].fn && (chosen[0].g2.n_split > 1) == r.cut, "T %d d_model %d d_ffn %d", r.s.T, r.s.d_model, r.s.d_ffn);
+    CHECK(gemm2(r.s, r.list, o, true) == hipSuccess && g_log[0].fn == chosen[0].fn && (chosen[0].g2.n_split > 1) == r.cut,
+          "T %d d_model %d d_ffn %d", r.s.T, r.s.d_model, r.s.d_ffn);
   }
 }
 
@@ -258,12 +260,13 @@ static void check_gemm2_prices() {
       // more 128 x 256 there
       {{5000, 128, 256, 688, 0, 688, 0, 0}, false, 9}, {{7000, 128, 256, 688, 0, 688, 0, 0}, false, 9}, {{9500, 128, 256, 688, 0, 688, 0, 0}, false, 8},
       {{5000, 128, 256, 688, 16, 344, 0, 0}, true, 9}, {{7000, 256, 256, 688, 0, 344, 0, 0}, true, 9}, {{14000, 128, 256, 688, 16, 344, 0, 0}, true, 4},
-      {{14000, 128, 256, 688, 16, 172, 0, 0}, true, 8}, {{2000, 128, 256, 688, 16, 344, 688, 2}, true, 9}, {{5000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{7000, 128, 256, 688, 16, 344, 688, 2}, true, 8},
+      {{14000, 128, 256, 688, 16, 172, 0, 0}, true, 8},
+      {{2000, 128, 256, 688, 16, 344, 688, 2}, true, 9}, {{5000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{7000, 128, 256, 688, 16, 344, 688, 2}, true, 8},
       {{9000, 128, 256, 688, 16, 344, 688, 2}, true, 8}, {{11582, 128, 256, 688, 16, 688, 0, -1}, true, 4},   // (the last of merged lists)
       // ... and where it is not; a few longer lists' pieces beside more than a round of common tiles, and beside less
       {{2909, 64, 4096, 14336, 64, 3584, 14336, 2}, true, 6}, {{3000, 64, 3584, 18944, 64, 4736, 18944, 2}, true, 6},
-      {{11490, 256, 2048, 8192, 32, 2327, 8192, 2}, true, 5}, {{11609, 128, 2048, 8192, 32, 2048, 8192, 2}, true, 5}, {{4951, 128, 4096, 14336, 64, 7168, 14336, 2}, true, 7},
-      {{2300, 64, 3584, 18944, 64, 9472, 18944, 2}, true, 8},
+      {{11490, 256, 2048, 8192, 32, 2327, 8192, 2}, true, 5}, {{11609, 128, 2048, 8192, 32, 2048, 8192, 2}, true, 5},
+      {{4951, 128, 4096, 14336, 64, 7168, 14336, 2}, true, 7}, {{2300, 64, 3584, 18944, 64, 9472, 18944, 2}, true, 8},
       {{1700, 64, 2048, 8192, 32, 2048, 8192, 2}, true, 6}, {{2048, 64, 2048, 8192, 32, 2048, 8192, 2}, true, 6},
       {{4096, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}, {{1350, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}};
   for (const auto &c : calls) {
@@ -271,7 +274,8 @@ static void check_gemm2_prices() {
     o.variant = c.variant;
     gemm2(c.s, c.list, o, true);
     const void *fn = g_log.empty() ? nullptr : g_log[0].fn;
-    CHECK(gemm2(c.s, c.list, DownOptions(), true) == hipSuccess && !g_log.empty() && g_log[0].fn == fn, "T %d block %d d_model %d K %d, not tile %d", c.s.T, c.s.block, c.s.d_model, c.s.k, c.variant);
+    CHECK(gemm2(c.s, c.list, DownOptions(), true) == hipSuccess && !g_log.empty() && g_log[0].fn == fn,
+          "T %d block %d d_model %d K %d, not tile %d", c.s.T, c.s.block, c.s.d_model, c.s.k, c.variant);
   }
   // no tile of 512 columns for 256 or fewer, whatever the lists
   std::set<const void *> wide;
@@ -384,7 +388,8 @@ static void check_few_tokens() {
     p.T = c.T; p.block = c.block; p.n_blocks = (c.T + c.block - 1) / c.block; p.d_model = c.dm; p.d_ffn = p.k_stride = 18944; p.idx = g_idx; p.part = g_room;
     p.k.uniform = p.k.k_max = p.k.k_base = c.k;
     g_log.clear();
-    CHECK(ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess && g_log[0].threads == c.threads && g_log[1].grid == c.grid2, "%d tokens of %d, K %d: %u threads, then %u workgroups", c.T, c.dm, c.k,
+    CHECK(ff_launch_gemv(p, kLds, nullptr, nullptr) == hipSuccess && g_log[0].threads == c.threads && g_log[1].grid == c.grid2,
+          "%d tokens of %d, K %d: %u threads, then %u workgroups", c.T, c.dm, c.k,
           g_log[0].threads, g_log[1].grid);
   }
   g_few = false;
@@ -407,7 +412,8 @@ static void check_pooling() {
       p.q_pred = c.softmax ? reinterpret_cast<const bf16_t *>(g_idx) : nullptr;
       p.k_stride = p.k.uniform = p.k.k_max = p.k.k_base = 344;
       const size_t bytes = ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, c.softmax), n = (size_t)p.n_blocks * c.r * sizeof(double);
-      CHECK(bytes == c.slices * n && ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, true) >= bytes, "T %d block %d d_model %d r %d: %zu bytes", c.T, c.block, c.dm, c.r, bytes);
+      CHECK(bytes == c.slices * n && ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, true) >= bytes,
+            "T %d block %d d_model %d r %d: %zu bytes", c.T, c.block, c.dm, c.r, bytes);
       p.hpart_fine = reinterpret_cast<double *>(g_room);
       p.hpart_fine_bytes = room ? bytes : bytes - (bytes > 0);
       g_log.clear();

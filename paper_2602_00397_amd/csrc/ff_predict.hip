@@ -578,21 +578,21 @@ constexpr int TOPK_FEW = 16;   // candidates that are ranked by fours of lanes
 
 // LDS of the threshold search, shared by both top-K kernels
 struct TopkShared {
-  __align__(16) unsigned int no_bucket[64];        // in front of the histogram: what buckets -1 .. -64 count
-  unsigned int hist[TOPK_BUCKETS];                 // also the 256-bin histogram of the radix path
+  __align__(16) unsigned int bins[64 + TOPK_BUCKETS];   // in front of the histogram: what buckets -1 .. -64 count
   double cand[TOPK_CAND + TOPK_FEW];
   int wsum[16];
   unsigned int wtot[4];
   unsigned int sel_bin, sel_rem, n_cand;
   double theta;
   int ties, n_ties;
+  __device__ __forceinline__ unsigned int *hist() { return bins + 64; }   // (also the 256-bin histogram of the radix path)
 };
 
 // The bucket that holds the K-th largest score, and which of its scores that is (sh.sel_bin, sh.sel_rem), from a full histogram.
 __device__ __forceinline__ void topk_find_bucket(TopkShared &sh, int K) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // thread t owns buckets 4095-4t .. 4092-4t (descending); prefix over threads = scores in higher buckets
-  const uint4 h4 = *reinterpret_cast<const uint4 *>(&sh.hist[TOPK_BUCKETS - 4 - 4 * tid]);
+  const uint4 h4 = *reinterpret_cast<const uint4 *>(&sh.hist()[TOPK_BUCKETS - 4 - 4 * tid]);
   const int h[4] = {(int)h4.w, (int)h4.z, (int)h4.y, (int)h4.x};
   const int local = (h[0] + h[1]) + (h[2] + h[3]);
   const int inc = wave_incl_scan(local);
@@ -688,12 +688,12 @@ __device__ __forceinline__ bool topk_threshold(TopkShared &sh, int K, double lo_
   need_radix = need_radix || map.none;
   // bucket_of(score, rounding): the bucket map.  False: the threshold's bucket holds too many scores.
   auto by_buckets = [&](auto bucket_of) __attribute__((always_inline)) -> bool {
-    each([&](double v, float s) { atomicAdd(&sh.hist[bucket_of(v, s)], 1u); });
+    each([&](double v, float s) { atomicAdd(&sh.hist()[bucket_of(v, s)], 1u); });
     __syncthreads();
     topk_find_bucket(sh, K);
     const int tb = __builtin_amdgcn_readfirstlane((int)sh.sel_bin);
     const int need = __builtin_amdgcn_readfirstlane((int)sh.sel_rem);   // rank of theta inside bucket tb (1 = largest)
-    const int c = __builtin_amdgcn_readfirstlane((int)sh.hist[tb]);
+    const int c = __builtin_amdgcn_readfirstlane((int)sh.hist()[tb]);
     if (c > TOPK_CAND) return false;              // uniform: every thread reads the same hist[tb]
     topk_pad(sh, c);
     gather(bucket_of, tb, [&](double v) { sh.cand[atomicAdd(&sh.n_cand, 1u)] = v; });
@@ -714,18 +714,18 @@ __device__ __forceinline__ bool topk_threshold(TopkShared &sh, int K, double lo_
   for (int pass = 7; pass >= 0; --pass) {
     const int shift = pass * 8;
     __syncthreads();
-    if (tid < 256) sh.hist[tid] = 0;
+    if (tid < 256) sh.hist()[tid] = 0;
     __syncthreads();
     each([&](double v, float) {
       const unsigned long long k = score_key(v);
       const bool match = (pass == 7) || ((k >> (shift + 8)) == prefix);
-      if (match) atomicAdd(&sh.hist[(unsigned int)(k >> shift) & 255u], 1u);
+      if (match) atomicAdd(&sh.hist()[(unsigned int)(k >> shift) & 255u], 1u);
     });
     __syncthreads();
     // suffix sums S[d] = sum_{d' >= d} hist[d'] over the 256 digits
     unsigned int hv = 0, suf = 0;
     if (tid < 256) {
-      hv = sh.hist[tid];
+      hv = sh.hist()[tid];
       suf = hv;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
@@ -793,7 +793,7 @@ __global__ __launch_bounds__(1024) void ff_topk_kernel(const double *__restrict_
     hi_v = fmax(hi_v, __shfl_xor(hi_v, off));
   }
   if (lane == 0) { red_lo[wave] = lo_v; red_hi[wave] = hi_v; }
-  for (int i = tid; i < TOPK_BUCKETS; i += 1024) sh.hist[i] = 0;
+  for (int i = tid; i < TOPK_BUCKETS; i += 1024) sh.hist()[i] = 0;
   if (tid == 0) sh.n_cand = 0;
   // fmin/fmax skip a NaN, whose key nevertheless ranks above (or below) every number: the bucket map
   // would not be monotone over the keys.  The radix path orders the keys themselves, whatever they are.
@@ -913,7 +913,7 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
   int K = ks.per_block ? ks.per_block[b] : ks.uniform;
   K = max(1, min(K, min(d_ffn, k_stride)));
   static_assert(TOPK_BUCKETS == 4 * 1024, "a thread clears and scans four buckets");
-  *reinterpret_cast<uint4 *>(&sh.hist[4 * tid]) = make_uint4(0, 0, 0, 0);
+  *reinterpret_cast<uint4 *>(&sh.hist()[4 * tid]) = make_uint4(0, 0, 0, 0);
   if (tid == 0) sh.n_cand = 0;
   int bk[ROWS];                          // roundings, then buckets
   float lo = (float)v[0], hi = lo;
@@ -973,14 +973,14 @@ __global__ __launch_bounds__(1024) void ff_topk_reg_kernel(const double *__restr
 #pragma unroll
       for (int u = 0; u < ROWS; ++u) bk[u] = i0 + u * 64 < d_ffn ? bk[u] : ~lane;
     }
-    unsigned int *hist = sh.hist;
+    unsigned int *hist = sh.hist();
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) atomicAdd(hist + bk[u], 1u);
     __syncthreads();
     topk_find_bucket(sh, K);
     int tb = __builtin_amdgcn_readfirstlane((int)sh.sel_bin);
     const int need = __builtin_amdgcn_readfirstlane((int)sh.sel_rem);   // rank of theta inside bucket tb (1 = largest)
-    const int c = __builtin_amdgcn_readfirstlane((int)sh.hist[tb]);
+    const int c = __builtin_amdgcn_readfirstlane((int)sh.hist()[tb]);
     if (c <= TOPK_CAND) {                       // (uniform: every thread reads the same)
       topk_pad(sh, c);
       unsigned int open_rows = 0;               // rows that hold a candidate
@@ -1141,7 +1141,9 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
     const int lw = pool_fine_lanes(p.T, p.block, p.d_model, p.r, p.q_pred != nullptr);
     hpart = p.hpart_fine;
     n_slices = (p.d_model + 8 * lw - 1) / (8 * lw);
-    hipLaunchKernelGGL(lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>) : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>), dim3(n_slices, p.n_blocks), dim3(kPoolFineThreads), 0, s,
+    const auto fn = lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>)
+                             : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>);
+    hipLaunchKernelGGL(fn, dim3(n_slices, p.n_blocks), dim3(kPoolFineThreads), 0, s,
                        p.x, p.q_pred ? p.z : nullptr, p.w1, hpart, p.T, p.d_model, p.block, p.r);
   } else if (p.q_pred) {
     hipLaunchKernelGGL(ff_pool_kernel<true>, dim3(n_slices, p.n_blocks, oz), dim3(256),
