@@ -174,10 +174,9 @@ ff_status ff_layer_budgets(const double *importance, int32_t n_layers,
  * Scores are computed in float64 without intermediate rounding; the K highest
  * are kept and equal scores go to the lower index (-0 and +0 are equal).
  * A call repeated on the same inputs gives the same bits.  The order of the
- * sums depends on the number and length of the blocks in the call, and with
- * few of them on whether the workspace has all that ff_workspace_bytes asks
- * for: a prompt given in parts, or a call with less workspace, may differ in
- * the last bits of its scores.
+ * sums depends on the sizes of the call, the number and length of its blocks
+ * among them, and on nothing else: a prompt given in parts may differ from the
+ * whole prompt in the last bits of its scores.
  * Scores are expected to be finite; if one is not, exactly K in-range indices
  * are still written, with NaN ranked by its bit pattern. */
 ff_status ff_predict(ff_ctx *ctx, const ff_shape *shape, const void *x,

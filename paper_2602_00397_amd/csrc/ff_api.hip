@@ -265,7 +265,7 @@ ff_status run_predict(ff_ctx *ctx, const ff_shape &s, const Layout &L, const voi
   p.z = reinterpret_cast<double *>(base + L.z);
   p.hpart = reinterpret_cast<double *>(base + L.hpart);
   p.scores = scores_opt ? scores_opt : reinterpret_cast<double *>(base + L.scores);
-  // narrower slices: no part of what a call needs, used where scratch has the room
+  // narrower slices: no part of what a call needs, faster where scratch has the room, the same sums elsewhere
   const size_t fine_at = up(L.total, 256), have = scratch_base ? (size_t)FF_STATIC_SCRATCH_BYTES : ctx->ws_bytes;
   if (have > fine_at) {
     p.hpart_fine = reinterpret_cast<double *>(base + fine_at);

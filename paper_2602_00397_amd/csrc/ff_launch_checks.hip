@@ -18,13 +18,16 @@ struct Launch {
   Gemm1Params g1;
   Gemm2Params g2;
   dim3 dims;
+  const double *pooled;     // where a pooling kernel writes
 };
 static std::vector<Launch> g_log;
 static int g_fail = 0, g_calls = 0;
 static bool g_down = false, g_few = false, g_pred = false;   // whose launches are being recorded
+static size_t g_pool_at = 0;                                 // which of the predictor's is the pooling kernel
 
 extern "C" hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t) {
-  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, grid};
+  Launch l = {fn, grid.x * grid.y * grid.z, block.x, lds, {}, {}, grid, nullptr};
+  if (g_pred && g_log.size() == g_pool_at) memcpy(&l.pooled, args[3], sizeof(l.pooled));
   if (g_few || g_pred) {}                                                  // (the grid says enough)
   else if (g_down) memcpy(static_cast<void *>(&l.g2), args[0], sizeof(l.g2));
   else memcpy(static_cast<void *>(&l.g1), args[0], sizeof(l.g1));
@@ -395,8 +398,8 @@ static void check_few_tokens() {
   g_few = false;
 }
 
-// The predictor: which calls pool in narrow slices, and how narrow, given the room that ff_pool_fine_bytes asks for; without it, or
-// elsewhere, in 512 channels.
+// The predictor: which calls pool in narrow slices, and how narrow, given the room that ff_pool_fine_bytes asks for; without it the same
+// slices with a launch that adds them, or one workgroup for all of a block's where the scores' place does not hold them either.
 static void check_pooling() {
   g_pred = true;
   struct { int T, block, dm, r; bool softmax; unsigned slices; } calls[] = {      // slices: 0 = of 512 channels
@@ -406,23 +409,28 @@ static void check_pooling() {
       {16 * 128, 128, 4096, 64, false, 16}, {17 * 128, 128, 4096, 64, false, 0}, {128 * 128, 128, 512, 8, false, 4}, {129 * 128, 128, 512, 8, false, 0},
       {4096, 4096, 65536, 8, true, 512}, {4096, 4096, 65664, 8, true, 0}};
   for (const auto &c : calls)
-    for (bool room : {false, true}) {
+    for (int room : {0, 1, 2}) {                   // none and too few neurons, none and enough of them, all that is asked for
       PredictParams p = {};
-      p.T = c.T; p.block = c.block; p.d_model = c.dm; p.d_ffn = 688; p.r = c.r; p.n_blocks = (c.T + c.block - 1) / c.block;
+      p.T = c.T; p.block = c.block; p.d_model = c.dm; p.d_ffn = room == 1 ? c.slices * c.r + 8 : 24; p.r = c.r; p.n_blocks = (c.T + c.block - 1) / c.block;
       p.q_pred = c.softmax ? reinterpret_cast<const bf16_t *>(g_idx) : nullptr;
-      p.k_stride = p.k.uniform = p.k.k_max = p.k.k_base = 344;
+      p.k_stride = p.k.uniform = p.k.k_max = p.k.k_base = 8;
+      double at[3];
+      p.hpart = at; p.scores = at + 1; p.hpart_fine = at + 2;
       const size_t bytes = ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, c.softmax), n = (size_t)p.n_blocks * c.r * sizeof(double);
       CHECK(bytes == c.slices * n && ff_pool_fine_bytes(c.T, c.block, c.dm, c.r, true) >= bytes,
             "T %d block %d d_model %d r %d: %zu bytes", c.T, c.block, c.dm, c.r, bytes);
-      p.hpart_fine = reinterpret_cast<double *>(g_room);
-      p.hpart_fine_bytes = room ? bytes : bytes - (bytes > 0);
+      p.hpart_fine_bytes = room == 2 ? bytes : bytes - (bytes > 0);
       g_log.clear();
+      g_pool_at = c.softmax;
       ++g_calls;
-      CHECK(ff_launch_predict(p, kLds, nullptr, nullptr) == hipSuccess && g_log.size() == (c.softmax ? 4u : 3u), "T %d: %zu launches", c.T, g_log.size());
-      const Launch &pool = g_log[c.softmax];
-      const bool narrow = room && c.slices > 0;
-      CHECK(pool.threads == (narrow ? 512u : 256u) && pool.dims.x == (narrow ? c.slices : (unsigned)(c.dm + 511) / 512) && pool.dims.y == (unsigned)p.n_blocks,
+      const bool fine = c.slices > 0, sum = fine && room == 1;
+      CHECK(ff_launch_predict(p, kLds, nullptr, nullptr) == hipSuccess && g_log.size() == 3u + c.softmax + sum, "T %d: %zu launches", c.T, g_log.size());
+      const Launch &pool = g_log[c.softmax], &after = g_log[c.softmax + 1];
+      const unsigned x = !fine ? (c.dm + 511) / 512 : room == 0 ? 1 : c.slices;
+      CHECK(pool.threads == (fine ? 512u : 256u) && pool.dims.x == x && pool.dims.y == (unsigned)p.n_blocks &&
+                pool.pooled == (!fine || room == 0 ? p.hpart : room == 1 ? p.scores : p.hpart_fine),
             "T %d block %d d_model %d r %d softmax %d: %u x %u workgroups of %u", c.T, c.block, c.dm, c.r, c.softmax, pool.dims.x, pool.dims.y, pool.threads);
+      CHECK(!sum || (after.threads == 64 && after.dims.x == (unsigned)(c.r + 63) / 64 && after.dims.y == (unsigned)p.n_blocks), "T %d: sums", c.T);
     }
   g_pred = false;
 }

@@ -212,14 +212,11 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
 // softmax: 100 tokens of 4096/14336 23.2 -> 21.4, 2000 30.8 -> 29.3, 700 of 2048/8192 23.1 -> 19.6, 4096 27.0 -> 23.9, one block of 300
 // 27.4 -> 19.0, one of 4096 tokens of 4096/14336 165 -> 57; the mean: 700 of 2048/8192 17.1 -> 15.4, 250 of 4096/14336 17.7 ->
 // 16.6, blocks of 256 tokens of 3584/18944 28.9 -> 25.0, one block of 4096 of 4096/14336 107 -> 45.)
-// grid (slices of 8 LW channels, n_blocks)
+// This is one slice: out[h] = thread tid's output number tid + 512 h of its slice's sums (pool_fine_store says which).
 constexpr int kPoolFineThreads = 512;
 template <bool SOFTMAX, int LW>
-__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf16_t *__restrict__ x,
-                                                                       const double *__restrict__ z,
-                                                                       const bf16_t *__restrict__ w1,
-                                                                      double *__restrict__ hpart, int T,
-                                                                      int d_model, int Nb, int r) {
+__device__ __forceinline__ void pool_fine_slice(const bf16_t *__restrict__ x, const double *__restrict__ z, const bf16_t *__restrict__ w1,
+                                                int slice, int T, int d_model, int Nb, int r, double (&out)[2]) {
   constexpr int NT = kPoolFineThreads, NW = NT / 64, CH = 8 * LW, RPW = 64 / LW, STEP = NW * RPW, U = LW / 4, WU = LW / 4;
   __shared__ double red1[2 * NW];
   // Nb <= 4096 weights; rows' sums [wavefront][channel]; the outputs' [8][thread] and [group][output]
@@ -228,7 +225,7 @@ __global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf
   __shared__ double a_s[CH];               // this workgroup's pooled channels
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int b = blockIdx.y, t0 = b * Nb, n = min(T, t0 + Nb) - t0;
-  const int c_base = blockIdx.x * CH, n_ch = min(CH, d_model - c_base);
+  const int c_base = slice * CH, n_ch = min(CH, d_model - c_base);
   const int sub = lane / LW, c8 = 8 * (lane % LW);
   const bf16_t *xc = x + (size_t)t0 * d_model + c_base + min(c8, n_ch - 8);   // (channels past d_model: not used)
   const int row0 = wave * RPW + sub;
@@ -327,7 +324,6 @@ __global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf
 #pragma unroll
   for (int q = 0; q < 8; ++q) ps[q * NT + tid] = acc8[q];
   __syncthreads();
-  double *dst = hpart + ((size_t)b * gridDim.x + blockIdx.x) * r;
   const int cols = 8 << o_bits, per = min(8, CL), G = CL / per;     // cols * G = 8 NT / per
   double sum[2];
 #pragma unroll
@@ -346,14 +342,75 @@ __global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf
     if (e < cols * G) ps[e] = sum[h];
   }
   __syncthreads();
-  for (int j = tid; j < cols; j += NT) {
-    const int oo = j & (o_ceil - 1);
-    if (oo < n_oct) {
-      double tot = 0.0;
-      for (int g = 0; g < G; ++g) tot += ps[g * cols + j];
-      dst[8 * oo + (j >> o_bits)] = tot;
-    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = tid + h * NT;
+    out[h] = 0.0;
+    if (j < cols)
+      for (int g = 0; g < G; ++g) out[h] += ps[g * cols + j];
   }
+}
+// what pool_fine_slice's thread tid has in out[h] is an output of the first layer, at dst
+__device__ __forceinline__ void pool_fine_store(double *dst, int r, const double (&out)[2]) {
+  const int n_oct = r >> 3, o_bits = n_oct > 1 ? 32 - __builtin_clz(n_oct - 1) : 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = (int)threadIdx.x + h * kPoolFineThreads, oo = j & ((1 << o_bits) - 1);
+    if (j < (8 << o_bits) && oo < n_oct) dst[8 * oo + (j >> o_bits)] = out[h];
+  }
+}
+
+// grid (slices of 8 LW channels, n_blocks)
+template <bool SOFTMAX, int LW>
+__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf16_t *__restrict__ x,
+                                                                       const double *__restrict__ z,
+                                                                       const bf16_t *__restrict__ w1,
+                                                                      double *__restrict__ hpart, int T,
+                                                                      int d_model, int Nb, int r) {
+  double out[2];
+  pool_fine_slice<SOFTMAX, LW>(x, z, w1, blockIdx.x, T, d_model, Nb, r, out);
+  pool_fine_store(hpart + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * r, r, out);
+}
+
+// A workspace may have no room for the narrow slices' partial sums.  A call's scores have the same bits without it: the sums go where the
+// scores will be, and this kernel adds a block's in slice order, as the scores kernels would.  (ff_predict alone, us, with the room,
+// without it, without it by 512-channel slices and so with other bits: 100 tokens of 4096/14336 16.0, 17.2, 16.2, softmax 21.4, 22.2, 22.4; 700
+// of 2048/8192, softmax 18.8, 21.0, 22.6; 100 of 256/688 12.7, 15.7, 13.9.)
+// hid[b][j] = sum_s part[b][s][j]; grid (ceil(r / 64), n_blocks)
+__global__ __launch_bounds__(64) void ff_pool_sum_kernel(const double *__restrict__ part, double *__restrict__ hid, int n_slices, int r) {
+  const int j = blockIdx.x * 64 + threadIdx.x, b = blockIdx.y;
+  if (j >= r) return;
+  const double *src = part + (size_t)b * n_slices * r + j;
+  double acc = 0.0;
+  for (int s0 = 0; s0 < n_slices; s0 += 16) {    // sixteen loads in flight (past the end: the last again, not added)
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = src[(size_t)min(s0 + u, n_slices - 1) * r];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (s0 + u < n_slices) acc += v[u];
+  }
+  hid[(size_t)b * r + j] = acc;
+}
+
+// The same where the scores' place is too small for them as well (many outputs, few neurons): one workgroup takes a block's slices one
+// after the other.  Nothing that is in a hurry has such sizes.
+// grid (n_blocks)
+template <bool SOFTMAX, int LW>
+__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_serial_kernel(const bf16_t *__restrict__ x,
+                                                                              const double *__restrict__ z,
+                                                                              const bf16_t *__restrict__ w1,
+                                                                              double *__restrict__ hid, int T,
+                                                                              int d_model, int Nb, int r) {
+  double sum[2] = {0.0, 0.0}, out[2];
+  for (int slice = 0; slice * 8 * LW < d_model; ++slice) {
+    pool_fine_slice<SOFTMAX, LW>(x, z, w1, slice, T, d_model, Nb, r, out);
+    sum[0] += out[0];
+    sum[1] += out[1];
+    __syncthreads();                       // (the next slice uses the same LDS)
+  }
+  pool_fine_store(hid + (size_t)blockIdx.y * r, r, sum);
 }
 
 // ---- Eq. 13 in float64 ---------------------------------------------------------------------
@@ -1137,14 +1194,22 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
   prof_begin(prof, FF_STAGE_POOL, s);
   const size_t fine_bytes = ff_pool_fine_bytes(p.T, p.block, p.d_model, p.r, p.q_pred != nullptr);
   if (p.q_pred) hipLaunchKernelGGL(ff_logits_kernel, dim3((p.T + 3) / 4), dim3(256), 0, s, p.x, p.q_pred, p.z, p.T, p.d_model);
-  if (fine_bytes > 0 && p.hpart_fine_bytes >= fine_bytes) {
+  if (fine_bytes > 0) {
     const int lw = pool_fine_lanes(p.T, p.block, p.d_model, p.r, p.q_pred != nullptr);
-    hpart = p.hpart_fine;
+    const double *z = p.q_pred ? p.z : nullptr;
     n_slices = (p.d_model + 8 * lw - 1) / (8 * lw);
-    const auto fn = lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>)
-                             : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>);
-    hipLaunchKernelGGL(fn, dim3(n_slices, p.n_blocks), dim3(kPoolFineThreads), 0, s,
-                       p.x, p.q_pred ? p.z : nullptr, p.w1, hpart, p.T, p.d_model, p.block, p.r);
+    const bool room = p.hpart_fine_bytes >= fine_bytes, at_scores = !room && (int64_t)n_slices * p.r <= p.d_ffn;
+    double *part = room ? p.hpart_fine : at_scores ? p.scores : p.hpart;
+    auto fn = lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>)
+                       : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>);
+    if (!room && !at_scores)
+      fn = lw == 16 ? (p.q_pred ? ff_pool_fine_serial_kernel<true, 16> : ff_pool_fine_serial_kernel<false, 16>)
+                    : (p.q_pred ? ff_pool_fine_serial_kernel<true, 32> : ff_pool_fine_serial_kernel<false, 32>);
+    hipLaunchKernelGGL(fn, dim3(room || at_scores ? n_slices : 1, p.n_blocks), dim3(kPoolFineThreads), 0, s,
+                       p.x, z, p.w1, part, p.T, p.d_model, p.block, p.r);
+    if (at_scores) hipLaunchKernelGGL(ff_pool_sum_kernel, dim3((p.r + 63) / 64, p.n_blocks), dim3(64), 0, s, part, p.hpart, n_slices, p.r);
+    if (room) hpart = part;
+    else n_slices = 1;
   } else if (p.q_pred) {
     hipLaunchKernelGGL(ff_pool_kernel<true>, dim3(n_slices, p.n_blocks, oz), dim3(256),
                        (size_t)p.block * sizeof(double), s, p.x, p.z, p.w1, hpart, p.T, p.d_model,
