@@ -212,11 +212,15 @@ __global__ __launch_bounds__(256) void ff_pool_kernel(const bf16_t *__restrict__
 // softmax: 100 tokens of 4096/14336 23.2 -> 21.4, 2000 30.8 -> 29.3, 700 of 2048/8192 23.1 -> 19.6, 4096 27.0 -> 23.9, one block of 300
 // 27.4 -> 19.0, one of 4096 tokens of 4096/14336 165 -> 57; the mean: 700 of 2048/8192 17.1 -> 15.4, 250 of 4096/14336 17.7 ->
 // 16.6, blocks of 256 tokens of 3584/18944 28.9 -> 25.0, one block of 4096 of 4096/14336 107 -> 45.)
-// This is one slice: out[h] = thread tid's output number tid + 512 h of its slice's sums (pool_fine_store says which).
+// SERIAL: a workgroup takes all of its block's slices and adds them up, in the order in which the scores kernels would.
+// grid (slices of 8 LW channels, or 1, n_blocks)
 constexpr int kPoolFineThreads = 512;
-template <bool SOFTMAX, int LW>
-__device__ __forceinline__ void pool_fine_slice(const bf16_t *__restrict__ x, const double *__restrict__ z, const bf16_t *__restrict__ w1,
-                                                int slice, int T, int d_model, int Nb, int r, double (&out)[2]) {
+template <bool SOFTMAX, int LW, bool SERIAL>
+__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf16_t *__restrict__ x,
+                                                                       const double *__restrict__ z,
+                                                                       const bf16_t *__restrict__ w1,
+                                                                      double *__restrict__ hpart, int T,
+                                                                      int d_model, int Nb, int r) {
   constexpr int NT = kPoolFineThreads, NW = NT / 64, CH = 8 * LW, RPW = 64 / LW, STEP = NW * RPW, U = LW / 4, WU = LW / 4;
   __shared__ double red1[2 * NW];
   // Nb <= 4096 weights; rows' sums [wavefront][channel]; the outputs' [8][thread] and [group][output]
@@ -225,155 +229,141 @@ __device__ __forceinline__ void pool_fine_slice(const bf16_t *__restrict__ x, co
   __shared__ double a_s[CH];               // this workgroup's pooled channels
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int b = blockIdx.y, t0 = b * Nb, n = min(T, t0 + Nb) - t0;
-  const int c_base = slice * CH, n_ch = min(CH, d_model - c_base);
-  const int sub = lane / LW, c8 = 8 * (lane % LW);
-  const bf16_t *xc = x + (size_t)t0 * d_model + c_base + min(c8, n_ch - 8);   // (channels past d_model: not used)
-  const int row0 = wave * RPW + sub;
-  uint4 v[U];
-  auto load_rows = [&](int i) __attribute__((always_inline)) {     // past the end: the last row again, not added
+  const int first = SERIAL ? 0 : (int)blockIdx.x;
+  for (int slice = first; SERIAL ? slice * CH < d_model : slice == first; ++slice) {
+    const int c_base = slice * CH, n_ch = min(CH, d_model - c_base);
+    const int sub = lane / LW, c8 = 8 * (lane % LW);
+    const bf16_t *xc = x + (size_t)t0 * d_model + c_base + min(c8, n_ch - 8);   // (channels past d_model: not used)
+    const int row0 = wave * RPW + sub;
+    uint4 v[U];
+    auto load_rows = [&](int i) __attribute__((always_inline)) {     // past the end: the last row again, not added
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4 *>(xc + (size_t)min(i + u * STEP, n - 1) * d_model);
-  };
-  const double z0 = SOFTMAX ? z[t0 + min(tid, n - 1)] : 0.0;
-  load_rows(row0);
-  // thread (cl, o) takes the outputs 8 o .. 8 o + 7 over the channels cl, cl + CL, ...
-  const int n_oct = r >> 3;                                     // <= 128
-  const int o_bits = n_oct > 1 ? 32 - __builtin_clz(n_oct - 1) : 0, o_ceil = 1 << o_bits, CL = NT >> o_bits;
-  const int o = tid & (o_ceil - 1), cl = tid >> o_bits;
-  const bf16_t *wp = w1 + (size_t)c_base * r + 8 * min(o, n_oct - 1);
-  uint4 wv[WU];
-  auto load_w1 = [&](int cq) __attribute__((always_inline)) {
+      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4 *>(xc + (size_t)min(i + u * STEP, n - 1) * d_model);
+    };
+    const double z0 = SOFTMAX ? z[t0 + min(tid, n - 1)] : 0.0;
+    load_rows(row0);
+    // thread (cl, o) takes the outputs 8 o .. 8 o + 7 over the channels cl, cl + CL, ...
+    const int n_oct = r >> 3;                                     // <= 128
+    const int o_bits = n_oct > 1 ? 32 - __builtin_clz(n_oct - 1) : 0, o_ceil = 1 << o_bits, CL = NT >> o_bits;
+    const int o = tid & (o_ceil - 1), cl = tid >> o_bits;
+    const bf16_t *wp = w1 + (size_t)c_base * r + 8 * min(o, n_oct - 1);
+    uint4 wv[WU];
+    auto load_w1 = [&](int cq) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < WU; ++u) wv[u] = *reinterpret_cast<const uint4 *>(wp + (size_t)min(cq + u * CL, n_ch - 1) * r);
-  };
-  load_w1(cl);
-  __builtin_amdgcn_sched_barrier(0);
-  if (SOFTMAX) {
-    double m = -INFINITY;
-    for (int i = tid; i < n; i += NT) m = fmax(m, i == tid ? z0 : z[t0 + i]);
+      for (int u = 0; u < WU; ++u) wv[u] = *reinterpret_cast<const uint4 *>(wp + (size_t)min(cq + u * CL, n_ch - 1) * r);
+    };
+    load_w1(cl);
+    __builtin_amdgcn_sched_barrier(0);
+    if (SOFTMAX) {
+      double m = -INFINITY;
+      for (int i = tid; i < n; i += NT) m = fmax(m, i == tid ? z0 : z[t0 + i]);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    if (lane == 0) red1[wave] = m;
-    __syncthreads();
-    m = red1[0];
+      for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+      if (lane == 0) red1[wave] = m;
+      __syncthreads();
+      m = red1[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) m = fmax(m, red1[w]);
-    double part = 0.0;
-    for (int i = tid; i < n; i += NT) {
-      const double e = exp((i == tid ? z0 : z[t0 + i]) - m);
-      p_s[i] = e;
-      part += e;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    if (lane == 0) red1[NW + wave] = part;
-    __syncthreads();
-    double s = red1[NW];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) s += red1[NW + w];
-    for (int i = tid; i < n; i += NT) p_s[i] = p_s[i] / s;
-    __syncthreads();
-  }
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = row0; i < n; i += U * STEP) {
-    if (i > row0) load_rows(i);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i + u * STEP < n) {
-        double xv[8];
-        unpack8(v[u], xv);
-        const double w = SOFTMAX ? p_s[i + u * STEP] : 1.0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = SOFTMAX ? fma(w, xv[j], acc[j]) : acc[j] + xv[j];
+      for (int w = 1; w < NW; ++w) m = fmax(m, red1[w]);
+      double part = 0.0;
+      for (int i = tid; i < n; i += NT) {
+        const double e = exp((i == tid ? z0 : z[t0 + i]) - m);
+        p_s[i] = e;
+        part += e;
       }
-  }
 #pragma unroll
-  for (int off = LW; off < 64; off <<= 1)
+      for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+      if (lane == 0) red1[NW + wave] = part;
+      __syncthreads();
+      double s = red1[NW];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], off);
-  if (SOFTMAX) __syncthreads();            // (the weights have been read)
-  if (sub == 0) {
+      for (int w = 1; w < NW; ++w) s += red1[NW + w];
+      for (int i = tid; i < n; i += NT) p_s[i] = p_s[i] / s;
+      __syncthreads();
+    }
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int i = row0; i < n; i += U * STEP) {
+      if (i > row0) load_rows(i);
 #pragma unroll
-    for (int j = 0; j < 8; j += 2) *reinterpret_cast<double2 *>(&ps[wave * CH + c8 + j]) = make_double2(acc[j], acc[j + 1]);
-  }
-  __syncthreads();
-  if (tid < CH) {
-    double tot = ps[tid];
+      for (int u = 0; u < U; ++u)
+        if (i + u * STEP < n) {
+          double xv[8];
+          unpack8(v[u], xv);
+          const double w = SOFTMAX ? p_s[i + u * STEP] : 1.0;
 #pragma unroll
-    for (int w = 1; w < NW; ++w) tot += ps[w * CH + tid];
-    a_s[tid] = SOFTMAX ? tot : tot / (double)n;
-  }
-  __syncthreads();
-  double acc8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int cq = cl; cq < n_ch; cq += WU * CL) {
-    if (cq > cl) {
-      load_w1(cq);
-      __builtin_amdgcn_sched_barrier(0);
+          for (int j = 0; j < 8; ++j) acc[j] = SOFTMAX ? fma(w, xv[j], acc[j]) : acc[j] + xv[j];
+        }
     }
 #pragma unroll
-    for (int u = 0; u < WU; ++u)
-      if (cq + u * CL < n_ch) {
-        double wd[8];
-        unpack8(wv[u], wd);
-        const double av = a_s[cq + u * CL];
+    for (int off = LW; off < 64; off <<= 1)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc8[q] = fma(av, wd[q], acc8[q]);
+      for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], off);
+    if (SOFTMAX) __syncthreads();            // (the weights have been read)
+    if (sub == 0) {
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) *reinterpret_cast<double2 *>(&ps[wave * CH + c8 + j]) = make_double2(acc[j], acc[j + 1]);
+    }
+    __syncthreads();
+    if (tid < CH) {
+      double tot = ps[tid];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) tot += ps[w * CH + tid];
+      a_s[tid] = SOFTMAX ? tot : tot / (double)n;
+    }
+    __syncthreads();
+    double acc8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int cq = cl; cq < n_ch; cq += WU * CL) {
+      if (cq > cl) {
+        load_w1(cq);
+        __builtin_amdgcn_sched_barrier(0);
       }
-  }
-  // ps[q][cl][o]; an output's CL sums are added in eights, then those
 #pragma unroll
-  for (int q = 0; q < 8; ++q) ps[q * NT + tid] = acc8[q];
-  __syncthreads();
-  const int cols = 8 << o_bits, per = min(8, CL), G = CL / per;     // cols * G = 8 NT / per
-  double sum[2];
+      for (int u = 0; u < WU; ++u)
+        if (cq + u * CL < n_ch) {
+          double wd[8];
+          unpack8(wv[u], wd);
+          const double av = a_s[cq + u * CL];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {                                    // (cols = 1024: two outputs a thread)
-    const int e = tid + h * NT, j = e & (cols - 1), g = e / cols;
-    sum[h] = 0.0;
-    if (g < G) {
-      const double *src = &ps[(j >> o_bits) * NT + g * per * o_ceil + (j & (o_ceil - 1))];
-      for (int q = 0; q < per; ++q) sum[h] += src[q * o_ceil];
+          for (int q = 0; q < 8; ++q) acc8[q] = fma(av, wd[q], acc8[q]);
+        }
     }
-  }
-  __syncthreads();
+    // ps[q][cl][o]; an output's CL sums are added in eights, then those
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int e = tid + h * NT;
-    if (e < cols * G) ps[e] = sum[h];
-  }
-  __syncthreads();
+    for (int q = 0; q < 8; ++q) ps[q * NT + tid] = acc8[q];
+    __syncthreads();
+    double *dst = hpart + ((size_t)b * gridDim.x + blockIdx.x) * r;
+    const int cols = 8 << o_bits, per = min(8, CL), G = CL / per;     // cols * G = 8 NT / per
+    double sum[2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int j = tid + h * NT;
-    out[h] = 0.0;
-    if (j < cols)
-      for (int g = 0; g < G; ++g) out[h] += ps[g * cols + j];
-  }
-}
-// what pool_fine_slice's thread tid has in out[h] is an output of the first layer, at dst
-__device__ __forceinline__ void pool_fine_store(double *dst, int r, const double (&out)[2]) {
-  const int n_oct = r >> 3, o_bits = n_oct > 1 ? 32 - __builtin_clz(n_oct - 1) : 0;
+    for (int h = 0; h < 2; ++h) {                                    // (cols = 1024: two outputs a thread)
+      const int e = tid + h * NT, j = e & (cols - 1), g = e / cols;
+      sum[h] = 0.0;
+      if (g < G) {
+        const double *src = &ps[(j >> o_bits) * NT + g * per * o_ceil + (j & (o_ceil - 1))];
+        for (int q = 0; q < per; ++q) sum[h] += src[q * o_ceil];
+      }
+    }
+    __syncthreads();
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int j = (int)threadIdx.x + h * kPoolFineThreads, oo = j & ((1 << o_bits) - 1);
-    if (j < (8 << o_bits) && oo < n_oct) dst[8 * oo + (j >> o_bits)] = out[h];
+    for (int h = 0; h < 2; ++h) {
+      const int e = tid + h * NT;
+      if (e < cols * G) ps[e] = sum[h];
+    }
+    __syncthreads();
+    for (int j = tid; j < cols; j += NT) {
+      const int oo = j & (o_ceil - 1);
+      if (oo < n_oct) {
+        double tot = 0.0;
+        for (int g = 0; g < G; ++g) tot += ps[g * cols + j];
+        dst[8 * oo + (j >> o_bits)] = SERIAL && slice > 0 ? dst[8 * oo + (j >> o_bits)] + tot : tot;
+      }
+    }
+    if (SERIAL) __syncthreads();             // (the next slice uses the same LDS)
   }
-}
-
-// grid (slices of 8 LW channels, n_blocks)
-template <bool SOFTMAX, int LW>
-__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf16_t *__restrict__ x,
-                                                                       const double *__restrict__ z,
-                                                                       const bf16_t *__restrict__ w1,
-                                                                      double *__restrict__ hpart, int T,
-                                                                      int d_model, int Nb, int r) {
-  double out[2];
-  pool_fine_slice<SOFTMAX, LW>(x, z, w1, blockIdx.x, T, d_model, Nb, r, out);
-  pool_fine_store(hpart + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * r, r, out);
 }
 
 // A workspace may have no room for the narrow slices' partial sums.  A call's scores have the same bits without it: the sums go where the
-// scores will be, and this kernel adds a block's in slice order, as the scores kernels would.  (ff_predict alone, us, with the room,
+// scores will be, and this kernel adds a block's in slice order, as the scores kernels would; where that place is too small as well (many
+// outputs, few neurons) the pooling kernel does so itself (SERIAL).  (ff_predict alone, us, with the room,
 // without it, without it by 512-channel slices and so with other bits: 100 tokens of 4096/14336 16.0, 17.2, 16.2, softmax 21.4, 22.2, 22.4; 700
 // of 2048/8192, softmax 18.8, 21.0, 22.6; 100 of 256/688 12.7, 15.7, 13.9.)
 // hid[b][j] = sum_s part[b][s][j]; grid (ceil(r / 64), n_blocks)
@@ -392,25 +382,6 @@ __global__ __launch_bounds__(64) void ff_pool_sum_kernel(const double *__restric
       if (s0 + u < n_slices) acc += v[u];
   }
   hid[(size_t)b * r + j] = acc;
-}
-
-// The same where the scores' place is too small for them as well (many outputs, few neurons): one workgroup takes a block's slices one
-// after the other.  Nothing that is in a hurry has such sizes.
-// grid (n_blocks)
-template <bool SOFTMAX, int LW>
-__global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_serial_kernel(const bf16_t *__restrict__ x,
-                                                                              const double *__restrict__ z,
-                                                                              const bf16_t *__restrict__ w1,
-                                                                              double *__restrict__ hid, int T,
-                                                                              int d_model, int Nb, int r) {
-  double sum[2] = {0.0, 0.0}, out[2];
-  for (int slice = 0; slice * 8 * LW < d_model; ++slice) {
-    pool_fine_slice<SOFTMAX, LW>(x, z, w1, slice, T, d_model, Nb, r, out);
-    sum[0] += out[0];
-    sum[1] += out[1];
-    __syncthreads();                       // (the next slice uses the same LDS)
-  }
-  pool_fine_store(hid + (size_t)blockIdx.y * r, r, sum);
 }
 
 // ---- Eq. 13 in float64 ---------------------------------------------------------------------
@@ -1182,6 +1153,14 @@ size_t ff_pool_fine_bytes(int n_tokens, int block, int d_model, int r, bool soft
   return ch == 0 ? 0 : ((size_t)n_tokens + block - 1) / block * (((size_t)d_model + ch - 1) / ch) * r * sizeof(double);
 }
 
+static decltype(&ff_pool_fine_kernel<true, 16, true>) pool_fine_kernel(bool softmax, int lanes, bool serial) {
+  if (lanes == 16)
+    return softmax ? (serial ? ff_pool_fine_kernel<true, 16, true> : ff_pool_fine_kernel<true, 16, false>)
+                   : (serial ? ff_pool_fine_kernel<false, 16, true> : ff_pool_fine_kernel<false, 16, false>);
+  return softmax ? (serial ? ff_pool_fine_kernel<true, 32, true> : ff_pool_fine_kernel<true, 32, false>)
+                 : (serial ? ff_pool_fine_kernel<false, 32, true> : ff_pool_fine_kernel<false, 32, false>);
+}
+
 hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t s, Profiler *prof) {
   int n_slices = (p.d_model + 511) / 512;
   double *hpart = p.hpart;
@@ -1200,11 +1179,7 @@ hipError_t ff_launch_predict(const PredictParams &p, int lds_limit, hipStream_t 
     n_slices = (p.d_model + 8 * lw - 1) / (8 * lw);
     const bool room = p.hpart_fine_bytes >= fine_bytes, at_scores = !room && (int64_t)n_slices * p.r <= p.d_ffn;
     double *part = room ? p.hpart_fine : at_scores ? p.scores : p.hpart;
-    auto fn = lw == 16 ? (p.q_pred ? ff_pool_fine_kernel<true, 16> : ff_pool_fine_kernel<false, 16>)
-                       : (p.q_pred ? ff_pool_fine_kernel<true, 32> : ff_pool_fine_kernel<false, 32>);
-    if (!room && !at_scores)
-      fn = lw == 16 ? (p.q_pred ? ff_pool_fine_serial_kernel<true, 16> : ff_pool_fine_serial_kernel<false, 16>)
-                    : (p.q_pred ? ff_pool_fine_serial_kernel<true, 32> : ff_pool_fine_serial_kernel<false, 32>);
+    const auto fn = pool_fine_kernel(p.q_pred != nullptr, lw, !room && !at_scores);
     hipLaunchKernelGGL(fn, dim3(room || at_scores ? n_slices : 1, p.n_blocks), dim3(kPoolFineThreads), 0, s,
                        p.x, z, p.w1, part, p.T, p.d_model, p.block, p.r);
     if (at_scores) hipLaunchKernelGGL(ff_pool_sum_kernel, dim3((p.r + 63) / 64, p.n_blocks), dim3(64), 0, s, part, p.hpart, n_slices, p.r);
