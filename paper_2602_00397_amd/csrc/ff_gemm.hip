@@ -2156,8 +2156,8 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
     // where there are such, else ahead of everybody.  That favours the tiles with the weights in registers, the large ones, which
     // leave the most, ahead of the 64 x 64 ones; the others only where none of those applies.  (First and last block dense, us per call at 4096/14336,
     // priced without the pieces against this: 2000 tokens 502 / 471, 500 327 / 303, 2000 in blocks of 256 565 / 537, 1500 in
-    // blocks of 64, K 3584 361 / 336; 64 x 512 tiles must save a tenth, since they take twice the pieces, and so must
-    // those after them, but not 128 x 256: 4096/14336, K 7168, 4977 in blocks of 256 would take 902 us for 881.)  Not asked: ksplit, which is to
+    // blocks of 64, K 3584 361 / 336; 64 x 512 tiles must save a tenth, since they take twice the pieces, those
+    // after them 7%.)  Not asked: ksplit, which is to
     // change the long lists' sums and no others, hence no tile.
     const int surplus = up64(ntot) - up64(base);
     const bool heavy_cut = split != 1 && p.part != nullptr && p.k.n_heavy > 0 && 8L * surplus >= up64(base);
@@ -2181,27 +2181,22 @@ hipError_t ff_launch_gemm2(const Gemm2Params &p_in, int variant, int split, int 
           const long heavy = (long)p.k.n_heavy * ((p.block + v.bm - 1) / v.bm) * N;
           const long free_pieces = std::max<long>(1, std::min<long>(kNumCU / heavy, kMaxFreePieces));
           const double piece_steps = (double)((surplus + free_pieces - 1) / free_pieces) / 64;
-          const double whole = c.fixed + steps * c.full, piece = c.fixed + piece_steps * c.full;
-          // With more than a round of common tiles the CUs that no piece is on go on with those.  Pieces of 128-token tiles fill up the last round,
-          // so many tiles more; those of 64 x 512 in short blocks, on a quarter of the chip, cost their share; the other 64-token tiles' a round, as
-          // with fewer common tiles.  (First and last block dense, us, a round for all of them against this: 4096/14336, K 3584, 2600 tokens in
-          // blocks of 64 459 -> 434, 3000 483 -> 461; 3584/18944, K 4736, 2909 549 -> 515; 2048/8192, K 2048, blocks of 128, 11609 366 -> 338;
-          // 4096/14336, K 7168, blocks of 256, 2727 618 -> 634, 5713 996 -> 1023.  Of 320 calls, most of them sought out because one or another such
-          // price changes their tile, 118 change it, 46 gain more than 1% and 17 lose so much, the most 2.8%.)
-          const bool fills = p.block > 64 ? v.bm >= 128 : g.variant == kDirect64;
-          if (V * N + heavy * free_pieces <= kNumCU) {
+          // With more than a round of common tiles the CUs that no piece is on go on with those, which the large tiles, of few and long pieces, gain by
+          // most: 128 x 512 ones, in blocks of up to 64 tokens 64 x 512 ones, cost their share of a round, the others' pieces a round, as they do
+          // beside fewer common tiles.  (First and last block dense, us, a round for all of them against this: 4096/14336, K 3584, 2600 tokens in
+          // blocks of 64 459 -> 434, 3000 483 -> 461; 3584/18944, K 4736, 2909 549 -> 515; 2048/8192, K 2048, blocks of 128, 11609 366 -> 338.  Of every
+          // tile of 404 calls, 64 to 320 tokens a block: 1.003 of the fastest, a round for all of them 1.005; filling up the last round with all tiles' pieces
+          // as so many tiles more, 1.005 too, lost 6% and more on 4096/14336, K 3584, 1600 tokens in blocks of 192 (361 -> 385) and 3584/18944, K
+          // 9472, 2909 in blocks of 160 (1031 -> 1099).  What this loses against a round for all: 2048/8192, K 4096, 5713 in blocks of 160 493 -> 525,
+          // 4096/14336, K 7168, 3300 in blocks of 96 818 -> 845, 4951 in blocks of 128 922 -> 944.)
+          const bool shares = g.variant == (p.block > 64 ? kDirect128 : kDirect64);
+          const double rounds = (double)(heavy * free_pieces) / kNumCU;
+          if (V * N + heavy * free_pieces <= kNumCU)
             cost = c.fixed + steps * (c.idle + (c.full - c.idle) * (double)(V * N + heavy * free_pieces) / kNumCU);
-          } else if (V * N <= kNumCU || !fills) {
-            cost += (double)((heavy * free_pieces + kNumCU - 1) / kNumCU) * piece;
-          } else if (p.block <= 64) {
-            cost += (double)(heavy * free_pieces) / kNumCU * piece;
-          } else {
-            const double rounds = (V * N + heavy * free_pieces * piece / whole) / kNumCU, rest = rounds - std::floor(rounds);
-            cost = std::floor(rounds) * whole + (rest > 0.0 ? c.fixed + steps * (c.idle + (c.full - c.idle) * rest) : 0.0);
-          }
+          else
+            cost += (V * N > kNumCU && shares ? rounds : std::ceil(rounds)) * (c.fixed + piece_steps * c.full);
         }
-        const double must = !heavy_cut ? 0.98 : g.variant == kDirect128Narrow ? 0.98 : 0.9;
-        if (variant < 0 || cost < best * must) { variant = g.variant; pieces = n; best = cost; }
+        if (variant < 0 || cost < best * (!heavy_cut ? 0.98 : g.variant == kDirect64 ? 0.9 : 0.93)) { variant = g.variant; pieces = n; best = cost; }
       }
     }
   }

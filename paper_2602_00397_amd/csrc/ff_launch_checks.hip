@@ -269,7 +269,8 @@ static void check_gemm2_prices() {
       // ... and where it is not; a few longer lists' pieces beside more than a round of common tiles, and beside less
       {{2909, 64, 4096, 14336, 64, 3584, 14336, 2}, true, 6}, {{3000, 64, 3584, 18944, 64, 4736, 18944, 2}, true, 6},
       {{11490, 256, 2048, 8192, 32, 2327, 8192, 2}, true, 5}, {{11609, 128, 2048, 8192, 32, 2048, 8192, 2}, true, 5},
-      {{4951, 128, 4096, 14336, 64, 7168, 14336, 2}, true, 7}, {{2300, 64, 3584, 18944, 64, 9472, 18944, 2}, true, 8},
+      {{2062, 256, 4096, 14336, 64, 7168, 14336, 2}, true, 5},
+      {{2909, 160, 3584, 18944, 64, 9472, 18944, 2}, true, 6}, {{2300, 64, 3584, 18944, 64, 9472, 18944, 2}, true, 8},
       {{1700, 64, 2048, 8192, 32, 2048, 8192, 2}, true, 6}, {{2048, 64, 2048, 8192, 32, 2048, 8192, 2}, true, 6},
       {{4096, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}, {{1350, 128, 2048, 8192, 32, 4096, 0, 0}, true, 7}};
   for (const auto &c : calls) {
