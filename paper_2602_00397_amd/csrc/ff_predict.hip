@@ -229,8 +229,7 @@ __global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf
   __shared__ double a_s[CH];               // this workgroup's pooled channels
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int b = blockIdx.y, t0 = b * Nb, n = min(T, t0 + Nb) - t0;
-  const int first = SERIAL ? 0 : (int)blockIdx.x;
-  for (int slice = first; SERIAL ? slice * CH < d_model : slice == first; ++slice) {
+  auto one = [&](int slice) __attribute__((always_inline)) {
     const int c_base = slice * CH, n_ch = min(CH, d_model - c_base);
     const int sub = lane / LW, c8 = 8 * (lane % LW);
     const bf16_t *xc = x + (size_t)t0 * d_model + c_base + min(c8, n_ch - 8);   // (channels past d_model: not used)
@@ -357,7 +356,14 @@ __global__ __launch_bounds__(kPoolFineThreads) void ff_pool_fine_kernel(const bf
         dst[8 * oo + (j >> o_bits)] = SERIAL && slice > 0 ? dst[8 * oo + (j >> o_bits)] + tot : tot;
       }
     }
-    if (SERIAL) __syncthreads();             // (the next slice uses the same LDS)
+  };
+  if (SERIAL) {
+    for (int slice = 0; slice * CH < d_model; ++slice) {
+      one(slice);
+      __syncthreads();                       // (the next slice uses the same LDS)
+    }
+  } else {
+    one(blockIdx.x);
   }
 }
 
